@@ -252,11 +252,13 @@ cat_status cat_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t *idx_ou
  *   apply:  cat_pca_project -> cat_assign on z -> cat_apply_assigned
  *
  * cat_pca_fit: column means of lq, the D x D covariance with the 1/N
- * normalisation, its eigendecomposition (one-sided Jacobi rotations in double
- * precision, `sweeps` sweeps over all pairs; 0 picks the default, 12), and the p
+ * normalisation, its leading eigenpairs in double precision, and the p
  * directions of largest eigenvalue in descending order, each a unit vector whose
  * entry of largest magnitude (the first such entry) is positive.  1 <= p <= D <=
- * 2048.
+ * 2048.  sweeps = 0 (default): up to p = 256 by tridiagonalisation, multisection and
+ * inverse iteration, beyond that by 12 sweeps of one-sided Jacobi rotations over all
+ * pairs; sweeps in 1 .. 64: that number of Jacobi sweeps.  Both agree with LAPACK to
+ * a few D times the rounding of a double.
  *   mean         out, D float
  *   components   out, p x D float, row c = direction c
  *   eigenvalues  out, p doubles, nullable

@@ -8,6 +8,7 @@
 //   cat_pca_project   z = (x - mean) W^T
 //   cat_apply_assigned   corrected = x + alpha ((gamma_a x + beta_a) - x) for given labels a
 #include "cat_common.h"
+#include "cat_eig.h"
 
 namespace cat {
 
@@ -917,6 +918,7 @@ struct PcaWs {
     double* lambda;  // Dp
     double* W;       // Dp x Dp
     double* Vt;      // Dp x Dp
+    double* eig;     // eig_scratch_doubles(D)
     size_t bytes;
 };
 static PcaWs pca_carve(void* base, int64_t D) {
@@ -934,6 +936,8 @@ static PcaWs pca_carve(void* base, int64_t D) {
     off += pad256((size_t)Dp * Dp * 8);
     w.Vt = (double*)(b + off);
     off += pad256((size_t)Dp * Dp * 8);
+    w.eig = (double*)(b + off);
+    off += pad256(eig_scratch_doubles(D) * 8);
     w.bytes = off;
     return w;
 }
@@ -1017,6 +1021,9 @@ cat_status cat_pca_fit(const void* lq, int64_t N, int64_t D, int32_t p, cat_dtyp
                          (long long)N, (long long)D, (int)p, (int)dt);
     if (!lq || !mean || !components) return set_error(CAT_ERR_INVALID_ARG, "cat_pca_fit: null argument");
     if (sweeps < 0 || sweeps > 64) return set_error(CAT_ERR_INVALID_ARG, "cat_pca_fit: sweeps must be in 0 .. 64");
+    // Up to 256 directions come from a tridiagonalisation (cat_eig.hip); one workgroup makes its vectors orthogonal one after
+    // the other, and beyond that number, or when the caller asks for a number of sweeps, all D rows go through Jacobi.
+    const bool leading = sweeps == 0 && p <= kEigMaxP;
     if (sweeps == 0) sweeps = 12;
     PcaWs w = pca_carve(workspace, D);
     if (!workspace || workspace_bytes < w.bytes)
@@ -1076,6 +1083,7 @@ cat_status cat_pca_fit(const void* lq, int64_t N, int64_t D, int32_t p, cat_dtyp
         hipLaunchKernelGGL(k_pca_mirror, g2, dim3(256), 0, st, w.W, D, Dp);
         CAT_LAUNCH_CHECK("k_pca_mirror");
     }
+    if (leading) return launch_eig_leading(w.W, w.Vt, Dp, (int32_t)D, p, w.eig, components, eigenvalues, st);
     {
         const int ni = (int)((Dp + 255) / 256);
         const dim3 jb(256), gpair((unsigned)(Dp / 2)), gquad((unsigned)(Dp / 4)), goct((unsigned)(Dp / 8));
