@@ -77,6 +77,7 @@ struct FitWs {
     double* inertia;          // 1
     TileWs tile;              // scratch of the MFMA tile kernels
     LloydWs lloyd;            // changed-row list and counters of the fused Lloyd loop
+    BoundsWs bounds;          // that loop's distance bounds, where the plain fits keep them (tile_bounds_pay)
     uint32_t* sort;           // N + 2 K + 2  rows ordered by cluster, for the segmented sums
     size_t bytes;
 };
@@ -102,6 +103,11 @@ static FitWs carve_fit(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt
         w.lloyd = lloyd_carve(base ? (void*)(c.base + c.off) : nullptr, N, D, K);
         w.lloyd.sort_ws = w.sort;
         c.off += align256(w.lloyd.bytes);
+        if (tile_bounds_pay(N, D, K, dt)) {
+            w.bounds = bounds_carve(base ? (void*)(c.base + c.off) : nullptr, N, D, K);
+            w.bounds.record = true;
+            c.off += align256(w.bounds.bytes);
+        }
     }
     w.bytes = c.off;
     return w;
@@ -161,7 +167,7 @@ static std::atomic<bool> g_padded_fit{true};  // cat_debug_padded_fit
 static bool fit_runs_padded(int64_t N, int64_t D, int32_t K, cat_dtype dt, int32_t iters) {
     return g_padded_fit.load() && g_path.load() == CAT_PATH_AUTO && iters >= 2 && pad_applies(N, D, K, dt);
 }
-static PadWs carve_pad(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt, int32_t iters, bool with_bounds) {
+static PadWs carve_pad(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt, bool with_bounds) {
     PadWs w;
     w.Dp = padded_dim(D, dt);
     Carver c(base);
@@ -169,7 +175,7 @@ static PadWs carve_pad(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt
     w.cent = c.take<float>((size_t)K * (size_t)w.Dp);
     w.init = c.take<float>((size_t)K * (size_t)w.Dp);
     w.fit = c.take<char>(carve_fit(nullptr, N, w.Dp, K, dt).bytes);
-    if (with_bounds) w.bounds = c.take<char>(bounds_workspace_bytes(N, w.Dp, K, iters));
+    if (with_bounds) w.bounds = c.take<char>(bounds_workspace_bytes(N, w.Dp, K));
     w.bytes = c.off;
     return w;
 }
@@ -284,7 +290,12 @@ static cat_status run_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, 
         CAT_TRY(launch_gather_rows(lq, dt, D, K, w.idx, c0, st));
     }
     if (fused) {
-        if (!skipped && g_early_stop.load()) skipped = w.lloyd.skipped;
+        // long passes leave out the rows whose distance bounds say that they stay (same outputs; no pass needs to be left
+        // out as a whole then)
+        if (!skipped && !bw && w.bounds.expire)
+            bw = &w.bounds;
+        else if (!skipped && g_early_stop.load())
+            skipped = w.lloyd.skipped;
         // one assignment launch per Lloyd iteration; only the rows that change cluster touch the sums
         CAT_TRY(tile_lloyd(lq, dt, N, D, K, iters, centroids, w.acc, assignments, w.counts, inertia, w.rep, skipped, w.tile, w.lloyd, st, bw));
     } else {
@@ -379,7 +390,7 @@ cat_status cat_select_path(cat_path p) {
 size_t cat_fit_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     if (!shape_ok(N, D, K, dt)) return 0;
     size_t b = carve_fit(nullptr, N, D, K, dt).bytes;
-    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, 0, false).bytes;
+    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, false).bytes;
     return b;
 }
 
@@ -482,7 +493,7 @@ static cat_status fit_impl(const char* who, const void* lq, const void* fp, int6
     BoundsWs bw;
     size_t need = w.bytes;
     if (with_bounds) {
-        bw = bounds_carve(workspace ? (char*)workspace + align256(w.bytes) : nullptr, N, D, K, iters);
+        bw = bounds_carve(workspace ? (char*)workspace + align256(w.bytes) : nullptr, N, D, K);
         bw.evaluated = evaluated;
         need = align256(w.bytes) + bw.bytes;
     }
@@ -491,7 +502,7 @@ static cat_status fit_impl(const char* who, const void* lq, const void* fp, int6
     const bool padded = fit_runs_padded(N, D, K, dt, iters);
     PadWs pw;
     if (padded) {
-        pw = carve_pad(workspace ? (char*)workspace + align256(need) : nullptr, N, D, K, dt, iters, with_bounds);
+        pw = carve_pad(workspace ? (char*)workspace + align256(need) : nullptr, N, D, K, dt, with_bounds);
         need = align256(need) + pw.bytes;
     }
     CAT_TRY(check_ws(who, workspace, workspace_bytes, need));
@@ -501,7 +512,7 @@ static cat_status fit_impl(const char* who, const void* lq, const void* fp, int6
         FitWs wp = carve_fit(pw.fit, N, Dp, K, dt);
         BoundsWs bp;
         if (with_bounds) {
-            bp = bounds_carve(pw.bounds, N, Dp, K, iters);
+            bp = bounds_carve(pw.bounds, N, Dp, K);
             bp.evaluated = evaluated;
         }
         CAT_TRY(launch_pad_rows(lq, dt, N, D, Dp, pw.lq, st));
@@ -539,8 +550,8 @@ cat_status cat_fit_early_stop(const void* lq, const void* fp, int64_t N, int64_t
 
 size_t cat_fit_bounds_workspace_bytes(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
     if (!shape_ok(N, D, K, dt) || iters < 0) return 0;
-    size_t b = align256(carve_fit(nullptr, N, D, K, dt).bytes) + bounds_workspace_bytes(N, D, K, iters);
-    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, iters, true).bytes;
+    size_t b = align256(carve_fit(nullptr, N, D, K, dt).bytes) + bounds_workspace_bytes(N, D, K);
+    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, true).bytes;
     return b;
 }
 
@@ -592,7 +603,7 @@ static RestartWs carve_restarts(void* base, int64_t N, int64_t D, int32_t K, int
     w.inertia = (double*)take(((size_t)(iters < 0 ? 0 : iters) + 1) * sizeof(double));
     w.best = (double*)take(sizeof(double));
     w.state = (int32_t*)take(2 * sizeof(int32_t));
-    w.pad = pad_applies(N, D, K, dt) ? take(carve_pad(nullptr, N, D, K, dt, iters, false).bytes) : nullptr;
+    w.pad = pad_applies(N, D, K, dt) ? take(carve_pad(nullptr, N, D, K, dt, false).bytes) : nullptr;
     w.bytes = off;
     return w;
 }
@@ -630,7 +641,7 @@ cat_status cat_fit_restarts(const void* lq, const void* fp, int64_t N, int64_t D
     PadWs pw;
     FitWs wp;
     if (padded) {
-        pw = carve_pad(w.pad, N, D, K, dt, iters, false);
+        pw = carve_pad(w.pad, N, D, K, dt, false);
         wp = carve_fit(pw.fit, N, pw.Dp, K, dt);
         CAT_TRY(launch_pad_rows(lq, dt, N, D, pw.Dp, pw.lq, st));
     }

@@ -37,6 +37,32 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// Sum over the wave, the same bits in every lane: four steps inside the rows of 16 lanes as lane permutations fused into
+// the moves, then the four row sums by lane reads.  No LDS round trips (a butterfly of shuffles is six of them, one after
+// the other).  All 64 lanes must be active.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+    v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v = dpp_add<0x141>(v);  // row_half_mirror
+    v = dpp_add<0x140>(v);  // row_mirror
+    const long long b = __double_as_longlong(v);
+    double r[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), 16 * q);
+        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 16 * q);
+        r[q] = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+    }
+    return (r[0] + r[1]) + (r[2] + r[3]);
+}
+
 // ---- SplitMix64 (Steele, Lea, Flood 2014) as a counter-based generator -----
 __host__ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, uint64_t t) {
     uint64_t z = seed + (t + 1ull) * 0x9E3779B97F4A7C15ull;
@@ -88,6 +114,9 @@ cat_status launch_assign_lds(const void* lq, cat_dtype dt, int64_t N, int64_t D,
 // counts[k] and rep[k] from given assignments (both pre-initialised as above)
 cat_status launch_count_rep(const int32_t* assign, int64_t N, int32_t K, int32_t* counts,
                             unsigned long long* rep, hipStream_t st);
+// rep[k] = the first row with label k, given the counts (rep pre-initialised to ~0ull); N below 2^31
+cat_status launch_first_rows(const int32_t* assign, int64_t N, int32_t K, const int32_t* counts, unsigned long long* rep,
+                             hipStream_t st);
 // Segmented sums over the rows of each cluster.  NQ = 1: acc[0] += x.  NQ = 4: with x' = x - pivx[k],
 // y' = y - pivy[k]: acc[0] += x', acc[1] += y', acc[2] += x'^2, acc[3] += x'y'.  acc is NQ x K x D
 // doubles, pre-zeroed.

@@ -20,30 +20,6 @@ constexpr int kEigT = 256;                 // threads of a tridiagonalisation st
 constexpr int kEigWaves = kEigT / kWave;
 constexpr double kEps = 2.220446049250313e-16;
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return v + __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-// sum over the wave, the same bits in every lane; all 64 lanes active
-__device__ __forceinline__ double wave_total(double v) {
-    v = dpp_add<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-    v = dpp_add<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-    v = dpp_add<0x141>(v);  // row_half_mirror
-    v = dpp_add<0x140>(v);  // row_mirror
-    const long long b = __double_as_longlong(v);
-    double r[4];
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), 16 * q);
-        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 16 * q);
-        r[q] = __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-    }
-    return (r[0] + r[1]) + (r[2] + r[3]);
-}
-
 // ---- one column of the tridiagonalisation --------------------------------------------------------------------------
 // State before launch k: rows and columns i, j >= k of W hold the matrix after the reflections 0 .. k - 2; the reflection
 // k - 1 (v = row k - 1 of V, unit entry at position k, and tau[k - 1]) has been chosen and p_in = W v computed, but not

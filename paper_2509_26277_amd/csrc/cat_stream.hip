@@ -74,24 +74,43 @@ cat_status launch_copy_cols(const float* src, int64_t rows, int32_t src_ld, floa
 }
 
 // dst (rows x dst_ld) <- the first dst_ld columns of src (rows x src_ld), zeros where src has none (fp32 or 16-bit elements)
-template <typename T>
-__global__ __launch_bounds__(256) void k_pad_rows(const T* __restrict__ src, int64_t rows, int64_t src_ld, int64_t dst_ld, T* __restrict__ dst) {
-    const int64_t n = rows * dst_ld;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / dst_ld, c = i - r * dst_ld;
-        dst[i] = c < src_ld ? src[r * src_ld + c] : (T)0;
+// One wave per row, in 4-byte words (bf16 rows have an even number of channels): rows that are not whole 16-byte groups
+// start anywhere on a word, so a wave instruction covers 256 consecutive bytes of the row instead of a lane 16 of them.
+// Bound by memory, a read and a write of the matrix: 50021 x 1001 to 1004 floats, 126 us with an element and a 64-bit
+// division per thread.
+constexpr int kPadWaves = 4;
+__global__ __launch_bounds__(kPadWaves * kWave) void k_pad_words(const uint32_t* __restrict__ src, int64_t rows, int64_t src_w,
+                                                                 int64_t dst_w, uint32_t* __restrict__ dst) {
+    constexpr int U = 8;  // words in flight per lane
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t step = (int64_t)gridDim.x * kPadWaves;
+    for (int64_t r = (int64_t)blockIdx.x * kPadWaves + threadIdx.x / kWave; r < rows; r += step) {
+        const uint32_t* s = src + r * src_w;
+        uint32_t* d = dst + r * dst_w;
+        for (int64_t c0 = lane; c0 < dst_w; c0 += U * kWave) {
+            uint32_t v[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int64_t c = c0 + u * kWave;
+                v[u] = s[c < src_w ? c : src_w - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int64_t c = c0 + u * kWave;
+                if (c < dst_w) d[c] = c < src_w ? v[u] : 0u;
+            }
+        }
     }
 }
 cat_status launch_pad_rows(const void* src, cat_dtype dt, int64_t rows, int64_t src_ld, int64_t dst_ld, void* dst, hipStream_t st) {
-    const int64_t n = rows * dst_ld;
-    if (n == 0) return CAT_OK;
-    int64_t blocks = (n + 255) / 256;
-    blocks = blocks > (1 << 20) ? (1 << 20) : blocks;
-    if (dt == CAT_F32)
-        hipLaunchKernelGGL(k_pad_rows<float>, dim3((unsigned)blocks), dim3(256), 0, st, (const float*)src, rows, src_ld, dst_ld, (float*)dst);
-    else
-        hipLaunchKernelGGL(k_pad_rows<bf16_t>, dim3((unsigned)blocks), dim3(256), 0, st, (const bf16_t*)src, rows, src_ld, dst_ld, (bf16_t*)dst);
-    CAT_LAUNCH_CHECK("k_pad_rows");
+    if (rows * dst_ld == 0) return CAT_OK;
+    const int64_t per = dt == CAT_F32 ? 1 : 2;
+    if (src_ld % per || dst_ld % per) return set_error(CAT_ERR_INVALID_ARG, "row copy: rows of whole 4-byte words only");
+    int64_t blocks = (rows + kPadWaves - 1) / kPadWaves;
+    blocks = blocks > (1 << 16) ? (1 << 16) : blocks;
+    hipLaunchKernelGGL(k_pad_words, dim3((unsigned)blocks), dim3(kPadWaves * kWave), 0, st, (const uint32_t*)src, rows, src_ld / per,
+                       dst_ld / per, (uint32_t*)dst);
+    CAT_LAUNCH_CHECK("k_pad_words");
     return CAT_OK;
 }
 
@@ -169,15 +188,24 @@ __global__ __launch_bounds__(64) void k_init_indices(int64_t N, int32_t K, uint6
     const uint64_t cap = init_draw_cap(N);
     int32_t have = 0;
     uint64_t t = 0;
+    // 64 draws at a time, one per lane: a draw is dropped if it is among those already kept or equals an earlier draw of
+    // the batch, the others are kept in the order drawn (one draw at a time, with its 64-bit modulo and scan one after
+    // the other, took 89 us at K = 200)
     while (have < K && t < cap) {
-        int64_t cand = (int64_t)(splitmix64_at(seed, t) % (uint64_t)N);
-        t++;
-        bool dup = false;
-        for (int q = lane; q < have; q += kWave) dup |= (s_idx[q] == cand);
-        if (__ballot(dup) == 0ull) {
-            if (lane == 0) s_idx[have] = cand;
-            have++;
+        const uint64_t mine = t + (uint64_t)lane;
+        const int64_t cand = (int64_t)(splitmix64_at(seed, mine) % (uint64_t)N);
+        bool dup = mine >= cap;
+        for (int q = 0; q < have; q++) dup |= s_idx[q] == cand;
+        for (int l = 0; l < kWave - 1; l++) {
+            const int lo = __builtin_amdgcn_readlane((int)cand, l), hi = __builtin_amdgcn_readlane((int)(cand >> 32), l);
+            dup |= l < lane && lo == (int)cand && hi == (int)(cand >> 32);
         }
+        const unsigned long long keep = __ballot(!dup);
+        const int at = have + __builtin_popcountll(keep & ((1ull << lane) - 1ull));
+        if (!dup && at < K) s_idx[at] = cand;
+        have += __builtin_popcountll(keep);
+        have = have < K ? have : K;
+        t += kWave;
         __syncthreads();
     }
     // cap reached (not expected): complete with the smallest indices not yet taken
@@ -331,8 +359,9 @@ __global__ __launch_bounds__(256) void k_count_rep(const int32_t* __restrict__ a
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += step) {
         int a = assign[i];
         if (a >= 0 && a < K) {
-            atomicAdd(&s_cnt[a], 1);
-            atomicMin(&s_rep[a], (unsigned long long)i);
+            if (counts) atomicAdd(&s_cnt[a], 1);
+            // (rows come in rising order: after a cluster's first ones the minimum stands and a plain read tells)
+            if (rep && (unsigned long long)i < s_rep[a]) atomicMin(&s_rep[a], (unsigned long long)i);
         }
     }
     __syncthreads();
@@ -347,6 +376,49 @@ cat_status launch_count_rep(const int32_t* assign, int64_t N, int32_t K, int32_t
     hipLaunchKernelGGL(k_count_rep, dim3((unsigned)(b < 1024 ? b : 1024)), dim3(256), 0, st, assign, N, K, counts,
                        rep);
     CAT_LAUNCH_CHECK("k_count_rep");
+    return CAT_OK;
+}
+
+// The first row of every cluster alone: a block walks its contiguous share of the labels and stops once it has seen every
+// cluster that has rows (a later row of the share cannot come before those).  On labels in no particular order that is
+// after a few K rows; sorted labels make every block walk its whole share.  (k_count_rep, which looks at every label and
+// merges every block's table: 22 us for 1,048,576 labels, K = 32.)
+constexpr int kFirstThreads = 256, kFirstPer = 4;
+__global__ __launch_bounds__(kFirstThreads) void k_first_rows(const int32_t* __restrict__ assign, int64_t N, int32_t K, int64_t share,
+                                                              const int32_t* __restrict__ counts, unsigned long long* __restrict__ rep) {
+    __shared__ uint32_t s_first[CAT_MAX_K];
+    for (int k = threadIdx.x; k < K; k += kFirstThreads) s_first[k] = 0xFFFFFFFFu;
+    __syncthreads();
+    const int64_t b0 = (int64_t)blockIdx.x * share, b1 = b0 + share < N ? b0 + share : N;
+    for (int64_t r0 = b0; r0 < b1; r0 += kFirstThreads * kFirstPer) {
+        int a[kFirstPer];
+#pragma unroll
+        for (int u = 0; u < kFirstPer; u++) {
+            const int64_t r = r0 + u * kFirstThreads + threadIdx.x;
+            a[u] = r < b1 ? assign[r] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < kFirstPer; u++) {
+            const uint32_t at = (uint32_t)(r0 - b0) + u * kFirstThreads + threadIdx.x;
+            if (a[u] >= 0 && a[u] < K && at < s_first[a[u]]) atomicMin(&s_first[a[u]], at);
+        }
+        __syncthreads();
+        int all = 1;
+        for (int k = threadIdx.x; k < K; k += kFirstThreads) all &= (s_first[k] != 0xFFFFFFFFu || counts[k] == 0) ? 1 : 0;
+        if (__syncthreads_and(all)) break;  // uniform
+    }
+    for (int k = threadIdx.x; k < K; k += kFirstThreads)
+        if (s_first[k] != 0xFFFFFFFFu) atomicMin(&rep[k], (unsigned long long)(b0 + s_first[k]));
+}
+cat_status launch_first_rows(const int32_t* assign, int64_t N, int32_t K, const int32_t* counts, unsigned long long* rep,
+                             hipStream_t st) {
+    if (N >= ((int64_t)1 << 31) || K > CAT_MAX_K) return set_error(CAT_ERR_UNSUPPORTED, "first rows: N or K too large");
+    const int64_t step = kFirstThreads * kFirstPer;
+    int64_t blocks = (N + step - 1) / step;
+    blocks = blocks > 256 ? 256 : blocks;
+    const int64_t share = ((N + blocks - 1) / blocks + step - 1) / step * step;
+    hipLaunchKernelGGL(k_first_rows, dim3((unsigned)((N + share - 1) / share)), dim3(kFirstThreads), 0, st, assign, N, K, share, counts, rep);
+    CAT_LAUNCH_CHECK("k_first_rows");
     return CAT_OK;
 }
 
@@ -532,7 +604,10 @@ __global__ __launch_bounds__(256) void k_sort_scatter(const int32_t* __restrict_
 // times the waves in flight; V = 1 gains nothing more.
 constexpr int kSortWaves = 4;
 constexpr int kSortV = 2;
-template <typename T, int NQ>
+// ODD: fp32 rows of an odd length (rows start on 4 bytes, not 8): the lane's two channels are 64 apart, each a 4-byte load,
+// and a wave instruction still reads 256 consecutive bytes.  (50021 x 1001, K = 200: the statistics 538 us on the
+// LDS-panel kernel these rows took before.)
+template <typename T, int NQ, bool ODD = false>
 __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
     const T* __restrict__ lq, const T* __restrict__ fp, const uint32_t* __restrict__ perm,
     const uint32_t* __restrict__ offs, int64_t D, int32_t K, int32_t R, int32_t nsl, int64_t nitems,
@@ -551,14 +626,17 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
     const uint32_t p0 = (uint32_t)(item / nsl) * (uint32_t)R;
     const uint32_t p1 = (p0 + (uint32_t)R < total) ? p0 + (uint32_t)R : total;
     if (p0 >= p1) return;
-    const int64_t c0 = (int64_t)slice * (kWave * V) + (int64_t)lane * V;
-    const bool on = c0 < D;  // D is a multiple of V: a lane's group is inside or outside as a whole
+    constexpr int CS = ODD ? kWave : 1;  // distance between the channels of a lane
+    const int64_t c0 = (int64_t)slice * (kWave * V) + (int64_t)lane * (ODD ? 1 : V);
+    bool on[V];  // (unless ODD, D is a multiple of V: a lane's group is inside or outside as a whole)
+#pragma unroll
+    for (int v = 0; v < V; v++) on[v] = c0 + v * CS < D;
     const int64_t KD = (int64_t)K * D;
     // Every load of the loop below is issued by every wave on every path (a lane outside the row reads channel 0, a
     // round past the end reads the last row again; neither is used).  The compiler counts the loads still in flight
     // at each use; a load it cannot prove was issued makes it wait for all of them, which would empty the pipeline
     // once per row.
-    const int64_t cl = on ? c0 : 0;
+    const int64_t cl = on[0] ? c0 : 0, cl1 = on[V - 1] ? c0 + (V - 1) * CS : 0;
 
     // cluster of position p0: the last k with offs[k] <= p0
     int k = 0;
@@ -579,27 +657,27 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
         px[v] = py[v] = 0.f;
     }
     auto load_piv = [&]() {
-        if (NQ == 4 && on) {
+        if (NQ == 4) {
 #pragma unroll
             for (int v = 0; v < V; v++) {
-                px[v] = pivx[(int64_t)k * D + c0 + v];
-                py[v] = pivy[(int64_t)k * D + c0 + v];
+                if (!on[v]) continue;
+                px[v] = pivx[(int64_t)k * D + c0 + v * CS];
+                py[v] = pivy[(int64_t)k * D + c0 + v * CS];
             }
         }
     };
     auto flush = [&]() {
-        if (on) {
-            double* o = acc + (int64_t)k * D + c0;
+        double* o = acc + (int64_t)k * D + c0;
 #pragma unroll
-            for (int v = 0; v < V; v++) {
-                atomicAdd(o + v, sx[v]);
-                if (NQ == 4) {
-                    atomicAdd(o + KD + v, sy[v]);
-                    atomicAdd(o + 2 * KD + v, sxx[v]);
-                    atomicAdd(o + 3 * KD + v, sxy[v]);
-                }
-                sx[v] = sy[v] = sxx[v] = sxy[v] = 0.0;
+        for (int v = 0; v < V; v++) {
+            if (!on[v]) continue;
+            atomicAdd(o + v * CS, sx[v]);
+            if (NQ == 4) {
+                atomicAdd(o + KD + v * CS, sy[v]);
+                atomicAdd(o + 2 * KD + v * CS, sxx[v]);
+                atomicAdd(o + 3 * KD + v * CS, sxy[v]);
             }
+            sx[v] = sy[v] = sxx[v] = sxy[v] = 0.0;
         }
     };
     load_piv();
@@ -626,8 +704,17 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
             uint32_t i = (uint32_t)(r * RB + u);
             if (i >= n) i = n - 1;  // past the end: the last row again, unused
             const int64_t row = (int64_t)__builtin_amdgcn_readlane(src, (int)(i & (kWave - 1)));
-            xv[u] = *(const u4*)(lq + row * D + cl);
-            if (NQ == 4) yv[u] = *(const u4*)(fp + row * D + cl);
+            if (ODD) {
+                xv[u][0] = *(const uint32_t*)(lq + row * D + cl);
+                xv[u][V * sizeof(T) / 4 - 1] = *(const uint32_t*)(lq + row * D + cl1);
+                if (NQ == 4) {
+                    yv[u][0] = *(const uint32_t*)(fp + row * D + cl);
+                    yv[u][V * sizeof(T) / 4 - 1] = *(const uint32_t*)(fp + row * D + cl1);
+                }
+            } else {
+                xv[u] = *(const u4*)(lq + row * D + cl);
+                if (NQ == 4) yv[u] = *(const u4*)(fp + row * D + cl);
+            }
         }
     };
     auto consume = [&](int r, const u4 (&xv)[RB], const u4 (&yv)[RB]) {
@@ -648,7 +735,7 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
                 // cluster boundary instead
                 __builtin_amdgcn_s_waitcnt(0x0F70);
             }
-            if (on) {
+            if (on[0]) {  // (a second channel past the row adds up numbers nobody keeps)
 #pragma unroll
                 for (int v = 0; v < V; v++) {
                     float x, y = 0.f;
@@ -693,7 +780,7 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
 
 bool segsum_sorted_supported(int nq, int64_t N, int64_t D, cat_dtype dt) {
     (void)nq;
-    if (N >= ((int64_t)1 << 31) || D % kSortV) return false;
+    if (N >= ((int64_t)1 << 31) || (dt == CAT_BF16 && D % kSortV)) return false;
     // Where it pays (measured): always for bf16 rows (the LDS-panel kernel reads them two bytes per
     // lane); for fp32 rows from a few million elements on (65536 x 1000: 105 against 156 us for the
     // statistics, 47 against 64 us for the plain sums; 65536 x 256: 32 against 62 us).  Below that the two
@@ -720,17 +807,20 @@ cat_status launch_segsum_sorted(int nq, const void* lq, const void* fp, cat_dtyp
     // One wave per run: as many runs as waves are resident at once (or a multiple of that), so
     // the launch has no ragged second round; a run is at least 64 rows (shorter runs only add
     // merge traffic) and at most about a thousand.
-    static thread_local int slots_cache[2][2] = {{0, 0}, {0, 0}}, slots_dev = -1;
+    static thread_local int slots_cache[3][2] = {{0, 0}, {0, 0}, {0, 0}}, slots_dev = -1;
     int dev = 0;
     CAT_HIP_TRY(hipGetDevice(&dev));
     if (dev != slots_dev) {
-        slots_cache[0][0] = slots_cache[0][1] = slots_cache[1][0] = slots_cache[1][1] = 0;
+        for (auto& c : slots_cache) c[0] = c[1] = 0;
         slots_dev = dev;
     }
-    int& slots = slots_cache[dt == CAT_BF16][nq == 4];
+    const bool odd = D % V != 0;  // fp32 only (segsum_sorted_supported)
+    if (odd && dt == CAT_BF16) return set_error(CAT_ERR_UNSUPPORTED, "ordered sums: bf16 rows of an odd length");
+    int& slots = slots_cache[dt == CAT_BF16 ? 1 : odd ? 2 : 0][nq == 4];
     if (slots == 0) {
-        const void* fn = dt == CAT_F32 ? (nq == 1 ? (const void*)k_segsum_sorted<float, 1> : (const void*)k_segsum_sorted<float, 4>)
-                                       : (nq == 1 ? (const void*)k_segsum_sorted<bf16_t, 1> : (const void*)k_segsum_sorted<bf16_t, 4>);
+        const void* fn = dt == CAT_BF16 ? (nq == 1 ? (const void*)k_segsum_sorted<bf16_t, 1> : (const void*)k_segsum_sorted<bf16_t, 4>)
+                         : odd          ? (nq == 1 ? (const void*)k_segsum_sorted<float, 1, true> : (const void*)k_segsum_sorted<float, 4, true>)
+                                        : (nq == 1 ? (const void*)k_segsum_sorted<float, 1> : (const void*)k_segsum_sorted<float, 4>);
         int nb = 0, ncu = 0;
         CAT_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kSortWaves * kWave, 0));
         CAT_HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -744,10 +834,12 @@ cat_status launch_segsum_sorted(int nq, const void* lq, const void* fp, cat_dtyp
     if (R < 64) R = 64;
     const int64_t nitems = ((N + R - 1) / R) * nsl;
     dim3 grid((unsigned)((nitems + kSortWaves - 1) / kSortWaves)), block(kSortWaves * kWave);
-#define CAT_SEGS(T, NQ_)                                                                                          \
-    hipLaunchKernelGGL((k_segsum_sorted<T, NQ_>), grid, block, 0, st, (const T*)lq, (const T*)fp, perm, offs, D, K, \
+#define CAT_SEGS(T, ...)                                                                                          \
+    hipLaunchKernelGGL((k_segsum_sorted<T, __VA_ARGS__>), grid, block, 0, st, (const T*)lq, (const T*)fp, perm, offs, D, K, \
                        (int32_t)R, nsl, nitems, pivx, pivy, acc)
-    if (dt == CAT_F32) {
+    if (odd) {
+        if (nq == 1) CAT_SEGS(float, 1, true); else CAT_SEGS(float, 4, true);
+    } else if (dt == CAT_F32) {
         if (nq == 1) CAT_SEGS(float, 1); else CAT_SEGS(float, 4);
     } else {
         if (nq == 1) CAT_SEGS(bf16_t, 1); else CAT_SEGS(bf16_t, 4);

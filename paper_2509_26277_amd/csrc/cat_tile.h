@@ -41,7 +41,7 @@ struct LloydWs {
     int32_t* skipped = nullptr;          //   then one word: passes left out, for callers that bring no word of their own
     double* norm_part = nullptr;         // slices x K
     int32_t* counts2 = nullptr;          // K: the second half of the counts double buffer
-    float2* carry = nullptr;             // N pairs, only for more than 128 clusters: what the first of two launches that
+    float4* carry = nullptr;             // N entries, only for more than 128 clusters: what the first of two launches that
     float* carry_cmax = nullptr;         //   split the clusters hands to the second (per row; the largest centroid norm)
     uint32_t* sort_ws = nullptr;         // not carved here: the caller's scratch for launch_segsum_sorted
     size_t bytes = 0;
@@ -54,15 +54,20 @@ struct BoundsWs {
     double* expire = nullptr;         // N        per row: the drift at which it has to be evaluated again
     int32_t* rows = nullptr;          // N        the rows of the coming pass
     uint32_t* n_rows = nullptr;       // 1        their number
-    double* drift = nullptr;          // iters+1  accumulated centroid drift up to each pass
+    double* drift = nullptr;          // 2        accumulated centroid drift up to a pass (by parity of the pass)
+    uint32_t* quiet = nullptr;        // 2        (by parity of the pass) no row changed cluster in the pass before
+    double* objective = nullptr;      // 1        the part of the objective that depends on the centroids, of the first listed pass
     double* move_part = nullptr;      // slices x K
     int32_t* slice_counts = nullptr;  // slices x K
     int32_t* evaluated = nullptr;     // iters+1  out: rows evaluated by each pass (the caller's array, nullable)
+    bool record = false;              // see tile_lloyd: every entry of the objective, and a last pass that leaves rows out too
     size_t bytes = 0;
 };
-size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K, int32_t iters);
-BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K, int32_t iters);
+size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K);
+BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K);
 bool tile_bounds_supports(int64_t N, int64_t D, int32_t K, cat_dtype dt);
+// Whether the plain fits run their loop with bounds (record): the shape allows it and the passes are long enough.
+bool tile_bounds_pay(int64_t N, int64_t D, int32_t K, cat_dtype dt);
 cat_status launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 
 // `iters` Lloyd iterations from cent0 plus the final assignment.  cent_io holds the initial
@@ -74,6 +79,9 @@ cat_status launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 // on, a pass also leaves every row's distance bound, and the passes between that one and the last evaluate only the
 // rows whose bound the centroid drift has used up.  Same centroids, assignments, counts and rep; of the objective
 // only the entries of the passes that evaluate every row (0, 1, 2 and the last) are written, the others are NaN.
+// With bw->record the last pass leaves rows out as well and every entry of the objective is written: with the sums S_k
+// of the clusters, which the update keeps in double, the objective of a pass is a constant of the rows plus
+// sum_k c_k . (n_k c_k - 2 S_k); the constant comes from pass 2, which evaluates every row.
 cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters,
                       float* cent_io, double* sums, int32_t* assign, int32_t* counts, double* inertia,
                       unsigned long long* rep, int32_t* skipped, const TileWs& ws, const LloydWs& lw, hipStream_t st,

@@ -108,6 +108,19 @@ struct DeltaParams {
     int32_t seed_counts;
     double* move_part;
     uint32_t* n_rows_clear;      // nullable: cleared (the row selection that follows counts into it)
+    // The objective of the pass before, whose centroids are still `cent` on entry and whose sums this launch completes:
+    // constant + sum_k c_k . (n_k c_k - 2 S_k).  Every slice adds its share of that sum to obj_out; with obj_ref (the same
+    // sum of a pass whose objective in_ref[0] is known) one workgroup adds the constant, in_ref[0] - obj_ref[0].
+    double* obj_out;             // nullable, zero on entry
+    const double* obj_ref;
+    const double* in_ref;
+    // Words for the loops with bounds: quiet_next receives whether the pass before listed no row.  If the launch before
+    // found that too (*quiet), the centroids did not move in it either: everything stays as it is.
+    const uint32_t* quiet;       // nullable
+    uint32_t* quiet_next;
+    // The launch after the last pass: no centroids follow, only the objective and the counts are wanted.
+    int32_t last;
+    int32_t* counts_out;
 };
 
 constexpr int kDeltaWaves = 8;
@@ -154,6 +167,20 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
             if (q.n_rows_clear) *q.n_rows_clear = 0;
         }
         if ((int)threadIdx.x < q.inertia_n && q.inertia_slot) q.inertia_slot[threadIdx.x] = 0.0;
+    }
+    if (q.quiet) {
+        const bool still = len == 0u && *q.quiet != 0u;  // uniform over the grid
+        if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) *q.quiet_next = len == 0u ? 1u : 0u;
+        if (still) {
+            // same sums, same centroids, same partition: the movements, norms, operand and counts of the launch before
+            // stand, the objective of the pass before is that of the pass before it
+            if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
+                if (threadIdx.x == 0 && q.obj_out) *q.obj_out = q.obj_out[-1];
+                if (q.last)
+                    for (int k = threadIdx.x; k < q.K; k += blockDim.x) q.counts_out[k] = q.slice_counts[k];
+            }
+            return;
+        }
     }
     const uint32_t per = (len + q.G - 1) / q.G;
     const uint32_t e0 = blockIdx.x * per;
@@ -274,6 +301,9 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
                 if (s_moved[i]) atomicAdd(q.slice_counts + (size_t)slice * q.K + k0 + i, s_moved[i]);
     }
 
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && q.obj_out && q.obj_ref)
+        atomicAdd(q.obj_out, q.in_ref[0] - q.obj_ref[0]);
+
     // ---- who finishes the slice? ----
     // What crosses workgroups here (delta, the counter) goes through device-scope atomics, which
     // are performed where every XCD sees them; waiting for this wave's own atomics to be
@@ -292,6 +322,7 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
     // eight clusters per wave at a time: all their loads first (a load is not moved above the
     // stores of the cluster before it, so one cluster at a time would cost a round trip each)
     constexpr int KB = 8;
+    double obj = 0.0;
     for (int kb = wave; kb < q.K; kb += kDeltaWaves * KB) {
         double S[KB];
         float cold[KB];
@@ -316,6 +347,11 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
             const int k = kb + u * kDeltaWaves;
             if (k >= q.K) break;  // wave-uniform
             double nn = 0.0, mv = 0.0;
+            if (ch_ok) obj += (double)cold[u] * ((double)n[u] * (double)cold[u] - 2.0 * S[u]);
+            if (q.last) {
+                if (slice == 0 && lane == 0) q.counts_out[k] = n[u];
+                continue;
+            }
             if (ch_ok) {
                 const int64_t i = (int64_t)k * q.D + ch;
                 q.base[i] = S[u];
@@ -342,16 +378,20 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
                     q.packA[((blk + 1) * 64 + ol) * 8 + j] = (uint16_t)lw;
                 }
             }
-            nn = wave_sum(nn);
+            nn = wave_total(nn);
             if (lane == 0) q.norm_part[(size_t)slice * q.K + k] = nn;
             if (q.move_part) {
-                mv = wave_sum(mv);
+                mv = wave_total(mv);
                 if (lane == 0) {
                     q.move_part[(size_t)slice * q.K + k] = mv;
                     if (q.seed_counts) q.slice_counts[(size_t)slice * q.K + k] = q.counts[k];
                 }
             }
         }
+    }
+    if (q.obj_out) {
+        obj = wave_total(obj);
+        if (lane == 0) atomicAdd(q.obj_out, obj);
     }
 }
 
@@ -362,15 +402,27 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
 // to the running drift G; a row whose bound expire[i] (the drift at its last evaluation plus its margin then) is
 // still above G keeps its nearest centroid and is left out.  Every workgroup computes the same G (same data, same
 // order); the rows are taken in contiguous pieces and the kept ones appended to `rows` with one reservation per piece.
+// A row evaluated without a margin has expire = the drift of that pass and is kept as soon as any centroid moves at all
+// (the drift then grows, by its last bit at least); while none moves its nearest centroid is what it was.  A margin is
+// rounded down by 1e-9 of itself, so a drift equal to expire has not used it up.
+// Matrices below this size keep the plain loop in the plain fits: a pass over them is launches and dependent steps, to
+// which the selection of the rows adds one (4096 x 64, K = 4: a pass of 16.6 us gains nothing from the 85 % of the
+// rows it need not read and pays 4.3 us).
+constexpr double kBoundsBytes = 32.0 * 1024 * 1024;
 constexpr int kSelThreads = 256;
 constexpr int kSelPerThread = 8;
 __global__ __launch_bounds__(kSelThreads) void k_bound_select(const double* __restrict__ move_part, int32_t slices, int32_t K,
                                                               const double* __restrict__ g_prev, double* __restrict__ g_now,
                                                               const double* __restrict__ expire, int64_t N,
-                                                              int32_t* __restrict__ rows, uint32_t* __restrict__ n_rows) {
+                                                              int32_t* __restrict__ rows, uint32_t* __restrict__ n_rows,
+                                                              const uint32_t* __restrict__ quiet) {
+    if (quiet && *quiet) {  // nothing moved (k_delta_prep): no row is due, the list stays empty
+        if (blockIdx.x == 0 && threadIdx.x == 0) *g_now = *g_prev;
+        return;
+    }
     __shared__ double s_p[256];
     __shared__ double s_g;
-    __shared__ uint32_t s_wave[kSelThreads / kWave + 1];
+    __shared__ uint32_t s_cnt[kSelPerThread * kSelThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     double pk = 0.0;
     if ((int)threadIdx.x < K) {
@@ -412,7 +464,10 @@ __global__ __launch_bounds__(kSelThreads) void k_bound_select(const double* __re
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) w2 = fmax(w2, __shfl_xor(w2, o, kWave));
         if (threadIdx.x == 0) {
-            s_g = *g_prev + (w1 + w2) * (1.0 + 1e-9);
+            const double g0 = *g_prev;
+            double g1 = g0 + (w1 + w2) * (1.0 + 1e-9);
+            if (w1 + w2 > 0.0 && g1 == g0) g1 = __longlong_as_double(__double_as_longlong(g0) + 1);  // (drifts are >= 0)
+            s_g = g1;
             if (blockIdx.x == 0) *g_now = s_g;
         }
     }
@@ -420,40 +475,43 @@ __global__ __launch_bounds__(kSelThreads) void k_bound_select(const double* __re
     const double G = s_g;
     constexpr int64_t kPiece = (int64_t)kSelThreads * kSelPerThread;
     for (int64_t r0 = (int64_t)blockIdx.x * kPiece; r0 < N; r0 += (int64_t)gridDim.x * kPiece) {
-        // thread t takes rows r0 + t * 8 .. + 7: the kept rows of a piece stay in row order
-        const int64_t mine = r0 + (int64_t)threadIdx.x * kSelPerThread;
-        uint32_t keep = 0;
-        int cnt = 0;
+        // step j of thread t is row r0 + 256 j + t: the loads are coalesced, and the kept rows of a piece stay in row order
+        // (8 consecutive rows per thread: 13 us over 1,048,576 rows)
+        unsigned long long m[kSelPerThread];
+        double ex[kSelPerThread];
 #pragma unroll
         for (int j = 0; j < kSelPerThread; j++) {
-            const int64_t i = mine + j;
-            const bool k = i < N && !(G < expire[i]);
-            keep |= (uint32_t)k << j;
-            cnt += k;
+            const int64_t i = r0 + (int64_t)j * kSelThreads + threadIdx.x;
+            ex[j] = expire[i < N ? i : N - 1];
         }
-        // exclusive prefix over the workgroup: shuffle scan per wave, wave totals through LDS
-        int incl = cnt;
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int v = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += v;
+        for (int j = 0; j < kSelPerThread; j++) {
+            const int64_t i = r0 + (int64_t)j * kSelThreads + threadIdx.x;
+            m[j] = __ballot(i < N && !(G <= ex[j]));
+            if (lane == 0) s_cnt[j * (kSelThreads / kWave) + wave] = (uint32_t)__builtin_popcountll(m[j]);
         }
-        if (lane == kWave - 1) s_wave[wave] = (uint32_t)incl;
         __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t tot = 0;
-            for (int w = 0; w < kSelThreads / kWave; w++) {
-                const uint32_t v = s_wave[w];
-                s_wave[w] = tot;
-                tot += v;
+        if (threadIdx.x < kWave) {  // exclusive prefix over the 32 counts, one reservation for the piece
+            constexpr int NC = kSelPerThread * kSelThreads / kWave;
+            uint32_t v = threadIdx.x < NC ? s_cnt[threadIdx.x] : 0u;
+            const uint32_t mine = v;
+#pragma unroll
+            for (int o = 1; o < NC; o <<= 1) {
+                const uint32_t u = __shfl_up(v, o, kWave);
+                if (lane >= o) v += u;
             }
-            s_wave[kSelThreads / kWave] = tot ? atomicAdd(n_rows, tot) : 0u;
+            const uint32_t tot = __shfl(v, NC - 1, kWave);
+            uint32_t base = 0;
+            if (lane == 0 && tot) base = atomicAdd(n_rows, tot);
+            base = __shfl(base, 0, kWave);
+            if (threadIdx.x < NC) s_cnt[threadIdx.x] = base + v - mine;
         }
         __syncthreads();
-        uint32_t pos = s_wave[kSelThreads / kWave] + s_wave[wave] + (uint32_t)(incl - cnt);
 #pragma unroll
         for (int j = 0; j < kSelPerThread; j++)
-            if (keep >> j & 1u) rows[pos++] = (int32_t)(mine + j);
+            if (m[j] >> lane & 1ull)
+                rows[s_cnt[j * (kSelThreads / kWave) + wave] + __builtin_popcountll(m[j] & ((1ull << lane) - 1ull))] =
+                    (int32_t)(r0 + (int64_t)j * kSelThreads + threadIdx.x);
         __syncthreads();
     }
 }
@@ -560,7 +618,7 @@ static inline size_t lloyd_ctrl_words(int64_t D) { return (size_t)(3 + 2 * delta
 
 size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K) {
     return a256((size_t)N * 8) + a256(lloyd_ctrl_words(D) * 4) + a256((size_t)delta_slices(D) * K * 8) +
-           a256((size_t)K * 4) + (K > kSplitTiles * 16 ? a256((size_t)N * 8) + 256 : 0);
+           a256((size_t)K * 4) + (K > kSplitTiles * 16 ? a256((size_t)N * sizeof(float4)) + 256 : 0);
 }
 LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K) {
     LloydWs w;
@@ -577,8 +635,8 @@ LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K) {
     w.counts2 = (int32_t*)b;
     b += a256((size_t)K * 4);
     if (K > kSplitTiles * 16) {
-        w.carry = (float2*)b;
-        b += a256((size_t)N * 8);
+        w.carry = (float4*)b;
+        b += a256((size_t)N * sizeof(float4));
         w.carry_cmax = (float*)b;
     }
     return w;
@@ -599,13 +657,18 @@ bool tile_bounds_supports(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     // row numbers in the list of rows are 32-bit; the bounds are derived for the two-part operand
     return N < ((int64_t)1 << 31) && tile_config(TILE_LLOYD, D, K, dt, true).ok;
 }
-size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K, int32_t iters) {
-    const size_t sk = (size_t)delta_slices(D) * (size_t)K;
-    return a256((size_t)N * 8) + a256((size_t)N * 4) + a256(4) + a256(((size_t)iters + 1) * 8) + a256(sk * 8) + a256(sk * 4);
+bool tile_bounds_pay(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
+    const double bytes = (double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0);
+    if (bytes < kBoundsBytes || N >= ((int64_t)1 << 31)) return false;
+    return tile_config(TILE_LLOYD, D, K, dt, true).ok || split_config(D, K, dt, nullptr);
 }
-BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K, int32_t iters) {
+size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K) {
+    const size_t sk = (size_t)delta_slices(D) * (size_t)K;
+    return a256((size_t)N * 8) + a256((size_t)N * 4) + a256(4) + a256(4 * 8) + a256(sk * 8) + a256(sk * 4);
+}
+BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K) {
     BoundsWs w;
-    w.bytes = bounds_workspace_bytes(N, D, K, iters);
+    w.bytes = bounds_workspace_bytes(N, D, K);
     if (!base) return w;
     const size_t sk = (size_t)delta_slices(D) * (size_t)K;
     char* b = (char*)base;
@@ -616,7 +679,9 @@ BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K, int32_t iters
     w.n_rows = (uint32_t*)b;
     b += a256(4);
     w.drift = (double*)b;
-    b += a256(((size_t)iters + 1) * 8);
+    w.objective = w.drift + 2;
+    w.quiet = (uint32_t*)(w.drift + 3);
+    b += a256(4 * 8);
     w.move_part = (double*)b;
     b += a256(sk * 8);
     w.slice_counts = (int32_t*)b;
@@ -640,14 +705,22 @@ static cat_status launch_delta_prep(const void* lq, cat_dtype dt, int64_t D, int
                                     double* delta, const int32_t* counts_prev, int32_t* counts_next,
                                     double* inertia_slot, unsigned long long* rep, int32_t* skipped, hipStream_t st,
                                     int32_t inertia_n = 1, const BoundsWs* bw = nullptr, bool seed_counts = false,
-                                    int32_t split_tiles = 0) {
+                                    int32_t split_tiles = 0, double* obj_out = nullptr, const double* in_ref = nullptr,
+                                    bool last = false, int32_t* counts_out = nullptr) {
     DeltaParams q = {};
+    q.obj_out = obj_out;
+    q.obj_ref = in_ref ? bw->objective : nullptr;
+    q.in_ref = in_ref;
+    q.last = last ? 1 : 0;
+    q.counts_out = counts_out;
     q.KTs = split_tiles ? split_tiles : c.KT;
     if (bw) {
         q.slice_counts = bw->slice_counts;
         q.seed_counts = seed_counts ? 1 : 0;
         q.move_part = bw->move_part;
         q.n_rows_clear = bw->n_rows;
+        q.quiet = seed_counts ? nullptr : bw->quiet + (par ^ 1);
+        q.quiet_next = bw->quiet + par;
     }
     q.lq = lq;
     q.D = D;
@@ -787,7 +860,7 @@ cat_status tile_assign(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32
 
 // The two launches of a pass whose clusters are split (p: the parameters of the pass as for one launch).
 static cat_status launch_split_pair(const TileParams& p, const TileCfg& c, cat_dtype dt, int32_t K, const TileWs& ws,
-                                    float2* carry, float* carry_cmax, hipStream_t st) {
+                                    float4* carry, float* carry_cmax, hipStream_t st) {
     // first launch: clusters 0 .. 127, no bookkeeping, leaves (best score, nearest centroid) per row
     const int32_t K0 = kSplitTiles * 16;
     TileParams a = p;
@@ -802,6 +875,8 @@ static cat_status launch_split_pair(const TileParams& p, const TileCfg& c, cat_d
     a.rep = nullptr;
     a.list = nullptr;
     a.delta_mode = 0;
+    a.expire = nullptr;
+    a.evaluated_slot = nullptr;
     cat_status s = dt == CAT_BF16 ? launch_split_bf16(a, c, st) : launch_split_f32(a, c, st);
     if (s != CAT_OK) return s;
     // second launch: the other clusters beside that pair, and the bookkeeping of the pass
@@ -818,7 +893,7 @@ static cat_status launch_split_pair(const TileParams& p, const TileCfg& c, cat_d
 }
 
 size_t tile_split_scratch_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
-    return split_config(D, K, dt, nullptr, TILE_ASSIGN) ? a256((size_t)N * 8) + 256 : 0;
+    return split_config(D, K, dt, nullptr, TILE_ASSIGN) ? a256((size_t)N * sizeof(float4)) + 256 : 0;
 }
 
 // tile_assign (assignment only) for more than 128 clusters, ranked by two launches; scratch: tile_split_scratch_bytes.
@@ -843,19 +918,21 @@ cat_status tile_assign_split(const void* lq, cat_dtype dt, int64_t N, int64_t D,
     p.counts = counts;
     p.inertia = inertia;
     p.rep = rep;
-    return launch_split_pair(p, c, dt, K, ws, (float2*)scratch, (float*)((char*)scratch + a256((size_t)N * 8)), st);
+    return launch_split_pair(p, c, dt, K, ws, (float4*)scratch, (float*)((char*)scratch + a256((size_t)N * sizeof(float4))), st);
 }
 
 cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters,
                       float* cent_io, double* sums, int32_t* assign, int32_t* counts, double* inertia,
                       unsigned long long* rep, int32_t* skipped, const TileWs& ws, const LloydWs& lw, hipStream_t st,
                       const BoundsWs* bw) {
-    // rows are left out by their bounds in the passes 3 .. iters - 1
-    const bool bounds = bw && bw->expire && iters >= 4 && tile_bounds_supports(N, D, K, dt);
+    // rows are left out by their bounds in the passes 3 .. iters - 1 (record: and in the last)
+    const bool record = bw && bw->record;
+    const bool one_launch = tile_bounds_supports(N, D, K, dt);
+    const bool bounds = bw && bw->expire && iters >= 4 && (one_launch || (record && lw.carry && split_config(D, K, dt, nullptr)));
     if (bounds) skipped = nullptr;  // (a pass over an empty list of rows costs next to nothing already)
-    TileCfg c = tile_config(TILE_LLOYD, D, K, dt, bounds);
+    TileCfg c = tile_config(TILE_LLOYD, D, K, dt, bounds && one_launch);
     if (!c.ok) return set_error(CAT_ERR_UNSUPPORTED, "tile kernels do not fit D=%lld K=%d", (long long)D, (int)K);
-    const bool split = !bounds && lw.carry && split_config(D, K, dt, &c);  // (c then describes one of the two launches)
+    const bool split = !(bounds && one_launch) && lw.carry && split_config(D, K, dt, &c);  // (c then describes one of the two launches)
     const int32_t arrays = split ? 2 : 1;
     const size_t KD = (size_t)K * (size_t)D;
     double* base = sums;
@@ -872,7 +949,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D) * 4, st));
     if (skipped) CAT_T(launch_fill_zero(skipped, sizeof(int32_t), st));
     if (bw && bw->evaluated) CAT_T(launch_fill_i32(bw->evaluated, (int64_t)iters + 1, (int32_t)N, st));
-    if (bounds) CAT_T(launch_fill_zero(bw->drift, ((size_t)iters + 1) * sizeof(double), st));
+    if (bounds) CAT_T(launch_fill_zero(bw->drift, 4 * sizeof(double), st));
     // Passes 0 and 1 are each followed by a full segmented sum: after the first reassignment most
     // rows still move, and moving them one by one costs several times a fresh sum (measured: 0.97 ms
     // against 0.33 ms on a 262144 x 2048 bf16 matrix).  From pass 2 on a pass lists the rows that
@@ -896,21 +973,24 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
         else
             CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, t & 1, cent_io, base, delta, cnt_prev, cnt_t, slot,
                                     last ? rep : nullptr, last ? nullptr : skipped, st, 1, bounds ? bw : nullptr,
-                                    t == kFullPasses + 1, split ? kSplitTiles : 0));
+                                    t == kFullPasses + 1, split ? kSplitTiles : 0,
+                                    !(bounds && record && inertia) ? nullptr : t == kFullPasses + 1 ? bw->objective : inertia + t - 1,
+                                    bounds && record && inertia && t > kFullPasses + 1 ? inertia + kFullPasses : nullptr));
         // With bounds: pass 2 evaluates every row and leaves its bound; the passes 3 .. iters - 1 evaluate the rows
         // whose bound the drift of the centroids has used up (selected here, after the update that moved them)
-        const bool keeps_bounds = bounds && t >= kFullPasses && !last;
+        const bool keeps_bounds = bounds && t >= kFullPasses && (!last || record);
         const bool listed = keeps_bounds && t > kFullPasses;
         if (listed) {
             const int64_t piece = (int64_t)kSelThreads * kSelPerThread;
             int64_t blocks = (N + piece - 1) / piece;
             blocks = blocks > 2048 ? 2048 : blocks;
             hipLaunchKernelGGL(k_bound_select, dim3((unsigned)blocks), dim3(kSelThreads), 0, st, bw->move_part,
-                               (int32_t)delta_slices(D), K, bw->drift + t - 1, bw->drift + t, bw->expire, N, bw->rows, bw->n_rows);
+                               (int32_t)delta_slices(D), K, bw->drift + ((t - 1) & 1), bw->drift + (t & 1), bw->expire, N, bw->rows, bw->n_rows,
+                               t > kFullPasses + 1 ? bw->quiet + (t & 1) : nullptr);
             CAT_LAUNCH_CHECK("k_bound_select");
         }
         p.expire = keeps_bounds ? bw->expire : nullptr;
-        p.gnow = keeps_bounds ? bw->drift + t : nullptr;
+        p.gnow = keeps_bounds ? bw->drift + (t & 1) : nullptr;
         p.rows = listed ? bw->rows : nullptr;
         p.n_rows = listed ? bw->n_rows : nullptr;
         p.evaluated_slot = (keeps_bounds && bw->evaluated) ? bw->evaluated + t : nullptr;
@@ -918,8 +998,8 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
         p.norm_slices = t > kFullPasses ? (int32_t)delta_slices(D) : 0;
         p.counts = listed ? nullptr : cnt_t;  // (a pass over listed rows cannot count: the slices keep running counts)
         p.inertia = listed ? nullptr : slot;
-        p.rep = last ? rep : nullptr;  // the final pass describes the partition that is returned
-        p.list = (t >= kFullPasses && !last) ? lw.list : nullptr;
+        p.rep = last && !listed ? rep : nullptr;  // the final pass describes the partition that is returned
+        p.list = (t >= kFullPasses && (!last || listed)) ? lw.list : nullptr;
         p.list_count = lw.ctrl + (t & 1);
         p.list_cap = lloyd_list_capacity();
         p.delta_mode = p.list ? 1 : 0;
@@ -941,7 +1021,14 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
                 CAT_T(launch_segsum(1, lq, nullptr, dt, assign, N, D, K, nullptr, nullptr, base, st));
         }
     }
-    if (bounds && inertia && iters > kFullPasses + 1)  // the objective of a pass over listed rows is not known
+    if (bounds && record) {
+        // the rows the last pass moved, its objective and counts; the first rows of the clusters from the labels
+        CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, (iters + 1) & 1, cent_io, base, delta, counts, lw.counts2, nullptr, nullptr,
+                                nullptr, st, 1, bw, false, split ? kSplitTiles : 0, inertia ? inertia + iters : nullptr,
+                                inertia ? inertia + kFullPasses : nullptr, true, counts));
+        CAT_T(launch_fill_u64(rep, K, ~0ull, st));
+        CAT_T(launch_first_rows(assign, N, K, counts, rep, st));
+    } else if (bounds && inertia && iters > kFullPasses + 1)  // the objective of a pass over listed rows is not known
         CAT_T(launch_fill_u64((unsigned long long*)(inertia + kFullPasses + 1), iters - kFullPasses - 1, 0x7ff8000000000000ull, st));
 #undef CAT_T
     return CAT_OK;

@@ -67,7 +67,7 @@ struct TileParams {
     void* out;
     float tau, tau2;         // re-rank threshold T = tau |x| cmax + tau2 cmax^2
     uint32_t ldsA_bytes, off_cnorm, off_hist, off_rep, off_list, off_misc;
-    // Plain assignment passes: rows inside the error bound are not measured where they are found (the wave would
+    // Assignment passes (but those over several centroid sets): rows inside the error bound are not measured where they are found (the wave would
     // leave the pipeline of row loads it has in flight, and in the chunked-operand loop hold up the other seven) but
     // queued in LDS, queue_cap entries of DeferredRow after a 16-byte header at off_queue, and measured by all waves
     // when the workgroup has run out of tiles.  A row that finds the queue full, or has more than kQueueCand
@@ -98,8 +98,8 @@ struct TileParams {
     // nearest centroid of its share; the second (carry_in given) ranks that pair as one more cluster beside its own
     // and does the bookkeeping of the pass.  Tables per cluster (counts, first rows) span k_hist clusters.
     int32_t k_base, k_hist, norm_stride;
-    const float2* carry_in;
-    float2* carry_out;
+    const float4* carry_in;    // per row: best score, its cluster (int bits), second-best score
+    float4* carry_out;
     float* cmax_io;  // the first launch leaves the largest centroid norm of its share, the second takes the larger of the two
 };
 
@@ -202,7 +202,7 @@ struct ChunkRegs {
     int prev;     // previous assignment of row n (assignment passes only)
     u32x4 prevv;  // several sets: previous assignments of row n in the sets 4 g .. 4 g + 3
     int row;      // listed rows: the number of row n
-    float2 carry; // split clusters: (best score, its cluster as int bits) of row n in the clusters ranked before
+    float4 carry; // split clusters: (best score, its cluster as int bits, second-best score) of row n in the clusters ranked before
 };
 
 // Rows past N repeat the last row and channel groups past D read the start of the row (valid
@@ -319,7 +319,7 @@ __device__ __forceinline__ void rank_rows(const TileParams& p, const f32x4 (&acc
                                           bool* reranked = nullptr, float* bound = nullptr, int k_base = 0,
                                           bool has_carry = false, float carry_s = 0.f, int carry_i = 0,
                                           unsigned char* queue = nullptr, int prev = -1, bool* deferred = nullptr,
-                                          int k_last = -1) {
+                                          int k_last = -1, float carry_s2 = 0.f) {
     const int n = lane & 15, q = lane >> 4;
     float b1 = __builtin_inff(), b2 = __builtin_inff();
     int i1 = 16 * t0;
@@ -370,7 +370,7 @@ __device__ __forceinline__ void rank_rows(const TileParams& p, const f32x4 (&acc
     const float T = p.tau * sqrtf(xn2) * cmax + p.tau2 * cmax * cmax;
     const bool flag = valid && !(b2 - b1 > T);
     if (first) *first = b1;
-    if (second) *second = b2;
+    if (second) *second = has_carry ? fminf(b2, carry_s2) : b2;  // (with a pair carried in: the best of all others there, too)
     if (reranked) *reranked = flag;
     if (bound) *bound = T;
     dmin = fmaxf(xn2 + b1, 0.f);
@@ -475,7 +475,7 @@ __device__ __forceinline__ void rank_rows(const TileParams& p, const f32x4 (&acc
 // for that row (what finish_tile does for the rows ranked on the spot), by lane 0.
 template <bool BF16>
 __device__ __forceinline__ void finish_deferred(const TileParams& p, unsigned char* smem, const DeferredRow& e, int lane,
-                                                double& in_acc) {
+                                                double& in_acc, double gnow = 0.0) {
     double dbest = __builtin_inf();
     int kbest = 0x7fffffff;
     const int nc = __builtin_amdgcn_readfirstlane(e.ncand);
@@ -505,6 +505,11 @@ __device__ __forceinline__ void finish_deferred(const TileParams& p, unsigned ch
     }
     if (lane != 0) return;
     if (kbest == 0x7fffffff) kbest = (int)e.cand[0];  // no distance compares (non-finite input): any listed cluster
+    if (p.carry_out) {  // the first of two launches over the clusters: the pair's cluster (its scores are there already)
+        ((int*)(p.carry_out + row))[1] = kbest;
+        return;
+    }
+    if (p.expire) p.expire[row] = gnow;  // two centroids within the bound of each other: no margin
     int* s_hist = (int*)(smem + p.off_hist);
     unsigned long long* s_rep = (unsigned long long*)(smem + p.off_rep);
     int* s_misc = (int*)(smem + p.off_misc);
@@ -530,13 +535,14 @@ __device__ __forceinline__ void finish_deferred(const TileParams& p, unsigned ch
 template <int KT, bool BF16, int MODE, bool BOUNDS = false, bool SPLIT = false>
 __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* smem, f32x4 (&acc)[KT], float& nrm,
                                             int tile, int lane, float cmax, double& in_acc, int prev_in, int row_in = -1,
-                                            uint32_t n_listed = 0, double gnow = 0.0, float2 carry = float2{0.f, 0.f}) {
+                                            uint32_t n_listed = 0, double gnow = 0.0, float4 carry = float4{0.f, 0.f, 0.f, 0.f}) {
     const int n = lane & 15, q = lane >> 4;
-    const bool listed = BOUNDS && p.rows != nullptr;
-    const int64_t row0 = BOUNDS ? 0 : (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows;
-    const int64_t myrow = BOUNDS ? (int64_t)row_in : row0 + n;  // (BOUNDS: the clamped row the lane loaded)
+    constexpr bool BYROW = BOUNDS || SPLIT;  // may walk listed rows
+    const bool listed = BYROW && p.rows != nullptr;
+    const int64_t row0 = BYROW ? 0 : (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows;
+    const int64_t myrow = BYROW ? (int64_t)row_in : row0 + n;  // (BYROW: the clamped row the lane loaded)
     const bool valid = listed ? (uint32_t)(tile * kRows + n) < n_listed
-                              : (BOUNDS ? (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows + n < p.N : myrow < p.N);
+                              : (BYROW ? (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows + n < p.N : myrow < p.N);
     const float* s_cnorm = (const float*)(smem + p.off_cnorm);
     float xn2 = nrm;
     xn2 += __shfl_xor(xn2, 16, kWave);
@@ -544,23 +550,23 @@ __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* 
     int idx;
     float dmin, first = 0.f, second = 0.f, bound = 0.f;
     bool reranked = false, deferred = false;
-    constexpr bool DEFER = !BOUNDS && !SPLIT && MODE == MODE_ASSIGN;
+    constexpr bool DEFER = MODE == MODE_ASSIGN;
     const int prev = p.delta_mode ? prev_in : -1;
-    if (DEFER)
-        rank_rows<KT, BF16, true>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, nullptr, nullptr, nullptr,
-                                  nullptr, 0, false, 0.f, 0, smem + p.off_queue, prev, &deferred);
-    else if (SPLIT)
-        rank_rows<KT, BF16>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, &first, nullptr, nullptr, nullptr,
-                            p.k_base, p.carry_in != nullptr, carry.x, __float_as_int(carry.y));
+    if (SPLIT)
+        rank_rows<KT, BF16, DEFER>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, &first, &second, &reranked, &bound,
+                                   p.k_base, p.carry_in != nullptr, carry.x, __float_as_int(carry.y), smem + p.off_queue, prev,
+                                   &deferred, -1, carry.z);
     else
-        rank_rows<KT, BF16>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, BOUNDS ? &first : nullptr,
-                            BOUNDS ? &second : nullptr, BOUNDS ? &reranked : nullptr, BOUNDS ? &bound : nullptr);
+        rank_rows<KT, BF16, DEFER>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, BOUNDS ? &first : nullptr,
+                                   BOUNDS ? &second : nullptr, BOUNDS ? &reranked : nullptr, BOUNDS ? &bound : nullptr, 0, false,
+                                   0.f, 0, smem + p.off_queue, prev, &deferred);
 #pragma unroll
     for (int t = 0; t < KT; t++) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     nrm = 0.f;
     const bool owner = q == 0 && valid && !deferred;
-    if (SPLIT && p.carry_out) {  // the first of the two launches: hand the pair on, nothing else
-        if (owner) p.carry_out[myrow] = float2{first, __int_as_float(idx)};
+    if (SPLIT && p.carry_out) {  // the first of the two launches: hand the pair on, nothing else (a row whose re-rank is
+        // put off has its cluster written again at the end of the workgroup's tiles, after a barrier)
+        if (q == 0 && valid) p.carry_out[myrow] = float4{first, __int_as_float(idx), second, 0.f};
         return;
     }
 
@@ -651,7 +657,7 @@ __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* 
         if (p.rep) atomicMin(&s_rep[idx], (unsigned long long)myrow);
         in_acc += (double)dmin;
     }
-    if (BOUNDS && p.expire && owner) {
+    if (BYROW && p.expire && owner) {
         // How far the centroids may drift before this row's nearest centroid can change: with e the error bound of
         // a score (the re-rank threshold, which bounds a difference of two scores, plus the rounding of |x|^2), the
         // nearest centroid is at most sqrt(|x|^2 + s1 + e) away and every other at least sqrt(|x|^2 + s2 - e).  A row
@@ -766,13 +772,16 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool MULTI = VAR == VAR_MULTI, BOUNDS = VAR == VAR_BOUNDS, SPLIT = VAR == VAR_SPLIT;
     if (p.skip_when_zero && *p.skip_when_zero == 0u) return;  // uniform over the grid, before any barrier
-    const bool listed = BOUNDS && p.rows != nullptr;
+    constexpr bool BYROW = BOUNDS || SPLIT;  // may walk listed rows
+    const bool listed = BYROW && p.rows != nullptr;
     const uint32_t n_listed = listed ? *p.n_rows : 0u;
-    const double gnow = (BOUNDS && p.gnow) ? *p.gnow : 0.0;
-    if (BOUNDS && p.evaluated_slot && blockIdx.x == 0 && threadIdx.x == 0)
+    const double gnow = (BYROW && p.gnow) ? *p.gnow : 0.0;
+    if (BYROW && p.evaluated_slot && blockIdx.x == 0 && threadIdx.x == 0)
         *p.evaluated_slot = listed ? (int32_t)n_listed : (int32_t)p.N;
-    // listed rows: a workgroup none of whose waves has a tile leaves before any barrier
-    if (listed && (uint32_t)blockIdx.x * (uint32_t)p.waves * kRows >= n_listed) return;
+    // listed rows: the tiles go to the workgroups in turn, so that a short list occupies one wave of every workgroup and
+    // not all waves of a few (65536 x 1000, K = 16, 3,300 listed rows: with that and the queue of near-tie rows 16 us a pass,
+    // 22 us before); a workgroup none of whose waves has a tile leaves before any barrier
+    if (listed && (uint32_t)blockIdx.x * kRows >= n_listed) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform: keeps tile math scalar
     constexpr int P = PASSES == 1 ? 1 : 2;
@@ -783,7 +792,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
 
     const int ntiles = listed ? (int)((n_listed + kRows - 1) / kRows) : (int)p.ntiles;
     const int tstride = (int)gridDim.x * p.waves;
-    const int tile0 = __builtin_amdgcn_readfirstlane((int)blockIdx.x * p.waves + wave);
+    const int tile0 = __builtin_amdgcn_readfirstlane(listed ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * p.waves + wave);
     int tl = tile0, cl = 0;  // load cursor
     float cmax_out;
     ChunkRegs<BF16> b0, b1, b2;
@@ -801,7 +810,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         const int nv = (p.N - row0) < kRows ? (int)(p.N - row0) : kRows;
         return (int)row0 + ((lane & 15) < nv ? (lane & 15) : nv - 1);  // (N is below 2^31 in these passes)
     };
-    if (BOUNDS) {
+    if (BYROW) {
         lrow = tile_row(tile0 < ntiles ? tile0 : 0);
         lrow_nx = tile_row(tile0 + tstride < ntiles ? tile0 + tstride : 0);
     }
@@ -810,14 +819,14 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
     // every wait instead of draining to one; measured, that was 2-5 % slower, not faster.)
 #define CAT_ISSUE(buf)                                                                     \
     if (tl < ntiles) {                                                                     \
-        if (BOUNDS)                                                                        \
-            load_chunk<BF16, 1, true>(buf, p, tl, cl, lane, lrow);                         \
+        if (BYROW)                                                                         \
+            load_chunk<BF16, SPLIT ? 3 : 1, true>(buf, p, tl, cl, lane, lrow);             \
         else                                                                               \
-            load_chunk<BF16, MODE == MODE_ASSIGN ? (MULTI ? 2 : SPLIT ? 3 : 1) : 0>(buf, p, tl, cl, lane); \
+            load_chunk<BF16, MODE == MODE_ASSIGN ? (MULTI ? 2 : 1) : 0>(buf, p, tl, cl, lane); \
         if (++cl == p.nchunks) {                                                           \
             cl = 0;                                                                        \
             tl += tstride;                                                                 \
-            if (BOUNDS) {                                                                  \
+            if (BYROW) {                                                                   \
                 lrow = lrow_nx;                                                            \
                 lrow_nx = tile_row(tl + tstride < ntiles ? tl + tstride : 0);              \
             }                                                                              \
@@ -889,7 +898,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
             s_rep[k] = ~0ull;
         }
         if (threadIdx.x == 0) s_misc[0] = 0;
-        if (VAR == VAR_PLAIN && MODE == MODE_ASSIGN && p.queue_cap > 0 && threadIdx.x == 0) *(int*)(smem + p.off_queue) = 0;
+        if (VAR != VAR_MULTI && MODE == MODE_ASSIGN && p.queue_cap > 0 && threadIdx.x == 0) *(int*)(smem + p.off_queue) = 0;
     }
     __syncthreads();
     {
@@ -926,7 +935,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         else if (BOUNDS)                                                                                       \
             finish_tile<KT, BF16, MODE, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow); \
         else if (SPLIT)                                                                                        \
-            finish_tile<KT, BF16, MODE, false, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, -1, 0, 0.0, buf.carry); \
+            finish_tile<KT, BF16, MODE, false, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow, buf.carry); \
         else                                                                                                   \
             finish_tile<KT, BF16, MODE>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev);                  \
         cc = 0;                                                                                                \
@@ -939,7 +948,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         // the operand travels global -> registers -> LDS while the current one is contracted.
         constexpr int chunkA = 4 * KT * P * 1024;
         constexpr int AREG = (chunkA / 16 + kMaxWaves * kWave - 1) / (kMaxWaves * kWave);
-        const int wg_tile0 = (int)blockIdx.x * p.waves;
+        const int wg_tile0 = listed ? (int)blockIdx.x : (int)blockIdx.x * p.waves;  // its first wave's: that wave has the most
         const int wg_tiles = wg_tile0 < ntiles ? (ntiles - 1 - wg_tile0) / tstride + 1 : 0;
         const int nsteps = wg_tiles * p.nchunks;
         int s = 0;
@@ -972,7 +981,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
                 else if (BOUNDS)                                                                              \
                     finish_tile<KT, BF16, MODE, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow); \
                 else if (SPLIT)                                                                               \
-                    finish_tile<KT, BF16, MODE, false, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, -1, 0, 0.0, bufcur.carry); \
+                    finish_tile<KT, BF16, MODE, false, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow, bufcur.carry); \
                 else                                                                                          \
                     finish_tile<KT, BF16, MODE>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev);      \
                 cc = 0;                                                                                       \
@@ -1022,13 +1031,13 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
 
     if (MODE != MODE_ASSIGN) return;
 
-    if (VAR == VAR_PLAIN && p.queue_cap > 0) {
+    if (VAR != VAR_MULTI && p.queue_cap > 0) {
         // the rows whose exact re-rank was put off: shared out over the waves, one row at a time
         __syncthreads();
         const int pushed = *(const int*)(smem + p.off_queue);
         const int qn = pushed < p.queue_cap ? pushed : p.queue_cap;
         const DeferredRow* qe = (const DeferredRow*)(smem + p.off_queue + 16);
-        for (int e = wave; e < qn; e += p.waves) finish_deferred<BF16>(p, smem, qe[e], lane, in_acc);
+        for (int e = wave; e < qn; e += p.waves) finish_deferred<BF16>(p, smem, qe[e], lane, in_acc, gnow);
     }
 
     // workgroup epilogue: counts, first rows, objective
