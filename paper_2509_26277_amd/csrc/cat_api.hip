@@ -11,6 +11,7 @@
 #include "cat_common.h"
 #include "cat_infer.h"
 #include "cat_tile.h"
+#include "cat_wide.h"
 
 namespace cat {
 
@@ -942,6 +943,14 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     if (which == 2 && !rowtile_ok)
         return set_error(CAT_ERR_UNSUPPORTED, "row-tile inference kernel forced but D=%lld K=%d dt=%d does not fit it",
                          (long long)D, (int)K, (int)dt);
+    // The streamed-operand kernel (every row read once, two-part ranking): where the row-tile kernel has no instance (us,
+    // 262144 x 2048 bf16, K = 64: 725 on the tile kernel, 690; 65536 x 1000, K = 128: 250, 180; 50021 x 1001, K = 50: 495 on
+    // the LDS kernel, 135), and instead of its one-part instance for rows of 2 .. 4 KB, which re-ranks whatever lies within
+    // 1.6 % of |x||c|, from some thousand rows on (65536 x 1000, K = 50 fitted: 136, 124; 8000 rows: 34, 27; 2000: 19, 21).
+    // Its one-part instance for rows of up to 2 KB and 65 .. 128 clusters keeps them: a third faster on separated rows.
+    const bool wide = wide_supported(N, D, K, dt) && (!rowtile_ok || (!infer_two_parts(D, K, dt) && D > 512 && N >= 4096));
+    if (path == CAT_PATH_AUTO && which == 0 && wide)
+        return wide_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st);
     if (rowtile_ok && path != CAT_PATH_STREAM && which != 1)
         return infer_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st);
     if (tile_ok && path != CAT_PATH_STREAM && w.split && which == 0) {

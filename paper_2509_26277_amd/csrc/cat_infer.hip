@@ -100,6 +100,11 @@ bool infer_supported(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     return N < ((int64_t)1 << 40) && infer_config(D, K, dt).ok;
 }
 
+bool infer_two_parts(int64_t D, int32_t K, cat_dtype dt) {
+    const InferCfg c = infer_config(D, K, dt);
+    return c.ok && kInst[c.inst].P == 2;
+}
+
 cat_status infer_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, const float* cent,
                        const float* gamma, const float* beta, void* corrected, int32_t* assign, const TileWs& ws,
                        hipStream_t st, bool out_bf16, double* inertia) {
