@@ -588,7 +588,7 @@ __global__ __launch_bounds__(kProjWaves * kWave) void k_pca_project(const T* __r
 //
 // FUSED: Algorithm 2 with the PCA front-end in one kernel (p <= 16 NT, K <= 256).  The scores of a tile stay
 // in registers; the centroids of score space go into the LDS the directions no longer need; every row takes the
-// centroid of smallest squared distance (direct form, doubles, lowest index on ties), and the wave then reads its
+// centroid of smallest squared distance (direct form, decided in doubles, lowest index on ties), and the wave then reads its
 // 16 rows once more, four at a time with 16-byte (bf16: 8-byte) loads, and writes the blended affine map.
 struct ProjFuse {
     const float* cz;     // K x p centroids in score space
@@ -724,25 +724,75 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
         }
         __syncthreads();
         if (tile >= ntiles) continue;
-        double dbest = __builtin_inf();
+        // fp32 distances first, four clusters at a time: lane g of a row ends with the sum for cluster k + g, and keeps its two
+        // smallest.  Their relative error is below 67 x 2^-24 = 4e-6 (p <= 64 terms), so only clusters within 1e-5 of the
+        // smallest can be the nearest one; where more than one is (that includes every cluster of a row whose distances
+        // overflow or are no numbers), the wave compares in doubles.  (All clusters of every row in doubles, against this, us per
+        // cat_apply_pca: 200000 x 256, K = p = 50: 194 -> 172; 2000000 x 160: 1555 -> 1278; 65536 x 1000 bf16, K = 200,
+        // p = 30: 160 -> 142; 65536 x 1000, K = p = 50: 215 -> 213, bound by the projection and the map.)
+        float d1 = __builtin_inff(), d2 = __builtin_inff();
         int kbest = 0;
-        for (int k = 0; k < f.K; k++) {
-            double d = 0.0;
+#pragma unroll 1
+        for (int k = 0; k < f.K; k += 4) {
+            float d[4];
 #pragma unroll
-            for (int t = 0; t < NT; t++) {
-                const f32x4_t cv = *(const f32x4_t*)&s_cz[k * CW + 16 * t + 4 * g];
-                const double d0 = (double)acc[t].x - (double)cv.x, d1 = (double)acc[t].y - (double)cv.y;
-                const double d2 = (double)acc[t].z - (double)cv.z, d3 = (double)acc[t].w - (double)cv.w;
-                d = fma(d0, d0, d);
-                d = fma(d1, d1, d);
-                d = fma(d2, d2, d);
-                d = fma(d3, d3, d);
+            for (int u = 0; u < 4; u++) {
+                const int ku = k + u < f.K ? k + u : k;
+                d[u] = 0.f;
+#pragma unroll
+                for (int t = 0; t < NT; t++) {
+                    const f32x4_t e = acc[t] - *(const f32x4_t*)&s_cz[ku * CW + 16 * t + 4 * g];
+                    d[u] = fmaf(e.x, e.x, d[u]);
+                    d[u] = fmaf(e.y, e.y, d[u]);
+                    d[u] = fmaf(e.z, e.z, d[u]);
+                    d[u] = fmaf(e.w, e.w, d[u]);
+                }
             }
-            d += __shfl_xor(d, 16, kWave);  // the four lanes of a row end with the same bits (addition commutes)
-            d += __shfl_xor(d, 32, kWave);
-            if (d < dbest) {
-                dbest = d;
-                kbest = k;
+            // lanes g and g ^ 2 exchange the halves they don't keep, then g and g ^ 1
+            const bool hi = g & 2, odd = g & 1;
+            const float p0 = (hi ? d[2] : d[0]) + __shfl_xor(hi ? d[0] : d[2], 32, kWave);
+            const float p1 = (hi ? d[3] : d[1]) + __shfl_xor(hi ? d[1] : d[3], 32, kWave);
+            const float v = (odd ? p1 : p0) + __shfl_xor(odd ? p0 : p1, 16, kWave);
+            if (k + g < f.K) {
+                if (v < d1) {
+                    d2 = d1;
+                    d1 = v;
+                    kbest = k + g;
+                } else if (!(v >= d2)) {
+                    d2 = v;
+                }
+            }
+        }
+        float dm = fminf(d1, __shfl_xor(d1, 16, kWave));
+        dm = fminf(dm, __shfl_xor(dm, 32, kWave));
+        const float lim = fmaf(dm, 1.00001f, 1e-35f);
+        int cand = (!(d1 > lim) ? 1 : 0) + (!(d2 > lim) ? 1 : 0);
+        cand += __shfl_xor(cand, 16, kWave);
+        cand += __shfl_xor(cand, 32, kWave);
+        if (!(d1 <= lim)) kbest = 0x7fffffff;
+        kbest = min(kbest, __shfl_xor(kbest, 16, kWave));
+        kbest = min(kbest, __shfl_xor(kbest, 32, kWave));
+        if (__ballot(cand != 1)) {
+            double dbest = __builtin_inf();
+            kbest = 0;
+            for (int k = 0; k < f.K; k++) {
+                double d = 0.0;
+#pragma unroll
+                for (int t = 0; t < NT; t++) {
+                    const f32x4_t cv = *(const f32x4_t*)&s_cz[k * CW + 16 * t + 4 * g];
+                    const double d0 = (double)acc[t].x - (double)cv.x, d1 = (double)acc[t].y - (double)cv.y;
+                    const double d2 = (double)acc[t].z - (double)cv.z, d3 = (double)acc[t].w - (double)cv.w;
+                    d = fma(d0, d0, d);
+                    d = fma(d1, d1, d);
+                    d = fma(d2, d2, d);
+                    d = fma(d3, d3, d);
+                }
+                d += __shfl_xor(d, 16, kWave);  // the four lanes of a row end with the same bits (addition commutes)
+                d += __shfl_xor(d, 32, kWave);
+                if (d < dbest) {
+                    dbest = d;
+                    kbest = k;
+                }
             }
         }
         if (f.assign && g == 0 && row < N) f.assign[row] = kbest;
