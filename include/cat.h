@@ -128,7 +128,7 @@ size_t cat_apply_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt);
  *                 1e-4 of the sum where the rows are as far from their centroid as from the
  *                 origin, a larger share of it where the data sit far from the origin
  *                 compared with their spread.  The assignments do not depend on it.
- *                 On matrices of 32 MB and more a pass leaves out the rows whose distance
+ *                 On matrices of 64 MB and more (32 MB with K > 128) a pass leaves out the rows whose distance
  *                 bounds (cat_fit_bounds) say that they keep their centroid; from pass 3 on the
  *                 objective then is that of pass 2 plus the change of
  *                 sum_k c_k . (n_k c_k - 2 S_k), S_k the cluster sums, in double precision.

@@ -406,10 +406,14 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
 // A row evaluated without a margin has expire = the drift of that pass and is kept as soon as any centroid moves at all
 // (the drift then grows, by its last bit at least); while none moves its nearest centroid is what it was.  A margin is
 // rounded down by 1e-9 of itself, so a drift equal to expire has not used it up.
-// Matrices below this size keep the plain loop in the plain fits: a pass over them is launches and dependent steps, to
-// which the selection of the rows adds one (4096 x 64, K = 4: a pass of 16.6 us gains nothing from the 85 % of the
-// rows it need not read and pays 4.3 us).
-constexpr double kBoundsBytes = 32.0 * 1024 * 1024;
+// Matrices below these sizes keep the plain loop in the plain fits: a pass over them is launches and dependent steps, to
+// which the selection of the rows adds one of 5 us.  One launch per pass, us per cat_fit of 15 to 20 iterations, plain ->
+// with bounds: logits 16384 x 1000 (62 MB) 695 -> 522, 32768 x 1000 878 -> 388; features 32768 x 256 (32 MB) 490 -> 534,
+// 65536 x 256 (64 MB) 615 -> 545; mixture 131072 x 64 (32 MB) 704 -> 697, 65536 x 256 645 -> 307.  Components that overlap
+// until the end, so that no row can be left out: bf16 16384 x 1024 (32 MB) 701 -> 820, 65536 x 1024 (128 MB) 1138 -> 1225,
+// 131072 x 1024 1771 -> 1764.  A pass of two launches (K > 128) costs more, and the selection less of it: logits 16384 x 1000,
+// K = 200 (62 MB) 2267 -> 793; overlapping 32768 x 512 (64 MB) 1932 -> 2005.
+constexpr double kBoundsBytes = 64.0 * 1024 * 1024, kBoundsBytesSplit = 32.0 * 1024 * 1024;
 constexpr int kSelThreads = 256;
 constexpr int kSelPerThread = 8;
 __global__ __launch_bounds__(kSelThreads) void k_bound_select(const double* __restrict__ move_part, int32_t slices, int32_t K,
@@ -660,8 +664,9 @@ bool tile_bounds_supports(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
 }
 bool tile_bounds_pay(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     const double bytes = (double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0);
-    if (bytes < kBoundsBytes || N >= ((int64_t)1 << 31)) return false;
-    return tile_config(TILE_LLOYD, D, K, dt, true).ok || split_config(D, K, dt, nullptr);
+    if (bytes < kBoundsBytesSplit || N >= ((int64_t)1 << 31)) return false;
+    if (tile_config(TILE_LLOYD, D, K, dt, true).ok) return bytes >= kBoundsBytes;
+    return split_config(D, K, dt, nullptr);
 }
 size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K) {
     const size_t sk = (size_t)delta_slices(D) * (size_t)K;

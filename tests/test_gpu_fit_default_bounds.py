@@ -1,5 +1,5 @@
-"""cat_fit on matrices large enough for its loop to leave rows out by distance bounds (from 32 MB on), against the loop that
-evaluates every row (cat_fit_early_stop: the same outputs by contract, no bounds).
+"""cat_fit on matrices large enough for its loop to leave rows out by distance bounds (from 64 MB on; 32 MB with two launches
+per pass), against the loop that evaluates every row (cat_fit_early_stop: the same outputs by contract, no bounds).
 
 Centroids, assignments and counts are the same bit for bit.  The objective of the plain loop is a sum of float32 terms
 |x|^2 + score (relative error of a term up to about 1e-4 |x||c| over the distance, far less in the sum); cat_fit takes the
@@ -34,17 +34,17 @@ def _same(a, b, what=""):
 
 
 SHAPES = [
-    (34000, 256, 9, 8, "f32", 1.0),
-    (66000, 130, 31, 6, "f32", 0.5),     # not a whole number of 16-byte groups: the loop runs on a padded copy
-    (9000, 1000, 48, 9, "f32", 0.3),     # chunked operand, overlapping components: rows keep moving
-    (17000, 1024, 64, 7, "bf16", 0.5),
-    (132000, 64, 17, 4, "f32", 1.0),     # one pass over listed rows before the last
-    (132000, 64, 5, 3, "f32", 1.0),      # too few iterations: the plain loop
+    (68000, 256, 9, 8, "f32", 1.0),
+    (130000, 130, 31, 6, "f32", 0.5),    # not a whole number of 16-byte groups: the loop runs on a padded copy
+    (17000, 1000, 48, 9, "f32", 0.3),     # chunked operand, overlapping components: rows keep moving
+    (33000, 1024, 64, 7, "bf16", 0.5),
+    (264000, 64, 17, 4, "f32", 1.0),     # one pass over listed rows before the last
+    (264000, 64, 5, 3, "f32", 1.0),      # too few iterations: the plain loop
     (33000, 256, 150, 7, "f32", 0.4),    # two launches per pass
     (9100, 1001, 200, 6, "f32", 0.3),    # two launches per pass, on a padded copy
     (20000, 840, 256, 5, "bf16", 0.3),
-    (40000, 256, 1, 5, "f32", 1.0),      # one cluster
-    (140000, 64, 250, 5, "f32", 0.5),    # 16 cluster tiles in one launch
+    (66000, 256, 1, 5, "f32", 1.0),      # one cluster
+    (264000, 64, 250, 5, "f32", 0.5),    # 16 cluster tiles in one launch
 ]
 
 
@@ -65,13 +65,13 @@ def test_duplicates_empty_clusters_and_exact_ties():
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
     base = torch.randint(-3, 4, (8, 64), generator=g, device="cuda").float()
-    x = base.repeat_interleave(17000, 0).contiguous()
+    x = base.repeat_interleave(34000, 0).contiguous()
     y = (x * 1.5 + 0.25).contiguous()
     for K in (3, 20, 140):
         _same(cat_fit(x, y, K, 6, seed=K), cat_fit(x, y, K, 6, seed=K, early_stop=True), K)
 
 
-@pytest.mark.parametrize("N,D,K,dt", [(34000, 256, 9, "f32"), (17000, 1024, 64, "bf16"), (33000, 256, 150, "f32")])
+@pytest.mark.parametrize("N,D,K,dt", [(68000, 256, 9, "f32"), (33000, 1024, 64, "bf16"), (33000, 256, 150, "f32")])
 def test_results_do_not_depend_on_the_list_and_queue_capacities(N, D, K, dt):
     x, y = _rows(11, N, D, max(2, K // 3), dt, 0.3)
     want = cat_fit(x, y, K, 7, seed=2)
@@ -86,7 +86,7 @@ def test_results_do_not_depend_on_the_list_and_queue_capacities(N, D, K, dt):
 
 
 def test_restarts_and_the_process_wide_early_stop():
-    x, y = _rows(4, 34000, 256, 6, "f32", 0.5)
+    x, y = _rows(4, 68000, 256, 6, "f32", 0.5)
     r = cat_fit_restarts(x, y, 9, 8, seed=3, restarts=3)
     best = int(r["best_run"])
     _same(r, cat_fit(x, y, 9, 8, seed=3 + best, early_stop=True))
@@ -100,7 +100,7 @@ def test_restarts_and_the_process_wide_early_stop():
 
 def test_captures_into_a_hip_graph_and_replays():
     """which rows a pass evaluates is decided on the device: one graph, different inputs"""
-    N, D, K, iters = 34000, 256, 9, 6
+    N, D, K, iters = 68000, 256, 9, 6
     x, y = _rows(1, N, D, 4, "f32", 0.5)
     ws = torch.empty(binding.cat_fit_workspace_bytes(N, D, K), dtype=torch.uint8, device="cuda")
     cat_fit(x, y, K, iters, seed=1, workspace=ws)  # kernels loaded before the capture
@@ -119,10 +119,10 @@ def test_captures_into_a_hip_graph_and_replays():
 
 
 def test_non_finite_rows_leave_the_others_alone():
-    x, y = _rows(9, 34000, 256, 5, "f32", 2.0)
+    x, y = _rows(9, 68000, 256, 5, "f32", 2.0)
     x[100] = float("nan")
     x[20000, 7] = float("inf")
     r = cat_fit(x, y, 6, 6, seed=1)
     torch.cuda.synchronize()
     a = r["assignments"]
-    assert int(a.min()) >= 0 and int(a.max()) < 6 and int(r["counts"].sum()) == 34000
+    assert int(a.min()) >= 0 and int(a.max()) < 6 and int(r["counts"].sum()) == 68000
