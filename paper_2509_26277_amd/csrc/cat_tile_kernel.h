@@ -532,12 +532,13 @@ __device__ __forceinline__ void finish_deferred(const TileParams& p, unsigned ch
 // BOUNDS: the pass also leaves the row's distance bound (TileParams::expire); with listed rows (row_in >= 0 is the
 // number of row n, n_listed their count) the tile is 16 entries of the list instead of 16 consecutive rows.
 // SPLIT: the clusters of the pass are ranked by two launches (TileParams::carry_in / carry_out).
-template <int KT, bool BF16, int MODE, bool BOUNDS = false, bool SPLIT = false>
+// ROWS: the pass may walk a list of rows.
+template <int KT, bool BF16, int MODE, bool BOUNDS = false, bool SPLIT = false, bool ROWS = BOUNDS>
 __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* smem, f32x4 (&acc)[KT], float& nrm,
                                             int tile, int lane, float cmax, double& in_acc, int prev_in, int row_in = -1,
                                             uint32_t n_listed = 0, double gnow = 0.0, float4 carry = float4{0.f, 0.f, 0.f, 0.f}) {
     const int n = lane & 15, q = lane >> 4;
-    constexpr bool BYROW = BOUNDS || SPLIT;  // may walk listed rows
+    constexpr bool BYROW = ROWS;
     const bool listed = BYROW && p.rows != nullptr;
     const int64_t row0 = BYROW ? 0 : (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows;
     const int64_t myrow = BYROW ? (int64_t)row_in : row0 + n;  // (BYROW: the clamped row the lane loaded)
@@ -550,7 +551,7 @@ __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* 
     int idx;
     float dmin, first = 0.f, second = 0.f, bound = 0.f;
     bool reranked = false, deferred = false;
-    constexpr bool DEFER = MODE == MODE_ASSIGN;
+    constexpr bool DEFER = MODE == MODE_ASSIGN && !(SPLIT && !ROWS);
     const int prev = p.delta_mode ? prev_in : -1;
     if (SPLIT)
         rank_rows<KT, BF16, DEFER>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, &first, &second, &reranked, &bound,
@@ -766,13 +767,15 @@ __device__ __forceinline__ void finish_tile_multi(const TileParams& p, unsigned 
 // VAR: 0 the plain pass, 1 several centroid sets side by side (finish_tile_multi), 2 a pass that keeps distance
 // bounds and may walk a list of rows instead of all of them (TileParams::expire, rows), 3 one of the two launches
 // that rank the halves of a large cluster set (TileParams::carry_in, carry_out).
-enum { VAR_PLAIN = 0, VAR_MULTI = 1, VAR_BOUNDS = 2, VAR_SPLIT = 3 };
+// 4 the same where the pass keeps bounds or walks a list (100000 x 512 bf16, K = 200 without either: 191 us in variant 3, 217 in
+// variant 4).
+enum { VAR_PLAIN = 0, VAR_MULTI = 1, VAR_BOUNDS = 2, VAR_SPLIT = 3, VAR_SPLIT_ROWS = 4 };
 template <int KT, int PASSES, bool BF16, int MODE, bool CA, int VAR = VAR_PLAIN>
 __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr bool MULTI = VAR == VAR_MULTI, BOUNDS = VAR == VAR_BOUNDS, SPLIT = VAR == VAR_SPLIT;
+    constexpr bool MULTI = VAR == VAR_MULTI, BOUNDS = VAR == VAR_BOUNDS, SPLIT = VAR == VAR_SPLIT || VAR == VAR_SPLIT_ROWS;
     if (p.skip_when_zero && *p.skip_when_zero == 0u) return;  // uniform over the grid, before any barrier
-    constexpr bool BYROW = BOUNDS || SPLIT;  // may walk listed rows
+    constexpr bool BYROW = BOUNDS || VAR == VAR_SPLIT_ROWS;  // may walk listed rows
     const bool listed = BYROW && p.rows != nullptr;
     const uint32_t n_listed = listed ? *p.n_rows : 0u;
     const double gnow = (BYROW && p.gnow) ? *p.gnow : 0.0;
@@ -822,7 +825,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         if (BYROW)                                                                         \
             load_chunk<BF16, SPLIT ? 3 : 1, true>(buf, p, tl, cl, lane, lrow);             \
         else                                                                               \
-            load_chunk<BF16, MODE == MODE_ASSIGN ? (MULTI ? 2 : 1) : 0>(buf, p, tl, cl, lane); \
+            load_chunk<BF16, MODE == MODE_ASSIGN ? (MULTI ? 2 : SPLIT ? 3 : 1) : 0>(buf, p, tl, cl, lane); \
         if (++cl == p.nchunks) {                                                           \
             cl = 0;                                                                        \
             tl += tstride;                                                                 \
@@ -935,7 +938,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         else if (BOUNDS)                                                                                       \
             finish_tile<KT, BF16, MODE, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow); \
         else if (SPLIT)                                                                                        \
-            finish_tile<KT, BF16, MODE, false, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow, buf.carry); \
+            finish_tile<KT, BF16, MODE, false, true, BYROW>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow, buf.carry); \
         else                                                                                                   \
             finish_tile<KT, BF16, MODE>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev);                  \
         cc = 0;                                                                                                \
@@ -981,7 +984,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
                 else if (BOUNDS)                                                                              \
                     finish_tile<KT, BF16, MODE, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow); \
                 else if (SPLIT)                                                                               \
-                    finish_tile<KT, BF16, MODE, false, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow, bufcur.carry); \
+                    finish_tile<KT, BF16, MODE, false, true, BYROW>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow, bufcur.carry); \
                 else                                                                                          \
                     finish_tile<KT, BF16, MODE>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev);      \
                 cc = 0;                                                                                       \
@@ -1152,6 +1155,9 @@ static inline cat_status launch_kt_bounds(const TileParams& p, const TileCfg& c,
 template <bool BF16>
 static inline cat_status launch_split(const TileParams& p, const TileCfg& c, hipStream_t st) {
     if (c.KT != 8 || c.P != 2) return set_error(CAT_ERR_UNSUPPORTED, "split ranking: 8 cluster tiles and the two-part operand only");
+    if (p.rows || p.expire)
+        return c.chunked ? launch_one<8, 3, BF16, MODE_ASSIGN, true, VAR_SPLIT_ROWS>(p, c, st)
+                         : launch_one<8, 3, BF16, MODE_ASSIGN, false, VAR_SPLIT_ROWS>(p, c, st);
     if (c.chunked) return launch_one<8, 3, BF16, MODE_ASSIGN, true, VAR_SPLIT>(p, c, st);
     return launch_one<8, 3, BF16, MODE_ASSIGN, false, VAR_SPLIT>(p, c, st);
 }
