@@ -157,10 +157,10 @@ cat_status cat_fit(const void *lq, const void *fp, int64_t N, int64_t D, int32_t
  *                 whole 16-byte groups where no padded copy is made) run every pass and report 0.
  * Other arguments, workspace and errors: as cat_fit.
  *
- * cat_allow_early_stop(on != 0) lets every Lloyd loop the library runs stop in the same way
- * (cat_fit, each run of cat_fit_restarts, the clustering of the scores in cat_fit_pca), without
- * the count of passes left out; their outputs do not change.  Process-wide, default off; returns
- * CAT_OK.
+ * The other Lloyd loops of the library (cat_fit, each run of cat_fit_restarts, the clustering of
+ * the scores in cat_fit_pca) stop in the same way by themselves, without the count of passes left
+ * out, or leave out rows instead (see cat_fit); their outputs are those of the full loop.
+ * cat_allow_early_stop, which used to ask for that, changes nothing any more and returns CAT_OK.
  */
 cat_status cat_allow_early_stop(int on);
 cat_status cat_fit_early_stop(const void *lq, const void *fp, int64_t N, int64_t D, int32_t K,

@@ -181,7 +181,7 @@ def select_path(path):
 
 
 def allow_early_stop(on):
-    """Let every Lloyd loop of the library leave out the passes after the partition has stopped changing (same outputs)."""
+    """No effect any more: the Lloyd loops leave out the passes after the partition has stopped changing by themselves."""
     _check(load_library().cat_allow_early_stop(1 if on else 0))
 
 

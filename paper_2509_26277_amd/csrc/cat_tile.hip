@@ -953,7 +953,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     p.cent = cent_io;
     p.assign = assign;
     if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D) * 4, st));
-    if (skipped) CAT_T(launch_fill_zero(skipped, sizeof(int32_t), st));
+    if (skipped && skipped != lw.skipped) CAT_T(launch_fill_zero(skipped, sizeof(int32_t), st));  // (that word is one of ctrl's)
     if (bw && bw->evaluated) CAT_T(launch_fill_i32(bw->evaluated, (int64_t)iters + 1, (int32_t)N, st));
     if (bounds) CAT_T(launch_fill_zero(bw->drift, 4 * sizeof(double), st));
     // Passes 0 and 1 are each followed by a full segmented sum: after the first reassignment most
