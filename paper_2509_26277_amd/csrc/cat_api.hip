@@ -929,8 +929,9 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     CAT_TRY(check_ws(who, workspace, workspace_bytes, w.bytes));
     const float* g = gamma;
     const float* b = beta;
-    if (alpha != 1.0f) {
-        CAT_TRY(launch_fold_alpha(gamma, beta, alpha, w.g_eff, w.b_eff, (int64_t)K * D, st));
+    const FoldAlpha fa = {gamma, beta, alpha, w.g_eff, w.b_eff, (int64_t)K * D};
+    const FoldAlpha* fold = alpha != 1.0f ? &fa : nullptr;
+    if (fold) {
         g = w.g_eff;
         b = w.b_eff;
     }
@@ -953,9 +954,10 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     // Its one-part instance for rows of up to 2 KB and 65 .. 128 clusters keeps them: a third faster on separated rows.
     const bool wide = wide_supported(N, D, K, dt) && (!rowtile_ok || (!infer_two_parts(D, K, dt) && D > 512 && N >= 4096));
     if (path == CAT_PATH_AUTO && which == 0 && wide)
-        return wide_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st);
+        return wide_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st, fold);
     if (rowtile_ok && path != CAT_PATH_STREAM && which != 1)
-        return infer_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st);
+        return infer_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st, false, nullptr, fold);
+    if (fold) CAT_TRY(launch_fold_alpha(gamma, beta, alpha, w.g_eff, w.b_eff, (int64_t)K * D, st));
     if (tile_ok && path != CAT_PATH_STREAM && w.split && which == 0) {
         // more than 128 clusters: ranked by two launches of 8 cluster tiles, then mapped by the labels (the fused
         // 16-tile kernel ranks with the one-part operand and re-ranks most rows: several times slower)

@@ -96,6 +96,15 @@ cat_status set_error(cat_status st, const char* fmt, ...);
 // ---- streaming kernels (cat_stream.hip) ------------------------------------------
 // Every launcher enqueues on `st` and returns a status; none synchronises.
 cat_status launch_fill_zero(void* p, size_t bytes, hipStream_t st);
+// gamma and beta with the blending coefficient folded in: 1 + alpha (gamma - 1) and alpha beta, n entries each
+struct FoldAlpha {
+    const float* gamma;
+    const float* beta;
+    float alpha;
+    float* g;
+    float* b;
+    int64_t n;
+};
 cat_status launch_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t* idx, hipStream_t st);
 cat_status launch_gather_rows(const void* lq, cat_dtype dt, int64_t D, int32_t K, const int64_t* idx,
                               float* out, hipStream_t st);

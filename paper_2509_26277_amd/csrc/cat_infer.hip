@@ -7,7 +7,8 @@ namespace cat {
 
 // centroid preparation shared with the tile kernels (cat_tile.hip)
 cat_status launch_tile_prep_plain(cat_dtype dt, const float* cent, int64_t D, int32_t K, int32_t KT, int32_t P,
-                                  int32_t nchunks, int rows_layout_f32, uint16_t* packA, float* cnorm, hipStream_t st);
+                                  int32_t nchunks, int rows_layout_f32, uint16_t* packA, float* cnorm, hipStream_t st,
+                                  const FoldAlpha* fold);
 
 namespace {
 
@@ -107,7 +108,7 @@ bool infer_two_parts(int64_t D, int32_t K, cat_dtype dt) {
 
 cat_status infer_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, const float* cent,
                        const float* gamma, const float* beta, void* corrected, int32_t* assign, const TileWs& ws,
-                       hipStream_t st, bool out_bf16, double* inertia) {
+                       hipStream_t st, bool out_bf16, double* inertia, const FoldAlpha* fold) {
     const InferCfg c = infer_config(D, K, dt);
     if (!c.ok) return set_error(CAT_ERR_UNSUPPORTED, "row-tile inference kernel does not fit D=%lld K=%d", (long long)D, (int)K);
     const Inst& in = kInst[c.inst];
@@ -119,7 +120,7 @@ cat_status infer_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32
         cw = ws.cent;
     }
     const int nchunks = (int)((D + 127) / 128);
-    cat_status s = launch_tile_prep_plain(dt, cw, D, K, c.KT, in.P, nchunks, 0, ws.packA, ws.cnorm, st);
+    cat_status s = launch_tile_prep_plain(dt, cw, D, K, c.KT, in.P, nchunks, 0, ws.packA, ws.cnorm, st, fold);
     if (s != CAT_OK) return s;
     InferParams p = {};
     p.lq = lq;

@@ -5,7 +5,8 @@ namespace cat {
 
 // centroid preparation shared with the tile kernels (cat_tile.hip)
 cat_status launch_tile_prep_plain(cat_dtype dt, const float* cent, int64_t D, int32_t K, int32_t KT, int32_t P,
-                                  int32_t nchunks, int rows_layout, uint16_t* packA, float* cnorm, hipStream_t st);
+                                  int32_t nchunks, int rows_layout, uint16_t* packA, float* cnorm, hipStream_t st,
+                                  const FoldAlpha* fold);
 
 namespace {
 
@@ -44,7 +45,8 @@ bool wide_supported(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
 }
 
 cat_status wide_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, const float* cent, const float* gamma,
-                      const float* beta, void* corrected, int32_t* assign, const TileWs& ws, hipStream_t st) {
+                      const float* beta, void* corrected, int32_t* assign, const TileWs& ws, hipStream_t st,
+                      const FoldAlpha* fold) {
     const int inst = wide_instance(D, K, dt);
     if (inst < 0 || !corrected)
         return set_error(CAT_ERR_UNSUPPORTED, "streamed-operand inference does not fit D=%lld K=%d", (long long)D, (int)K);
@@ -58,7 +60,7 @@ cat_status wide_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
         cw = ws.cent;
     }
     const int nchunks = (int)((D + 127) / 128);
-    cat_status s = launch_tile_prep_plain(dt, cw, D, K, in.KT, 2, nchunks, 0, ws.packA, ws.cnorm, st);
+    cat_status s = launch_tile_prep_plain(dt, cw, D, K, in.KT, 2, nchunks, 0, ws.packA, ws.cnorm, st, fold);
     if (s != CAT_OK) return s;
     WideParams p = {};
     p.lq = lq;
