@@ -952,7 +952,15 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     // the LDS kernel, 135), and instead of its one-part instance for rows of 2 .. 4 KB, which re-ranks whatever lies within
     // 1.6 % of |x||c|, from some thousand rows on (65536 x 1000, K = 50 fitted: 136, 124; 8000 rows: 34, 27; 2000: 19, 21).
     // Its one-part instance for rows of up to 2 KB and 65 .. 128 clusters keeps them: a third faster on separated rows.
-    const bool wide = wide_supported(N, D, K, dt) && (!rowtile_ok || (!infer_two_parts(D, K, dt) && D > 512 && N >= 4096));
+    // The tile kernel keeps short rows, where the streamed operand outweighs the second read (400000 x 128 bf16, K = 100: 182
+    // against 236 here; 200000 x 256: 116, 130; 400000 x 64, K = 256: 225, 641; 100000 x 256, K = 200: 116 .. 130, 127 .. 140; x 300
+    // the other way: 215 .. 236, 147 .. 153; 200000 x 512 bf16, K = 90: 200, 148; 100000 x 512, K = 200: 178 .. 191, 185), and of the longer bf16
+    // rows those of few clusters (60000 x 1200, K = 10: 83, 87) and the longest ones of many (60000 x 2048, K = 100: 226, 267):
+    // as long as it ranks them with two parts, in one launch or in two (one part: 60000 x 1500, K = 100: 1087 .. 8192, 213).
+    const bool tile_two = tile_ok && (w.split || tile_two_parts(TILE_APPLY, D, K, dt));
+    const bool tile_keeps = tile_two && (D <= 256 || (dt == CAT_BF16 && (K <= 16 || (K > 64 && D > 1536))));
+    const bool wide = wide_supported(N, D, K, dt) && !tile_keeps &&
+                      (!rowtile_ok || (!infer_two_parts(D, K, dt) && D > 512 && N >= 4096));
     if (path == CAT_PATH_AUTO && which == 0 && wide)
         return wide_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st, fold);
     if (rowtile_ok && path != CAT_PATH_STREAM && which != 1)

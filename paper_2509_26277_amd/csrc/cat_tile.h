@@ -67,6 +67,8 @@ size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K);
 BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K);
 bool tile_bounds_supports(int64_t N, int64_t D, int32_t K, cat_dtype dt);
 // Whether the plain fits run their loop with bounds (record): the shape allows it and the passes are long enough.
+// Whether one launch of the kernel ranks this shape with the two-part operand.
+bool tile_two_parts(TileMode mode, int64_t D, int32_t K, cat_dtype dt);
 bool tile_bounds_pay(int64_t N, int64_t D, int32_t K, cat_dtype dt);
 cat_status launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 

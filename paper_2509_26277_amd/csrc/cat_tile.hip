@@ -723,6 +723,10 @@ static bool split_config(int64_t D, int32_t K, cat_dtype dt, TileCfg* out, TileM
     return true;
 }
 
+bool tile_two_parts(TileMode mode, int64_t D, int32_t K, cat_dtype dt) {
+    const TileCfg c = tile_config(mode, D, K, dt);
+    return c.ok && c.P == 2;
+}
 bool tile_bounds_supports(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     // row numbers in the list of rows are 32-bit; the bounds are derived for the two-part operand
     return N < ((int64_t)1 << 31) && tile_config(TILE_LLOYD, D, K, dt, true).ok;
