@@ -74,10 +74,10 @@ cat_status launch_copy_cols(const float* src, int64_t rows, int32_t src_ld, floa
 }
 
 // dst (rows x dst_ld) <- the first dst_ld columns of src (rows x src_ld), zeros where src has none (fp32 or 16-bit elements)
-// One wave per row, in 4-byte words (bf16 rows have an even number of channels): rows that are not whole 16-byte groups
-// start anywhere on a word, so a wave instruction covers 256 consecutive bytes of the row instead of a lane 16 of them.
-// Bound by memory, a read and a write of the matrix: 50021 x 1001 to 1004 floats, 126 us with an element and a 64-bit
-// division per thread.
+// In 4-byte words (bf16 rows have an even number of channels).  Rows of more than kPadFlat words: one wave per row; rows
+// that are not whole 16-byte groups start anywhere on a word, so a wave instruction covers 256 consecutive bytes of the
+// row instead of a lane 16 of them.  Bound by memory, a read and a write of the matrix: 50021 x 1001 to 1004 floats, 126 us
+// with an element and a 64-bit division per thread, 68 us so.
 constexpr int kPadWaves = 4;
 __global__ __launch_bounds__(kPadWaves * kWave) void k_pad_words(const uint32_t* __restrict__ src, int64_t rows, int64_t src_w,
                                                                  int64_t dst_w, uint32_t* __restrict__ dst) {
@@ -102,14 +102,60 @@ __global__ __launch_bounds__(kPadWaves * kWave) void k_pad_words(const uint32_t*
         }
     }
 }
+// Short rows leave most of a wave idle that way (879,482 x 28 bf16: 116 us, 46 us with an element per thread).  Here the
+// output words are taken in order whatever row they are in, 512 consecutive ones per wave and round: 17 us there (a fit of 9 iterations 1266 -> 1190).  The row of a
+// word comes from a multiplication (exact below 2^16 for divisors up to kPadFlat), the start of a round from the one before.
+constexpr int kPadFlat = 192;
+constexpr int kPadU = 8;
+__global__ __launch_bounds__(kPadWaves * kWave) void k_pad_flat(const uint32_t* __restrict__ src, int64_t rows, uint32_t src_w,
+                                                                uint32_t dst_w, uint32_t inv, uint32_t* __restrict__ dst) {
+    constexpr uint32_t W = kPadU * kWave;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t n = rows * dst_w, step = (int64_t)gridDim.x * kPadWaves * W;
+    int64_t i0 = ((int64_t)blockIdx.x * kPadWaves + threadIdx.x / kWave) * W;
+    int64_t r0 = i0 / dst_w;
+    uint32_t c0 = (uint32_t)(i0 - r0 * dst_w);
+    const int64_t rstep = step / dst_w;
+    const uint32_t cstep = (uint32_t)(step - rstep * dst_w);
+    for (; i0 < n; i0 += step) {
+        uint32_t v[kPadU];
+#pragma unroll
+        for (int u = 0; u < kPadU; u++) {
+            const uint32_t c = c0 + lane + u * kWave, q = __umulhi(c, inv), cc = c - q * dst_w;
+            const int64_t r = r0 + q < rows ? r0 + q : rows - 1;
+            const uint32_t w = src[r * src_w + (cc < src_w ? cc : src_w - 1)];
+            v[u] = cc < src_w ? w : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kPadU; u++) {
+            const int64_t i = i0 + lane + u * kWave;
+            if (i < n) dst[i] = v[u];
+        }
+        r0 += rstep;
+        c0 += cstep;
+        if (c0 >= dst_w) {
+            c0 -= dst_w;
+            r0++;
+        }
+    }
+}
 cat_status launch_pad_rows(const void* src, cat_dtype dt, int64_t rows, int64_t src_ld, int64_t dst_ld, void* dst, hipStream_t st) {
     if (rows * dst_ld == 0) return CAT_OK;
     const int64_t per = dt == CAT_F32 ? 1 : 2;
     if (src_ld % per || dst_ld % per) return set_error(CAT_ERR_INVALID_ARG, "row copy: rows of whole 4-byte words only");
+    const int64_t src_w = src_ld / per, dst_w = dst_ld / per;
+    if (dst_w > 1 && dst_w <= kPadFlat) {
+        int64_t blocks = (rows * dst_w + kPadWaves * kPadU * kWave - 1) / (kPadWaves * kPadU * kWave);
+        blocks = blocks > 2048 ? 2048 : blocks;
+        hipLaunchKernelGGL(k_pad_flat, dim3((unsigned)blocks), dim3(kPadWaves * kWave), 0, st, (const uint32_t*)src, rows, (uint32_t)src_w,
+                           (uint32_t)dst_w, 0xFFFFFFFFu / (uint32_t)dst_w + 1u, (uint32_t*)dst);
+        CAT_LAUNCH_CHECK("k_pad_flat");
+        return CAT_OK;
+    }
     int64_t blocks = (rows + kPadWaves - 1) / kPadWaves;
     blocks = blocks > (1 << 16) ? (1 << 16) : blocks;
-    hipLaunchKernelGGL(k_pad_words, dim3((unsigned)blocks), dim3(kPadWaves * kWave), 0, st, (const uint32_t*)src, rows, src_ld / per,
-                       dst_ld / per, (uint32_t*)dst);
+    hipLaunchKernelGGL(k_pad_words, dim3((unsigned)blocks), dim3(kPadWaves * kWave), 0, st, (const uint32_t*)src, rows, src_w, dst_w,
+                       (uint32_t*)dst);
     CAT_LAUNCH_CHECK("k_pad_words");
     return CAT_OK;
 }

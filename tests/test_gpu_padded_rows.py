@@ -74,6 +74,21 @@ def test_fit_on_the_copy_matches_the_oracle_and_the_streaming_kernels(N, D, K, i
         _against_oracle(s, o, x, dt, "streaming kernels")
 
 
+@pytest.mark.parametrize("N,D,K,dt", [
+    (700, 189, 4, "f32"),      # 192 words per padded row: the last length the copy takes word by word across rows
+    (700, 193, 4, "f32"),      # the first one it takes a row per wave
+    (700, 382, 4, "bf16"),
+    (700, 386, 4, "bf16"),
+    (900, 2, 3, "bf16"),       # one word per row, four on the copy
+    (1200007, 3, 2, "f32"),    # more words than one round of the grid
+])
+def test_copies_at_the_edges_of_their_two_kernels(N, D, K, dt):
+    x, y = _mixture(N + D, N, D, K, dt, 4.0)
+    r = cat_fit(dev_matrix(x, dt), dev_matrix(y, dt), K, 2, seed=5)
+    o = oracle.fit(x, y, K, 2, seed=5)
+    _against_oracle(r, o, x, dt, f"{N}x{D} K={K} {dt}")
+
+
 def test_the_copy_is_made_only_for_two_or_more_iterations_and_the_default_path():
     N, D, K = 2000, 203, 7
     x, y = _mixture(1, N, D, 7, "f32")
