@@ -729,49 +729,53 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
         // smallest can be the nearest one; where more than one is (that includes every cluster of a row whose distances
         // overflow or are no numbers), the wave compares in doubles.  (All clusters of every row in doubles, against this, us per
         // cat_apply_pca: 200000 x 256, K = p = 50: 194 -> 172; 2000000 x 160: 1555 -> 1278; 65536 x 1000 bf16, K = 200,
-        // p = 30: 160 -> 142; 65536 x 1000, K = p = 50: 215 -> 213, bound by the projection and the map.)
-        float d1 = __builtin_inff(), d2 = __builtin_inff();
-        int kbest = 0;
+        // p = 30: 160 -> 142; 65536 x 1000, K = p = 50: 215 -> 213, bound by the projection and the map.)  One or two
+        // clusters are compared in doubles at once (267130 x 200 bf16, p = 6, K = 1 and 2, screened first: 75.6 -> 77.2 and
+        // 73.5 -> 76.3; K = 3: 72.8 -> 73.3 there, 69.9 -> 68.8 on 300000 x 64 bf16, p = 32).
+        int kbest = 0, cand = 0;
+        if (f.K > 2) {
+            float d1 = __builtin_inff(), d2 = __builtin_inff();
 #pragma unroll 1
-        for (int k = 0; k < f.K; k += 4) {
-            float d[4];
+            for (int k = 0; k < f.K; k += 4) {
+                float d[4];
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const int ku = k + u < f.K ? k + u : k;
-                d[u] = 0.f;
+                for (int u = 0; u < 4; u++) {
+                    const int ku = k + u < f.K ? k + u : k;
+                    d[u] = 0.f;
 #pragma unroll
-                for (int t = 0; t < NT; t++) {
-                    const f32x4_t e = acc[t] - *(const f32x4_t*)&s_cz[ku * CW + 16 * t + 4 * g];
-                    d[u] = fmaf(e.x, e.x, d[u]);
-                    d[u] = fmaf(e.y, e.y, d[u]);
-                    d[u] = fmaf(e.z, e.z, d[u]);
-                    d[u] = fmaf(e.w, e.w, d[u]);
+                    for (int t = 0; t < NT; t++) {
+                        const f32x4_t e = acc[t] - *(const f32x4_t*)&s_cz[ku * CW + 16 * t + 4 * g];
+                        d[u] = fmaf(e.x, e.x, d[u]);
+                        d[u] = fmaf(e.y, e.y, d[u]);
+                        d[u] = fmaf(e.z, e.z, d[u]);
+                        d[u] = fmaf(e.w, e.w, d[u]);
+                    }
+                }
+                // lanes g and g ^ 2 exchange the halves they don't keep, then g and g ^ 1
+                const bool hi = g & 2, odd = g & 1;
+                const float p0 = (hi ? d[2] : d[0]) + __shfl_xor(hi ? d[0] : d[2], 32, kWave);
+                const float p1 = (hi ? d[3] : d[1]) + __shfl_xor(hi ? d[1] : d[3], 32, kWave);
+                const float v = (odd ? p1 : p0) + __shfl_xor(odd ? p0 : p1, 16, kWave);
+                if (k + g < f.K) {
+                    if (v < d1) {
+                        d2 = d1;
+                        d1 = v;
+                        kbest = k + g;
+                    } else if (!(v >= d2)) {
+                        d2 = v;
+                    }
                 }
             }
-            // lanes g and g ^ 2 exchange the halves they don't keep, then g and g ^ 1
-            const bool hi = g & 2, odd = g & 1;
-            const float p0 = (hi ? d[2] : d[0]) + __shfl_xor(hi ? d[0] : d[2], 32, kWave);
-            const float p1 = (hi ? d[3] : d[1]) + __shfl_xor(hi ? d[1] : d[3], 32, kWave);
-            const float v = (odd ? p1 : p0) + __shfl_xor(odd ? p0 : p1, 16, kWave);
-            if (k + g < f.K) {
-                if (v < d1) {
-                    d2 = d1;
-                    d1 = v;
-                    kbest = k + g;
-                } else if (!(v >= d2)) {
-                    d2 = v;
-                }
-            }
+            float dm = fminf(d1, __shfl_xor(d1, 16, kWave));
+            dm = fminf(dm, __shfl_xor(dm, 32, kWave));
+            const float lim = fmaf(dm, 1.00001f, 1e-35f);
+            cand = (!(d1 > lim) ? 1 : 0) + (!(d2 > lim) ? 1 : 0);
+            cand += __shfl_xor(cand, 16, kWave);
+            cand += __shfl_xor(cand, 32, kWave);
+            if (!(d1 <= lim)) kbest = 0x7fffffff;
+            kbest = min(kbest, __shfl_xor(kbest, 16, kWave));
+            kbest = min(kbest, __shfl_xor(kbest, 32, kWave));
         }
-        float dm = fminf(d1, __shfl_xor(d1, 16, kWave));
-        dm = fminf(dm, __shfl_xor(dm, 32, kWave));
-        const float lim = fmaf(dm, 1.00001f, 1e-35f);
-        int cand = (!(d1 > lim) ? 1 : 0) + (!(d2 > lim) ? 1 : 0);
-        cand += __shfl_xor(cand, 16, kWave);
-        cand += __shfl_xor(cand, 32, kWave);
-        if (!(d1 <= lim)) kbest = 0x7fffffff;
-        kbest = min(kbest, __shfl_xor(kbest, 16, kWave));
-        kbest = min(kbest, __shfl_xor(kbest, 32, kWave));
         if (__ballot(cand != 1)) {
             double dbest = __builtin_inf();
             kbest = 0;
