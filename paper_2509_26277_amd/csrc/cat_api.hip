@@ -104,7 +104,7 @@ static FitWs carve_fit(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt
         w.lloyd.sort_ws = w.sort;
         c.off += align256(w.lloyd.bytes);
         if (tile_bounds_pay(N, D, K, dt)) {
-            w.bounds = bounds_carve(base ? (void*)(c.base + c.off) : nullptr, N, D, K);
+            w.bounds = bounds_carve(base ? (void*)(c.base + c.off) : nullptr, N, D, K, tile_bounds_split(D, K, dt));
             w.bounds.record = true;
             c.off += align256(w.bounds.bytes);
         }

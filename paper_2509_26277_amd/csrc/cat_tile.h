@@ -41,7 +41,7 @@ struct LloydWs {
     int32_t* skipped = nullptr;          //   then one word: passes left out, for callers that bring no word of their own
     double* norm_part = nullptr;         // slices x K
     int32_t* counts2 = nullptr;          // K: the second half of the counts double buffer
-    float4* carry = nullptr;             // N entries, only for more than 128 clusters: what the first of two launches that
+    float2* carry = nullptr;             // N pairs, only for more than 128 clusters: what the first of two launches that
     float* carry_cmax = nullptr;         //   split the clusters hands to the second (per row; the largest centroid norm)
     uint32_t* sort_ws = nullptr;         // not carved here: the caller's scratch for launch_segsum_sorted
     size_t bytes = 0;
@@ -57,18 +57,21 @@ struct BoundsWs {
     double* drift = nullptr;          // 2        accumulated centroid drift up to a pass (by parity of the pass)
     uint32_t* quiet = nullptr;        // 2        (by parity of the pass) no row changed cluster in the pass before
     double* objective = nullptr;      // 1        the part of the objective that depends on the centroids, of the first listed pass
+    float* second = nullptr;          // N        passes of two launches: the second-best score the first hands to the second
     double* move_part = nullptr;      // slices x K
     int32_t* slice_counts = nullptr;  // slices x K
     int32_t* evaluated = nullptr;     // iters+1  out: rows evaluated by each pass (the caller's array, nullable)
     bool record = false;              // see tile_lloyd: every entry of the objective, and a last pass that leaves rows out too
     size_t bytes = 0;
 };
-size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K);
-BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K);
+// two_launches: for the loops whose passes rank the clusters in two launches (tile_bounds_split)
+size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K, bool two_launches = false);
+BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K, bool two_launches = false);
+bool tile_bounds_split(int64_t D, int32_t K, cat_dtype dt);
 bool tile_bounds_supports(int64_t N, int64_t D, int32_t K, cat_dtype dt);
-// Whether the plain fits run their loop with bounds (record): the shape allows it and the passes are long enough.
 // Whether one launch of the kernel ranks this shape with the two-part operand.
 bool tile_two_parts(TileMode mode, int64_t D, int32_t K, cat_dtype dt);
+// Whether the plain fits run their loop with bounds (record): the shape allows it and the passes are long enough.
 bool tile_bounds_pay(int64_t N, int64_t D, int32_t K, cat_dtype dt);
 cat_status launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 

@@ -688,7 +688,7 @@ static inline size_t lloyd_ctrl_words(int64_t D) { return (size_t)(3 + 2 * delta
 
 size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K) {
     return a256((size_t)N * 8) + a256(lloyd_ctrl_words(D) * 4) + a256((size_t)delta_slices(D) * K * 8) +
-           a256((size_t)K * 4) + (K > kSplitTiles * 16 ? a256((size_t)N * sizeof(float4)) + 256 : 0);
+           a256((size_t)K * 4) + (K > kSplitTiles * 16 ? a256((size_t)N * 8) + 256 : 0);
 }
 LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K) {
     LloydWs w;
@@ -705,8 +705,8 @@ LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K) {
     w.counts2 = (int32_t*)b;
     b += a256((size_t)K * 4);
     if (K > kSplitTiles * 16) {
-        w.carry = (float4*)b;
-        b += a256((size_t)N * sizeof(float4));
+        w.carry = (float2*)b;
+        b += a256((size_t)N * 8);
         w.carry_cmax = (float*)b;
     }
     return w;
@@ -737,13 +737,14 @@ bool tile_bounds_pay(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     if (tile_config(TILE_LLOYD, D, K, dt, true).ok) return bytes >= kBoundsBytes;
     return split_config(D, K, dt, nullptr);
 }
-size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K) {
+bool tile_bounds_split(int64_t D, int32_t K, cat_dtype dt) { return split_config(D, K, dt, nullptr); }
+size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K, bool two_launches) {
     const size_t sk = (size_t)delta_slices(D) * (size_t)K;
-    return a256((size_t)N * 8) + a256((size_t)N * 4) + a256(4) + a256(4 * 8) + a256(sk * 8) + a256(sk * 4);
+    return (two_launches ? a256((size_t)N * 4) : 0) + a256((size_t)N * 8) + a256((size_t)N * 4) + a256(4) + a256(4 * 8) + a256(sk * 8) + a256(sk * 4);
 }
-BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K) {
+BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K, bool two_launches) {
     BoundsWs w;
-    w.bytes = bounds_workspace_bytes(N, D, K);
+    w.bytes = bounds_workspace_bytes(N, D, K, two_launches);
     if (!base) return w;
     const size_t sk = (size_t)delta_slices(D) * (size_t)K;
     char* b = (char*)base;
@@ -760,6 +761,8 @@ BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K) {
     w.move_part = (double*)b;
     b += a256(sk * 8);
     w.slice_counts = (int32_t*)b;
+    b += a256(sk * 4);
+    if (two_launches) w.second = (float*)b;
     return w;
 }
 
@@ -933,9 +936,10 @@ cat_status tile_assign(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32
     return launch_tile(p, c, dt, st);
 }
 
-// The two launches of a pass whose clusters are split (p: the parameters of the pass as for one launch).
+// The two launches of a pass whose clusters are split (p: the parameters of the pass as for one launch; second: given in
+// the passes that keep bounds or walk a list).
 static cat_status launch_split_pair(const TileParams& p, const TileCfg& c, cat_dtype dt, int32_t K, const TileWs& ws,
-                                    float4* carry, float* carry_cmax, hipStream_t st) {
+                                    float2* carry, float* carry_cmax, float* second, hipStream_t st) {
     // first launch: clusters 0 .. 127, no bookkeeping, leaves (best score, nearest centroid) per row
     const int32_t K0 = kSplitTiles * 16;
     TileParams a = p;
@@ -944,6 +948,7 @@ static cat_status launch_split_pair(const TileParams& p, const TileCfg& c, cat_d
     a.k_hist = K;
     a.norm_stride = K;
     a.carry_out = carry;
+    a.second_out = second;
     a.cmax_io = carry_cmax;
     a.counts = nullptr;
     a.inertia = nullptr;
@@ -952,7 +957,11 @@ static cat_status launch_split_pair(const TileParams& p, const TileCfg& c, cat_d
     a.delta_mode = 0;
     a.expire = nullptr;
     a.evaluated_slot = nullptr;
-    cat_status s = dt == CAT_BF16 ? launch_split_bf16(a, c, st) : launch_split_f32(a, c, st);
+    auto launch = [&](const TileParams& q) {
+        if (second) return dt == CAT_BF16 ? launch_split_rows_bf16(q, c, st) : launch_split_rows_f32(q, c, st);
+        return dt == CAT_BF16 ? launch_split_bf16(q, c, st) : launch_split_f32(q, c, st);
+    };
+    cat_status s = launch(a);
     if (s != CAT_OK) return s;
     // second launch: the other clusters beside that pair, and the bookkeeping of the pass
     TileParams b = p;
@@ -963,12 +972,13 @@ static cat_status launch_split_pair(const TileParams& p, const TileCfg& c, cat_d
     b.packA = ws.packA + (size_t)c.nchunks * 4 * kSplitTiles * c.P * 512;
     b.cnorm = ws.cnorm + K0;
     b.carry_in = carry;
+    b.second_in = second;
     b.cmax_io = carry_cmax;
-    return dt == CAT_BF16 ? launch_split_bf16(b, c, st) : launch_split_f32(b, c, st);
+    return launch(b);
 }
 
 size_t tile_split_scratch_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
-    return split_config(D, K, dt, nullptr, TILE_ASSIGN) ? a256((size_t)N * sizeof(float4)) + 256 : 0;
+    return split_config(D, K, dt, nullptr, TILE_ASSIGN) ? a256((size_t)N * 8) + 256 : 0;
 }
 
 // tile_assign (assignment only) for more than 128 clusters, ranked by two launches; scratch: tile_split_scratch_bytes.
@@ -993,7 +1003,7 @@ cat_status tile_assign_split(const void* lq, cat_dtype dt, int64_t N, int64_t D,
     p.counts = counts;
     p.inertia = inertia;
     p.rep = rep;
-    return launch_split_pair(p, c, dt, K, ws, (float4*)scratch, (float*)((char*)scratch + a256((size_t)N * sizeof(float4))), st);
+    return launch_split_pair(p, c, dt, K, ws, (float2*)scratch, (float*)((char*)scratch + a256((size_t)N * 8)), nullptr, st);
 }
 
 cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters,
@@ -1003,7 +1013,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     // rows are left out by their bounds in the passes 3 .. iters - 1 (record: and in the last)
     const bool record = bw && bw->record;
     const bool one_launch = tile_bounds_supports(N, D, K, dt);
-    const bool bounds = bw && bw->expire && iters >= 4 && (one_launch || (record && lw.carry && split_config(D, K, dt, nullptr)));
+    const bool bounds = bw && bw->expire && iters >= 4 && (one_launch || (record && lw.carry && bw->second && split_config(D, K, dt, nullptr)));
     if (bounds) skipped = nullptr;  // (a pass over an empty list of rows costs next to nothing already)
     TileCfg c = tile_config(TILE_LLOYD, D, K, dt, bounds && one_launch);
     if (!c.ok) return set_error(CAT_ERR_UNSUPPORTED, "tile kernels do not fit D=%lld K=%d", (long long)D, (int)K);
@@ -1083,7 +1093,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
         p.reverse = listed ? 0 : (t & 1);
         p.skip_when_zero = (skipped && t > kFullPasses && !last) ? lw.ctrl + ((t - 1) & 1) : nullptr;
         if (split) {
-            CAT_T(launch_split_pair(p, c, dt, K, ws, lw.carry, lw.carry_cmax, st));
+            CAT_T(launch_split_pair(p, c, dt, K, ws, lw.carry, lw.carry_cmax, keeps_bounds ? bw->second : nullptr, st));
         } else if (keeps_bounds)
             CAT_T(dt == CAT_BF16 ? launch_bounds_bf16(p, c, st) : launch_bounds_f32(p, c, st));
         else

@@ -98,8 +98,10 @@ struct TileParams {
     // nearest centroid of its share; the second (carry_in given) ranks that pair as one more cluster beside its own
     // and does the bookkeeping of the pass.  Tables per cluster (counts, first rows) span k_hist clusters.
     int32_t k_base, k_hist, norm_stride;
-    const float4* carry_in;    // per row: best score, its cluster (int bits), second-best score
-    float4* carry_out;
+    const float2* carry_in;    // per row: best score, its cluster (int bits)
+    float2* carry_out;
+    const float* second_in;    // passes that keep bounds: the second-best score as well (a word of its own: the passes
+    float* second_out;         //   without bounds, 131619 x 864, K = 131, take 6 % longer with 16 bytes per row)
     float* cmax_io;  // the first launch leaves the largest centroid norm of its share, the second takes the larger of the two
 };
 
@@ -202,7 +204,8 @@ struct ChunkRegs {
     int prev;     // previous assignment of row n (assignment passes only)
     u32x4 prevv;  // several sets: previous assignments of row n in the sets 4 g .. 4 g + 3
     int row;      // listed rows: the number of row n
-    float4 carry; // split clusters: (best score, its cluster as int bits, second-best score) of row n in the clusters ranked before
+    float2 carry; // split clusters: (best score, its cluster as int bits) of row n in the clusters ranked before
+    float second; //   the second-best score there (passes that keep bounds)
 };
 
 // Rows past N repeat the last row and channel groups past D read the start of the row (valid
@@ -213,7 +216,7 @@ struct ChunkRegs {
 // tile's finishing code it would have to be waited for there, and since loads return in order
 // that wait would also drain the chunks requested ahead.
 // LISTED: the tile's rows are not consecutive; lrow is the number of the row this lane loads (already clamped).
-template <bool BF16, int PREV, bool LISTED = false>  // PREV: 0 none, 1 the row's previous assignment, 2 its previous assignments in all sets, 3 as 1 plus the carried pair of a split ranking
+template <bool BF16, int PREV, bool LISTED = false>  // PREV: 0 none, 1 the row's previous assignment, 2 its previous assignments in all sets, 3 as 1 plus the carried pair of a split ranking, 4 and the second-best score
 __device__ __forceinline__ void load_chunk(ChunkRegs<BF16>& r, const TileParams& p, int tile, int chunk, int lane, int lrow = 0) {
     const int n = lane & 15, g = lane >> 4;
     int64_t row;
@@ -226,8 +229,9 @@ __device__ __forceinline__ void load_chunk(ChunkRegs<BF16>& r, const TileParams&
         row = row0 + (n < nv ? n : nv - 1);
     }
     const int ch = chunk * kChunk + 8 * g;
-    if (PREV == 1 || PREV == 3) r.prev = p.assign[row];
-    if (PREV == 3 && p.carry_in) r.carry = p.carry_in[row];
+    if (PREV == 1 || PREV == 3 || PREV == 4) r.prev = p.assign[row];
+    if ((PREV == 3 || PREV == 4) && p.carry_in) r.carry = p.carry_in[row];
+    if (PREV == 4 && p.second_in) r.second = p.second_in[row];
     if (PREV == 2) r.prevv = *(const u32x4*)(p.assign + row * 16 + 4 * g);
     if (BF16) {
         const bf16_t* x = (const bf16_t*)p.lq + row * p.D;
@@ -536,7 +540,7 @@ __device__ __forceinline__ void finish_deferred(const TileParams& p, unsigned ch
 template <int KT, bool BF16, int MODE, bool BOUNDS = false, bool SPLIT = false, bool ROWS = BOUNDS>
 __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* smem, f32x4 (&acc)[KT], float& nrm,
                                             int tile, int lane, float cmax, double& in_acc, int prev_in, int row_in = -1,
-                                            uint32_t n_listed = 0, double gnow = 0.0, float4 carry = float4{0.f, 0.f, 0.f, 0.f}) {
+                                            uint32_t n_listed = 0, double gnow = 0.0, float2 carry = float2{0.f, 0.f}, float second_in = 0.f) {
     const int n = lane & 15, q = lane >> 4;
     constexpr bool BYROW = ROWS;
     const bool listed = BYROW && p.rows != nullptr;
@@ -553,10 +557,13 @@ __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* 
     bool reranked = false, deferred = false;
     constexpr bool DEFER = MODE == MODE_ASSIGN && !(SPLIT && !ROWS);
     const int prev = p.delta_mode ? prev_in : -1;
-    if (SPLIT)
+    if (SPLIT && ROWS)
         rank_rows<KT, BF16, DEFER>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, &first, &second, &reranked, &bound,
                                    p.k_base, p.carry_in != nullptr, carry.x, __float_as_int(carry.y), smem + p.off_queue, prev,
-                                   &deferred, -1, carry.z);
+                                   &deferred, -1, second_in);
+    else if (SPLIT)
+        rank_rows<KT, BF16>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, &first, nullptr, nullptr, nullptr,
+                            p.k_base, p.carry_in != nullptr, carry.x, __float_as_int(carry.y));
     else
         rank_rows<KT, BF16, DEFER>(p, acc, s_cnorm, xn2, cmax, myrow, valid, lane, idx, dmin, 0, KT, BOUNDS ? &first : nullptr,
                                    BOUNDS ? &second : nullptr, BOUNDS ? &reranked : nullptr, BOUNDS ? &bound : nullptr, 0, false,
@@ -567,7 +574,10 @@ __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* 
     const bool owner = q == 0 && valid && !deferred;
     if (SPLIT && p.carry_out) {  // the first of the two launches: hand the pair on, nothing else (a row whose re-rank is
         // put off has its cluster written again at the end of the workgroup's tiles, after a barrier)
-        if (q == 0 && valid) p.carry_out[myrow] = float4{first, __int_as_float(idx), second, 0.f};
+        if (q == 0 && valid) {
+            p.carry_out[myrow] = float2{first, __int_as_float(idx)};
+            if (ROWS) p.second_out[myrow] = second;
+        }
         return;
     }
 
@@ -787,6 +797,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
     if (listed && (uint32_t)blockIdx.x * kRows >= n_listed) return;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform: keeps tile math scalar
+    constexpr bool DEFERS = MODE == MODE_ASSIGN && VAR != VAR_MULTI && VAR != VAR_SPLIT;  // uses the queue of near-tie rows
     constexpr int P = PASSES == 1 ? 1 : 2;
     float* s_cnorm = (float*)(smem + p.off_cnorm);
     int* s_hist = (int*)(smem + p.off_hist);
@@ -823,7 +834,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
 #define CAT_ISSUE(buf)                                                                     \
     if (tl < ntiles) {                                                                     \
         if (BYROW)                                                                         \
-            load_chunk<BF16, SPLIT ? 3 : 1, true>(buf, p, tl, cl, lane, lrow);             \
+            load_chunk<BF16, SPLIT ? 4 : 1, true>(buf, p, tl, cl, lane, lrow);             \
         else                                                                               \
             load_chunk<BF16, MODE == MODE_ASSIGN ? (MULTI ? 2 : SPLIT ? 3 : 1) : 0>(buf, p, tl, cl, lane); \
         if (++cl == p.nchunks) {                                                           \
@@ -901,7 +912,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
             s_rep[k] = ~0ull;
         }
         if (threadIdx.x == 0) s_misc[0] = 0;
-        if (VAR != VAR_MULTI && MODE == MODE_ASSIGN && p.queue_cap > 0 && threadIdx.x == 0) *(int*)(smem + p.off_queue) = 0;
+        if (DEFERS && p.queue_cap > 0 && threadIdx.x == 0) *(int*)(smem + p.off_queue) = 0;
     }
     __syncthreads();
     {
@@ -938,7 +949,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         else if (BOUNDS)                                                                                       \
             finish_tile<KT, BF16, MODE, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow); \
         else if (SPLIT)                                                                                        \
-            finish_tile<KT, BF16, MODE, false, true, BYROW>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow, buf.carry); \
+            finish_tile<KT, BF16, MODE, false, true, BYROW>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev, buf.row, n_listed, gnow, buf.carry, buf.second); \
         else                                                                                                   \
             finish_tile<KT, BF16, MODE>(p, smem, acc, nrm, tc, lane, cmax, in_acc, buf.prev);                  \
         cc = 0;                                                                                                \
@@ -984,7 +995,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
                 else if (BOUNDS)                                                                              \
                     finish_tile<KT, BF16, MODE, true>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow); \
                 else if (SPLIT)                                                                               \
-                    finish_tile<KT, BF16, MODE, false, true, BYROW>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow, bufcur.carry); \
+                    finish_tile<KT, BF16, MODE, false, true, BYROW>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev, bufcur.row, n_listed, gnow, bufcur.carry, bufcur.second); \
                 else                                                                                          \
                     finish_tile<KT, BF16, MODE>(p, smem, acc, nrm, tc, lane, cmax, in_acc, bufcur.prev);      \
                 cc = 0;                                                                                       \
@@ -1034,7 +1045,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
 
     if (MODE != MODE_ASSIGN) return;
 
-    if (VAR != VAR_MULTI && p.queue_cap > 0) {
+    if (DEFERS && p.queue_cap > 0) {
         // the rows whose exact re-rank was put off: shared out over the waves, one row at a time
         __syncthreads();
         const int pushed = *(const int*)(smem + p.off_queue);
@@ -1151,15 +1162,13 @@ static inline cat_status launch_kt_bounds(const TileParams& p, const TileCfg& c,
     return launch_one<KT, 3, BF16, MODE_ASSIGN, false, VAR_BOUNDS>(p, c, st);
 }
 
-// one of the two launches over the halves of a large cluster set (8 cluster tiles each, two-part operand)
-template <bool BF16>
+// one of the two launches over the halves of a large cluster set (8 cluster tiles each, two-part operand); VAR_SPLIT_ROWS in
+// passes that keep bounds
+template <bool BF16, int VAR>
 static inline cat_status launch_split(const TileParams& p, const TileCfg& c, hipStream_t st) {
     if (c.KT != 8 || c.P != 2) return set_error(CAT_ERR_UNSUPPORTED, "split ranking: 8 cluster tiles and the two-part operand only");
-    if (p.rows || p.expire)
-        return c.chunked ? launch_one<8, 3, BF16, MODE_ASSIGN, true, VAR_SPLIT_ROWS>(p, c, st)
-                         : launch_one<8, 3, BF16, MODE_ASSIGN, false, VAR_SPLIT_ROWS>(p, c, st);
-    if (c.chunked) return launch_one<8, 3, BF16, MODE_ASSIGN, true, VAR_SPLIT>(p, c, st);
-    return launch_one<8, 3, BF16, MODE_ASSIGN, false, VAR_SPLIT>(p, c, st);
+    if (c.chunked) return launch_one<8, 3, BF16, MODE_ASSIGN, true, VAR>(p, c, st);
+    return launch_one<8, 3, BF16, MODE_ASSIGN, false, VAR>(p, c, st);
 }
 
 // one translation unit per (KT, dtype), for compile time: cat_tile_k<KT>_<dtype>.hip
@@ -1179,6 +1188,10 @@ cat_status launch_multi_bf16(const TileParams& p, const TileCfg& c, hipStream_t 
 // the instantiations for the halves of a large cluster set: cat_tile_split.hip
 cat_status launch_split_f32(const TileParams& p, const TileCfg& c, hipStream_t st);
 cat_status launch_split_bf16(const TileParams& p, const TileCfg& c, hipStream_t st);
+// the same in passes that keep distance bounds: cat_tile_split_rows.hip (a unit of its own: with both variants in one, the
+// register allocation of this one spills 100 registers instead of 77, and 131619 x 864, K = 131 takes 3 % longer)
+cat_status launch_split_rows_f32(const TileParams& p, const TileCfg& c, hipStream_t st);
+cat_status launch_split_rows_bf16(const TileParams& p, const TileCfg& c, hipStream_t st);
 // the instantiations that keep distance bounds: cat_tile_bounds_<dtype>.hip
 cat_status launch_bounds_f32(const TileParams& p, const TileCfg& c, hipStream_t st);
 cat_status launch_bounds_bf16(const TileParams& p, const TileCfg& c, hipStream_t st);

@@ -49,6 +49,13 @@ def test_workspace_sizes(lib):
     assert binding.cat_apply_workspace_bytes(4096, 8, 2000, binding.CAT_F32) == 0  # K > CAT_MAX_K
 
 
+def test_scratch_of_the_ranking_in_two_launches(lib):
+    """More than 128 clusters on long rows: a pair (8 bytes) and a label (4 bytes) per row, nothing else that grows with N."""
+    f = binding.cat_apply_workspace_bytes
+    for D, K, dt in [(864, 131, binding.CAT_F32), (2048, 200, binding.CAT_BF16), (300, 256, binding.CAT_F32)]:
+        assert f(1 << 21, D, K, dt) - f(1 << 20, D, K, dt) == 12 << 20
+
+
 FAKE = 0x7F0000001000  # never dereferenced: every case below fails validation first
 
 
