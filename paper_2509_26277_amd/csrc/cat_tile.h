@@ -39,6 +39,10 @@ struct LloydWs {
     unsigned long long* list = nullptr;  // N entries
     uint32_t* ctrl = nullptr;            // [0..1] list length (two halves), then 2 x slices finished-workgroup counters,
     int32_t* skipped = nullptr;          //   then one word: passes left out, for callers that bring no word of their own
+    //   then (cleared with ctrl) the state of a loop with bounds, by parity of the pass where two:
+    double* drift = nullptr;             // 2  accumulated centroid drift up to a pass
+    double* objective = nullptr;         // 1  the part of the objective that depends on the centroids, of the first listed pass
+    uint32_t* quiet = nullptr;           // 2  no row changed cluster in the pass before
     double* norm_part = nullptr;         // slices x K
     int32_t* counts2 = nullptr;          // K: the second half of the counts double buffer
     float2* carry = nullptr;             // N pairs, only for more than 128 clusters: what the first of two launches that
@@ -52,11 +56,7 @@ LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K);
 // Scratch of the loops that leave rows out by distance bounds (Hamerly, SDM 2010): see tile_lloyd.
 struct BoundsWs {
     double* expire = nullptr;         // N        per row: the drift at which it has to be evaluated again
-    int32_t* rows = nullptr;          // N        the rows of the coming pass
-    uint32_t* n_rows = nullptr;       // 1        their number
-    double* drift = nullptr;          // 2        accumulated centroid drift up to a pass (by parity of the pass)
-    uint32_t* quiet = nullptr;        // 2        (by parity of the pass) no row changed cluster in the pass before
-    double* objective = nullptr;      // 1        the part of the objective that depends on the centroids, of the first listed pass
+    int32_t* rows = nullptr;          // N + 63   the rows of the coming pass, a region per workgroup
     float* second = nullptr;          // N        passes of two launches: the second-best score the first hands to the second
     double* move_part = nullptr;      // slices x K
     int32_t* slice_counts = nullptr;  // slices x K

@@ -173,7 +173,6 @@ struct DeltaParams {
     int32_t* slice_counts;
     int32_t seed_counts;
     double* move_part;
-    uint32_t* n_rows_clear;      // nullable: cleared (the row selection that follows counts into it)
     // The objective of the pass before, whose centroids are still `cent` on entry and whose sums this launch completes:
     // constant + sum_k c_k . (n_k c_k - 2 S_k).  Every slice adds its share of that sum to obj_out; with obj_ref (the same
     // sum of a pass whose objective in_ref[0] is known) one workgroup adds the constant, in_ref[0] - obj_ref[0].
@@ -228,10 +227,7 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
             if (q.rep) q.rep[k] = ~0ull;
         }
         for (int s = threadIdx.x; s < nslices; s += blockDim.x) q.done_next[s] = 0;
-        if (threadIdx.x == 0) {
-            *q.list_count_next = 0;
-            if (q.n_rows_clear) *q.n_rows_clear = 0;
-        }
+        if (threadIdx.x == 0) *q.list_count_next = 0;
         if ((int)threadIdx.x < q.inertia_n && q.inertia_slot) q.inertia_slot[threadIdx.x] = 0.0;
     }
     if (q.quiet) {
@@ -461,130 +457,14 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
     }
 }
 
-// ---- which rows does the next pass have to evaluate? (distance bounds; Hamerly, SDM 2010) ----
-// The update just done moved centroid k by p(k) = sqrt(sum over the slices of move_part[.][k]).  A row's distance to
-// its own centroid grew by at most p(own) and its distance to any other shrank by at most the largest p among the
-// others, so the difference of the two shrank by at most the sum of the two largest movements.  That sum is added
-// to the running drift G; a row whose bound expire[i] (the drift at its last evaluation plus its margin then) is
-// still above G keeps its nearest centroid and is left out.  Every workgroup computes the same G (same data, same
-// order); the rows are taken in contiguous pieces and the kept ones appended to `rows` with one reservation per piece.
-// A row evaluated without a margin has expire = the drift of that pass and is kept as soon as any centroid moves at all
-// (the drift then grows, by its last bit at least); while none moves its nearest centroid is what it was.  A margin is
-// rounded down by 1e-9 of itself, so a drift equal to expire has not used it up.
 // Matrices below these sizes keep the plain loop in the plain fits: a pass over them is launches and dependent steps, to
-// which the selection of the rows adds one of 5 us.  One launch per pass, us per cat_fit of 15 to 20 iterations, plain ->
+// which the selection of the rows adds.  One launch per pass, us per cat_fit of 15 to 20 iterations, plain ->
 // with bounds: logits 16384 x 1000 (62 MB) 695 -> 522, 32768 x 1000 878 -> 388; features 32768 x 256 (32 MB) 490 -> 534,
 // 65536 x 256 (64 MB) 615 -> 545; mixture 131072 x 64 (32 MB) 704 -> 697, 65536 x 256 645 -> 307.  Components that overlap
 // until the end, so that no row can be left out: bf16 16384 x 1024 (32 MB) 701 -> 820, 65536 x 1024 (128 MB) 1138 -> 1225,
 // 131072 x 1024 1771 -> 1764.  A pass of two launches (K > 128) costs more, and the selection less of it: logits 16384 x 1000,
 // K = 200 (62 MB) 2267 -> 793; overlapping 32768 x 512 (64 MB) 1932 -> 2005.
 constexpr double kBoundsBytes = 64.0 * 1024 * 1024, kBoundsBytesSplit = 32.0 * 1024 * 1024;
-constexpr int kSelThreads = 256;
-constexpr int kSelPerThread = 8;
-__global__ __launch_bounds__(kSelThreads) void k_bound_select(const double* __restrict__ move_part, int32_t slices, int32_t K,
-                                                              const double* __restrict__ g_prev, double* __restrict__ g_now,
-                                                              const double* __restrict__ expire, int64_t N,
-                                                              int32_t* __restrict__ rows, uint32_t* __restrict__ n_rows,
-                                                              const uint32_t* __restrict__ quiet) {
-    if (quiet && *quiet) {  // nothing moved (k_delta_prep): no row is due, the list stays empty
-        if (blockIdx.x == 0 && threadIdx.x == 0) *g_now = *g_prev;
-        return;
-    }
-    __shared__ double s_p[256];
-    __shared__ double s_g;
-    __shared__ uint32_t s_cnt[kSelPerThread * kSelThreads / kWave];
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    double pk = 0.0;
-    if ((int)threadIdx.x < K) {
-        double m2 = 0.0;
-        const double* mp = move_part + threadIdx.x;
-        int sl = 0;
-        for (; sl + 8 <= slices; sl += 8) {  // eight loads in flight, added in slice order
-            double v[8];
-#pragma unroll
-            for (int u = 0; u < 8; u++) v[u] = mp[(size_t)(sl + u) * K];
-#pragma unroll
-            for (int u = 0; u < 8; u++) m2 += v[u];
-        }
-        for (; sl < slices; sl++) m2 += mp[(size_t)sl * K];
-        pk = sqrt(m2);
-    }
-    s_p[threadIdx.x] = pk;
-    __syncthreads();
-    if (threadIdx.x < kWave) {
-        // the two largest movements: every lane ranks its four entries, then the wave's largest and, with that one
-        // taken out at the lane that holds it, the largest of the rest
-        double t1 = 0.0, t2 = 0.0;
-#pragma unroll
-        for (int j = 0; j < kSelThreads / kWave; j++) {
-            const double v = s_p[threadIdx.x + j * kWave];
-            if (v > t1) {
-                t2 = t1;
-                t1 = v;
-            } else if (v > t2) {
-                t2 = v;
-            }
-        }
-        double w1 = t1;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) w1 = fmax(w1, __shfl_xor(w1, o, kWave));
-        const unsigned long long holders = __ballot(t1 == w1);
-        const bool mine = lane == (int)__builtin_ctzll(holders);
-        double w2 = mine ? t2 : t1;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) w2 = fmax(w2, __shfl_xor(w2, o, kWave));
-        if (threadIdx.x == 0) {
-            const double g0 = *g_prev;
-            double g1 = g0 + (w1 + w2) * (1.0 + 1e-9);
-            if (w1 + w2 > 0.0 && g1 == g0) g1 = __longlong_as_double(__double_as_longlong(g0) + 1);  // (drifts are >= 0)
-            s_g = g1;
-            if (blockIdx.x == 0) *g_now = s_g;
-        }
-    }
-    __syncthreads();
-    const double G = s_g;
-    constexpr int64_t kPiece = (int64_t)kSelThreads * kSelPerThread;
-    for (int64_t r0 = (int64_t)blockIdx.x * kPiece; r0 < N; r0 += (int64_t)gridDim.x * kPiece) {
-        // step j of thread t is row r0 + 256 j + t: the loads are coalesced, and the kept rows of a piece stay in row order
-        // (8 consecutive rows per thread: 13 us over 1,048,576 rows)
-        unsigned long long m[kSelPerThread];
-        double ex[kSelPerThread];
-#pragma unroll
-        for (int j = 0; j < kSelPerThread; j++) {
-            const int64_t i = r0 + (int64_t)j * kSelThreads + threadIdx.x;
-            ex[j] = expire[i < N ? i : N - 1];
-        }
-#pragma unroll
-        for (int j = 0; j < kSelPerThread; j++) {
-            const int64_t i = r0 + (int64_t)j * kSelThreads + threadIdx.x;
-            m[j] = __ballot(i < N && !(G <= ex[j]));
-            if (lane == 0) s_cnt[j * (kSelThreads / kWave) + wave] = (uint32_t)__builtin_popcountll(m[j]);
-        }
-        __syncthreads();
-        if (threadIdx.x < kWave) {  // exclusive prefix over the 32 counts, one reservation for the piece
-            constexpr int NC = kSelPerThread * kSelThreads / kWave;
-            uint32_t v = threadIdx.x < NC ? s_cnt[threadIdx.x] : 0u;
-            const uint32_t mine = v;
-#pragma unroll
-            for (int o = 1; o < NC; o <<= 1) {
-                const uint32_t u = __shfl_up(v, o, kWave);
-                if (lane >= o) v += u;
-            }
-            const uint32_t tot = __shfl(v, NC - 1, kWave);
-            uint32_t base = 0;
-            if (lane == 0 && tot) base = atomicAdd(n_rows, tot);
-            base = __shfl(base, 0, kWave);
-            if (threadIdx.x < NC) s_cnt[threadIdx.x] = base + v - mine;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kSelPerThread; j++)
-            if (m[j] >> lane & 1ull)
-                rows[s_cnt[j * (kSelThreads / kWave) + wave] + __builtin_popcountll(m[j] & ((1ull << lane) - 1ull))] =
-                    (int32_t)(r0 + (int64_t)j * kSelThreads + threadIdx.x);
-        __syncthreads();
-    }
-}
 
 // ---- host side ----------------------------------------------------------------------------
 
@@ -684,7 +564,9 @@ TileWs tile_carve(void* base, int64_t D, int32_t K, cat_dtype dt) {
 static inline int64_t delta_slices(int64_t D) { return (D + kDeltaSW - 1) / kDeltaSW; }
 constexpr int kSplitTiles = 8;  // cluster tiles per launch when the clusters of a pass are split over two
 
-static inline size_t lloyd_ctrl_words(int64_t D) { return (size_t)(3 + 2 * delta_slices(D)); }
+// two list lengths, the finished-workgroup counters, the word of the early stop, padding to 8 bytes, the state of the bounds
+constexpr size_t kBoundsStateWords = 8;
+static inline size_t lloyd_ctrl_words(int64_t D) { return (size_t)(4 + 2 * delta_slices(D)) + kBoundsStateWords; }
 
 size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K) {
     return a256((size_t)N * 8) + a256(lloyd_ctrl_words(D) * 4) + a256((size_t)delta_slices(D) * K * 8) +
@@ -699,7 +581,10 @@ LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K) {
     b += a256((size_t)N * 8);
     w.ctrl = (uint32_t*)b;
     b += a256(lloyd_ctrl_words(D) * 4);
-    w.skipped = (int32_t*)(w.ctrl + lloyd_ctrl_words(D) - 1);
+    w.skipped = (int32_t*)(w.ctrl + 2 + 2 * delta_slices(D));
+    w.drift = (double*)(w.ctrl + 4 + 2 * delta_slices(D));
+    w.objective = w.drift + 2;
+    w.quiet = (uint32_t*)(w.drift + 3);
     w.norm_part = (double*)b;
     b += a256((size_t)delta_slices(D) * K * 8);
     w.counts2 = (int32_t*)b;
@@ -740,7 +625,7 @@ bool tile_bounds_pay(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
 bool tile_bounds_split(int64_t D, int32_t K, cat_dtype dt) { return split_config(D, K, dt, nullptr); }
 size_t bounds_workspace_bytes(int64_t N, int64_t D, int32_t K, bool two_launches) {
     const size_t sk = (size_t)delta_slices(D) * (size_t)K;
-    return (two_launches ? a256((size_t)N * 4) : 0) + a256((size_t)N * 8) + a256((size_t)N * 4) + a256(4) + a256(4 * 8) + a256(sk * 8) + a256(sk * 4);
+    return (two_launches ? a256((size_t)N * 4) : 0) + a256((size_t)N * 8) + a256(((size_t)N + kWave - 1) * 4) + a256(sk * 8) + a256(sk * 4);
 }
 BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K, bool two_launches) {
     BoundsWs w;
@@ -751,13 +636,7 @@ BoundsWs bounds_carve(void* base, int64_t N, int64_t D, int32_t K, bool two_laun
     w.expire = (double*)b;
     b += a256((size_t)N * 8);
     w.rows = (int32_t*)b;
-    b += a256((size_t)N * 4);
-    w.n_rows = (uint32_t*)b;
-    b += a256(4);
-    w.drift = (double*)b;
-    w.objective = w.drift + 2;
-    w.quiet = (uint32_t*)(w.drift + 3);
-    b += a256(4 * 8);
+    b += a256(((size_t)N + kWave - 1) * 4);
     w.move_part = (double*)b;
     b += a256(sk * 8);
     w.slice_counts = (int32_t*)b;
@@ -787,7 +666,7 @@ static cat_status launch_delta_prep(const void* lq, cat_dtype dt, int64_t D, int
                                     bool last = false, int32_t* counts_out = nullptr) {
     DeltaParams q = {};
     q.obj_out = obj_out;
-    q.obj_ref = in_ref ? bw->objective : nullptr;
+    q.obj_ref = in_ref ? lw.objective : nullptr;
     q.in_ref = in_ref;
     q.last = last ? 1 : 0;
     q.counts_out = counts_out;
@@ -796,9 +675,8 @@ static cat_status launch_delta_prep(const void* lq, cat_dtype dt, int64_t D, int
         q.slice_counts = bw->slice_counts;
         q.seed_counts = seed_counts ? 1 : 0;
         q.move_part = bw->move_part;
-        q.n_rows_clear = bw->n_rows;
-        q.quiet = seed_counts ? nullptr : bw->quiet + (par ^ 1);
-        q.quiet_next = bw->quiet + par;
+        q.quiet = seed_counts ? nullptr : lw.quiet + (par ^ 1);
+        q.quiet_next = lw.quiet + par;
     }
     q.lq = lq;
     q.D = D;
@@ -1033,8 +911,11 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     p.assign = assign;
     if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D) * 4, st));
     if (skipped && skipped != lw.skipped) CAT_T(launch_fill_zero(skipped, sizeof(int32_t), st));  // (that word is one of ctrl's)
-    if (bw && bw->evaluated) CAT_T(launch_fill_i32(bw->evaluated, (int64_t)iters + 1, (int32_t)N, st));
-    if (bounds) CAT_T(launch_fill_zero(bw->drift, 4 * sizeof(double), st));
+    if (bw && bw->evaluated) {
+        CAT_T(launch_fill_i32(bw->evaluated, (int64_t)iters + 1, (int32_t)N, st));
+        // (the passes over listed rows add up theirs)
+        if (bounds) CAT_T(launch_fill_i32(bw->evaluated + 3, (int64_t)iters - 3 + (record ? 1 : 0), 0, st));
+    }
     // Passes 0 and 1 are each followed by a full segmented sum: after the first reassignment most
     // rows still move, and moving them one by one costs several times a fresh sum (measured: 0.97 ms
     // against 0.33 ms on a 262144 x 2048 bf16 matrix).  From pass 2 on a pass lists the rows that
@@ -1059,26 +940,22 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
             CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, t & 1, cent_io, base, delta, cnt_prev, cnt_t, slot,
                                     last ? rep : nullptr, last ? nullptr : skipped, st, 1, bounds ? bw : nullptr,
                                     t == kFullPasses + 1, split ? kSplitTiles : 0,
-                                    !(bounds && record && inertia) ? nullptr : t == kFullPasses + 1 ? bw->objective : inertia + t - 1,
+                                    !(bounds && record && inertia) ? nullptr : t == kFullPasses + 1 ? lw.objective : inertia + t - 1,
                                     bounds && record && inertia && t > kFullPasses + 1 ? inertia + kFullPasses : nullptr));
         // With bounds: pass 2 evaluates every row and leaves its bound; the passes 3 .. iters - 1 evaluate the rows
-        // whose bound the drift of the centroids has used up (selected here, after the update that moved them)
+        // whose bound the drift of the centroids has used up
         const bool keeps_bounds = bounds && t >= kFullPasses && (!last || record);
         const bool listed = keeps_bounds && t > kFullPasses;
-        if (listed) {
-            const int64_t piece = (int64_t)kSelThreads * kSelPerThread;
-            int64_t blocks = (N + piece - 1) / piece;
-            blocks = blocks > 2048 ? 2048 : blocks;
-            hipLaunchKernelGGL(k_bound_select, dim3((unsigned)blocks), dim3(kSelThreads), 0, st, bw->move_part,
-                               (int32_t)delta_slices(D), K, bw->drift + ((t - 1) & 1), bw->drift + (t & 1), bw->expire, N, bw->rows, bw->n_rows,
-                               t > kFullPasses + 1 ? bw->quiet + (t & 1) : nullptr);
-            CAT_LAUNCH_CHECK("k_bound_select");
-        }
         p.expire = keeps_bounds ? bw->expire : nullptr;
-        p.gnow = keeps_bounds ? bw->drift + (t & 1) : nullptr;
-        p.rows = listed ? bw->rows : nullptr;
-        p.n_rows = listed ? bw->n_rows : nullptr;
-        p.evaluated_slot = (keeps_bounds && bw->evaluated) ? bw->evaluated + t : nullptr;
+        p.expire_read = p.expire;
+        p.rows = keeps_bounds ? bw->rows : nullptr;
+        p.move_part = listed ? bw->move_part : nullptr;
+        p.move_slices = (int32_t)delta_slices(D);
+        p.move_K = K;
+        p.g_prev = lw.drift + ((t - 1) & 1);
+        p.g_now = lw.drift + (t & 1);
+        p.still = listed && t > kFullPasses + 1 ? lw.quiet + (t & 1) : nullptr;
+        p.evaluated_slot = (listed && bw->evaluated) ? bw->evaluated + t : nullptr;
         p.norm_part = t > kFullPasses ? lw.norm_part : nullptr;
         p.norm_slices = t > kFullPasses ? (int32_t)delta_slices(D) : 0;
         p.counts = listed ? nullptr : cnt_t;  // (a pass over listed rows cannot count: the slices keep running counts)
@@ -1090,7 +967,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
         p.delta_mode = p.list ? 1 : 0;
         // alternate the scan direction: the rows a pass reads last are the ones most likely still in
         // the memory-side cache when the next pass starts
-        p.reverse = listed ? 0 : (t & 1);
+        p.reverse = t & 1;
         p.skip_when_zero = (skipped && t > kFullPasses && !last) ? lw.ctrl + ((t - 1) & 1) : nullptr;
         if (split) {
             CAT_T(launch_split_pair(p, c, dt, K, ws, lw.carry, lw.carry_cmax, keeps_bounds ? bw->second : nullptr, st));
@@ -1108,10 +985,9 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     }
     if (bounds && record) {
         // the rows the last pass moved, its objective and counts; the first rows of the clusters from the labels
-        CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, (iters + 1) & 1, cent_io, base, delta, counts, lw.counts2, nullptr, nullptr,
+        CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, (iters + 1) & 1, cent_io, base, delta, counts, lw.counts2, nullptr, rep,
                                 nullptr, st, 1, bw, false, split ? kSplitTiles : 0, inertia ? inertia + iters : nullptr,
                                 inertia ? inertia + kFullPasses : nullptr, true, counts));
-        CAT_T(launch_fill_u64(rep, K, ~0ull, st));
         CAT_T(launch_first_rows(assign, N, K, counts, rep, st));
     } else if (bounds && inertia && iters > kFullPasses + 1)  // the objective of a pass over listed rows is not known
         CAT_T(launch_fill_u64((unsigned long long*)(inertia + kFullPasses + 1), iters - kFullPasses - 1, 0x7ff8000000000000ull, st));

@@ -85,13 +85,16 @@ struct TileParams {
     // Distance bounds (BOUNDS instantiations only; Hamerly, SDM 2010).  A pass that evaluates a row leaves in
     // expire[row] the value the accumulated centroid drift *gnow must reach before the row's nearest centroid can
     // change: the drift at the evaluation plus a lower bound of (distance to the second nearest) - (distance to the
-    // nearest).  With `rows` given the pass walks only the *n_rows listed rows (16 to a tile, in list order) instead
-    // of all N; row numbers everywhere (assignments, list entries, expire) are the real ones.
-    double* expire;            // N doubles, nullable
-    const double* gnow;        // accumulated drift up to this pass
-    const int32_t* rows;       // nullable: listed rows
-    const uint32_t* n_rows;    // their number
-    int32_t* evaluated_slot;   // nullable: receives the number of rows this pass evaluates
+    // nearest).  Such a pass evaluates only the rows that are due; every workgroup selects its own (select_rows).
+    double* expire;            // N doubles; nullable in the first of two launches
+    const double* expire_read; // the same array, given in both
+    int32_t* rows;             // N + 63 entries: the workgroups' lists of due rows
+    const double* move_part;   // move_slices x move_K shares of the squared movements of the centroids in the update
+    int32_t move_slices, move_K;  // before; nullptr: every row is due
+    const double* g_prev;      // accumulated drift up to the pass before
+    double* g_now;             // receives that up to this pass
+    const uint32_t* still;     // nullable: if nonzero, no centroid moved and no row is due
+    int32_t* evaluated_slot;   // nullable: the number of rows this pass evaluates is added
     // More clusters than one launch ranks with the two-part operand (SPLIT instantiations only): the clusters are
     // split over two launches.  This launch ranks the K clusters k_base .. k_base + K - 1 (packA, cnorm point at its
     // share).  The first launch (carry_out given) only leaves, per row, the best score of its share and the exact
@@ -204,6 +207,7 @@ struct ChunkRegs {
     int prev;     // previous assignment of row n (assignment passes only)
     u32x4 prevv;  // several sets: previous assignments of row n in the sets 4 g .. 4 g + 3
     int row;      // listed rows: the number of row n
+    int row_ahead;  // listed rows: the number of row n in the tile that the load three loads later belongs to
     float2 carry; // split clusters: (best score, its cluster as int bits) of row n in the clusters ranked before
     float second; //   the second-best score there (passes that keep bounds)
 };
@@ -215,14 +219,18 @@ struct ChunkRegs {
 // With PREV the row's previous assignment rides along with every chunk: fetched inside the
 // tile's finishing code it would have to be waited for there, and since loads return in order
 // that wait would also drain the chunks requested ahead.
-// LISTED: the tile's rows are not consecutive; lrow is the number of the row this lane loads (already clamped).
+// LISTED: the tile's rows are not consecutive; lrow is the number of the row this lane loads (already clamped), ahead
+// the list entry with the number it will load three loads later.  That entry rides along with every chunk for the same
+// reason: requested where a tile ends, in a branch, it was waited for there.
 template <bool BF16, int PREV, bool LISTED = false>  // PREV: 0 none, 1 the row's previous assignment, 2 its previous assignments in all sets, 3 as 1 plus the carried pair of a split ranking, 4 and the second-best score
-__device__ __forceinline__ void load_chunk(ChunkRegs<BF16>& r, const TileParams& p, int tile, int chunk, int lane, int lrow = 0) {
+__device__ __forceinline__ void load_chunk(ChunkRegs<BF16>& r, const TileParams& p, int tile, int chunk, int lane, int lrow = 0,
+                                           const int32_t* ahead = nullptr) {
     const int n = lane & 15, g = lane >> 4;
     int64_t row;
     if (LISTED) {
         row = lrow;
         r.row = lrow;
+        r.row_ahead = *ahead;
     } else {
         const int64_t row0 = (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows;
         const int nv = (p.N - row0) < kRows ? (int)(p.N - row0) : kRows;
@@ -254,11 +262,25 @@ __device__ __forceinline__ void load_chunk(ChunkRegs<BF16>& r, const TileParams&
 
 // The 4 MFMA steps of one chunk against the centroid operand in LDS.  nrm accumulates the
 // lane's share of |x|^2 of row n.
-template <int KT, int PASSES, bool BF16>
+// AHEAD: the operand reads are written out that many (step, cluster tile) pairs ahead of their MFMAs.  The variants that walk
+// lists need that: there the scheduler gives up on these blocks and leaves the order of the source, and with every read right
+// before its MFMA the LDS latency is paid each time (262144 x 2048 bf16, K = 64, all rows listed: 300 us a pass, 275 so; the
+// pass without lists 260).
+template <int KT, int PASSES, bool BF16, int AHEAD = 0>
 __device__ __forceinline__ void contract_chunk(const ChunkRegs<BF16>& r, f32x4 (&acc)[KT], float& nrm,
                                                const unsigned char* ldsA_chunk, int lane, int chunk, int64_t D) {
     constexpr int P = PASSES == 1 ? 1 : 2;
     const int ch = chunk * kChunk + 8 * (lane >> 4);
+    bf16x8 ra[AHEAD + 1][P];
+    auto read = [&](int i) {
+#pragma unroll
+        for (int q = 0; q < P; q++)
+            ra[i % (AHEAD + 1)][q] = __builtin_bit_cast(bf16x8, *(const u32x4*)(ldsA_chunk + (size_t)(i * P + q) * 1024 + lane * 16));
+    };
+    if (AHEAD > 0) {
+#pragma unroll
+        for (int i = 0; i < AHEAD; i++) read(i);
+    }
 #pragma unroll
     for (int s = 0; s < 4; s++) {
         const int c = ch + 32 * s;
@@ -294,11 +316,18 @@ __device__ __forceinline__ void contract_chunk(const ChunkRegs<BF16>& r, f32x4 (
         }
 #pragma unroll
         for (int t = 0; t < KT; t++) {
-            const unsigned char* ap = ldsA_chunk + (size_t)((s * KT + t) * P) * 1024 + lane * 16;
-            bf16x8 ah = __builtin_bit_cast(bf16x8, *(const u32x4*)ap);
+            const int i = s * KT + t;
+            const unsigned char* ap = ldsA_chunk + (size_t)(i * P) * 1024 + lane * 16;
+            bf16x8 ah;
+            if (AHEAD > 0) {
+                if (i + AHEAD < 4 * KT) read(i + AHEAD);
+                ah = ra[i % (AHEAD + 1)][0];
+            } else {
+                ah = __builtin_bit_cast(bf16x8, *(const u32x4*)ap);
+            }
             acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc[t], 0, 0, 0);
             if (PASSES == 3) {
-                bf16x8 al = __builtin_bit_cast(bf16x8, *(const u32x4*)(ap + 1024));
+                const bf16x8 al = AHEAD > 0 ? ra[i % (AHEAD + 1)][P - 1] : __builtin_bit_cast(bf16x8, *(const u32x4*)(ap + 1024));
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc[t], 0, 0, 0);
                 if (!BF16) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc[t], 0, 0, 0);
             }
@@ -533,21 +562,18 @@ __device__ __forceinline__ void finish_deferred(const TileParams& p, unsigned ch
 }
 
 // Per-tile finishing work of the streaming modes: rank, write, book-keep; resets acc / nrm.
-// BOUNDS: the pass also leaves the row's distance bound (TileParams::expire); with listed rows (row_in >= 0 is the
-// number of row n, n_listed their count) the tile is 16 entries of the list instead of 16 consecutive rows.
+// BOUNDS: the pass also leaves the row's distance bound (TileParams::expire).
 // SPLIT: the clusters of the pass are ranked by two launches (TileParams::carry_in / carry_out).
-// ROWS: the pass may walk a list of rows.
+// ROWS: the tile is 16 entries of the workgroup's list of rows (row_in is the number of row n, n_listed the length of the
+// list) instead of 16 consecutive rows.
 template <int KT, bool BF16, int MODE, bool BOUNDS = false, bool SPLIT = false, bool ROWS = BOUNDS>
 __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* smem, f32x4 (&acc)[KT], float& nrm,
                                             int tile, int lane, float cmax, double& in_acc, int prev_in, int row_in = -1,
                                             uint32_t n_listed = 0, double gnow = 0.0, float2 carry = float2{0.f, 0.f}, float second_in = 0.f) {
     const int n = lane & 15, q = lane >> 4;
-    constexpr bool BYROW = ROWS;
-    const bool listed = BYROW && p.rows != nullptr;
-    const int64_t row0 = BYROW ? 0 : (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows;
-    const int64_t myrow = BYROW ? (int64_t)row_in : row0 + n;  // (BYROW: the clamped row the lane loaded)
-    const bool valid = listed ? (uint32_t)(tile * kRows + n) < n_listed
-                              : (BYROW ? (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows + n < p.N : myrow < p.N);
+    const int64_t row0 = ROWS ? 0 : (int64_t)(p.reverse ? (int)p.ntiles - 1 - tile : tile) * kRows;
+    const int64_t myrow = ROWS ? (int64_t)row_in : row0 + n;  // (ROWS: the clamped row the lane loaded)
+    const bool valid = ROWS ? (uint32_t)(tile * kRows + n) < n_listed : myrow < p.N;
     const float* s_cnorm = (const float*)(smem + p.off_cnorm);
     float xn2 = nrm;
     xn2 += __shfl_xor(xn2, 16, kWave);
@@ -668,7 +694,7 @@ __device__ __forceinline__ void finish_tile(const TileParams& p, unsigned char* 
         if (p.rep) atomicMin(&s_rep[idx], (unsigned long long)myrow);
         in_acc += (double)dmin;
     }
-    if (BYROW && p.expire && owner) {
+    if (ROWS && p.expire && owner) {
         // How far the centroids may drift before this row's nearest centroid can change: with e the error bound of
         // a score (the re-rank threshold, which bounds a difference of two scores, plus the rounding of |x|^2), the
         // nearest centroid is at most sqrt(|x|^2 + s1 + e) away and every other at least sqrt(|x|^2 + s2 - e).  A row
@@ -773,30 +799,134 @@ __device__ __forceinline__ void finish_tile_multi(const TileParams& p, unsigned 
     if (valid) *(u32x4*)(p.assign + (row0 + n) * 16 + 4 * q) = newa;
 }
 
+// ---- which rows does a pass with distance bounds evaluate? (Hamerly, SDM 2010) ----------
+// The update before moved centroid k by p(k) = sqrt(sum over the slices of move_part[.][k]).  A row's distance to
+// its own centroid grew by at most p(own) and its distance to any other shrank by at most the largest p among the
+// others, so the difference of the two shrank by at most the sum of the two largest movements.  That sum is added
+// to the running drift G; a row whose bound expire[i] (the drift at its last evaluation plus its margin then) is
+// still above G keeps its nearest centroid and is left out.  Every workgroup computes the same G (same data, same order).
+// A row evaluated without a margin has expire = the drift of that pass and is kept as soon as any centroid moves at all
+// (the drift then grows, by its last bit at least); while none moves its nearest centroid is what it was.  A margin is
+// rounded down by 1e-9 of itself, so a drift equal to expire has not used it up.
+//
+// Workgroup b of G takes the blocks of 64 rows b, b + G, b + 2 G, ...: rows that are due lie together where the matrix
+// is sorted, and this way every workgroup gets its share of them.  It writes their numbers to a region of `rows` of its
+// own and walks that list, so nothing crosses workgroups and no launch of its own stands between the update and the
+// pass.  (As a launch of its own, with one list for all, it took 5.4 us of a pass over 65536 x 1000, against 3 us here.
+// Taking all rows for a few passes after one that found nearly all of them due saved 2 us of such a pass, but the code
+// for both cost the ranking in two launches 6 .. 13 %.)
+// Returns the length of the list.
+__device__ __forceinline__ uint32_t select_rows(const TileParams& p, unsigned char* smem, int lane, int wave, const int32_t*& list_out,
+                                                double& gnow) {
+    int* s_misc = (int*)(smem + p.off_misc);  // [1] length of the list, [2 ..] doubles: the two largest movements per wave
+    double* s_top = (double*)(s_misc + 2);
+    const uint32_t nb = (uint32_t)((p.N + kWave - 1) / kWave), G = gridDim.x, b = blockIdx.x;
+    const uint32_t per = nb / G, extra = nb % G, mine = per + (b < extra ? 1u : 0u);  // (G <= nb: mine is at least 1)
+    int32_t* list = p.rows + (int64_t)kWave * ((int64_t)b * per + (b < extra ? b : extra));
+    list_out = list;
+    constexpr uint32_t U = 4;  // blocks per wave and round
+    const bool all = p.move_part == nullptr;
+    double ex[U];
+    auto block_row = [&](uint32_t i) { return (int64_t)kWave * ((int64_t)b + (int64_t)G * i) + lane; };
+    auto fetch = [&](uint32_t i0) {
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            const uint32_t i = i0 + kMaxWaves * u;
+            const int64_t row = block_row(i < mine ? i : mine - 1);
+            ex[u] = p.expire_read[row < p.N ? row : p.N - 1];
+        }
+    };
+    if (threadIdx.x == 0) s_misc[1] = 0;
+    gnow = 0.0;
+    if (!all) {
+        fetch((uint32_t)wave);
+        double t1 = 0.0, t2 = 0.0;
+        if ((int)threadIdx.x < p.move_K) {
+            double m2 = 0.0;
+            const double* mp = p.move_part + threadIdx.x;
+            int sl = 0;
+            for (; sl + 8 <= p.move_slices; sl += 8) {  // eight loads in flight, added in slice order
+                double v[8];
+#pragma unroll
+                for (int u = 0; u < 8; u++) v[u] = mp[(size_t)(sl + u) * p.move_K];
+#pragma unroll
+                for (int u = 0; u < 8; u++) m2 += v[u];
+            }
+            for (; sl < p.move_slices; sl++) m2 += mp[(size_t)sl * p.move_K];
+            t1 = fmax(sqrt(m2), 0.0);
+        }
+        // the two largest of the wave's movements (the second: with one holder of the first taken out)
+        double w1 = t1;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) w1 = fmax(w1, __shfl_xor(w1, o, kWave));
+        const unsigned long long holders = __ballot(t1 == w1);
+        double w2 = lane == (int)__builtin_ctzll(holders) ? t2 : t1;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) w2 = fmax(w2, __shfl_xor(w2, o, kWave));
+        if (lane == 0) {
+            s_top[2 * wave] = w1;
+            s_top[2 * wave + 1] = w2;
+        }
+    }
+    const double g0 = all ? 0.0 : *p.g_prev;
+    __syncthreads();
+    if (!all) {
+        double t1 = 0.0, t2 = 0.0;
+#pragma unroll
+        for (int w = 0; w < kMaxWaves; w++) {
+            const double a = s_top[2 * w], c = s_top[2 * w + 1];
+            t2 = fmax(fmax(t2, c), fmin(t1, a));
+            t1 = fmax(t1, a);
+        }
+        gnow = g0 + (t1 + t2) * (1.0 + 1e-9);
+        if (t1 + t2 > 0.0 && gnow == g0) gnow = __longlong_as_double(__double_as_longlong(g0) + 1);  // (drifts are >= 0)
+        if (b == 0 && threadIdx.x == 0) *p.g_now = gnow;
+    }
+    for (uint32_t i0 = (uint32_t)wave; i0 < mine; i0 += U * kMaxWaves) {
+        if (!all && i0 != (uint32_t)wave) fetch(i0);
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            const uint32_t i = i0 + kMaxWaves * u;
+            const int64_t row = block_row(i);
+            const bool due = i < mine && row < p.N && (all || !(gnow <= ex[u]));
+            const unsigned long long m = __ballot(due);
+            if (!m) continue;
+            int pos = 0;
+            if (lane == 0) pos = atomicAdd(&s_misc[1], (int)__builtin_popcountll(m));
+            pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+            if (due) list[pos] = (int32_t)row;
+        }
+    }
+    __syncthreads();
+    return (uint32_t)__builtin_amdgcn_readfirstlane(s_misc[1]);
+}
+
 // ---- the kernel ----------------------------------------------------------------------
 // VAR: 0 the plain pass, 1 several centroid sets side by side (finish_tile_multi), 2 a pass that keeps distance
-// bounds and may walk a list of rows instead of all of them (TileParams::expire, rows), 3 one of the two launches
-// that rank the halves of a large cluster set (TileParams::carry_in, carry_out).
-// 4 the same where the pass keeps bounds or walks a list (100000 x 512 bf16, K = 200 without either: 191 us in variant 3, 217 in
-// variant 4).
+// bounds and evaluates the rows that are due (select_rows), 3 one of the two launches that rank the halves of a large
+// cluster set (TileParams::carry_in, carry_out), 4 the same in a pass that keeps bounds.
 enum { VAR_PLAIN = 0, VAR_MULTI = 1, VAR_BOUNDS = 2, VAR_SPLIT = 3, VAR_SPLIT_ROWS = 4 };
 template <int KT, int PASSES, bool BF16, int MODE, bool CA, int VAR = VAR_PLAIN>
 __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool MULTI = VAR == VAR_MULTI, BOUNDS = VAR == VAR_BOUNDS, SPLIT = VAR == VAR_SPLIT || VAR == VAR_SPLIT_ROWS;
     if (p.skip_when_zero && *p.skip_when_zero == 0u) return;  // uniform over the grid, before any barrier
-    constexpr bool BYROW = BOUNDS || VAR == VAR_SPLIT_ROWS;  // may walk listed rows
-    const bool listed = BYROW && p.rows != nullptr;
-    const uint32_t n_listed = listed ? *p.n_rows : 0u;
-    const double gnow = (BYROW && p.gnow) ? *p.gnow : 0.0;
-    if (BYROW && p.evaluated_slot && blockIdx.x == 0 && threadIdx.x == 0)
-        *p.evaluated_slot = listed ? (int32_t)n_listed : (int32_t)p.N;
-    // listed rows: the tiles go to the workgroups in turn, so that a short list occupies one wave of every workgroup and
-    // not all waves of a few (65536 x 1000, K = 16, 3,300 listed rows: with that and the queue of near-tie rows 16 us a pass,
-    // 22 us before); a workgroup none of whose waves has a tile leaves before any barrier
-    if (listed && (uint32_t)blockIdx.x * kRows >= n_listed) return;
+    constexpr bool BYROW = BOUNDS || VAR == VAR_SPLIT_ROWS;  // walks a list of rows
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform: keeps tile math scalar
+    uint32_t n_listed = 0;
+    double gnow = 0.0;
+    const int32_t* list = nullptr;
+    if (BYROW) {
+        if (p.still && *p.still) {  // uniform over the grid, before any barrier
+            if (blockIdx.x == 0 && threadIdx.x == 0) *p.g_now = *p.g_prev;
+            return;
+        }
+        n_listed = select_rows(p, smem, lane, wave, list, gnow);
+        if (n_listed == 0) return;  // uniform over the workgroup
+        if (p.evaluated_slot && threadIdx.x == 0) atomicAdd(p.evaluated_slot, (int)n_listed);
+    }
+    constexpr int AHEAD = !BYROW ? 0 : KT >= 8 && !BF16 ? 1 : 2;  // (two spill 48 registers more in the largest fp32 one)
     constexpr bool DEFERS = MODE == MODE_ASSIGN && VAR != VAR_MULTI && VAR != VAR_SPLIT;  // uses the queue of near-tie rows
     constexpr int P = PASSES == 1 ? 1 : 2;
     float* s_cnorm = (float*)(smem + p.off_cnorm);
@@ -804,46 +934,49 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
     unsigned long long* s_rep = (unsigned long long*)(smem + p.off_rep);
     int* s_misc = (int*)(smem + p.off_misc);  // [0] list count, [2..] doubles for the objective
 
-    const int ntiles = listed ? (int)((n_listed + kRows - 1) / kRows) : (int)p.ntiles;
-    const int tstride = (int)gridDim.x * p.waves;
-    const int tile0 = __builtin_amdgcn_readfirstlane(listed ? wave * (int)gridDim.x + (int)blockIdx.x : (int)blockIdx.x * p.waves + wave);
+    const int ntiles = BYROW ? (int)((n_listed + kRows - 1) / kRows) : (int)p.ntiles;
+    const int tstride = BYROW ? p.waves : (int)gridDim.x * p.waves;
+    const int tile0 = __builtin_amdgcn_readfirstlane(BYROW ? wave : (int)blockIdx.x * p.waves + wave);
     int tl = tile0, cl = 0;  // load cursor
     float cmax_out;
     ChunkRegs<BF16> b0, b1, b2;
-    // BOUNDS: the number of the row this lane loads in the tile at the load cursor, and in the tile after it: an
-    // entry of the list (requested a whole tile ahead: waiting for it where it is needed would drain the chunks in
-    // flight) or, without a list, the tile's own rows.  Either way the chunk loads themselves sit in no branch.
-    int lrow = 0, lrow_nx = 0;
-    auto tile_row = [&](int tile) -> int {
-        if (listed) {
-            uint32_t e = (uint32_t)tile * kRows + (uint32_t)(lane & 15);
-            e = e < n_listed ? e : n_listed - 1u;  // n_listed > 0 here (the workgroup has a tile)
-            return p.rows[e];
+    // Listed rows: the number of the row this lane loads next (lrow).  Load i of the wave carries the number for load
+    // i + 3 (ChunkRegs::row_ahead), which becomes lrow when load i is consumed: at most two loads are outstanding then.
+    // ta, ca: the tile and chunk of that load.
+    int lrow = 0, lrow1 = 0, lrow2 = 0, ta = tile0, ca = 0;
+    auto entry = [&](int tile) -> const int32_t* {  // of row n; a tile past the last: the list's last row
+        uint32_t e = (uint32_t)tile * kRows + (uint32_t)(lane & 15);
+        e = e < n_listed ? e : n_listed - 1u;  // n_listed > 0
+        return list + (p.reverse ? n_listed - 1u - e : e);
+    };
+    auto step_ahead = [&]() {
+        if (++ca == p.nchunks) {
+            ca = 0;
+            ta += tstride;
         }
-        const int64_t row0 = (int64_t)(p.reverse ? ntiles - 1 - tile : tile) * kRows;
-        const int nv = (p.N - row0) < kRows ? (int)(p.N - row0) : kRows;
-        return (int)row0 + ((lane & 15) < nv ? (lane & 15) : nv - 1);  // (N is below 2^31 in these passes)
     };
     if (BYROW) {
-        lrow = tile_row(tile0 < ntiles ? tile0 : 0);
-        lrow_nx = tile_row(tile0 + tstride < ntiles ? tile0 + tstride : 0);
+        lrow = *entry(ta);
+        step_ahead();
+        lrow1 = *entry(ta);
+        step_ahead();
+        lrow2 = *entry(ta);
+        step_ahead();
     }
     // A wave stops requesting rows once its cursor has passed its last tile.  (Requesting them
     // unconditionally, the last tile again, lets the compiler count on two chunks in flight at
     // every wait instead of draining to one; measured, that was 2-5 % slower, not faster.)
 #define CAT_ISSUE(buf)                                                                     \
     if (tl < ntiles) {                                                                     \
-        if (BYROW)                                                                         \
-            load_chunk<BF16, SPLIT ? 4 : 1, true>(buf, p, tl, cl, lane, lrow);             \
-        else                                                                               \
+        if (BYROW) {                                                                       \
+            load_chunk<BF16, SPLIT ? 4 : 1, true>(buf, p, tl, cl, lane, lrow, entry(ta));  \
+            step_ahead();                                                                  \
+        } else {                                                                           \
             load_chunk<BF16, MODE == MODE_ASSIGN ? (MULTI ? 2 : SPLIT ? 3 : 1) : 0>(buf, p, tl, cl, lane); \
+        }                                                                                  \
         if (++cl == p.nchunks) {                                                           \
             cl = 0;                                                                        \
             tl += tstride;                                                                 \
-            if (BYROW) {                                                                   \
-                lrow = lrow_nx;                                                            \
-                lrow_nx = tile_row(tl + tstride < ntiles ? tl + tstride : 0);              \
-            }                                                                              \
         }                                                                                  \
     }
     // prologue: centroids (operand order) and their norms into LDS.  Returns come back in issue order,
@@ -885,7 +1018,9 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
             }
         }
         CAT_ISSUE(b0)
+        lrow = lrow1;
         CAT_ISSUE(b1)
+        lrow = lrow2;
         if (first) {
 #pragma unroll
             for (int u = 0; u < 8; u++) dst[i + u * nt] = t[u];
@@ -927,7 +1062,8 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         if (SPLIT) {
             // the error bound of a comparison involves the norms of both shares
             if (p.carry_in) cmax_out = fmaxf(cmax_out, *p.cmax_io);
-            if (p.carry_out && blockIdx.x == 0 && threadIdx.x == 0) *p.cmax_io = cmax_out;
+            // (listed rows: any workgroup may have left; those that have rows write the same value)
+            if (p.carry_out && (BYROW || blockIdx.x == 0) && threadIdx.x == 0) *p.cmax_io = cmax_out;
         }
     }
     const float cmax = cmax_out;
@@ -942,7 +1078,8 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
     for (int t = 0; t < KT; t++) acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     int tc = tile0, cc = 0;  // compute cursor
 #define CAT_STEP(buf)                                                                                          \
-    contract_chunk<KT, PASSES, BF16>(buf, acc, nrm, smem + (size_t)cc * 4 * KT * P * 1024, lane, cc, p.D);     \
+    contract_chunk<KT, PASSES, BF16, AHEAD>(buf, acc, nrm, smem + (size_t)cc * 4 * KT * P * 1024, lane, cc, p.D);     \
+    if (BYROW) lrow = buf.row_ahead;                                                                           \
     if (++cc == p.nchunks) {                                                                                   \
         if (MULTI)                                                                                             \
             finish_tile_multi<KT, BF16>(p, smem, acc, nrm, tc, lane, cmax, buf.prevv);                         \
@@ -962,7 +1099,7 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         // the operand travels global -> registers -> LDS while the current one is contracted.
         constexpr int chunkA = 4 * KT * P * 1024;
         constexpr int AREG = (chunkA / 16 + kMaxWaves * kWave - 1) / (kMaxWaves * kWave);
-        const int wg_tile0 = listed ? (int)blockIdx.x : (int)blockIdx.x * p.waves;  // its first wave's: that wave has the most
+        const int wg_tile0 = BYROW ? 0 : (int)blockIdx.x * p.waves;  // its first wave's: that wave has the most
         const int wg_tiles = wg_tile0 < ntiles ? (ntiles - 1 - wg_tile0) / tstride + 1 : 0;
         const int nsteps = wg_tiles * p.nchunks;
         int s = 0;
@@ -988,7 +1125,8 @@ __global__ __launch_bounds__(kMaxWaves * kWave) void k_tile(const TileParams p) 
         CAT_CA_LOAD(regl)                                                                                     \
         CAT_ISSUE(bufnext)                                                                                    \
         if (tc < ntiles) {                                                                                    \
-            contract_chunk<KT, PASSES, BF16>(bufcur, acc, nrm, smem + (size_t)(s & 1) * chunkA, lane, cc, p.D); \
+            contract_chunk<KT, PASSES, BF16, AHEAD>(bufcur, acc, nrm, smem + (size_t)(s & 1) * chunkA, lane, cc, p.D); \
+            if (BYROW) lrow = bufcur.row_ahead;                                                               \
             if (++cc == p.nchunks) {                                                                          \
                 if (MULTI)                                                                                    \
                     finish_tile_multi<KT, BF16>(p, smem, acc, nrm, tc, lane, cmax, bufcur.prevv);             \
@@ -1154,19 +1292,23 @@ static inline cat_status launch_kt_multi(const TileParams& p, const TileCfg& c, 
                     : launch_one<KT, 1, BF16, MODE_ASSIGN, false, VAR_MULTI>(p, c, st);
 }
 
-// assignment passes that keep distance bounds (two-part operand only)
+// assignment passes that keep distance bounds (two-part operand only; kMaxWaves waves, row numbers below 2^31)
 template <int KT, bool BF16>
 static inline cat_status launch_kt_bounds(const TileParams& p, const TileCfg& c, hipStream_t st) {
+    if (c.waves != kMaxWaves || p.N >= ((int64_t)1 << 31))
+        return set_error(CAT_ERR_UNSUPPORTED, "tile kernel with distance bounds: %d waves, N = %lld", c.waves, (long long)p.N);
     if (c.P != 2) return set_error(CAT_ERR_UNSUPPORTED, "tile kernel with distance bounds: two-part operand only");
     if (c.chunked) return launch_one<KT, 3, BF16, MODE_ASSIGN, true, VAR_BOUNDS>(p, c, st);
     return launch_one<KT, 3, BF16, MODE_ASSIGN, false, VAR_BOUNDS>(p, c, st);
 }
 
 // one of the two launches over the halves of a large cluster set (8 cluster tiles each, two-part operand); VAR_SPLIT_ROWS in
-// passes that keep bounds
+// passes that keep bounds (kMaxWaves waves, row numbers below 2^31)
 template <bool BF16, int VAR>
 static inline cat_status launch_split(const TileParams& p, const TileCfg& c, hipStream_t st) {
     if (c.KT != 8 || c.P != 2) return set_error(CAT_ERR_UNSUPPORTED, "split ranking: 8 cluster tiles and the two-part operand only");
+    if (VAR == VAR_SPLIT_ROWS && (c.waves != kMaxWaves || p.N >= ((int64_t)1 << 31)))
+        return set_error(CAT_ERR_UNSUPPORTED, "tile kernel with distance bounds: %d waves, N = %lld", c.waves, (long long)p.N);
     if (c.chunked) return launch_one<8, 3, BF16, MODE_ASSIGN, true, VAR>(p, c, st);
     return launch_one<8, 3, BF16, MODE_ASSIGN, false, VAR>(p, c, st);
 }

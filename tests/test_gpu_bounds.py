@@ -143,3 +143,22 @@ def test_full_size_workloads(name):
     ev = b["rows_evaluated"].cpu().numpy()
     print(name, "rows evaluated per pass:", ev.tolist())
     assert ev[0] == w["N"] and ev[-1] == w["N"] and ev[3:-1].min() < w["N"]
+
+
+@pytest.mark.parametrize("N,D,K", [
+    (1, 64, 1), (63, 16, 2), (64, 64, 3), (65, 200, 3), (127, 128, 5), (129, 132, 5),  # blocks of 64 rows and their remainders
+    (16 * 8 * 300 + 7, 64, 4),     # more blocks of rows than workgroups: several rounds of the selection; one chunk per row
+    (70001, 200, 6), (40007, 300, 7),  # two and three chunks per row
+])
+def test_selected_rows_at_the_edges_of_blocks_and_lists(N, D, K):
+    rng = np.random.default_rng(N + D)
+    centres = rng.standard_normal((K, D)) * 1.2
+    lab = np.sort(rng.integers(0, K, N))  # sorted: the rows that are due lie together
+    x = (centres[lab] + rng.standard_normal((N, D))).astype(np.float32)
+    xd, yd = dev_matrix(x, "f32"), dev_matrix(x * 2, "f32")
+    b = cat_fit(xd, yd, K, 8, seed=3, bounds=True)
+    _same_as_plain(b, cat_fit(xd, yd, K, 8, seed=3), 8)
+    o = oracle.fit_bounds(x, x * 2, K, 8, seed=3)
+    assert (b["assignments"].cpu().numpy() == o["assignments"]).all()
+    ev = b["rows_evaluated"].cpu().numpy()
+    assert (ev >= np.asarray(_rows_that_change(x, K, 8, 3))).all() and (ev <= N).all()
