@@ -130,8 +130,8 @@ size_t cat_apply_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt);
  *                 compared with their spread.  The assignments do not depend on it.
  *                 On matrices of 64 MB and more (32 MB with K > 128) a pass leaves out the rows whose distance
  *                 bounds (cat_fit_bounds) say that they keep their centroid; from pass 3 on the
- *                 objective then is that of pass 2 plus the change of
- *                 sum_k c_k . (n_k c_k - 2 S_k), S_k the cluster sums, in double precision.
+ *                 objective then is sum |x|^2 + sum_k c_k . (n_k c_k - 2 S_k), S_k the cluster
+ *                 sums, in double precision throughout and not below zero.
  */
 cat_status cat_fit(const void *lq, const void *fp, int64_t N, int64_t D, int32_t K,
                    int32_t iters, uint64_t seed, cat_dtype dt,

@@ -124,8 +124,9 @@ cat_status launch_assign_lds(const void* lq, cat_dtype dt, int64_t N, int64_t D,
 cat_status launch_count_rep(const int32_t* assign, int64_t N, int32_t K, int32_t* counts,
                             unsigned long long* rep, hipStream_t st);
 // rep[k] = the first row with label k, given the counts (rep pre-initialised to ~0ull); N below 2^31
+// objective: nonneg entries from there on are raised to zero if they are below (sums of large numbers that should cancel).
 cat_status launch_first_rows(const int32_t* assign, int64_t N, int32_t K, const int32_t* counts, unsigned long long* rep,
-                             hipStream_t st);
+                             double* objective, int32_t nonneg, hipStream_t st);
 // Segmented sums over the rows of each cluster.  NQ = 1: acc[0] += x.  NQ = 4: with x' = x - pivx[k],
 // y' = y - pivy[k]: acc[0] += x', acc[1] += y', acc[2] += x'^2, acc[3] += x'y'.  acc is NQ x K x D
 // doubles, pre-zeroed.
@@ -141,9 +142,12 @@ bool segsum_sorted_supported(int nq, int64_t N, int64_t D, cat_dtype dt);
 // whatever the size heuristics say (this is how the tests reach them on small shapes)
 bool fast_paths_forced();
 size_t sort_workspace_words(int64_t N, int32_t K);
+// (sumsq, with nq = 1: the sum of x^2 over the whole matrix is added, spread over kSumSqSlots entries kSumSqStride apart:
+// the waves end together, and one address takes their additions one after the other)
+constexpr int kSumSqSlots = 64, kSumSqStride = 16;
 cat_status launch_segsum_sorted(int nq, const void* lq, const void* fp, cat_dtype dt, const int32_t* assign,
                                 const int32_t* counts, int64_t N, int64_t D, int32_t K, const float* pivx,
-                                const float* pivy, double* acc, uint32_t* sort_ws, hipStream_t st);
+                                const float* pivy, double* acc, uint32_t* sort_ws, hipStream_t st, double* sumsq = nullptr);
 cat_status launch_finalize_centroids(const double* sums, const int32_t* counts, const float* prev,
                                      float* cent, int64_t D, int32_t K, hipStream_t st);
 // pivx = hint (if given) else lq[rep[k]]; pivy = fp[rep[k]]; rows of empty clusters are zero

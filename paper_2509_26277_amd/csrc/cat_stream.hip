@@ -431,7 +431,11 @@ cat_status launch_count_rep(const int32_t* assign, int64_t N, int32_t K, int32_t
 // merges every block's table: 22 us for 1,048,576 labels, K = 32.)
 constexpr int kFirstThreads = 256, kFirstPer = 4;
 __global__ __launch_bounds__(kFirstThreads) void k_first_rows(const int32_t* __restrict__ assign, int64_t N, int32_t K, int64_t share,
-                                                              const int32_t* __restrict__ counts, unsigned long long* __restrict__ rep) {
+                                                              const int32_t* __restrict__ counts, unsigned long long* __restrict__ rep,
+                                                              double* __restrict__ objective, int32_t nonneg) {
+    if (blockIdx.x == 0)
+        for (int t = threadIdx.x; t < nonneg; t += kFirstThreads)
+            if (objective[t] < 0.0) objective[t] = 0.0;
     __shared__ uint32_t s_first[CAT_MAX_K];
     for (int k = threadIdx.x; k < K; k += kFirstThreads) s_first[k] = 0xFFFFFFFFu;
     __syncthreads();
@@ -457,13 +461,14 @@ __global__ __launch_bounds__(kFirstThreads) void k_first_rows(const int32_t* __r
         if (s_first[k] != 0xFFFFFFFFu) atomicMin(&rep[k], (unsigned long long)(b0 + s_first[k]));
 }
 cat_status launch_first_rows(const int32_t* assign, int64_t N, int32_t K, const int32_t* counts, unsigned long long* rep,
-                             hipStream_t st) {
+                             double* objective, int32_t nonneg, hipStream_t st) {
     if (N >= ((int64_t)1 << 31) || K > CAT_MAX_K) return set_error(CAT_ERR_UNSUPPORTED, "first rows: N or K too large");
     const int64_t step = kFirstThreads * kFirstPer;
     int64_t blocks = (N + step - 1) / step;
     blocks = blocks > 256 ? 256 : blocks;
     const int64_t share = ((N + blocks - 1) / blocks + step - 1) / step * step;
-    hipLaunchKernelGGL(k_first_rows, dim3((unsigned)((N + share - 1) / share)), dim3(kFirstThreads), 0, st, assign, N, K, share, counts, rep);
+    hipLaunchKernelGGL(k_first_rows, dim3((unsigned)((N + share - 1) / share)), dim3(kFirstThreads), 0, st, assign, N, K, share, counts, rep,
+                       objective, objective ? nonneg : 0);
     CAT_LAUNCH_CHECK("k_first_rows");
     return CAT_OK;
 }
@@ -653,11 +658,12 @@ constexpr int kSortV = 2;
 // ODD: fp32 rows of an odd length (rows start on 4 bytes, not 8): the lane's two channels are 64 apart, each a 4-byte load,
 // and a wave instruction still reads 256 consecutive bytes.  (50021 x 1001, K = 200: the statistics 538 us on the
 // LDS-panel kernel these rows took before.)
-template <typename T, int NQ, bool ODD = false>
+// SQ (with NQ = 1): the sum of all x^2 as well, spread over kSumSqSlots entries of sumsq.
+template <typename T, int NQ, bool ODD = false, bool SQ = false>
 __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
     const T* __restrict__ lq, const T* __restrict__ fp, const uint32_t* __restrict__ perm,
     const uint32_t* __restrict__ offs, int64_t D, int32_t K, int32_t R, int32_t nsl, int64_t nitems,
-    const float* __restrict__ pivx, const float* __restrict__ pivy, double* __restrict__ acc) {
+    const float* __restrict__ pivx, const float* __restrict__ pivy, double* __restrict__ acc, double* __restrict__ sumsq) {
     constexpr int V = kSortV;
     constexpr int RB = 4;  // rows per round; two rounds are in flight
     __shared__ uint32_t s_offs[CAT_MAX_K + 1];
@@ -702,6 +708,7 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
         sx[v] = sy[v] = sxx[v] = sxy[v] = 0.0;
         px[v] = py[v] = 0.f;
     }
+    double sq = 0.0;
     auto load_piv = [&]() {
         if (NQ == 4) {
 #pragma unroll
@@ -798,6 +805,7 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
                     }
                     if (NQ == 1) {
                         sx[v] += (double)x;
+                        if (SQ && on[v]) sq = fma((double)x, (double)x, sq);
                     } else {
                         // the shifts keep the raw second moments close to the centred ones
                         const float xs = x - px[v], ys = y - py[v];
@@ -822,6 +830,10 @@ __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(
         consume(r + 1, xb, yb);
     }
     flush();
+    if (SQ) {
+        sq = wave_total(sq);
+        if (lane == 0) atomicAdd(sumsq + (item % kSumSqSlots) * kSumSqStride, sq);
+    }
 }
 
 bool segsum_sorted_supported(int nq, int64_t N, int64_t D, cat_dtype dt) {
@@ -838,7 +850,7 @@ size_t sort_workspace_words(int64_t N, int32_t K) { return (size_t)N + 2 * (size
 
 cat_status launch_segsum_sorted(int nq, const void* lq, const void* fp, cat_dtype dt, const int32_t* assign,
                                 const int32_t* counts, int64_t N, int64_t D, int32_t K, const float* pivx,
-                                const float* pivy, double* acc, uint32_t* sort_ws, hipStream_t st) {
+                                const float* pivy, double* acc, uint32_t* sort_ws, hipStream_t st, double* sumsq) {
     uint32_t* offs = sort_ws;            // K + 1
     uint32_t* cursor = sort_ws + K + 1;  // K
     uint32_t* perm = sort_ws + 2 * (size_t)K + 2;
@@ -882,8 +894,12 @@ cat_status launch_segsum_sorted(int nq, const void* lq, const void* fp, cat_dtyp
     dim3 grid((unsigned)((nitems + kSortWaves - 1) / kSortWaves)), block(kSortWaves * kWave);
 #define CAT_SEGS(T, ...)                                                                                          \
     hipLaunchKernelGGL((k_segsum_sorted<T, __VA_ARGS__>), grid, block, 0, st, (const T*)lq, (const T*)fp, perm, offs, D, K, \
-                       (int32_t)R, nsl, nitems, pivx, pivy, acc)
-    if (odd) {
+                       (int32_t)R, nsl, nitems, pivx, pivy, acc, sumsq)
+    if (sumsq && nq == 1) {
+        if (odd) CAT_SEGS(float, 1, true, true);
+        else if (dt == CAT_F32) CAT_SEGS(float, 1, false, true);
+        else CAT_SEGS(bf16_t, 1, false, true);
+    } else if (odd) {
         if (nq == 1) CAT_SEGS(float, 1, true); else CAT_SEGS(float, 4, true);
     } else if (dt == CAT_F32) {
         if (nq == 1) CAT_SEGS(float, 1); else CAT_SEGS(float, 4);

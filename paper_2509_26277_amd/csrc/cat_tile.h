@@ -41,8 +41,9 @@ struct LloydWs {
     int32_t* skipped = nullptr;          //   then one word: passes left out, for callers that bring no word of their own
     //   then (cleared with ctrl) the state of a loop with bounds, by parity of the pass where two:
     double* drift = nullptr;             // 2  accumulated centroid drift up to a pass
-    double* objective = nullptr;         // 1  the part of the objective that depends on the centroids, of the first listed pass
+    double* sq_total = nullptr;          // 1  the sum of |x|^2 over all rows
     uint32_t* quiet = nullptr;           // 2  no row changed cluster in the pass before
+    double* sumsq = nullptr;             // kSumSqSlots entries: that sum as it is added up (launch_segsum_sorted)
     double* norm_part = nullptr;         // slices x K
     int32_t* counts2 = nullptr;          // K: the second half of the counts double buffer
     float2* carry = nullptr;             // N pairs, only for more than 128 clusters: what the first of two launches that
@@ -85,8 +86,8 @@ cat_status launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 // rows whose bound the centroid drift has used up.  Same centroids, assignments, counts and rep; of the objective
 // only the entries of the passes that evaluate every row (0, 1, 2 and the last) are written, the others are NaN.
 // With bw->record the last pass leaves rows out as well and every entry of the objective is written: with the sums S_k
-// of the clusters, which the update keeps in double, the objective of a pass is a constant of the rows plus
-// sum_k c_k . (n_k c_k - 2 S_k); the constant comes from pass 2, which evaluates every row.
+// of the clusters, which the update keeps in double, the objective of a pass is sum |x|^2 + sum_k c_k . (n_k c_k - 2 S_k),
+// in double precision throughout; the sum of |x|^2 is added up along with the cluster sums of pass 1.
 cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters,
                       float* cent_io, double* sums, int32_t* assign, int32_t* counts, double* inertia,
                       unsigned long long* rep, int32_t* skipped, const TileWs& ws, const LloydWs& lw, hipStream_t st,

@@ -173,12 +173,16 @@ struct DeltaParams {
     int32_t* slice_counts;
     int32_t seed_counts;
     double* move_part;
+    // (given here rather than read from the launch's own arguments: with those the kernel spills 170 scalar registers
+    // instead of 67, 0.3 us of each launch)
+    int32_t slices;
+    uint32_t groups;             // workgroups per slice
     // The objective of the pass before, whose centroids are still `cent` on entry and whose sums this launch completes:
-    // constant + sum_k c_k . (n_k c_k - 2 S_k).  Every slice adds its share of that sum to obj_out; with obj_ref (the same
-    // sum of a pass whose objective in_ref[0] is known) one workgroup adds the constant, in_ref[0] - obj_ref[0].
+    // sum |x|^2 + sum_k c_k . (n_k c_k - 2 S_k).  Every slice adds its share of that sum to obj_out, one workgroup the first
+    // term (sq_total), which the first of these launches has added up from sumsq.
     double* obj_out;             // nullable, zero on entry
-    const double* obj_ref;
-    const double* in_ref;
+    const double* sumsq;         // nullable
+    double* sq_total;
     // Words for the loops with bounds: quiet_next receives whether the pass before listed no row.  If the launch before
     // found that too (*quiet), the centroids did not move in it either: everything stays as it is.
     const uint32_t* quiet;       // nullable
@@ -193,12 +197,13 @@ constexpr int kDeltaSW = 64;  // channels per slice: one per lane
 
 template <typename T>
 __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaParams q) {
+    constexpr int NT = kDeltaWaves * kWave;
     extern __shared__ double s_panel[];  // KC x 64
     __shared__ int s_flag;
     __shared__ int s_moved[128];         // KC: rows that joined minus rows that left, per cluster of the range
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int slice = blockIdx.y, nslices = gridDim.y;
+    const int slice = blockIdx.y, nslices = q.slices;
     const int64_t ch = (int64_t)slice * kDeltaSW + lane;
     const bool ch_ok = ch < q.D;
     const int k0 = blockIdx.z * q.KC;
@@ -211,8 +216,8 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
         // written is carried forward instead, and the double buffers are left as a pass with an empty list
         // leaves them, so that the next launch of this kernel takes the same branch.
         if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
-            for (int k = threadIdx.x; k < q.K; k += blockDim.x) q.counts_next[k] = q.counts[k];
-            for (int s = threadIdx.x; s < nslices; s += blockDim.x) q.done_next[s] = 0;
+            for (int k = threadIdx.x; k < q.K; k += NT) q.counts_next[k] = q.counts[k];
+            for (int s = threadIdx.x; s < nslices; s += NT) q.done_next[s] = 0;
             if (threadIdx.x == 0) {
                 *q.list_count_next = 0;
                 if (q.inertia_slot) q.inertia_slot[0] = q.inertia_slot[-1];
@@ -222,11 +227,11 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
         return;
     }
     if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {  // the other halves of the double buffers
-        for (int k = threadIdx.x; k < q.K; k += blockDim.x) {
+        for (int k = threadIdx.x; k < q.K; k += NT) {
             q.counts_next[k] = 0;
             if (q.rep) q.rep[k] = ~0ull;
         }
-        for (int s = threadIdx.x; s < nslices; s += blockDim.x) q.done_next[s] = 0;
+        for (int s = threadIdx.x; s < nslices; s += NT) q.done_next[s] = 0;
         if (threadIdx.x == 0) *q.list_count_next = 0;
         if ((int)threadIdx.x < q.inertia_n && q.inertia_slot) q.inertia_slot[threadIdx.x] = 0.0;
     }
@@ -239,7 +244,7 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
             if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) {
                 if (threadIdx.x == 0 && q.obj_out) *q.obj_out = q.obj_out[-1];
                 if (q.last)
-                    for (int k = threadIdx.x; k < q.K; k += blockDim.x) q.counts_out[k] = q.slice_counts[k];
+                    for (int k = threadIdx.x; k < q.K; k += NT) q.counts_out[k] = q.slice_counts[k];
             }
             return;
         }
@@ -249,9 +254,9 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
     const uint32_t e1 = (e0 + per < len) ? e0 + per : len;
     const bool moving_counts = q.slice_counts && !q.seed_counts;
     if (e0 < e1) {
-        for (int i = threadIdx.x; i < kc * kDeltaSW; i += blockDim.x) s_panel[i] = 0.0;
+        for (int i = threadIdx.x; i < kc * kDeltaSW; i += NT) s_panel[i] = 0.0;
         if (moving_counts)
-            for (int i = threadIdx.x; i < kc; i += blockDim.x) s_moved[i] = 0;
+            for (int i = threadIdx.x; i < kc; i += NT) s_moved[i] = 0;
         __syncthreads();
         // each wave takes a contiguous run of the share: 64 entries per load, then 8 rows in flight
         const uint32_t pw = (e1 - e0 + kDeltaWaves - 1) / kDeltaWaves;
@@ -352,19 +357,26 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
             }
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < kc * kDeltaSW; i += blockDim.x) {
+        for (int i = threadIdx.x; i < kc * kDeltaSW; i += NT) {
             const int k = i / kDeltaSW, c = i - k * kDeltaSW;
             const double v = s_panel[i];
             const int64_t cg = (int64_t)slice * kDeltaSW + c;
             if (v != 0.0 && cg < q.D) atomicAdd(q.delta + (int64_t)(k0 + k) * q.D + cg, v);
         }
         if (moving_counts)
-            for (int i = threadIdx.x; i < kc; i += blockDim.x)
+            for (int i = threadIdx.x; i < kc; i += NT)
                 if (s_moved[i]) atomicAdd(q.slice_counts + (size_t)slice * q.K + k0 + i, s_moved[i]);
     }
 
-    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0 && q.obj_out && q.obj_ref)
-        atomicAdd(q.obj_out, q.in_ref[0] - q.obj_ref[0]);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && wave == 0) {
+        if (q.sumsq) {
+            double v = 0.0;
+            for (int i = lane; i < kSumSqSlots; i += kWave) v += q.sumsq[i * kSumSqStride];
+            v = wave_total(v);
+            if (lane == 0) *q.sq_total = v;
+        }
+        if (lane == 0 && q.obj_out) atomicAdd(q.obj_out, *q.sq_total);
+    }
 
     // ---- who finishes the slice? ----
     // What crosses workgroups here (delta, the counter) goes through device-scope atomics, which
@@ -374,7 +386,7 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
-        const uint32_t total = gridDim.x * gridDim.z;
+        const uint32_t total = q.groups;
         s_flag = atomicAdd(q.done + slice, 1u) == total - 1;
     }
     __syncthreads();
@@ -565,7 +577,7 @@ static inline int64_t delta_slices(int64_t D) { return (D + kDeltaSW - 1) / kDel
 constexpr int kSplitTiles = 8;  // cluster tiles per launch when the clusters of a pass are split over two
 
 // two list lengths, the finished-workgroup counters, the word of the early stop, padding to 8 bytes, the state of the bounds
-constexpr size_t kBoundsStateWords = 8;
+constexpr size_t kBoundsStateWords = 8 + 2 * kSumSqSlots * kSumSqStride;
 static inline size_t lloyd_ctrl_words(int64_t D) { return (size_t)(4 + 2 * delta_slices(D)) + kBoundsStateWords; }
 
 size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K) {
@@ -583,8 +595,9 @@ LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K) {
     b += a256(lloyd_ctrl_words(D) * 4);
     w.skipped = (int32_t*)(w.ctrl + 2 + 2 * delta_slices(D));
     w.drift = (double*)(w.ctrl + 4 + 2 * delta_slices(D));
-    w.objective = w.drift + 2;
+    w.sq_total = w.drift + 2;
     w.quiet = (uint32_t*)(w.drift + 3);
+    w.sumsq = w.drift + 4;
     w.norm_part = (double*)b;
     b += a256((size_t)delta_slices(D) * K * 8);
     w.counts2 = (int32_t*)b;
@@ -662,12 +675,12 @@ static cat_status launch_delta_prep(const void* lq, cat_dtype dt, int64_t D, int
                                     double* delta, const int32_t* counts_prev, int32_t* counts_next,
                                     double* inertia_slot, unsigned long long* rep, int32_t* skipped, hipStream_t st,
                                     int32_t inertia_n = 1, const BoundsWs* bw = nullptr, bool seed_counts = false,
-                                    int32_t split_tiles = 0, double* obj_out = nullptr, const double* in_ref = nullptr,
-                                    bool last = false, int32_t* counts_out = nullptr) {
+                                    int32_t split_tiles = 0, double* obj_out = nullptr, bool last = false,
+                                    int32_t* counts_out = nullptr) {
     DeltaParams q = {};
     q.obj_out = obj_out;
-    q.obj_ref = in_ref ? lw.objective : nullptr;
-    q.in_ref = in_ref;
+    q.sumsq = bw && bw->record && seed_counts ? lw.sumsq : nullptr;
+    q.sq_total = lw.sq_total;
     q.last = last ? 1 : 0;
     q.counts_out = counts_out;
     q.KTs = split_tiles ? split_tiles : c.KT;
@@ -706,6 +719,8 @@ static cat_status launch_delta_prep(const void* lq, cat_dtype dt, int64_t D, int
     q.inertia_n = inertia_n;
     q.rep = rep;
     q.skipped = skipped;
+    q.slices = (int32_t)slices;
+    q.groups = (uint32_t)q.G * (uint32_t)kchunks;
     dim3 grid((unsigned)q.G, (unsigned)slices, (unsigned)kchunks), block(kDeltaWaves * kWave);
     const size_t lds = (size_t)q.KC * kDeltaSW * sizeof(double);
     if (dt == CAT_BF16)
@@ -891,7 +906,8 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     // rows are left out by their bounds in the passes 3 .. iters - 1 (record: and in the last)
     const bool record = bw && bw->record;
     const bool one_launch = tile_bounds_supports(N, D, K, dt);
-    const bool bounds = bw && bw->expire && iters >= 4 && (one_launch || (record && lw.carry && bw->second && split_config(D, K, dt, nullptr)));
+    const bool bounds = bw && bw->expire && iters >= 4 && (!record || (lw.sort_ws && segsum_sorted_supported(1, N, D, dt))) &&
+                        (one_launch || (record && lw.carry && bw->second && split_config(D, K, dt, nullptr)));
     if (bounds) skipped = nullptr;  // (a pass over an empty list of rows costs next to nothing already)
     TileCfg c = tile_config(TILE_LLOYD, D, K, dt, bounds && one_launch);
     if (!c.ok) return set_error(CAT_ERR_UNSUPPORTED, "tile kernels do not fit D=%lld K=%d", (long long)D, (int)K);
@@ -940,8 +956,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
             CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, t & 1, cent_io, base, delta, cnt_prev, cnt_t, slot,
                                     last ? rep : nullptr, last ? nullptr : skipped, st, 1, bounds ? bw : nullptr,
                                     t == kFullPasses + 1, split ? kSplitTiles : 0,
-                                    !(bounds && record && inertia) ? nullptr : t == kFullPasses + 1 ? lw.objective : inertia + t - 1,
-                                    bounds && record && inertia && t > kFullPasses + 1 ? inertia + kFullPasses : nullptr));
+                                    bounds && record && inertia && t > kFullPasses + 1 ? inertia + t - 1 : nullptr));
         // With bounds: pass 2 evaluates every row and leaves its bound; the passes 3 .. iters - 1 evaluate the rows
         // whose bound the drift of the centroids has used up
         const bool keeps_bounds = bounds && t >= kFullPasses && (!last || record);
@@ -978,7 +993,8 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
         if (t < kFullPasses && !last) {  // full sums of this pass's partition
             CAT_T(launch_fill_zero(sums, (t == 0 ? 2 : 1) * KD * sizeof(double), st));
             if (lw.sort_ws && segsum_sorted_supported(1, N, D, dt))
-                CAT_T(launch_segsum_sorted(1, lq, nullptr, dt, assign, cnt_t, N, D, K, nullptr, nullptr, base, lw.sort_ws, st));
+                CAT_T(launch_segsum_sorted(1, lq, nullptr, dt, assign, cnt_t, N, D, K, nullptr, nullptr, base, lw.sort_ws, st,
+                                           bounds && record && inertia && t == 1 ? lw.sumsq : nullptr));
             else
                 CAT_T(launch_segsum(1, lq, nullptr, dt, assign, N, D, K, nullptr, nullptr, base, st));
         }
@@ -986,9 +1002,8 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     if (bounds && record) {
         // the rows the last pass moved, its objective and counts; the first rows of the clusters from the labels
         CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, (iters + 1) & 1, cent_io, base, delta, counts, lw.counts2, nullptr, rep,
-                                nullptr, st, 1, bw, false, split ? kSplitTiles : 0, inertia ? inertia + iters : nullptr,
-                                inertia ? inertia + kFullPasses : nullptr, true, counts));
-        CAT_T(launch_first_rows(assign, N, K, counts, rep, st));
+                                nullptr, st, 1, bw, false, split ? kSplitTiles : 0, inertia ? inertia + iters : nullptr, true, counts));
+        CAT_T(launch_first_rows(assign, N, K, counts, rep, inertia ? inertia + kFullPasses + 1 : nullptr, iters - kFullPasses, st));
     } else if (bounds && inertia && iters > kFullPasses + 1)  // the objective of a pass over listed rows is not known
         CAT_T(launch_fill_u64((unsigned long long*)(inertia + kFullPasses + 1), iters - kFullPasses - 1, 0x7ff8000000000000ull, st));
 #undef CAT_T

@@ -2,8 +2,8 @@
 per pass), against the loop that evaluates every row (cat_fit_early_stop: the same outputs by contract, no bounds).
 
 Centroids, assignments and counts are the same bit for bit.  The objective of the plain loop is a sum of float32 terms
-|x|^2 + score (relative error of a term up to about 1e-4 |x||c| over the distance, far less in the sum); cat_fit takes the
-constant from the same sum and the rest from double sums, so the two agree to 1e-5 here."""
+|x|^2 + score (relative error of a term up to about 1e-4 |x||c| over the distance, far less in the sum); cat_fit has it from
+double sums from pass 3 on, and the two agree to 1e-5 here."""
 import numpy as np
 import pytest
 import torch
@@ -55,10 +55,33 @@ def test_same_outputs_as_the_loop_that_reads_every_row(N, D, K, iters, dt, sprea
     _same(a, cat_fit(x, y, K, iters, seed=5, early_stop=True))
     assert int(a["counts"].sum()) == N
     assert torch.equal(a["counts"].long(), torch.bincount(a["assignments"].long(), minlength=K))
-    # the last entry of the objective against its definition in double (float32 terms enter through pass 2 only)
+    # the last entry of the objective against its definition in double (float32 terms where no row was left out)
     d = sum(float((xc.double() - a["centroids"].double()[ac.long()]).square().sum())
             for xc, ac in zip(x.split(20000), a["assignments"].split(20000)))
     np.testing.assert_allclose(float(a["inertia"][-1]), d, rtol=2e-5)
+
+
+@pytest.mark.parametrize("D,K,points,init", [
+    (256, 24, 40, False), (256, 24, 24, True),
+    (255, 24, 40, False),                       # on the padded copy
+    (256, 150, 200, False), (256, 150, 150, True),  # two launches per pass
+])
+def test_objective_of_repeated_rows_far_from_the_origin(D, K, points, init):
+    """Rows 300 from the origin in every channel, a hundredth apart: the objective is 1e-9 of the sums it is the difference of.
+    Double sums leave it with a few hundred roundings of that size; it is never negative, and zero where every row is a centroid
+    (started from the points themselves)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(D + K)
+    base = 300.0 + 0.01 * torch.randn(points, D, generator=g, device="cuda")
+    x = base[torch.randint(0, points, (70000,), generator=g, device="cuda")].contiguous()
+    r = cat_fit(x, 2 * x, K, 8, seed=4, init_centroids=base.contiguous() if init else None)
+    total = float(x.double().square().sum())
+    d = float((x.double() - r["centroids"].double()[r["assignments"].long()]).square().sum())
+    j = r["inertia"].cpu().numpy()
+    assert (j >= 0.0).all()
+    assert abs(j[-1] - d) <= 512 * 2.0 ** -53 * total
+    if init:
+        assert d == 0.0
 
 
 def test_duplicates_empty_clusters_and_exact_ties():
