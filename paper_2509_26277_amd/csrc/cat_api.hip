@@ -82,7 +82,10 @@ struct FitWs {
     size_t bytes;
 };
 
-static FitWs carve_fit(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt) {
+// bounds: with the scratch of the distance bounds, where the plain fits use them (single passes and the loops that stop
+// early or bring bounds of their own do not; the latter need bounds_state)
+static FitWs carve_fit(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt, bool bounds = false,
+                       bool bounds_state = false) {
     Carver c(base);
     FitWs w;
     size_t KD = (size_t)K * (size_t)D;
@@ -100,10 +103,11 @@ static FitWs carve_fit(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt
     w.tile = tile_carve(base ? (void*)(c.base + c.off) : nullptr, D, K, dt);
     c.off += align256(tb);
     if (tb) {
-        w.lloyd = lloyd_carve(base ? (void*)(c.base + c.off) : nullptr, N, D, K);
+        const bool keep = bounds && tile_bounds_pay(N, D, K, dt);
+        w.lloyd = lloyd_carve(base ? (void*)(c.base + c.off) : nullptr, N, D, K, keep || bounds_state);
         w.lloyd.sort_ws = w.sort;
         c.off += align256(w.lloyd.bytes);
-        if (tile_bounds_pay(N, D, K, dt)) {
+        if (keep) {
             w.bounds = bounds_carve(base ? (void*)(c.base + c.off) : nullptr, N, D, K, tile_bounds_split(D, K, dt));
             w.bounds.record = true;
             c.off += align256(w.bounds.bytes);
@@ -167,14 +171,14 @@ static std::atomic<bool> g_padded_fit{true};  // cat_debug_padded_fit
 static bool fit_runs_padded(int64_t N, int64_t D, int32_t K, cat_dtype dt, int32_t iters) {
     return g_padded_fit.load() && g_path.load() == CAT_PATH_AUTO && iters >= 2 && pad_applies(N, D, K, dt);
 }
-static PadWs carve_pad(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt, bool with_bounds) {
+static PadWs carve_pad(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt, bool with_bounds, bool fit_bounds) {
     PadWs w;
     w.Dp = padded_dim(D, dt);
     Carver c(base);
     w.lq = c.take<char>((size_t)N * (size_t)w.Dp * (dt == CAT_BF16 ? 2 : 4));
     w.cent = c.take<float>((size_t)K * (size_t)w.Dp);
     w.init = c.take<float>((size_t)K * (size_t)w.Dp);
-    w.fit = c.take<char>(carve_fit(nullptr, N, w.Dp, K, dt).bytes);
+    w.fit = c.take<char>(carve_fit(nullptr, N, w.Dp, K, dt, fit_bounds, with_bounds).bytes);
     if (with_bounds) w.bounds = c.take<char>(bounds_workspace_bytes(N, w.Dp, K));
     w.bytes = c.off;
     return w;
@@ -393,8 +397,8 @@ cat_status cat_select_path(cat_path p) {
 
 size_t cat_fit_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     if (!shape_ok(N, D, K, dt)) return 0;
-    size_t b = carve_fit(nullptr, N, D, K, dt).bytes;
-    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, false).bytes;
+    size_t b = carve_fit(nullptr, N, D, K, dt, true).bytes;
+    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, false, true).bytes;
     return b;
 }
 
@@ -493,27 +497,39 @@ static cat_status fit_impl(const char* who, const void* lq, const void* fp, int6
     CAT_TRY(check_ptr(who, "beta", beta, 16));
     CAT_TRY(check_ptr(who, "assignments", assignments, 4));
     if (inertia) CAT_TRY(check_ptr(who, "inertia", inertia, 8));
-    FitWs w = carve_fit(workspace, N, D, K, dt);
-    BoundsWs bw;
-    size_t need = w.bytes;
-    if (with_bounds) {
-        bw = bounds_carve(workspace ? (char*)workspace + align256(w.bytes) : nullptr, N, D, K);
-        bw.evaluated = evaluated;
-        need = align256(w.bytes) + bw.bytes;
-    }
     // rows that are not whole 16-byte groups: the clustering runs on a zero-padded copy (the scratch sizes of the fits
     // include it; the entry points that size their scratch from the pieces do not come through here)
     const bool padded = fit_runs_padded(N, D, K, dt, iters);
+    bool fit_bounds = !with_bounds && !skipped;  // the plain fit: distance bounds from the size on where they pay
+    FitWs w;
+    BoundsWs bw;
     PadWs pw;
-    if (padded) {
-        pw = carve_pad(workspace ? (char*)workspace + align256(need) : nullptr, N, D, K, dt, with_bounds);
-        need = align256(need) + pw.bytes;
+    auto carve = [&]() {
+        w = carve_fit(workspace, N, D, K, dt, fit_bounds, with_bounds);
+        size_t need = w.bytes;
+        if (with_bounds) {
+            bw = bounds_carve(workspace ? (char*)workspace + align256(w.bytes) : nullptr, N, D, K);
+            bw.evaluated = evaluated;
+            need = align256(w.bytes) + bw.bytes;
+        }
+        if (padded) {
+            pw = carve_pad(workspace ? (char*)workspace + align256(need) : nullptr, N, D, K, dt, with_bounds, fit_bounds);
+            need = align256(need) + pw.bytes;
+        }
+        return need;
+    };
+    size_t need = carve();
+    if (fit_bounds && workspace && workspace_bytes < need) {  // without the scratch of the bounds: every pass reads every row
+        const size_t full = need;
+        fit_bounds = false;
+        need = carve();
+        if (workspace_bytes < need) need = full;  // (the size to name)
     }
     CAT_TRY(check_ws(who, workspace, workspace_bytes, need));
     hipStream_t st = (hipStream_t)hip_stream;
     if (padded) {
         const int64_t Dp = pw.Dp;
-        FitWs wp = carve_fit(pw.fit, N, Dp, K, dt);
+        FitWs wp = carve_fit(pw.fit, N, Dp, K, dt, fit_bounds, with_bounds);
         BoundsWs bp;
         if (with_bounds) {
             bp = bounds_carve(pw.bounds, N, Dp, K);
@@ -554,8 +570,8 @@ cat_status cat_fit_early_stop(const void* lq, const void* fp, int64_t N, int64_t
 
 size_t cat_fit_bounds_workspace_bytes(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
     if (!shape_ok(N, D, K, dt) || iters < 0) return 0;
-    size_t b = align256(carve_fit(nullptr, N, D, K, dt).bytes) + bounds_workspace_bytes(N, D, K);
-    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, true).bytes;
+    size_t b = align256(carve_fit(nullptr, N, D, K, dt, false, true).bytes) + bounds_workspace_bytes(N, D, K);
+    if (pad_applies(N, D, K, dt)) b = align256(b) + carve_pad(nullptr, N, D, K, dt, true, false).bytes;
     return b;
 }
 
@@ -590,7 +606,7 @@ struct RestartWs {
 };
 static RestartWs carve_restarts(void* base, int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
     RestartWs w;
-    w.fit_bytes = carve_fit(nullptr, N, D, K, dt).bytes;
+    w.fit_bytes = carve_fit(nullptr, N, D, K, dt, true).bytes;
     w.pp_bytes = cat_init_kmeanspp_workspace_bytes(N, K);
     char* b = (char*)base;
     size_t off = 0;
@@ -607,7 +623,7 @@ static RestartWs carve_restarts(void* base, int64_t N, int64_t D, int32_t K, int
     w.inertia = (double*)take(((size_t)(iters < 0 ? 0 : iters) + 1) * sizeof(double));
     w.best = (double*)take(sizeof(double));
     w.state = (int32_t*)take(2 * sizeof(int32_t));
-    w.pad = pad_applies(N, D, K, dt) ? take(carve_pad(nullptr, N, D, K, dt, false).bytes) : nullptr;
+    w.pad = pad_applies(N, D, K, dt) ? take(carve_pad(nullptr, N, D, K, dt, false, true).bytes) : nullptr;
     w.bytes = off;
     return w;
 }
@@ -638,15 +654,15 @@ cat_status cat_fit_restarts(const void* lq, const void* fp, int64_t N, int64_t D
     RestartWs w = carve_restarts(workspace, N, D, K, iters, dt);
     CAT_TRY(check_ws("cat_fit_restarts", workspace, workspace_bytes, w.bytes));
     hipStream_t st = (hipStream_t)hip_stream;
-    FitWs fw = carve_fit(w.fit, N, D, K, dt);
+    FitWs fw = carve_fit(w.fit, N, D, K, dt, true);
     const size_t KD = (size_t)K * (size_t)D;
     // as in cat_fit: rows that are not whole 16-byte groups are padded once, every run clusters the copy
     const bool padded = fit_runs_padded(N, D, K, dt, iters);
     PadWs pw;
     FitWs wp;
     if (padded) {
-        pw = carve_pad(w.pad, N, D, K, dt, false);
-        wp = carve_fit(pw.fit, N, pw.Dp, K, dt);
+        pw = carve_pad(w.pad, N, D, K, dt, false, true);
+        wp = carve_fit(pw.fit, N, pw.Dp, K, dt, true);
         CAT_TRY(launch_pad_rows(lq, dt, N, D, pw.Dp, pw.lq, st));
     }
     for (int32_t r = 0; r < restarts; r++) {
@@ -753,7 +769,7 @@ static MultiWs carve_multi(void* base, int64_t N, int64_t D, const int32_t* Ks, 
     w.fit_bytes = 0;  // the scratch of one fit is not monotone in K (the tile kernels take some K and not others)
     int32_t Kmax = 1;
     for (int i = 0; i < nK; i++) {
-        size_t b = carve_fit(nullptr, N, D, Ks[i], dt).bytes;
+        size_t b = carve_fit(nullptr, N, D, Ks[i], dt, true).bytes;
         if (Dorig != D) {
             const size_t bo = carve_fit(nullptr, N, Dorig, Ks[i], dt).bytes;
             b = bo > b ? bo : b;
@@ -864,7 +880,7 @@ cat_status cat_fit_multi_k(const void* lq, const void* fp, int64_t N, int64_t D,
             double* in_i = inertia ? inertia + i * nin : nullptr;
             // (a count the matrix-core kernels do not take at the padded length either: the original rows, as cat_fit does)
             const bool on_copy = padded && tile_supports(TILE_LLOYD, N, Dl, K, dt);
-            FitWs fw = carve_fit(w.fit, N, on_copy ? Dl : D, K, dt);
+            FitWs fw = carve_fit(w.fit, N, on_copy ? Dl : D, K, dt, true);
             if (on_copy) {
                 CAT_TRY(run_lloyd(w.lqpad, dt, N, Dl, K, iters, seed, nullptr, w.centpad, asg_i, in_i, fw, st));
                 CAT_TRY(launch_pad_rows(w.centpad, CAT_F32, K, Dl, D, cent_i, st));
@@ -1118,7 +1134,7 @@ static PcaFitWs carve_pca_fit(void* base, int64_t N, int64_t D, int32_t K, int32
     PcaFitWs w;
     w.pca_bytes = cat_pca_workspace_bytes(N, D, p, dt);
     const int32_t pp = pad4(p);
-    w.lloyd_bytes = carve_fit(nullptr, N, pp, K, CAT_F32).bytes;
+    w.lloyd_bytes = carve_fit(nullptr, N, pp, K, CAT_F32, true).bytes;
     w.stats_bytes = carve_fit(nullptr, N, D, K, dt).bytes;
     char* b = (char*)base;
     size_t off = 0;
@@ -1165,7 +1181,7 @@ cat_status cat_fit_pca(const void* lq, const void* fp, int64_t N, int64_t D, int
     const int32_t pp = pad4(p);
     CAT_TRY(pca_project_ld(lq, N, D, p, dt, mean, components, w.z, pp, st));
     // clusters from the scores ...
-    FitWs wz = carve_fit(w.lloyd, N, pp, K, CAT_F32);
+    FitWs wz = carve_fit(w.lloyd, N, pp, K, CAT_F32, true);
     float* cz = pp == p ? centroids_z : w.cz;
     CAT_TRY(run_lloyd(w.z, CAT_F32, N, pp, K, iters, seed, nullptr, cz, assignments, inertia, wz, st));
     if (pp != p) CAT_TRY(launch_copy_cols(cz, K, pp, centroids_z, p, p, st));

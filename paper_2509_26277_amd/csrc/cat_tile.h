@@ -39,7 +39,7 @@ struct LloydWs {
     unsigned long long* list = nullptr;  // N entries
     uint32_t* ctrl = nullptr;            // [0..1] list length (two halves), then 2 x slices finished-workgroup counters,
     int32_t* skipped = nullptr;          //   then one word: passes left out, for callers that bring no word of their own
-    //   then (cleared with ctrl) the state of a loop with bounds, by parity of the pass where two:
+    //   then (only with bounds_state; cleared with ctrl) the state of a loop with bounds, by parity of the pass where two:
     double* drift = nullptr;             // 2  accumulated centroid drift up to a pass
     double* sq_total = nullptr;          // 1  the sum of |x|^2 over all rows
     uint32_t* quiet = nullptr;           // 2  no row changed cluster in the pass before
@@ -51,8 +51,8 @@ struct LloydWs {
     uint32_t* sort_ws = nullptr;         // not carved here: the caller's scratch for launch_segsum_sorted
     size_t bytes = 0;
 };
-size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K);
-LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K);
+size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K, bool bounds_state = false);
+LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K, bool bounds_state = false);
 
 // Scratch of the loops that leave rows out by distance bounds (Hamerly, SDM 2010): see tile_lloyd.
 struct BoundsWs {

@@ -578,26 +578,28 @@ constexpr int kSplitTiles = 8;  // cluster tiles per launch when the clusters of
 
 // two list lengths, the finished-workgroup counters, the word of the early stop, padding to 8 bytes, the state of the bounds
 constexpr size_t kBoundsStateWords = 8 + 2 * kSumSqSlots * kSumSqStride;
-static inline size_t lloyd_ctrl_words(int64_t D) { return (size_t)(4 + 2 * delta_slices(D)) + kBoundsStateWords; }
+static inline size_t lloyd_ctrl_words(int64_t D, bool state) { return (size_t)(4 + 2 * delta_slices(D)) + (state ? kBoundsStateWords : 0); }
 
-size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K) {
-    return a256((size_t)N * 8) + a256(lloyd_ctrl_words(D) * 4) + a256((size_t)delta_slices(D) * K * 8) +
+size_t lloyd_workspace_bytes(int64_t N, int64_t D, int32_t K, bool bounds_state) {
+    return a256((size_t)N * 8) + a256(lloyd_ctrl_words(D, bounds_state) * 4) + a256((size_t)delta_slices(D) * K * 8) +
            a256((size_t)K * 4) + (K > kSplitTiles * 16 ? a256((size_t)N * 8) + 256 : 0);
 }
-LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K) {
+LloydWs lloyd_carve(void* base, int64_t N, int64_t D, int32_t K, bool bounds_state) {
     LloydWs w;
-    w.bytes = lloyd_workspace_bytes(N, D, K);
+    w.bytes = lloyd_workspace_bytes(N, D, K, bounds_state);
     if (!base) return w;
     char* b = (char*)base;
     w.list = (unsigned long long*)b;
     b += a256((size_t)N * 8);
     w.ctrl = (uint32_t*)b;
-    b += a256(lloyd_ctrl_words(D) * 4);
+    b += a256(lloyd_ctrl_words(D, bounds_state) * 4);
     w.skipped = (int32_t*)(w.ctrl + 2 + 2 * delta_slices(D));
-    w.drift = (double*)(w.ctrl + 4 + 2 * delta_slices(D));
-    w.sq_total = w.drift + 2;
-    w.quiet = (uint32_t*)(w.drift + 3);
-    w.sumsq = w.drift + 4;
+    if (bounds_state) {
+        w.drift = (double*)(w.ctrl + 4 + 2 * delta_slices(D));
+        w.sq_total = w.drift + 2;
+        w.quiet = (uint32_t*)(w.drift + 3);
+        w.sumsq = w.drift + 4;
+    }
     w.norm_part = (double*)b;
     b += a256((size_t)delta_slices(D) * K * 8);
     w.counts2 = (int32_t*)b;
@@ -906,7 +908,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     // rows are left out by their bounds in the passes 3 .. iters - 1 (record: and in the last)
     const bool record = bw && bw->record;
     const bool one_launch = tile_bounds_supports(N, D, K, dt);
-    const bool bounds = bw && bw->expire && iters >= 4 && (!record || (lw.sort_ws && segsum_sorted_supported(1, N, D, dt))) &&
+    const bool bounds = bw && bw->expire && lw.drift && iters >= 4 && (!record || (lw.sort_ws && segsum_sorted_supported(1, N, D, dt))) &&
                         (one_launch || (record && lw.carry && bw->second && split_config(D, K, dt, nullptr)));
     if (bounds) skipped = nullptr;  // (a pass over an empty list of rows costs next to nothing already)
     TileCfg c = tile_config(TILE_LLOYD, D, K, dt, bounds && one_launch);
@@ -925,7 +927,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     TileParams p = base_params(lq, N, D, K, c, ws, dt);
     p.cent = cent_io;
     p.assign = assign;
-    if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D) * 4, st));
+    if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D, bounds) * 4, st));
     if (skipped && skipped != lw.skipped) CAT_T(launch_fill_zero(skipped, sizeof(int32_t), st));  // (that word is one of ctrl's)
     if (bw && bw->evaluated) {
         CAT_T(launch_fill_i32(bw->evaluated, (int64_t)iters + 1, (int32_t)N, st));
@@ -1056,7 +1058,7 @@ cat_status tile_lloyd_multi(const void* lq, cat_dtype dt, int64_t N, int64_t D, 
     p.nsets = ms.nsets;
     for (int i = 0; i < ms.nsets; i++) p.set_k[i] = (int16_t)ms.k[i];
     for (int i = 0; i <= ms.nsets; i++) p.set_t0[i] = (uint8_t)ms.t0[i];
-    if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D) * 4, st));
+    if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D, false) * 4, st));
     // The same sequence as tile_lloyd over the concatenated cluster slots (no early stop: the sets settle at
     // different passes).  The full sums after passes 0 and 1 run set by set on that set's column of the table.
     constexpr int32_t kFullPasses = 2;

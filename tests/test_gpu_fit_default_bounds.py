@@ -121,6 +121,25 @@ def test_restarts_and_the_process_wide_early_stop():
         binding.allow_early_stop(False)
 
 
+@pytest.mark.parametrize("N,D,K", [(68000, 256, 9), (33000, 256, 150), (130000, 130, 31)])
+def test_a_workspace_without_the_scratch_of_the_bounds_is_enough(N, D, K):
+    """Single passes never use it; cat_fit then reads every row in every pass.  (12 bytes per row are less than that scratch.)"""
+    x, y = _rows(2, N, D, 5, "f32", 1.0)
+    full = binding.cat_fit_workspace_bytes(N, D, K)
+    ws = torch.empty(full - 12 * N, dtype=torch.uint8, device="cuda")
+    want = cat_fit(x, y, K, 6, seed=1)
+    _same(cat_fit(x, y, K, 6, seed=1, workspace=ws), want)
+    _same(cat_fit(x, y, K, 6, seed=1, workspace=ws, early_stop=True), want)
+    a, counts, _ = binding.cat_assign(x, want["centroids"], workspace=ws)
+    assert torch.equal(a, want["assignments"]) and torch.equal(counts, want["counts"])
+    cent, _ = binding.cat_update(x, a, want["centroids"], workspace=ws)
+    assert torch.isfinite(cent).all()
+    g, b = binding.cat_stats(x, y, a, K, centroids=want["centroids"], workspace=ws)[:2]
+    torch.testing.assert_close(g, want["gamma"], rtol=1e-5, atol=1e-6)
+    with pytest.raises(binding.CatError):
+        cat_fit(x, y, K, 6, seed=1, workspace=torch.empty((full - 12 * N) // 2, dtype=torch.uint8, device="cuda"))
+
+
 def test_captures_into_a_hip_graph_and_replays():
     """which rows a pass evaluates is decided on the device: one graph, different inputs"""
     N, D, K, iters = 68000, 256, 9, 6

@@ -56,6 +56,13 @@ def test_scratch_of_the_ranking_in_two_launches(lib):
         assert f(1 << 21, D, K, dt) - f(1 << 20, D, K, dt) == 12 << 20
 
 
+def test_scratch_of_single_passes_has_no_part_for_the_loops_of_the_fits(lib):
+    """cat_apply_pca: p scores, a label and the scratch of one assignment per row (K > 128: a pair more)."""
+    f = lib.cat_apply_pca_workspace_bytes
+    for D, K, p, per_row in [(1000, 50, 64, 272), (1000, 200, 64, 280), (256, 50, 20, 96)]:
+        assert f(1 << 22, D, K, p, binding.CAT_F32) - f(1 << 21, D, K, p, binding.CAT_F32) == per_row << 21
+
+
 FAKE = 0x7F0000001000  # never dereferenced: every case below fails validation first
 
 
