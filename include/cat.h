@@ -104,7 +104,8 @@ size_t cat_apply_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt);
  *             lq picked by cat_init_indices(N, K, seed).
  *   Lloyd     `iters` times: assign every row to its nearest centroid, then move
  *             each centroid to the mean of its rows (a centroid with no rows
- *             stays where it is).  No early stop.
+ *             stays where it is).  The outputs are those of exactly `iters` iterations; passes
+ *             or rows that cannot change them are left out.
  *   final     one more assignment against the final centroids: this is what
  *             `assignments`, `counts` and the last inertia entry describe, and
  *             what cat_apply reproduces on the same rows.
@@ -521,6 +522,13 @@ cat_status cat_debug_rerank_queue(int entries);
  * rounding-equivalent ties.  Process-wide.  CAT_ERR_INVALID_ARG for other values.
  */
 cat_status cat_debug_apply_kernel(int which);
+
+/*
+ * Test hook.  on != 0: the Lloyd loops of cat_fit, cat_fit_restarts, cat_fit_pca and the single entries of cat_fit_multi_k run
+ * every pass over every row (no early stop, no distance bounds), which is what their shorter loops are compared
+ * with.  cat_fit_early_stop and cat_fit_bounds are not affected.  Process-wide, default 0; returns CAT_OK.
+ */
+cat_status cat_debug_full_loop(int on);
 
 /* Message of the last non-OK status on the calling thread ("" if none).  The
  * pointer stays valid until the next failing call on the same thread. */

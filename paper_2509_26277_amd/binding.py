@@ -28,7 +28,7 @@ EXPORTS = ("cat_select_path", "cat_fit_workspace_bytes", "cat_apply_workspace_by
            "cat_apply_static", "cat_apply_static_max_workspace_bytes", "cat_debug_apply_kernel",
            "cat_fit_multi_k_workspace_bytes", "cat_fit_multi_k", "cat_debug_multi_group_tiles",
            "cat_params_to_bf16", "cat_apply_lp_workspace_bytes", "cat_apply_lp",
-           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_stream_probe")
+           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_stream_probe")
 
 
 class CatError(RuntimeError):
@@ -133,6 +133,8 @@ def load_library():
     lib.cat_debug_multi_group_tiles.restype = c.c_int
     lib.cat_stream_probe.argtypes = [vp, vp, sz, vp]
     lib.cat_stream_probe.restype = c.c_int
+    lib.cat_debug_full_loop.argtypes = [c.c_int]
+    lib.cat_debug_full_loop.restype = c.c_int
     lib.cat_debug_padded_fit.argtypes = [c.c_int]
     lib.cat_debug_padded_fit.restype = c.c_int
     lib.cat_debug_apply_kernel.argtypes = [c.c_int]
@@ -494,6 +496,11 @@ def stream_probe(src, dst=None):
 def debug_padded_fit(on):
     """False keeps fits of rows that are not whole 16-byte groups on the streaming kernels (default: a padded copy)."""
     _check(load_library().cat_debug_padded_fit(int(bool(on))))
+
+
+def debug_full_loop(on):
+    """Test hook: True runs every pass of the plain fits over every row, without early stop and distance bounds."""
+    _check(load_library().cat_debug_full_loop(int(bool(on))))
 
 
 def debug_multi_group_tiles(tiles):

@@ -168,6 +168,7 @@ static bool pad_applies(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
 }
 // (one pass or none: the copy would cost as much as it saves)
 static std::atomic<bool> g_padded_fit{true};  // cat_debug_padded_fit
+static std::atomic<bool> g_full_loop{false};  // cat_debug_full_loop
 static bool fit_runs_padded(int64_t N, int64_t D, int32_t K, cat_dtype dt, int32_t iters) {
     return g_padded_fit.load() && g_path.load() == CAT_PATH_AUTO && iters >= 2 && pad_applies(N, D, K, dt);
 }
@@ -298,7 +299,7 @@ static cat_status run_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, 
         // out as a whole then).  Short ones are left out as a whole once the partition repeats, which costs the others nothing
         // (one word per launch, read beside the first loads): 4096 x 64, K = 4, 20 iterations, settled after a few:
         // 349 -> 232 us.
-        if (!skipped && !bw) {
+        if (!skipped && !bw && !g_full_loop.load()) {
             if (w.bounds.expire)
                 bw = &w.bounds;
             else
@@ -380,6 +381,11 @@ cat_status cat_debug_apply_kernel(int which) {
 
 cat_status cat_debug_padded_fit(int on) {
     g_padded_fit.store(on != 0);
+    return CAT_OK;
+}
+
+cat_status cat_debug_full_loop(int on) {
+    g_full_loop.store(on != 0);
     return CAT_OK;
 }
 

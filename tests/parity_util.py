@@ -1,4 +1,6 @@
 """Helpers of the GPU-vs-oracle parity tests (tolerances, device transfer)."""
+import contextlib
+
 import numpy as np
 import torch
 
@@ -74,3 +76,14 @@ def check_assignments_lazy(got, want, lq, centroids, what):
     assert (a == want[bad]).all(), f"{what}: `want` was not taken against these centroids"
     check_assignments(got[bad], want[bad], d1, d2, what)
     return bad.size
+
+
+@contextlib.contextmanager
+def full_loop():
+    """Inside, the plain fits run every pass over every row: what the loops that leave passes or rows out are compared with."""
+    from paper_2509_26277_amd import binding
+    binding.debug_full_loop(True)
+    try:
+        yield
+    finally:
+        binding.debug_full_loop(False)

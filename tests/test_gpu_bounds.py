@@ -14,7 +14,7 @@ import oracle
 from paper_2509_26277_amd import cat_fit, workloads
 from paper_2509_26277_amd.binding import CAT_PATH_AUTO, CAT_PATH_STREAM, select_path
 
-from parity_util import CENTROID_RTOL, RTOL, check_values, dev_matrix, host_matrix
+from parity_util import CENTROID_RTOL, RTOL, check_values, dev_matrix, host_matrix, full_loop
 
 pytestmark = pytest.mark.gpu
 
@@ -75,6 +75,9 @@ def test_same_outputs_as_the_plain_loop_and_the_oracle(N, D, K, iters, dt, sprea
     x, y = _mixture(N + D + K, N, D, max(K, 2), dt, spread)
     xd, yd = dev_matrix(x, dt), dev_matrix(y, dt)
     b = cat_fit(xd, yd, K, iters, seed=7, bounds=True)
+    with full_loop():
+        full = cat_fit(xd, yd, K, iters, seed=7)
+    _same_as_plain(b, full, iters)
     _same_as_plain(b, cat_fit(xd, yd, K, iters, seed=7), iters)
     o = oracle.fit_bounds(x, y, K, iters, seed=7)
     assert (b["assignments"].cpu().numpy() == o["assignments"]).all()

@@ -9,7 +9,7 @@ import torch
 import oracle
 from paper_2509_26277_amd import binding, cat_fit, workloads
 
-from parity_util import RTOL, check_assignments, check_values, dev_matrix, host_matrix
+from parity_util import RTOL, check_assignments, check_values, dev_matrix, host_matrix, full_loop
 
 pytestmark = pytest.mark.gpu
 
@@ -110,11 +110,16 @@ def test_the_cases_cover_both_outcomes():
 
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_same_outputs_as_the_full_loop(dt):
-    """against cat_fit itself, as a property at a size the oracle is not run at: the integer outputs and the
-    centroids bit for bit (both loops end with the same preparation from the same sums), the rest to rounding"""
+    """against cat_fit with every pass, as a property at a size the oracle is not run at: the integer outputs and the
+    centroids bit for bit (both loops end with the same preparation from the same sums), the rest to rounding; cat_fit
+    as it is too"""
     x, y = _mixture(21, 60000, 256, 4, 3.0, dt)
     xd, yd = dev_matrix(x, dt), dev_matrix(y, dt)
-    full = cat_fit(xd, yd, 4, 40, seed=5)
+    with full_loop():
+        full = cat_fit(xd, yd, 4, 40, seed=5)
+    plain = cat_fit(xd, yd, 4, 40, seed=5)
+    for k in ("assignments", "counts", "centroids"):
+        assert torch.equal(plain[k], full[k]), k
     r = cat_fit(xd, yd, 4, 40, seed=5, early_stop=True)
     assert int(r["passes_skipped"].item()) > 0
     for k in ("assignments", "counts", "centroids"):
@@ -215,8 +220,8 @@ def test_captures_into_a_hip_graph_and_replays():
         torch.testing.assert_close(r["inertia"], eager["inertia"], rtol=1e-12, atol=0)
 
 
-def test_process_wide_switch_leaves_the_other_fits_unchanged():
-    """best-of-several fit and the fit with the PCA front-end, with and without the switch: the integer outputs and
+def test_the_other_fits_stop_with_the_outputs_of_the_full_loop():
+    """best-of-several fit and the fit with the PCA front-end, as they are and with every pass: the integer outputs and
     the centroids bit for bit, the objectives to rounding; cat_fit itself too"""
     from paper_2509_26277_amd import cat_fit_pca, cat_fit_restarts
     x, y = _mixture(0, 4096, 64, 4, 3.0, "f32")
@@ -226,12 +231,9 @@ def test_process_wide_switch_leaves_the_other_fits_unchanged():
         return (cat_fit_restarts(xd, yd, 4, 30, seed=2, restarts=3, seeding=binding.CAT_SEED_KMEANSPP),
                 cat_fit_pca(xd, yd, 4, 8, 30, seed=2), cat_fit(xd, yd, 4, 30, seed=2))
 
-    ref = runs()
-    binding.allow_early_stop(True)
-    try:
-        got = runs()
-    finally:
-        binding.allow_early_stop(False)
+    with full_loop():
+        ref = runs()
+    got = runs()
     for which, (g, r) in enumerate(zip(got, ref)):
         for k, v in r.items():
             if v is None:

@@ -1,5 +1,5 @@
 """cat_fit on matrices large enough for its loop to leave rows out by distance bounds (from 64 MB on; 32 MB with two launches
-per pass), against the loop that evaluates every row (cat_fit_early_stop: the same outputs by contract, no bounds).
+per pass), against the loop that runs every pass over every row.
 
 Centroids, assignments and counts are the same bit for bit.  The objective of the plain loop is a sum of float32 terms
 |x|^2 + score (relative error of a term up to about 1e-4 |x||c| over the distance, far less in the sum); cat_fit has it from
@@ -9,6 +9,8 @@ import pytest
 import torch
 
 from paper_2509_26277_amd import binding, cat_fit, cat_fit_restarts
+
+from parity_util import full_loop
 
 pytestmark = pytest.mark.gpu
 
@@ -33,6 +35,11 @@ def _same(a, b, what=""):
     np.testing.assert_allclose(ja, jb, rtol=1e-5)
 
 
+def _full(*args, **kw):
+    with full_loop():
+        return cat_fit(*args, **kw)
+
+
 SHAPES = [
     (68000, 256, 9, 8, "f32", 1.0),
     (130000, 130, 31, 6, "f32", 0.5),    # not a whole number of 16-byte groups: the loop runs on a padded copy
@@ -52,6 +59,7 @@ SHAPES = [
 def test_same_outputs_as_the_loop_that_reads_every_row(N, D, K, iters, dt, spread):
     x, y = _rows(N + D, N, D, max(K // 2, 2), dt, spread)
     a = cat_fit(x, y, K, iters, seed=5)
+    _same(a, _full(x, y, K, iters, seed=5))
     _same(a, cat_fit(x, y, K, iters, seed=5, early_stop=True))
     assert int(a["counts"].sum()) == N
     assert torch.equal(a["counts"].long(), torch.bincount(a["assignments"].long(), minlength=K))
@@ -91,7 +99,7 @@ def test_duplicates_empty_clusters_and_exact_ties():
     x = base.repeat_interleave(34000, 0).contiguous()
     y = (x * 1.5 + 0.25).contiguous()
     for K in (3, 20, 140):
-        _same(cat_fit(x, y, K, 6, seed=K), cat_fit(x, y, K, 6, seed=K, early_stop=True), K)
+        _same(cat_fit(x, y, K, 6, seed=K), _full(x, y, K, 6, seed=K), K)
 
 
 @pytest.mark.parametrize("N,D,K,dt", [(68000, 256, 9, "f32"), (33000, 1024, 64, "bf16"), (33000, 256, 150, "f32")])
@@ -108,17 +116,13 @@ def test_results_do_not_depend_on_the_list_and_queue_capacities(N, D, K, dt):
         binding.debug_list_capacity(0)
 
 
-def test_restarts_and_the_process_wide_early_stop():
+def test_restarts():
     x, y = _rows(4, 68000, 256, 6, "f32", 0.5)
     r = cat_fit_restarts(x, y, 9, 8, seed=3, restarts=3)
     best = int(r["best_run"])
-    _same(r, cat_fit(x, y, 9, 8, seed=3 + best, early_stop=True))
-    want = cat_fit(x, y, 9, 8, seed=3)
-    try:
-        binding.allow_early_stop(True)
-        _same(cat_fit(x, y, 9, 8, seed=3), want)
-    finally:
-        binding.allow_early_stop(False)
+    _same(r, _full(x, y, 9, 8, seed=3 + best))
+    with full_loop():
+        assert int(cat_fit_restarts(x, y, 9, 8, seed=3, restarts=3)["best_run"]) == best
 
 
 @pytest.mark.parametrize("N,D,K", [(68000, 256, 9), (33000, 256, 150), (130000, 130, 31)])
@@ -157,7 +161,7 @@ def test_captures_into_a_hip_graph_and_replays():
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
-        _same({k: v.clone() for k, v in out.items()}, cat_fit(xs, ys, K, iters, seed=1, early_stop=True), seed)
+        _same({k: v.clone() for k, v in out.items()}, _full(xs, ys, K, iters, seed=1), seed)
 
 
 def test_non_finite_rows_leave_the_others_alone():

@@ -109,6 +109,7 @@ def test_apply_and_step_argument_errors(lib):
     assert lib.cat_stats(FAKE, FAKE, FAKE, 64, 8, 4, 0, None, None, FAKE, None, FAKE, 0, None) == INVALID
     assert lib.cat_stats(FAKE, FAKE, FAKE, 64, 8, 4, 0, None, FAKE, FAKE, None, FAKE, 0, None) == WORKSPACE
     assert lib.cat_select_path(9) == INVALID and lib.cat_select_path(0) == 0
+    assert lib.cat_allow_early_stop(1) == 0 and lib.cat_allow_early_stop(0) == 0  # accepted, without effect
     buf = (ctypes.c_int64 * 4)()
     assert lib.cat_init_indices(3, 4, 0, buf) == INVALID
     assert lib.cat_init_indices(8, 4, 0, None) == INVALID
