@@ -503,8 +503,7 @@ cat_status cat_stream_probe(const void *src, void *dst, size_t bytes, void *hip_
 cat_status cat_debug_list_capacity(int entries);
 
 /*
- * Test hook.  In the assignment passes of the tile path (cat_assign, the passes of cat_fit without distance
- * bounds), a row whose two best scores are within the error bound of the split arithmetic is measured exactly,
+ * Test hook.  In the assignment passes of the tile path (cat_assign, the passes of the fits), a row whose two best scores are within the error bound of the split arithmetic is measured exactly,
  * in double precision.  A workgroup does not do that where it finds the row: it queues the row in fast memory
  * and its waves share the queued rows out when the workgroup has no tiles left; a row that finds the queue
  * full, or has more than 8 candidates, is measured on the spot.  This call sets the capacity of the queue for
@@ -515,11 +514,11 @@ cat_status cat_debug_list_capacity(int entries);
 cat_status cat_debug_rerank_queue(int entries);
 
 /*
- * Test hook.  cat_apply (and cat_apply_static) on the fused path has two kernels: one that keeps a tile of rows
- * on the chip between the ranking and the affine map (used whenever it has an instance for the shape), and the
- * tile kernel shared with cat_assign.  0 = automatic (default), 1 = never the row-tile kernel, 2 = only the
- * row-tile kernel (CAT_ERR_UNSUPPORTED on a shape it has no instance for).  Results never depend on it beyond
- * rounding-equivalent ties.  Process-wide.  CAT_ERR_INVALID_ARG for other values.
+ * Test hook.  cat_apply (and cat_apply_static) on the fused path has three kernels: one that keeps a tile of rows
+ * on the chip between the ranking and the affine map and the centroids in registers, one that keeps the rows and
+ * streams the centroids (larger products of clusters and channels), and the tile kernel shared with cat_assign.
+ * 0 = automatic (default), 1 = neither of the first two, 2 = only the first, 3 = only the second (2 and 3:
+ * CAT_ERR_UNSUPPORTED on a shape it has no instance for).  Results never depend on it beyond rounding-equivalent ties.  Process-wide.  CAT_ERR_INVALID_ARG for other values.
  */
 cat_status cat_debug_apply_kernel(int which);
 

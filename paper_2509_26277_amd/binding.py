@@ -198,7 +198,8 @@ def debug_rerank_queue(entries):
 
 
 def debug_apply_kernel(which):
-    """Test hook: 0 automatic, 1 never the row-tile inference kernel, 2 only the row-tile inference kernel."""
+    """Test hook: 0 automatic, 1 neither of the two inference kernels, 2 only the row-tile kernel, 3 only the one that streams
+    the centroids."""
     _check(load_library().cat_debug_apply_kernel(int(which)))
 
 

@@ -126,14 +126,14 @@ struct ApplyWs {
     size_t bytes;
 };
 // N = 0: without the scratch of the split ranking (cat_apply_static: its array has a fixed size)
-static ApplyWs carve_apply(void* base, int64_t D, int32_t K, cat_dtype dt, int64_t N = 0) {
+static ApplyWs carve_apply(void* base, int64_t D, int32_t K, cat_dtype dt, int64_t N = 0, bool wide = true) {
     Carver c(base);
     ApplyWs w;
     size_t KD = (size_t)K * (size_t)D;
     w.g_eff = c.take<float>(KD);
     w.b_eff = c.take<float>(KD);
-    size_t tb = tile_workspace_bytes(D, K, dt);
-    w.tile = tile_carve(base ? (void*)(c.base + c.off) : nullptr, D, K, dt);
+    size_t tb = tile_workspace_bytes(D, K, dt, wide);
+    w.tile = tile_carve(base ? (void*)(c.base + c.off) : nullptr, D, K, dt, wide);
     c.off += align256(tb);
     w.split = nullptr;
     w.labels = nullptr;
@@ -374,7 +374,7 @@ cat_status cat_debug_rerank_queue(int entries) {
 }
 
 cat_status cat_debug_apply_kernel(int which) {
-    if (which < 0 || which > 2) return set_error(CAT_ERR_INVALID_ARG, "cat_debug_apply_kernel: 0, 1 or 2, got %d", which);
+    if (which < 0 || which > 3) return set_error(CAT_ERR_INVALID_ARG, "cat_debug_apply_kernel: 0 .. 3, got %d", which);
     g_apply_kernel.store(which);
     return CAT_OK;
 }
@@ -945,10 +945,16 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     CAT_TRY(check_ptr(who, "corrected", corrected, 16));
     if (corrected == lq) return set_error(CAT_ERR_INVALID_ARG, "%s: corrected may not alias lq", who);
     if (!std::isfinite(alpha)) return set_error(CAT_ERR_INVALID_ARG, "%s: alpha is not finite", who);
-    // (a workspace of the size without the scratch of the split ranking is accepted: cat_apply_static has no more)
+    // (a workspace without the scratch of the split ranking is accepted: cat_apply_static has no more; and one without the
+    // operand of the streamed-operand kernel, which some rows that are not whole 16-byte groups alone need it for)
     ApplyWs w = carve_apply(workspace, D, K, dt, N);
-    if (w.split && workspace && workspace_bytes < w.bytes) w = carve_apply(workspace, D, K, dt);
-    CAT_TRY(check_ws(who, workspace, workspace_bytes, w.bytes));
+    const size_t need = w.bytes;
+    bool wide_scratch = true;
+    for (int less = 1; less < 4 && workspace && workspace_bytes < w.bytes; less++) {
+        wide_scratch = less < 2;
+        w = carve_apply(workspace, D, K, dt, less == 2 ? N : 0, wide_scratch);
+    }
+    CAT_TRY(check_ws(who, workspace, workspace_bytes, workspace && workspace_bytes >= w.bytes ? w.bytes : need));
     const float* g = gamma;
     const float* b = beta;
     const FoldAlpha fa = {gamma, beta, alpha, w.g_eff, w.b_eff, (int64_t)K * D};
@@ -970,8 +976,9 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
         return set_error(CAT_ERR_UNSUPPORTED, "row-tile inference kernel forced but D=%lld K=%d dt=%d does not fit it",
                          (long long)D, (int)K, (int)dt);
     // The streamed-operand kernel (every row read once, two-part ranking): where the row-tile kernel has no instance (us,
-    // 262144 x 2048 bf16, K = 64: 725 on the tile kernel, 690; 65536 x 1000, K = 128: 250, 180; 50021 x 1001, K = 50: 495 on
-    // the LDS kernel, 135), and instead of its one-part instance for rows of 2 .. 4 KB, which re-ranks whatever lies within
+    // 262144 x 2048 bf16, K = 64: 725 on the tile kernel, 570; 65536 x 1000, K = 128: 250, 180; 50021 x 1001, K = 50: 495 on
+    // the LDS kernel, 121), whatever the number of rows (256 rows: 512 bf16, K = 100: 34, 18; 1000, K = 100: 74, 24; 1001,
+    // K = 50: 348, 22; 2048 bf16, K = 64: 65, 27; 768, K = 256: 83, 25), and instead of its one-part instance for rows of 2 .. 4 KB, which re-ranks whatever lies within
     // 1.6 % of |x||c|, from some thousand rows on (65536 x 1000, K = 50 fitted: 136, 124; 8000 rows: 34, 27; 2000: 19, 21).
     // Its one-part instance for rows of up to 2 KB and 65 .. 128 clusters keeps them: a third faster on separated rows.
     // The tile kernel keeps short rows, where the streamed operand outweighs the second read (400000 x 128 bf16, K = 100: 182
@@ -981,9 +988,12 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     // as long as it ranks them with two parts, in one launch or in two (one part: 60000 x 1500, K = 100: 1087 .. 8192, 213).
     const bool tile_two = tile_ok && (w.split || tile_two_parts(TILE_APPLY, D, K, dt));
     const bool tile_keeps = tile_two && (D <= 256 || (dt == CAT_BF16 && (K <= 16 || (K > 64 && D > 1536))));
-    const bool wide = wide_supported(N, D, K, dt) && !tile_keeps &&
-                      (!rowtile_ok || (!infer_two_parts(D, K, dt) && D > 512 && N >= 4096));
-    if (path == CAT_PATH_AUTO && which == 0 && wide)
+    const bool wide_ok = wide_scratch && wide_supported(N, D, K, dt);
+    if (which == 3 && !wide_ok)
+        return set_error(CAT_ERR_UNSUPPORTED, "streamed-operand inference kernel forced but D=%lld K=%d dt=%d does not fit it",
+                         (long long)D, (int)K, (int)dt);
+    const bool wide = wide_ok && !tile_keeps && (!rowtile_ok || N >= 4096);
+    if (path == CAT_PATH_AUTO && (which == 3 || (which == 0 && wide)))
         return wide_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st, fold);
     if (rowtile_ok && path != CAT_PATH_STREAM && which != 1)
         return infer_apply(lq, dt, N, D, K, centroids, g, b, corrected, assignments, w.tile, st, false, nullptr, fold);

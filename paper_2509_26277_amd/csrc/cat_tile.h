@@ -14,8 +14,9 @@ struct TileWs {
     size_t bytes = 0;
 };
 
-size_t tile_workspace_bytes(int64_t D, int32_t K, cat_dtype dt);
-TileWs tile_carve(void* base, int64_t D, int32_t K, cat_dtype dt);
+// wide: with room for the operand of the streamed-operand inference kernel (cat_wide.h)
+size_t tile_workspace_bytes(int64_t D, int32_t K, cat_dtype dt, bool wide = true);
+TileWs tile_carve(void* base, int64_t D, int32_t K, cat_dtype dt, bool wide = true);
 
 // Whether the tile kernels can run `mode` on this shape (LDS and register budgets, index widths).
 bool tile_supports(TileMode mode, int64_t N, int64_t D, int32_t K, cat_dtype dt);

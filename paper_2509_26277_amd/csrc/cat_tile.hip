@@ -546,27 +546,29 @@ bool tile_supports(TileMode mode, int64_t N, int64_t D, int32_t K, cat_dtype dt)
     return N < ((int64_t)1 << 34) && tile_config(mode, D, K, dt).ok;
 }
 
-static size_t packA_bytes(int64_t D, int32_t K, cat_dtype dt) {
+static size_t packA_bytes(int64_t D, int32_t K, cat_dtype dt, bool with_wide) {
     const int K16 = (K + 15) & ~15;
-    int KT = wide_supported(1, D, K, dt) ? 2 : 1;  // (that kernel's operand has two cluster tiles at least)
+    int KT = 1;
     while (KT * 16 < K16) KT *= 2;
+    const int wide = with_wide ? wide_cluster_tiles(D, K, dt) : 0;
+    KT = wide > KT ? wide : KT;
     const size_t nchunks = (size_t)((D + kChunk - 1) / kChunk);
     return nchunks * 4 * KT * 2 * 1024;
 }
 static inline size_t a256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-size_t tile_workspace_bytes(int64_t D, int32_t K, cat_dtype dt) {
+size_t tile_workspace_bytes(int64_t D, int32_t K, cat_dtype dt, bool wide) {
     // (the row-tile inference kernel shares this scratch and also takes rows that are not whole 16-byte groups)
-    if (!tile_config(TILE_ASSIGN, D, K, dt).ok && !infer_supported(1, D, K, dt) && !wide_supported(1, D, K, dt)) return 0;
-    return a256(packA_bytes(D, K, dt)) + a256(16 * 16 * 4 * sizeof(float)) + a256((size_t)K * D * sizeof(float));
+    if (!tile_config(TILE_ASSIGN, D, K, dt).ok && !infer_supported(1, D, K, dt) && !(wide && wide_supported(1, D, K, dt))) return 0;
+    return a256(packA_bytes(D, K, dt, wide)) + a256(16 * 16 * 4 * sizeof(float)) + a256((size_t)K * D * sizeof(float));
 }
-TileWs tile_carve(void* base, int64_t D, int32_t K, cat_dtype dt) {
+TileWs tile_carve(void* base, int64_t D, int32_t K, cat_dtype dt, bool wide) {
     TileWs w;
-    w.bytes = tile_workspace_bytes(D, K, dt);
+    w.bytes = tile_workspace_bytes(D, K, dt, wide);
     if (!base || w.bytes == 0) return w;
     char* b = (char*)base;
     w.packA = (uint16_t*)b;
-    b += a256(packA_bytes(D, K, dt));
+    b += a256(packA_bytes(D, K, dt, wide));
     w.cnorm = (float*)b;
     b += a256(16 * 16 * 4 * sizeof(float));
     w.cent = (float*)b;

@@ -1,6 +1,8 @@
 // Fused inference with the centroid operand streamed from L2 (cat_wide_kernel.h): variant selection on the host, launch.
 #include "cat_wide_kernel.h"
 
+#include "cat_infer.h"
+
 namespace cat {
 
 // centroid preparation shared with the tile kernels (cat_tile.hip)
@@ -18,20 +20,26 @@ struct WideInst {
 };
 #define CAT_WIDE(BF, KT, RG, VPR) \
     {BF, KT, RG, VPR, (const void*)k_wide<BF, KT, RG, VPR, false>, (const void*)k_wide<BF, KT, RG, VPR, true>}
-#define CAT_WIDE_ROWS(BF, KT) CAT_WIDE(BF, KT, 4, 1), CAT_WIDE(BF, KT, 3, 2), CAT_WIDE(BF, KT, 2, 3), CAT_WIDE(BF, KT, 2, 4)
 // K <= 16 KT, rows of at most VPR KB; the first in the list that holds a shape is taken.  Tiles of 64, 48
-// and 32 rows: 100 .. 150 KB of LDS with the partial products.
+// and 32 rows: 100 .. 150 KB of LDS with the partial products.  The shapes of fewer clusters or shorter rows belong to the
+// row-tile kernel (wide_instance).
 const WideInst kWideInst[] = {
-    CAT_WIDE_ROWS(false, 2), CAT_WIDE_ROWS(false, 4), CAT_WIDE_ROWS(false, 8),
+    CAT_WIDE(false, 4, 2, 3), CAT_WIDE(false, 4, 2, 4),
+    CAT_WIDE(false, 8, 2, 3), CAT_WIDE(false, 8, 2, 4),
     CAT_WIDE(false, 16, 2, 2), CAT_WIDE(false, 16, 2, 3),
-    CAT_WIDE_ROWS(true, 2), CAT_WIDE_ROWS(true, 4), CAT_WIDE_ROWS(true, 8),
+    CAT_WIDE(true, 2, 2, 3), CAT_WIDE(true, 2, 2, 4),
+    CAT_WIDE(true, 4, 3, 2), CAT_WIDE(true, 4, 2, 3), CAT_WIDE(true, 4, 2, 4),
+    CAT_WIDE(true, 8, 4, 1), CAT_WIDE(true, 8, 3, 2), CAT_WIDE(true, 8, 2, 3), CAT_WIDE(true, 8, 2, 4),
     CAT_WIDE(true, 16, 2, 2), CAT_WIDE(true, 16, 2, 3),
 };
 constexpr int kNWide = sizeof(kWideInst) / sizeof(kWideInst[0]);
 
+// -1: none, also where the row-tile kernel has an instance that cat_apply always prefers (two-part ranking, or rows of up to
+// 512 channels).
 int wide_instance(int64_t D, int32_t K, cat_dtype dt) {
     const bool bf = dt == CAT_BF16;
     if (bf && D % 2) return -1;
+    if (infer_supported(1, D, K, dt) && (infer_two_parts(D, K, dt) || D <= 512)) return -1;
     const int64_t row = D * (bf ? 2 : 4);
     for (int i = 0; i < kNWide; i++)
         if (kWideInst[i].bf16 == bf && K <= 16 * kWideInst[i].KT && row <= 1024 * kWideInst[i].VPR) return i;
@@ -42,6 +50,11 @@ int wide_instance(int64_t D, int32_t K, cat_dtype dt) {
 
 bool wide_supported(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     return N < ((int64_t)1 << 40) && wide_instance(D, K, dt) >= 0;
+}
+
+int wide_cluster_tiles(int64_t D, int32_t K, cat_dtype dt) {
+    const int i = wide_instance(D, K, dt);
+    return i >= 0 ? kWideInst[i].KT : 0;
 }
 
 cat_status wide_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, const float* cent, const float* gamma,
