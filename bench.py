@@ -51,7 +51,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0
 
-# HBM-side traffic of one launch of the two dominant kernels, from rocprofv3 --pmc runs of this file (FETCH_SIZE,
+# HBM-side traffic of one launch of the three dominant kernels, from rocprofv3 --pmc runs of this file (FETCH_SIZE,
 # then WRITE_SIZE; profiles/k_tile_hbm_traffic.md and profiles/k_infer_hbm_traffic.md have the commands and the raw
 # figures).  Each counter is scaled by what it reads for the plain device copy of the same matrix that this script
 # also times (a copy reads and writes exactly N*D*b bytes).  Per entry: (FETCH_SIZE of the kernel, FETCH_SIZE of the
@@ -59,15 +59,17 @@ HBM_PEAK_GBPS = 8000.0
 # one version of a kernel's source file: `traffic` is reported only while the hash of that file still matches, and the
 # line says that it comes from profiles/, not from this run.
 TRAFFIC_SOURCES = {
-    "k_tile": ("cat_tile_kernel.h", "f7df3b216487c7955991ad77a448159b9bc0e66c1d4168af298b081d3a85d32d"),
+    "k_tile": ("cat_tile_kernel.h", "b26e2d562f1b5f3e7a67ea908bec8edbfac505b7206dbcb8c950ad5aba245729"),
+    "k_wide": ("cat_wide_kernel.h", "8257ccbd4e0bf407f94e49428cdaecb7b6f7835751c949afdcdf2c3d64cd660d"),
     "k_infer": ("cat_infer_kernel.h", "d243d921fdcd31650ab229d15f5f562a3fb2bcae57aa0e239eb2055818ac6c93"),
 }
 TRAFFIC_COUNTERS = {
-    "cfg2": ("k_tile", (133499.5, 128011.7, 302.6, 256000.0)),
+    "cfg2": ("k_tile", (133614.6, 128011.7, 306.0, 256000.0)),
     "cfg2_apply": ("k_infer", (129304.7, 128011.7, 265969.1, 256000.0)),
-    "cfg3": ("k_tile", (526984.8, 524299.7, 4747.4, 1048576.0)),
+    "cfg3": ("k_tile", (527471.6, 524299.7, 4724.9, 1048576.0)),
     "cfg3_apply": ("k_infer", (524886.7, 524299.7, 1054738.2, 1048576.0)),
-    "cfg4": ("k_tile", (551642.5, 524299.7, 1273.3, 1048576.0)),
+    "cfg4": ("k_tile", (553901.8, 524299.7, 1277.7, 1048576.0)),
+    "cfg4_apply": ("k_wide", (646212.7, 524299.7, 1050689.9, 1048576.0)),
     "cfg5_apply": ("k_infer", (4197668.4, 4194317.9, 8413243.7, 8388608.0)),
 }
 
@@ -90,7 +92,7 @@ def _traffic_bytes(key, copy_bytes):
 
 def _traffic_source(key):
     kernel = TRAFFIC_COUNTERS[key][0] if key in TRAFFIC_COUNTERS else "k_tile"
-    return f"profiles/{kernel}_hbm_traffic.md (hardware counters of an earlier run of this kernel, not this run)"
+    return f"profiles/{'k_tile' if kernel == 'k_wide' else kernel}_hbm_traffic.md (hardware counters of an earlier run of this kernel, not this run)"
 
 
 def _events(fn, reps, torch):

@@ -1,7 +1,8 @@
 // The leading eigenpairs of a symmetric D x D matrix in double precision, for the PCA front-end (p of D directions).
 //
-//   1. Householder tridiagonalisation, one launch per column (k_eig_step): D launches, each bound by its latencies (the
-//      launch, one round of loads, two sums over a workgroup), not by the 16 MB at most that it reads and writes.
+//   1. Householder tridiagonalisation, one launch per column (k_eig_step): D launches, at D = 1000 each bound by its latencies
+//      (the launch, one round of loads, two sums over a workgroup) and not by the rows it reads and writes, 2 x 8 D^2 bytes
+//      at most (16 MB; 67 MB at D = 2048).
 //   2. The p largest eigenvalues of the tridiagonal matrix T by multisection on Sturm counts (k_eig_bisect).
 //   3. Their vectors by inverse iteration on T from pseudo-random starts (k_eig_invit), made orthogonal where
 //      eigenvalues lie close together (k_eig_ortho).

@@ -657,7 +657,7 @@ constexpr int kSortWaves = 4;
 constexpr int kSortV = 2;
 // ODD: fp32 rows of an odd length (rows start on 4 bytes, not 8): the lane's two channels are 64 apart, each a 4-byte load,
 // and a wave instruction still reads 256 consecutive bytes.  (50021 x 1001, K = 200: the statistics 538 us on the
-// LDS-panel kernel these rows took before.)
+// LDS-panel kernel these rows took before, 91 so.)
 // SQ (with NQ = 1): the sum of all x^2 as well, spread over kSumSqSlots entries of sumsq.
 template <typename T, int NQ, bool ODD = false, bool SQ = false>
 __global__ __launch_bounds__(kSortWaves * kWave) void k_segsum_sorted(

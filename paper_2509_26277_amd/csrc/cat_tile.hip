@@ -473,9 +473,10 @@ __global__ __launch_bounds__(kDeltaWaves * kWave) void k_delta_prep(const DeltaP
 // which the selection of the rows adds.  One launch per pass, us per cat_fit of 15 to 20 iterations, plain ->
 // with bounds: logits 16384 x 1000 (62 MB) 695 -> 522, 32768 x 1000 878 -> 388; features 32768 x 256 (32 MB) 490 -> 534,
 // 65536 x 256 (64 MB) 615 -> 545; mixture 131072 x 64 (32 MB) 704 -> 697, 65536 x 256 645 -> 307.  Components that overlap
-// until the end, so that no row can be left out: bf16 16384 x 1024 (32 MB) 701 -> 820, 65536 x 1024 (128 MB) 1138 -> 1225,
-// 131072 x 1024 1771 -> 1764.  A pass of two launches (K > 128) costs more, and the selection less of it: logits 16384 x 1000,
-// K = 200 (62 MB) 2267 -> 793; overlapping 32768 x 512 (64 MB) 1932 -> 2005.
+// until the end: bf16 65536 x 1024 (128 MB) 1104 -> 1104, 131072 x 1024 1719 -> 1605.  Rows without any structure, of which
+// none is ever left out: 65536 x 256, K = 64 982 -> 1086, bf16 65536 x 1024 1142 -> 1210, 262144 x 2048 4510 -> 4698.  A pass of
+// two launches (K > 128) costs more, and the selection less of it: logits 16384 x 1000, K = 200 (62 MB) 2267 -> 793; overlapping
+// 32768 x 512 (64 MB) 1932 -> 1970; without structure 2476 -> 2611.
 constexpr double kBoundsBytes = 64.0 * 1024 * 1024, kBoundsBytesSplit = 32.0 * 1024 * 1024;
 
 // ---- host side ----------------------------------------------------------------------------
