@@ -133,6 +133,10 @@ size_t cat_apply_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt);
  *                 bounds (cat_fit_bounds) say that they keep their centroid; from pass 3 on the
  *                 objective then is sum |x|^2 + sum_k c_k . (n_k c_k - 2 S_k), S_k the cluster
  *                 sums, in double precision throughout and not below zero.
+ * workspace       cat_fit_workspace_bytes(N, D, K, dt) bytes, 256-byte aligned.  From the sizes on
+ *                 that say so under inertia it holds 12 .. 20 bytes per row for the distance
+ *                 bounds; a workspace without them is taken too, and every pass then reads
+ *                 every row.
  */
 cat_status cat_fit(const void *lq, const void *fp, int64_t N, int64_t D, int32_t K,
                    int32_t iters, uint64_t seed, cat_dtype dt,
