@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "cat_common.h"
+#include "cat_direct.h"
 #include "cat_infer.h"
 #include "cat_tile.h"
 #include "cat_wide.h"
@@ -374,7 +375,7 @@ cat_status cat_debug_rerank_queue(int entries) {
 }
 
 cat_status cat_debug_apply_kernel(int which) {
-    if (which < 0 || which > 3) return set_error(CAT_ERR_INVALID_ARG, "cat_debug_apply_kernel: 0 .. 3, got %d", which);
+    if (which < 0 || which > 4) return set_error(CAT_ERR_INVALID_ARG, "cat_debug_apply_kernel: 0 .. 4, got %d", which);
     g_apply_kernel.store(which);
     return CAT_OK;
 }
@@ -964,13 +965,15 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
         b = w.b_eff;
     }
     const int path = g_path.load();
+    const int which = g_apply_kernel.load();
+    if (path == CAT_PATH_AUTO && (which == 4 || (which == 0 && direct_apply_pays(N, D, K, dt))))
+        return direct_apply(lq, dt, N, D, K, centroids, gamma, beta, alpha, corrected, assignments, st);
     const bool tile_ok = tile_supports(TILE_APPLY, N, D, K, dt);
     if (path == CAT_PATH_TILE && !tile_ok)
         return set_error(CAT_ERR_UNSUPPORTED, "tile path forced but D=%lld K=%d dt=%d does not fit it", (long long)D,
                          (int)K, (int)dt);
     // two fused kernels: the row-tile kernel reads every row once (its instances cover the shapes whose centroid
     // operand the 8 waves of a workgroup can hold in registers), the tile kernel takes the rest
-    const int which = g_apply_kernel.load();
     const bool rowtile_ok = infer_supported(N, D, K, dt);
     if (which == 2 && !rowtile_ok)
         return set_error(CAT_ERR_UNSUPPORTED, "row-tile inference kernel forced but D=%lld K=%d dt=%d does not fit it",
