@@ -4,15 +4,15 @@
 //      (the launch, one round of loads, two sums over a workgroup) and not by the rows it reads and writes, 2 x 8 D^2 bytes
 //      at most (16 MB; 67 MB at D = 2048).
 //   2. The p largest eigenvalues of the tridiagonal matrix T by multisection on Sturm counts (k_eig_bisect).
-//   3. Their vectors by inverse iteration on T from pseudo-random starts (k_eig_invit), made orthogonal where
-//      eigenvalues lie close together (k_eig_ortho).
+//   3. Their vectors from the two-sided factorisation of T - lambda I, or by inverse iteration from pseudo-random starts where
+//      eigenvalues all but coincide (k_eig_invit), made orthogonal where they lie close together (k_eig_ortho).
 //   4. The reflections applied to the p vectors, last one first (k_eig_back), sign and rounding.
 //
 // Against one-sided Jacobi on all D rows (cat_pca.hip, which remains for more than kEigMaxP directions and for callers
 // that ask for a number of sweeps) it does 4/3 D^3 flops instead of about 12 * 6 D^3, and D launches instead of 3 D.
 // Measured at D = 1000, p = 50 (a whole cat_pca_fit on 65536 rows, 1.5 ms of it the covariance): 56.3 ms with the sweeps,
-// 8.1 ms here; of that 4.6 ms the tridiagonalisation (3.5 us a launch over the last 256 columns, 6.2 us over the first),
-// 0.55 ms the eigenvalues, 0.8 ms their vectors, 0.63 ms the reflections.
+// 6.5 ms here; of that 4.6 ms the tridiagonalisation (3.5 us a launch over the last 256 columns, 6.2 us over the first),
+// 0.16 ms the eigenvalues, 0.06 ms their vectors, 0.28 ms the reflections.
 #include "cat_eig.h"
 
 namespace cat {
@@ -137,27 +137,25 @@ __global__ __launch_bounds__(kEigT) void k_eig_step(double* __restrict__ W, doub
 }
 
 // ---- eigenvalues of the tridiagonal matrix ---------------------------------------------------------------------------
-__device__ __forceinline__ double fast_rcp(double q) {  // within a few ulp for normal q
-    double r = __builtin_amdgcn_rcp(q);
-    r = fma(fma(-q, r, 1.0), r, r);
-    return fma(fma(-q, r, 1.0), r, r);
-}
 // Workgroup j finds the j-th largest eigenvalue: 256 shifts at a time inside the interval that holds it, the number of
-// eigenvalues below each shift from the signs of the pivots of T - x I, 8 bits of the interval a round.  Bound by the
-// serial chain of a count (n pivots, a reciprocal each).  out: lambda[j]; norm2[0] = a bound of |T| (workgroup 0).
+// eigenvalues below each shift from the sign changes of the leading minors of T - x I, 8 bits of the interval a round.
+// Bound by the serial chain of a count (n terms).  The minors follow P' = (d - x) P - e^2 P'' and need no division: the chain is
+// one fused multiply-add a term (the pivots, quotients of minors, cost a reciprocal each: D = 1000, p = 50: 547 us, 159 so).
+// T is scaled by a power of two to a norm of 1 .. 2, so that minors grow by less than 2^4 a term, and the pair at hand is
+// brought back to 1 .. 2 after every eight terms.  Where it has all but vanished by then (a shift that is an eigenvalue of a
+// leading block which nothing couples to the rest), the eight terms are taken again with each minor kept away from zero.
+// out: lambda[j]; tnorm[0] = a bound of |T| (workgroup 0).
 constexpr int kBisT = 256;
+constexpr int kBisU = 8;  // terms between two rescalings
+static inline int32_t bisect_terms(int32_t n) { return (n + kBisU - 1) / kBisU * kBisU + kBisU; }
 __global__ __launch_bounds__(kBisT) void k_eig_bisect(const double* __restrict__ d, const double* __restrict__ e, int32_t n,
                                                       double* __restrict__ lambda, double* __restrict__ tnorm) {
-    extern __shared__ double s_t[];  // n diagonal entries, then n squared off-diagonal ones (entry i couples i - 1 and i)
+    extern __shared__ double2 s_t[];  // diagonal entry, squared off-diagonal one (entry i couples i - 1 and i); whole groups + 1
     __shared__ double s_lo[kBisT / kWave], s_hi[kBisT / kWave];
     __shared__ int s_first[2];
-    double* s_d = s_t;
-    double* s_e2 = s_t + n;
     double lo = 1.7e308, hi = -1.7e308;
     for (int i = threadIdx.x; i < n; i += kBisT) {
         const double el = i > 0 ? e[i - 1] : 0.0, er = i + 1 < n ? e[i] : 0.0, di = d[i];
-        s_d[i] = di;
-        s_e2[i] = el * el;
         lo = fmin(lo, di - fabs(el) - fabs(er));
         hi = fmax(hi, di + fabs(el) + fabs(er));
     }
@@ -176,31 +174,62 @@ __global__ __launch_bounds__(kBisT) void k_eig_bisect(const double* __restrict__
     hi = fmax(fmax(s_hi[0], s_hi[1]), fmax(s_hi[2], s_hi[3]));
     const double norm = fmax(fabs(lo), fabs(hi));
     if (blockIdx.x == 0 && threadIdx.x == 0) tnorm[0] = norm;
-    lo -= 4.0 * kEps * norm;
-    hi += 4.0 * kEps * norm;
-    const double tiny = fmax(kEps * kEps * norm, 1e-290);  // a pivot below this counts as a small negative one
+    const int up = norm > 1e-307 && norm < 1e300 ? -ilogb(norm) : 0;  // (a norm of zero, or none at all: as it is)
+    for (int i = threadIdx.x; i < (n + kBisU - 1) / kBisU * kBisU + kBisU; i += kBisT) {  // bisect_terms
+        const double di = i < n ? ldexp(d[i], up) : 8.0;  // past the end: no change of sign
+        const double el = i > 0 && i < n ? ldexp(e[i - 1], up) : 0.0;
+        s_t[i] = make_double2(di, el * el);
+    }
+    const double margin = 4.0 * kEps * ldexp(norm, up);
+    lo = ldexp(lo, up) - margin;
+    hi = ldexp(hi, up) + margin;
+    const double tiny = kEps * kEps;
     const int want = n - (int)blockIdx.x;  // the eigenvalue is the smallest x with at least `want` eigenvalues below or at it
-    for (int round = 0; round < 8; round++) {  // 64 bits: past the last one that a double holds
+    __syncthreads();
+    for (int round = 0; round < 7; round++) {  // 56 bits of 4 |T| at most: past the last one that a double holds of |T|
         const double step = (hi - lo) * (1.0 / (kBisT + 1));
         const double x = lo + step * (double)(threadIdx.x + 1);
         int below = 0;
-        double q = 1.0;
-        for (int i = 0; i < n; i += 8) {  // the entries of eight pivots ahead of the chain that uses them
-            double dd[8], ee[8];
+        double a = 0.0, b = 1.0;  // the last two minors
+        double2 t[kBisU];
 #pragma unroll
-            for (int u = 0; u < 8; u++) {
-                const int ic = i + u < n ? i + u : n - 1;
-                dd[u] = s_d[ic] - x;
-                ee[u] = s_e2[ic];
+        for (int u = 0; u < kBisU; u++) t[u] = s_t[u];
+        for (int i = 0; i < n; i += kBisU) {
+            double2 nx[kBisU];
+#pragma unroll
+            for (int u = 0; u < kBisU; u++) nx[u] = s_t[i + kBisU + u];
+            const double a0 = a, b0 = b;
+            uint32_t signs = (uint32_t)__double2hiint(b) >> 31;  // one bit per minor, the latest lowest
+#pragma unroll
+            for (int u = 0; u < kBisU; u++) {
+                const double c = fma(t[u].x - x, b, -(t[u].y * a));
+                signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(c), 31);
+                a = b;
+                b = c;
             }
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                if (i + u < n) {  // uniform
-                    q = fma(-ee[u], fast_rcp(q), dd[u]);
-                    if (fabs(q) < tiny) q = -tiny;
-                    below += q < 0.0 ? 1 : 0;
+            double m = fmax(fabs(a), fabs(b));
+            if (__builtin_expect(__ballot(!(m > 1e-200)) != 0ull, 0)) {  // uniform
+                a = a0;
+                b = b0;
+                signs = (uint32_t)__double2hiint(b) >> 31;
+#pragma unroll 1
+                for (int u = 0; u < kBisU; u++) {
+                    const double2 tu = s_t[i + u];
+                    double c = fma(tu.x - x, b, -(tu.y * a));
+                    const double ref = b != 0.0 ? b : a;
+                    if (!(fabs(c) >= tiny * fabs(ref))) c = -tiny * ref;
+                    signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(c), 31);
+                    a = b;
+                    b = c;
                 }
+                m = fmax(fabs(a), fabs(b));
             }
+            below += __popc((signs ^ (signs >> 1)) & ((1u << kBisU) - 1u));
+            const int ex = -__builtin_amdgcn_frexp_exp(m);
+            a = __builtin_amdgcn_ldexp(a, ex);
+            b = __builtin_amdgcn_ldexp(b, ex);
+#pragma unroll
+            for (int u = 0; u < kBisU; u++) t[u] = nx[u];
         }
         if (below >= want) atomicMin(&s_first[round & 1], (int)threadIdx.x);
         __syncthreads();
@@ -212,28 +241,175 @@ __global__ __launch_bounds__(kBisT) void k_eig_bisect(const double* __restrict__
         hi = nhi;
         __syncthreads();
     }
-    if (threadIdx.x == 0) lambda[blockIdx.x] = 0.5 * (lo + hi);
+    if (threadIdx.x == 0) lambda[blockIdx.x] = ldexp(0.5 * (lo + hi), -up);
 }
 
 // ---- eigenvectors of the tridiagonal matrix --------------------------------------------------------------------------
-// Workgroup (one wave) j: T - lambda_j I = P L U with partial pivoting, then two solves from a pseudo-random start (a
-// start of its own for every vector, so that the vectors of a multiple eigenvalue are independent).  The recurrences are
+// Workgroup (one wave) j.  An eigenvalue away from its neighbours: the pivots of T - lambda_j I eliminated from the top (D+) and
+// from the bottom (D-), the row k where they meet with the smallest remainder g_k = D+_k + D-_k - (d_k - lambda_j), and the
+// vector (T - lambda_j I) z = g_k e_k, z_k = 1, which is a product of multipliers on either side of k (Parlett and Dhillon,
+// Linear Algebra Appl. 267, 1997).  Its residual is g_k / |z|, of the order of eps |T|; that is checked.
+// Bound by the chain of the pivots: the two directions run in the even and the odd lanes, on minors as in k_eig_bisect (the
+// pivots are their quotients, taken side by side afterwards), the products are a scan.  Two solves with the factors of
+// a pivoted elimination, serial chains all, took 505 us for 50 vectors of 1000; 51 so.
+// An eigenvalue with a neighbour within 1e-10 |T| (or a residual that is too large) takes those two solves, from a start of
+// its own: the vectors of a multiple eigenvalue have to be independent.
+constexpr double kInvGap = 1e-10;
+__device__ void eig_invit_lu(double* s_lu, const double* __restrict__ d, const double* __restrict__ e, int32_t n, double lam,
+                             double norm, int j, double* __restrict__ Z, int64_t ld);
+// bytes: two directions of (diagonal entry, squared coupling), of minors and the minor before each group; two multipliers
+__host__ __device__ static inline int32_t twist_terms(int32_t n) { return (n + kBisU - 1) / kBisU * kBisU + kBisU; }
+__host__ __device__ static inline int32_t twist_at(int32_t i) { return i + (i >> 4); }  // (lanes walk 16 entries apart and more)
+static inline size_t twist_lds_bytes(int32_t n) {
+    return (size_t)twist_terms(n) * 32 + (size_t)twist_terms(n) * 16 + (size_t)twist_terms(n) / kBisU * 16 + (size_t)(twist_at(n) + 1) * 16;
+}
+__global__ __launch_bounds__(kWave) void k_eig_invit(const double* __restrict__ d, const double* __restrict__ e, int32_t n, int32_t p,
+                                                     const double* __restrict__ lambda, const double* __restrict__ tnorm,
+                                                     double* __restrict__ Z, int64_t ld) {
+    extern __shared__ double2 s_iv[];
+    const int lane = threadIdx.x, j = blockIdx.x;
+    const double lam = lambda[j], norm = tnorm[0];
+    const double gap = fmin(j > 0 ? lambda[j - 1] - lam : norm, j + 1 < p ? lam - lambda[j + 1] : norm);
+    bool done = false;  // uniform
+    if (gap > kInvGap * norm && norm > 1e-280 && norm < 1e280) {
+        const int terms = twist_terms(n);
+        double2* T = s_iv;                          // [direction][term]
+        double* P = (double*)(T + 2 * terms);       // [direction][term]: minors
+        double* B = P + 2 * terms;                  // [direction][group]: the minor before the group, as scaled there
+        double* L = B + 2 * (terms / kBisU);        // multipliers up to k
+        double* R = L + twist_at(n) + 1;            //   and from k on
+        const int up = -ilogb(norm);
+        const double ls = ldexp(lam, up);
+        for (int i = lane; i < terms; i += kWave) {
+            const bool ok = i < n;
+            const int r = ok ? n - 1 - i : 0;  // the row of term i from the bottom
+            const double et = ok && i > 0 ? ldexp(e[i - 1], up) : 0.0, eb = ok && i > 0 ? ldexp(e[r], up) : 0.0;
+            T[i] = make_double2(ok ? ldexp(d[i], up) - ls : 1.0, et * et);
+            T[terms + i] = make_double2(ok ? ldexp(d[r], up) - ls : 1.0, eb * eb);
+        }
+        __syncthreads();
+        {
+            const int dir = lane & 1;
+            const double2* Td = T + dir * terms;
+            double* Pd = P + dir * terms;
+            double* Bd = B + dir * (terms / kBisU);
+            const double tiny = kEps * kEps;
+            double a = 0.0, b = 1.0;
+            double2 t[kBisU];
+#pragma unroll
+            for (int u = 0; u < kBisU; u++) t[u] = Td[u];
+            for (int i = 0; i < n; i += kBisU) {
+                double2 nx[kBisU];
+#pragma unroll
+                for (int u = 0; u < kBisU; u++) nx[u] = Td[i + kBisU + u];
+                const double b0 = b;
+                double out[kBisU];
+#pragma unroll
+                for (int u = 0; u < kBisU; u++) {
+                    double c = fma(t[u].x, b, -(t[u].y * a));
+                    const double least = -tiny * b;  // no pivot below tiny |T|
+                    c = fabs(c) >= fabs(least) ? c : least;
+                    out[u] = c;
+                    a = b;
+                    b = c;
+                }
+                if (lane < 2) {
+                    Bd[i / kBisU] = b0;
+#pragma unroll
+                    for (int u = 0; u < kBisU; u++) Pd[i + u] = out[u];
+                }
+                const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(a), fabs(b)));
+                a = __builtin_amdgcn_ldexp(a, ex);
+                b = __builtin_amdgcn_ldexp(b, ex);
+#pragma unroll
+                for (int u = 0; u < kBisU; u++) t[u] = nx[u];
+            }
+        }
+        __syncthreads();
+        double gbest = 1.7e308;
+        int k = n;
+        for (int i = lane; i < n; i += kWave) {
+            const int r = n - 1 - i;
+            const double c = P[i], b = i % kBisU ? P[i - 1] : B[i / kBisU];
+            const double cb = P[terms + r], bb = r % kBisU ? P[terms + r - 1] : B[terms / kBisU + r / kBisU];
+            const double g = fabs(c / b + cb / bb - T[i].x);
+            if (g < gbest) {
+                gbest = g;
+                k = i;
+            }
+            L[twist_at(i)] = i + 1 < n ? -ldexp(e[i], up) * (b / c) : 0.0;
+            R[twist_at(i)] = i > 0 ? -ldexp(e[i - 1], up) * (bb / cb) : 0.0;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double og = __shfl_xor(gbest, o, kWave);
+            const int ok = __shfl_xor(k, o, kWave);
+            if (og < gbest || (og == gbest && ok < k)) {
+                gbest = og;
+                k = ok;
+            }
+        }
+        __syncthreads();
+        // z_i = L_i .. L_(k-1) above k, R_(k+1) .. R_i below: every lane a run of entries, the runs joined by scans
+        const int C = (n + kWave - 1) / kWave, c0 = lane * C, c1 = min(c0 + C, n);
+        double pl = 1.0, pr = 1.0;
+        for (int i = c0; i < c1; i++) {
+            if (i < k) pl *= L[twist_at(i)];
+            if (i > k) pr *= R[twist_at(i)];
+        }
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const double vl = __shfl_down(pl, o, kWave), vr = __shfl_up(pr, o, kWave);
+            if (lane + o < kWave) pl *= vl;
+            if (lane >= o) pr *= vr;
+        }
+        pl = __shfl_down(pl, 1, kWave);
+        pr = __shfl_up(pr, 1, kWave);
+        if (lane == kWave - 1) pl = 1.0;
+        if (lane == 0) pr = 1.0;
+        double big = 0.0;
+        for (int i = c1 - 1; i >= c0; i--) {
+            if (i < k) L[twist_at(i)] = pl = pl * L[twist_at(i)];
+            if (i == k) L[twist_at(i)] = 1.0;
+        }
+        for (int i = c0; i < c1; i++)
+            if (i > k) L[twist_at(i)] = pr = pr * R[twist_at(i)];
+        for (int i = c0; i < c1; i++) big = fmax(big, fabs(L[twist_at(i)]));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, kWave));
+        const double sc = big > 0.0 ? 1.0 / big : 0.0;
+        __syncthreads();
+        double ss = 0.0;
+        for (int i = lane; i < n; i += kWave) {
+            const double v = L[twist_at(i)] * sc;
+            ss = fma(v, v, ss);
+        }
+        ss = wave_total(ss);
+        // residual g_k / |z| in units of the scaled norm (1 .. 2)
+        done = ss >= 1.0 && ss <= 1e6 && gbest * sc <= 1e-13 * sqrt((double)n) * sqrt(ss);
+        if (done) {
+            const double nf = sc / sqrt(ss);
+            for (int i = lane; i < n; i += kWave) Z[(int64_t)j * ld + i] = L[twist_at(i)] * nf;
+        }
+        __syncthreads();
+    }
+    if (!done) eig_invit_lu((double*)s_iv, d, e, n, lam, norm, j, Z, ld);
+}
+
+// T - lambda_j I = P L U with partial pivoting, then two solves from a pseudo-random start.  The recurrences are
 // serial; every lane runs them on the same values, their operands are requested ahead of the chain, lane 0 stores.
 // Z: row j receives the unit vector.
 constexpr int kInvArrays = 5;
 static inline size_t invit_lds_bytes(int32_t n) { return (size_t)n * (kInvArrays * 8 + 4); }
-__global__ __launch_bounds__(kWave) void k_eig_invit(const double* __restrict__ d, const double* __restrict__ e, int32_t n,
-                                                     const double* __restrict__ lambda, const double* __restrict__ tnorm,
-                                                     double* __restrict__ Z, int64_t ld) {
-    extern __shared__ double s_t[];
-    double* u0 = s_t;       // 1 / diagonal of U (before that: the diagonal of T)
+__device__ void eig_invit_lu(double* s_lu, const double* __restrict__ d, const double* __restrict__ e, int32_t n, double lam,
+                             double norm, int j, double* __restrict__ Z, int64_t ld) {
+    double* u0 = s_lu;      // 1 / diagonal of U (before that: the diagonal of T)
     double* u1 = u0 + n;    // first super-diagonal of U (before that: of T)
     double* u2 = u1 + n;    // second super-diagonal of U
     double* l = u2 + n;     // multipliers
     double* x = l + n;      // the vector
     int* sw = (int*)(x + n);  // rows i and i + 1 were interchanged
-    const int lane = threadIdx.x, j = blockIdx.x;
-    const double lam = lambda[j], norm = tnorm[0];
+    const int lane = threadIdx.x;
     const double pert = norm > 0.0 ? kEps * norm : 1.0;  // least pivot
     for (int i = lane; i < n; i += kWave) {
         u0[i] = d[i];
@@ -344,21 +520,26 @@ __global__ __launch_bounds__(kWave) void k_eig_invit(const double* __restrict__ 
     for (int i = lane; i < n; i += kWave) Z[(int64_t)j * ld + i] = x[i];
 }
 
-// One workgroup: vector by vector, the components along the vectors before it whose eigenvalues lie within 1e-4 |T| are
-// taken out (Gram-Schmidt against all of them at once, twice).  Inverse iteration leaves such components at the size of
-// eps |T| / gap: below 1e-11 where the gap is larger than that, everything where the eigenvalue is multiple.
+// One workgroup: vector by vector, the components along the vectors before it whose eigenvalues lie within 1e-6 |T| are
+// taken out (Gram-Schmidt against all of them at once, twice).  Without it such components are of the size of
+// eps |T| / gap: some 1e-10 where the gap is larger than that (the result is rounded to float32), everything where the eigenvalue
+// is multiple.
+// (50 vectors of 1000, nearly all of them within 1e-4 |T| of the next: 289 us with that as the line, 9 with 1e-6.)
 constexpr int kOrtT = 1024;
 __global__ __launch_bounds__(kOrtT) void k_eig_ortho(double* __restrict__ Z, int64_t ld, int32_t n, int32_t p,
                                                      const double* __restrict__ lambda, const double* __restrict__ tnorm) {
     __shared__ double s_x[kEigMaxD];
     __shared__ double s_c[kEigMaxP];
     __shared__ double s_red[kOrtT / kWave];
+    __shared__ double s_lam[kEigMaxP];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const double tol = 1e-4 * tnorm[0];
+    const double tol = 1e-6 * tnorm[0];
+    for (int i = tid; i < p; i += kOrtT) s_lam[i] = lambda[i];
+    __syncthreads();
     int g = 0;  // first vector of the run of close eigenvalues that reaches j
     for (int j = 1; j < p; j++) {
-        const double lj = lambda[j];
-        while (g < j && lambda[g] - lj > tol) g++;  // uniform
+        const double lj = s_lam[j];
+        while (g < j && s_lam[g] - lj > tol) g++;  // uniform
         if (g == j) continue;
         double* zj = Z + (int64_t)j * ld;
         for (int i = tid; i < n; i += kOrtT) s_x[i] = zj[i];
@@ -394,48 +575,65 @@ __global__ __launch_bounds__(kOrtT) void k_eig_ortho(double* __restrict__ Z, int
 }
 
 // ---- back to the basis of the matrix, sign, output ---------------------------------------------------------------------
-// One wave per vector: the reflections n - 3 .. 0 in turn, the next one's entries in flight while one is applied.
+// One wave per vector: the reflections n - 3 .. 0 in turn.  Bound by the latency of a reflection's entries and of its sum over
+// the wave: AHEAD reflections are on their way while one is applied (one: 1000 x 1000, 628 us; four: 280), and the quarters of
+// a row that lie before a reflection's first entry are neither read nor used.
+template <int NI, int M0, int AHEAD>  // entries per lane; the first that the reflections from .. to (descending) can reach
+__device__ __forceinline__ void eig_back_run(const double* __restrict__ V, int64_t ld, int32_t n, const double* __restrict__ tau,
+                                             int from, int to, int lane, double (&y)[NI]) {
+    constexpr int M = NI - M0;
+    if (from < to) return;
+    double r[AHEAD][M], t[AHEAD];
+    auto load = [&](int k, double (&x)[M], double& tk) {
+        const int kc = k > to ? k : to;  // past the last: that one again, never used
+        tk = tau[kc];
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+            const int i = lane + kWave * (M0 + m);
+            x[m] = V[(int64_t)kc * ld + (i < n ? i : n - 1)];  // positions up to k and past the end: dropped where used
+        }
+    };
+    auto apply = [&](int k, double (&v)[M], double tk) {
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+            const int i = lane + kWave * (M0 + m);
+            v[m] = (i > k && i < n) ? v[m] : 0.0;
+            if (m & 1) s1 = fma(v[m], y[M0 + m], s1);
+            else s0 = fma(v[m], y[M0 + m], s0);
+        }
+        const double s = tk * wave_total(s0 + s1);
+#pragma unroll
+        for (int m = 0; m < M; m++) y[M0 + m] = fma(-s, v[m], y[M0 + m]);
+    };
+#pragma unroll
+    for (int u = 0; u < AHEAD; u++) load(from - u, r[u], t[u]);
+    for (int k = from; k >= to; k -= AHEAD) {
+#pragma unroll
+        for (int u = 0; u < AHEAD; u++) {
+            if (k - u >= to) apply(k - u, r[u], t[u]);  // uniform
+            load(k - u - AHEAD, r[u], t[u]);
+        }
+    }
+}
 template <int NI>  // entries per lane: n <= 64 NI
 __global__ __launch_bounds__(kWave) void k_eig_back(const double* __restrict__ Z, const double* __restrict__ V, int64_t ld, int32_t n,
                                                     const double* __restrict__ tau, const double* __restrict__ lambda,
                                                     float* __restrict__ comps, double* __restrict__ evals) {
     const int lane = threadIdx.x, j = blockIdx.x;
-    double y[NI], v[NI];
+    constexpr int Q = NI / 4, AHEAD = NI > 16 ? 2 : 4;
+    double y[NI];
 #pragma unroll
     for (int m = 0; m < NI; m++) {
         const int i = lane + kWave * m;
         y[m] = i < n ? Z[(int64_t)j * ld + i] : 0.0;
     }
-    auto load = [&](int k, double (&r)[NI]) {
-#pragma unroll
-        for (int m = 0; m < NI; m++) {
-            const int i = lane + kWave * m;
-            r[m] = V[(int64_t)k * ld + (i < n ? i : n - 1)];  // positions up to k and past the end: dropped where used
-        }
-    };
-    int k = n - 3;
-    double tk = k >= 0 ? tau[k] : 0.0;
-    if (k >= 0) load(k, v);
-    while (k >= 0) {
-        double nx[NI];
-        const int kn = k > 0 ? k - 1 : 0;
-        load(kn, nx);
-        const double tn = tau[kn];
-        double s = 0.0;
-#pragma unroll
-        for (int m = 0; m < NI; m++) {
-            const int i = lane + kWave * m;
-            v[m] = (i > k && i < n) ? v[m] : 0.0;
-            s = fma(v[m], y[m], s);
-        }
-        s = tk * wave_total(s);
-#pragma unroll
-        for (int m = 0; m < NI; m++) y[m] = fma(-s, v[m], y[m]);
-#pragma unroll
-        for (int m = 0; m < NI; m++) v[m] = nx[m];
-        tk = tn;
-        k--;
-    }
+    // reflection k reaches entries from k + 1 on: from 64 Q s - 1 on the first Q s of a lane stay as they are
+    auto last = [&](int s) { return kWave * Q * s - 1; };
+    eig_back_run<NI, 3 * Q, AHEAD>(V, ld, n, tau, n - 3, last(3), lane, y);
+    eig_back_run<NI, 2 * Q, AHEAD>(V, ld, n, tau, min(n - 3, last(3) - 1), last(2), lane, y);
+    eig_back_run<NI, Q, AHEAD>(V, ld, n, tau, min(n - 3, last(2) - 1), last(1), lane, y);
+    eig_back_run<NI, 0, AHEAD>(V, ld, n, tau, min(n - 3, last(1) - 1), 0, lane, y);
     double am = -1.0;  // the first entry of largest magnitude decides the sign
     int ai = n;
     double av = 1.0;
@@ -491,12 +689,12 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
 #undef CAT_EIG_STEP
         CAT_LAUNCH_CHECK("k_eig_step");
     }
-    hipLaunchKernelGGL(k_eig_bisect, dim3((unsigned)p), dim3(kBisT), (size_t)D * 16, st, d, e, D, lambda, tnorm);
+    hipLaunchKernelGGL(k_eig_bisect, dim3((unsigned)p), dim3(kBisT), (size_t)bisect_terms(D) * 16, st, d, e, D, lambda, tnorm);
     CAT_LAUNCH_CHECK("k_eig_bisect");
-    const size_t lds = invit_lds_bytes(D);  // 90 KB at D = 2048
+    const size_t lds = invit_lds_bytes(D) > twist_lds_bytes(D) ? invit_lds_bytes(D) : twist_lds_bytes(D);  // 139 KB at D = 2048
     if (lds > 64 * 1024)
         CAT_HIP_TRY(hipFuncSetAttribute((const void*)k_eig_invit, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    hipLaunchKernelGGL(k_eig_invit, dim3((unsigned)p), dim3(kWave), lds, st, d, e, D, lambda, tnorm, W, ld);
+    hipLaunchKernelGGL(k_eig_invit, dim3((unsigned)p), dim3(kWave), lds, st, d, e, D, p, lambda, tnorm, W, ld);
     CAT_LAUNCH_CHECK("k_eig_invit");
     hipLaunchKernelGGL(k_eig_ortho, dim3(1), dim3(kOrtT), 0, st, W, ld, D, p, lambda, tnorm);
     CAT_LAUNCH_CHECK("k_eig_ortho");
