@@ -534,6 +534,13 @@ cat_status cat_debug_apply_kernel(int which);
  */
 cat_status cat_debug_full_loop(int on);
 
+/*
+ * Test hook.  The PCA's tridiagonalisation runs in workgroups that wait for each other, no longer than this many ticks of
+ * the GPU's 100 MHz counter; when one has waited longer (negative: at its first wait) a single workgroup does the work.
+ * Process-wide, default 100000000; returns CAT_OK.
+ */
+cat_status cat_debug_pca_patience(int64_t ticks);
+
 /* Message of the last non-OK status on the calling thread ("" if none).  The
  * pointer stays valid until the next failing call on the same thread. */
 const char *cat_last_error(void);

@@ -28,7 +28,7 @@ EXPORTS = ("cat_select_path", "cat_fit_workspace_bytes", "cat_apply_workspace_by
            "cat_apply_static", "cat_apply_static_max_workspace_bytes", "cat_debug_apply_kernel",
            "cat_fit_multi_k_workspace_bytes", "cat_fit_multi_k", "cat_debug_multi_group_tiles",
            "cat_params_to_bf16", "cat_apply_lp_workspace_bytes", "cat_apply_lp",
-           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_stream_probe")
+           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_debug_pca_patience", "cat_stream_probe")
 
 
 class CatError(RuntimeError):
@@ -133,6 +133,8 @@ def load_library():
     lib.cat_debug_multi_group_tiles.restype = c.c_int
     lib.cat_stream_probe.argtypes = [vp, vp, sz, vp]
     lib.cat_stream_probe.restype = c.c_int
+    lib.cat_debug_pca_patience.argtypes = [c.c_int64]
+    lib.cat_debug_pca_patience.restype = c.c_int
     lib.cat_debug_full_loop.argtypes = [c.c_int]
     lib.cat_debug_full_loop.restype = c.c_int
     lib.cat_debug_padded_fit.argtypes = [c.c_int]
@@ -502,6 +504,11 @@ def debug_padded_fit(on):
 def debug_full_loop(on):
     """Test hook: True runs every pass of the plain fits over every row, without early stop and distance bounds."""
     _check(load_library().cat_debug_full_loop(int(bool(on))))
+
+
+def debug_pca_patience(ticks):
+    """Test hook: how long (ticks of 10 ns; negative: not at all) the workgroups of the tridiagonalisation wait for each other."""
+    _check(load_library().cat_debug_pca_patience(int(ticks)))
 
 
 def debug_multi_group_tiles(tiles):

@@ -1,19 +1,21 @@
 // The leading eigenpairs of a symmetric D x D matrix in double precision, for the PCA front-end (p of D directions).
 //
-//   1. Householder tridiagonalisation, one launch per column (k_eig_step): D launches, at D = 1000 each bound by its latencies
-//      (the launch, one round of loads, two sums over a workgroup) and not by the rows it reads and writes, 2 x 8 D^2 bytes
-//      at most (16 MB; 67 MB at D = 2048).
+//   1. Householder tridiagonalisation: for 64 <= D <= 1024 one launch whose workgroups pass the products of a column on through
+//      memory (k_eig_grid), otherwise one launch per column (k_eig_step).  Either is a chain of D steps bound by latencies.
 //   2. The p largest eigenvalues of the tridiagonal matrix T by multisection on Sturm counts (k_eig_bisect).
 //   3. Their vectors from the two-sided factorisation of T - lambda I, or by inverse iteration from pseudo-random starts where
 //      eigenvalues all but coincide (k_eig_invit), made orthogonal where they lie close together (k_eig_ortho).
 //   4. The reflections applied to the p vectors, last one first (k_eig_back), sign and rounding.
 //
 // Against one-sided Jacobi on all D rows (cat_pca.hip, which remains for more than kEigMaxP directions and for callers
-// that ask for a number of sweeps) it does 4/3 D^3 flops instead of about 12 * 6 D^3, and D launches instead of 3 D.
+// that ask for a number of sweeps) it does 4/3 D^3 flops instead of about 12 * 6 D^3.
 // Measured at D = 1000, p = 50 (a whole cat_pca_fit on 65536 rows, 1.5 ms of it the covariance): 56.3 ms with the sweeps,
-// 6.5 ms here; of that 4.6 ms the tridiagonalisation (3.5 us a launch over the last 256 columns, 6.2 us over the first),
-// 0.16 ms the eigenvalues, 0.06 ms their vectors, 0.28 ms the reflections.
+// 4.5 ms here; of that 2.5 ms the tridiagonalisation (one launch per column: 4.6), 0.16 ms the eigenvalues, 0.06 ms their
+// vectors, 0.28 ms the reflections.
 #include "cat_eig.h"
+
+#include <atomic>
+#include <type_traits>
 
 namespace cat {
 
@@ -133,6 +135,363 @@ __global__ __launch_bounds__(kEigT) void k_eig_step(double* __restrict__ W, doub
     if (tid < NI) {
         const int i = k0 + (int)blockIdx.x + kEigT * tid;
         if (i > k && i < n) p_out[i] = (s_rows[tid][0] + s_rows[tid][1]) + (s_rows[tid][2] + s_rows[tid][3]);
+    }
+}
+
+// ---- all columns in one launch (64 <= n <= 1024) ------------------------------------------------------------------------
+// A chain of n - 1 dependent steps: what bounds it is what one step takes from the last product of one workgroup to the first
+// of the next.  As a launch per column that is 4.6 us at n = 1000 (the launch, the loads, three sums); here G workgroups keep
+// their rows of the matrix (i = blockIdx + G r) in registers from the first column to the last and pass each other two doubles
+// a row and step through memory: 2.5 us (n = 500: 1.9, 250: 1.6; 1.4 of the 2.5 the instructions of a step, which every
+// workgroup issues for its own copy of the vectors).  1000 x 1000: 4.55 -> 2.48 ms, 256 x 256: 0.88 -> 0.41.
+//
+// Step k, with the reflection k - 1 (v, tau) and p = A v known for the thread's columns j = tid + T m:
+//   sum 1: p . v over the workgroup; w = tau p - (tau^2 / 2)(p . v) v; x = row k of A - v w^T - w v^T
+//   own rows: A -= v w^T + w v^T; acc_i = sum over j > k + 1 of A[i][j] x[j];  the owner of row k + 1 hands it on at once
+//   sum 2: the acc_i and |x|^2; the acc_i are handed on; beta, tau, v = scale x + e_{k+1} meanwhile, from |x|^2
+//   wait for all acc_i and row k + 1; p_i = A[k+1][i] + scale acc_i (A is symmetric)
+// Two barriers a step; the square root and the quotients run while the products travel.
+//
+// Handing on: a double goes as two 8-byte words, each half of it in the upper and the number of the step in the lower 32
+// bits, so a word says by itself whether it is there: relaxed device-scope atomics, no fences, no counters.  The products go to
+// eight copies, each read by an eighth of the workgroups (one copy for all of them: 3.2 us a step; handing the row on a step
+// earlier: 3.5).  Two slots are used in turn.  A workgroup writes a slot again at step k + 2, after it has read the
+// products of step k + 1 of all workgroups that have rows left, and those were made after their workgroups had read the slot at
+// the end of step k; a workgroup leaves after the step before its last row becomes a pivot row, and does not read any more
+// then.  The owner of the last row stays to the end and writes V, d, e, tau.
+//
+// The workgroups wait for each other, so all of them must be resident: at most 128 of at most 8 waves and 128 registers, two to
+// a CU, so that four calls at once still fit.  Should other work keep some of them out for longer than `patience` ticks of the
+// 100 MHz counter, the waiting ones raise *fail and leave, and k_eig_whole, which the matrix in memory was left unchanged
+// for, does the columns in one workgroup.  Every wait ends.
+constexpr int kGridMin = 64, kGridMax = 1024;
+// rows of V, from the last one up, whose entries before the diagonal carry the words, and how many entries of each
+__host__ __device__ static inline int32_t grid_ring_rows(int32_t copies) { return 2 * (4 + 4 * copies); }
+__host__ __device__ static inline int32_t grid_ring_width(int32_t n, int32_t copies) { return n - grid_ring_rows(copies) - 4; }
+static inline int32_t grid_copies(int32_t n) { return n < 160 ? 1 : 8; }  // (below, two rows of V would not hold n words)
+
+typedef unsigned long long u64;
+__device__ __forceinline__ void pass_on(u64* at, int next, double v, uint32_t step) {
+    const u64 b = (u64)__double_as_longlong(v);
+    __hip_atomic_store(at, (b << 32) | step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(at - next, (b & 0xFFFFFFFF00000000ull) | step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void pass_half(u64* at, double v, int half, uint32_t step) {
+    const u64 b = (u64)__double_as_longlong(v);
+    __hip_atomic_store(at, (half ? b & 0xFFFFFFFF00000000ull : b << 32) | step, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ u64 peek(const u64* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double passed(u64 a, u64 b) { return __longlong_as_double((long long)((b & 0xFFFFFFFF00000000ull) | (a >> 32))); }
+
+// sums of R values over the wave: halves of the lanes take halves of the values while there are several (lane bits 0, 1, ...),
+// full sums over what is left of the wave afterwards.  The lane's value: number `lane & (R - 1)`, bit-reversed (wave_sum_slot).
+template <int CTRL>
+__device__ __forceinline__ double dpp_get(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// sums of R values (2, 4 or 8) over the 16 lanes of a row: halves of the row take halves of the values while there are several.
+// Lane l of the row ends with value l >> log2(16 / R).
+template <int R>
+__device__ __forceinline__ double row_sums(const double (&a)[R], int lane) {
+    double h[R];
+#pragma unroll
+    for (int u = 0; u < R; u++) h[u] = a[u];
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
+#pragma unroll
+    for (int u = 0; u < R / 2; u++) h[u] = (b3 ? h[u + R / 2] : h[u]) + dpp_get<0x140>(b3 ? h[u] : h[u + R / 2]);
+    if (R >= 4) {
+#pragma unroll
+        for (int u = 0; u < R / 4; u++) h[u] = (b2 ? h[u + R / 4] : h[u]) + dpp_get<0x141>(b2 ? h[u] : h[u + R / 4]);
+    } else {
+        h[0] = dpp_add<0x141>(h[0]);
+    }
+    if (R >= 8) h[0] = (b1 ? h[1] : h[0]) + dpp_get<0x4E>(b1 ? h[0] : h[1]);
+    else h[0] = dpp_add<0x4E>(h[0]);
+    return dpp_add<0xB1>(h[0]);
+}
+
+template <int T, int C, int R>  // threads, columns per thread, rows per workgroup
+__global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restrict__ W, double* V, int64_t ld, int32_t n,
+                                                        double* __restrict__ d, double* __restrict__ e, double* __restrict__ tau,
+                                                        int32_t copies, int64_t patience, uint32_t* fail) {
+    constexpr int NW = T / kWave, kParts = T / 16;
+    constexpr int kEvery = R == 8 ? 1 : R == 4 ? 2 : 3;  // log2(16 / R)
+    __shared__ double s_v[T * C], s_p[T * C];
+    __shared__ double s_part[R][kParts];
+    __shared__ double s_red[NW], s_ss[NW];
+    __shared__ double s_x0;
+    __shared__ int s_fail;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const int g = blockIdx.x, G = gridDim.x;
+    const int last = g + (n - 1 - g) / G * G;  // the last row of this workgroup
+    const bool writer = last == n - 1;
+    // Arrays of n words, two rows of V each: halves of the pivot rows (two slots), then of the products (two slots, copies)
+    const int next = 2 * (int)ld, width = grid_ring_width(n, copies);
+    auto word = [&](int i) { return (u64*)V + (i < width ? (n - 1) * (int)ld + i : (n - 2) * (int)ld + i - width); };
+    u64* at[C];
+#pragma unroll
+    for (int m = 0; m < C; m++) at[m] = word(tid + T * m < n ? tid + T * m : 0);
+    // 16 threads add up a row's product: each then hands on one half to one copy
+    u64* const mine = word(g + G * (tid >> 4) < n ? g + G * (tid >> 4) : 0) - (4 + (tid & 15)) * next;
+    const int copy = 4 + 2 * (g & (copies - 1));
+    double a[R][C], v[C], p[C], col[C];
+#pragma unroll
+    for (int m = 0; m < C; m++) {
+        const int j = tid + T * m;
+        col[m] = j < n ? W[j] : 0.0;
+        v[m] = p[m] = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int i = g + G * r;
+            a[r][m] = i < n && j < n ? W[(int64_t)i * ld + j] : 0.0;
+        }
+    }
+    if (tid == 0) s_fail = 0;
+    auto total = [&](const double (&part)[NW]) {
+        double t[NW];
+#pragma unroll
+        for (int h = 0; h < NW; h++) t[h] = part[h];
+#pragma unroll
+        for (int o = NW / 2; o > 0; o /= 2)
+#pragma unroll
+            for (int h = 0; h < o; h++) t[h] += t[h + o];
+        return t[0];
+    };
+    double tp = 0.0;
+    for (int k = 0;; k++) {
+        const uint32_t step = (uint32_t)k + 1u;
+        u64 in[C][4];
+        bool miss[C];
+        auto ask = [&](int m) {
+            const u64* pa = at[m] - (copy + 2 * copies * (k & 1)) * next;
+            const u64* pr = at[m] - 2 * (k & 1) * next;
+            in[m][0] = peek(pa);
+            in[m][1] = peek(pa - next);
+            in[m][2] = peek(pr);
+            in[m][3] = peek(pr - next);
+        };
+#pragma unroll
+        for (int m = 0; m < C; m++) {
+            const int j = tid + T * m;
+            miss[m] = j > k && j < n && last > k + 1;
+            in[m][0] = in[m][1] = in[m][2] = in[m][3] = 0;
+        }
+        double pv = 0.0;
+#pragma unroll
+        for (int m = 0; m < C; m++) {
+            const int j = tid + T * m;
+            s_v[j] = v[m];
+            s_p[j] = p[m];
+            pv = fma(p[m], v[m], pv);
+        }
+        pv = wave_total(pv);
+        if (lane == 0) s_red[wave] = pv;
+        __syncthreads();
+        if (s_fail) return;
+        pv = total(s_red);
+        const double c = 0.5 * tp * tp * pv;
+        const double wk = tp * s_p[k] - c;  // v[k] = 1 (column 0: nothing to apply, all zero)
+        double w[C], x[C], ss = 0.0, acc[R];
+#pragma unroll
+        for (int m = 0; m < C; m++) {
+            const int j = tid + T * m;
+            w[m] = tp * p[m] - c * v[m];
+            x[m] = j >= k && j < n ? col[m] - (v[m] * wk + w[m]) : 0.0;
+            if (j == k && writer) d[k] = x[m];
+            if (j == k + 1) s_x0 = x[m];
+            if (j <= k + 1) x[m] = 0.0;
+            ss = fma(x[m], x[m], ss);
+        }
+        // the rows and columns that are left: all of a register's, or of the upper half of them (rows and columns before k change
+        // nothing: there v and w are zero)
+        auto rows = [&](auto from) {
+            constexpr int R0 = decltype(from)::value ? R / 2 : 0, C0 = decltype(from)::value ? C / 2 : 0;
+            double vr[R], pr[R];
+#pragma unroll
+            for (int r = R0; r < R; r++) {
+                const int i = g + G * r < n ? g + G * r : 0;
+                vr[r] = s_v[i];
+                pr[r] = s_p[i];
+            }
+#pragma unroll
+            for (int r = 0; r < R0; r++) acc[r] = 0.0;
+#pragma unroll
+            for (int r = R0; r < R; r++) {
+                const double wr = c * vr[r] - tp * pr[r];
+                acc[r] = 0.0;
+#pragma unroll
+                for (int m = C0; m < C; m++) {
+                    a[r][m] = fma(-vr[r], w[m], fma(wr, v[m], a[r][m]));
+                    acc[r] = fma(a[r][m], x[m], acc[r]);
+                }
+            }
+        };
+        if (k >= T * (C / 2) && k >= G * (R / 2)) rows(std::true_type());
+        else rows(std::false_type());
+        if ((k + 1 - g) % G == 0) {
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                if (g + G * r != k + 1) continue;  // uniform
+#pragma unroll
+                for (int m = 0; m < C; m++) {
+                    const int j = tid + T * m;
+                    if (j > k && j < n) pass_on(at[m] - 2 * (k & 1) * next, next, a[r][m], step);
+                }
+            }
+        }
+        {
+            const double h = row_sums<R>(acc, lane);
+            if ((lane & ((1 << kEvery) - 1)) == 0) s_part[(lane & 15) >> kEvery][wave * 4 + (lane >> 4)] = h;
+        }
+        ss = wave_total(ss);
+        if (lane == 0) s_ss[wave] = ss;
+        __syncthreads();
+        if (wave < (16 * R + kWave - 1) / kWave) {  // 16 threads add up a row
+            double h = 0.0;
+            if (tid < 16 * R) {
+#pragma unroll
+                for (int q = 0; q < kParts; q += 16) h += s_part[tid >> 4][q + (tid & 15)];
+            }
+            h = dpp_add<0x140>(dpp_add<0x141>(dpp_add<0x4E>(dpp_add<0xB1>(h))));
+            const int i = g + G * (tid >> 4);
+            if ((tid & 15) < 2 * copies && tid < 16 * R && i > k && i < n) pass_half(mine - 2 * copies * (k & 1) * next, h, tid & 1, step);
+        }
+        ss = total(s_ss);
+        const double x0 = s_x0;
+        double beta = x0, tk = 0.0, scale = 0.0;
+        if (ss > 0.0) {
+            const double nrm = sqrt(fma(x0, x0, ss));
+            beta = x0 >= 0.0 ? -nrm : nrm;
+            tk = (beta - x0) / beta;
+            scale = 1.0 / (x0 - beta);
+        }
+#pragma unroll
+        for (int m = 0; m < C; m++) {
+            const int j = tid + T * m;
+            v[m] = j == k + 1 ? 1.0 : x[m] * scale;
+        }
+        // an answer that comes too early costs another round through memory: 64 x 8 cycles from here, the products are there
+        __builtin_amdgcn_s_sleep(8);
+#pragma unroll
+        for (int m = 0; m < C; m++)
+            if (miss[m]) ask(m);
+#pragma unroll
+        for (int m = 0; m < C; m++) {
+            const int j = tid + T * m;
+            if (writer && j > k && j < n) V[(int64_t)k * ld + j] = v[m];
+        }
+        if (writer && tid == 0) {
+            e[k] = beta;
+            tau[k] = tk;
+        }
+        if (last <= k + 1) {
+            if (writer) {  // k = n - 2: the last reflection is none
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+#pragma unroll
+                    for (int m = 0; m < C; m++)
+                        if (g + G * r == n - 1 && tid + T * m == n - 1) d[n - 1] = a[r][m];
+                }
+            }
+            return;
+        }
+        int64_t since = 0;
+        for (uint32_t spins = 0;; spins++) {
+            bool any = false;
+#pragma unroll
+            for (int m = 0; m < C; m++) {
+                miss[m] = miss[m] && ((uint32_t)in[m][0] != step || (uint32_t)in[m][1] != step || (uint32_t)in[m][2] != step ||
+                                      (uint32_t)in[m][3] != step);
+                any = any || miss[m];
+            }
+            if (patience >= 0 && !__any(any)) break;
+            if (patience < 0 || (spins & 63u) == 63u) {
+                const int64_t now = (int64_t)wall_clock64();
+                if (since == 0) since = now;
+                if (now - since > patience || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
+                    if (lane == 0) {
+                        __hip_atomic_store(fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        s_fail = 1;
+                    }
+                    break;
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < C; m++)
+                if (miss[m]) ask(m);
+        }
+        tp = tk;
+#pragma unroll
+        for (int m = 0; m < C; m++) {
+            const int j = tid + T * m;
+            const bool live = j > k && j < n;
+            col[m] = live ? passed(in[m][2], in[m][3]) : 0.0;
+            p[m] = live ? fma(scale, passed(in[m][0], in[m][1]), col[m]) : 0.0;
+        }
+    }
+}
+
+// The same columns by one workgroup on the matrix in memory, if *fail says that k_eig_grid gave up.
+constexpr int kWholeT = 1024;
+__global__ __launch_bounds__(kWholeT) void k_eig_whole(double* W, double* __restrict__ V, int64_t ld, int32_t n, double* __restrict__ d,
+                                                       double* __restrict__ e, double* __restrict__ tau, const uint32_t* fail) {
+    if (*fail == 0u) return;
+    constexpr int NW = kWholeT / kWave;
+    __shared__ double s_v[kGridMax], s_w[kGridMax], s_red[2][NW];
+    __shared__ double s_x0;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    for (int k = 0; k < n; k++) {
+        const bool live = tid > k && tid < n;
+        const double x = tid >= k && tid < n ? W[(int64_t)k * ld + tid] : 0.0;
+        if (tid == k) d[k] = x;
+        if (k + 1 >= n) return;
+        if (tid == k + 1) s_x0 = x;
+        double ss = wave_total(tid > k + 1 ? x * x : 0.0);
+        if (lane == 0) s_red[0][wave] = ss;
+        __syncthreads();
+        ss = 0.0;
+#pragma unroll
+        for (int h = 0; h < NW; h++) ss += s_red[0][h];
+        const double x0 = s_x0;
+        double beta = x0, tk = 0.0, scale = 0.0;
+        if (ss > 0.0) {
+            const double nrm = sqrt(fma(x0, x0, ss));
+            beta = x0 >= 0.0 ? -nrm : nrm;
+            tk = (beta - x0) / beta;
+            scale = 1.0 / (x0 - beta);
+        }
+        const double v = tid == k + 1 ? 1.0 : live ? x * scale : 0.0;
+        if (live) V[(int64_t)k * ld + tid] = v;
+        if (tid == 0) {
+            e[k] = beta;
+            tau[k] = tk;
+        }
+        s_v[tid] = v;
+        __syncthreads();
+        for (int i = k + 1 + wave; i < n; i += NW) {
+            double s = 0.0;
+            for (int j = k + 1 + lane; j < n; j += kWave) s = fma(W[(int64_t)i * ld + j], s_v[j], s);
+            s = wave_total(s);
+            if (lane == 0) s_w[i] = s;
+        }
+        __syncthreads();
+        const double p = live ? s_w[tid] : 0.0;
+        double pv = wave_total(p * v);
+        if (lane == 0) s_red[1][wave] = pv;
+        __syncthreads();
+        pv = 0.0;
+#pragma unroll
+        for (int h = 0; h < NW; h++) pv += s_red[1][h];
+        s_w[tid] = tk * p - 0.5 * tk * tk * pv * v;
+        __syncthreads();
+        for (int i = k + 1 + wave; i < n; i += NW) {
+            const double vi = s_v[i], wi = s_w[i];
+            for (int j = k + 1 + lane; j < n; j += kWave) W[(int64_t)i * ld + j] -= vi * s_w[j] + wi * s_v[j];
+        }
+        __syncthreads();
     }
 }
 
@@ -666,6 +1025,22 @@ __global__ __launch_bounds__(kWave) void k_eig_back(const double* __restrict__ Z
     if (lane == 0 && evals) evals[j] = lambda[j];
 }
 
+static std::atomic<int64_t> g_grid_patience{100000000};  // 1 s; cat_debug_pca_patience
+
+// 128 workgroups at two to a CU: with half a chip's worth of CUs there is room for two such calls at once
+static cat_status chip_holds_grid(bool* yes) {
+    static std::atomic<int> ncu[16];
+    int dev = 0;
+    CAT_HIP_TRY(hipGetDevice(&dev));
+    int v = dev < 16 ? ncu[dev].load() : 0;
+    if (v == 0) {
+        CAT_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
+        if (dev < 16) ncu[dev].store(v);
+    }
+    *yes = v >= 128;
+    return CAT_OK;
+}
+
 cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32_t p, double* scratch, float* comps,
                               double* evals, hipStream_t st) {
     if (D < 1 || D > kEigMaxD || p < 1 || p > D || p > kEigMaxP || ld < D)
@@ -676,18 +1051,36 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
     double* tau = e + D;
     double* lambda = tau + D;
     double* tnorm = pb[0];  // the products are no longer needed once the last column is done
-    for (int32_t k = 0; k < D; k++) {
-        const int32_t rest = D - (k & ~7);
-        const dim3 grid((unsigned)(rest < 256 ? rest : 256)), block(kEigT);
+    bool grid_fits = false;
+    if (cat_status s = chip_holds_grid(&grid_fits); s != CAT_OK) return s;
+    if (grid_fits && D >= kGridMin && D <= kGridMax) {
+        const int32_t copies = grid_copies(D), low = D - grid_ring_rows(copies);
+        if (cat_status s = launch_fill_zero(V + (int64_t)low * ld, (size_t)(D - low) * ld * 8, st); s != CAT_OK) return s;
+        uint32_t* fail = (uint32_t*)(V + (int64_t)low * ld + (low - 2));  // past the words, before the diagonal
+        const int64_t patience = g_grid_patience.load(std::memory_order_relaxed);
+#define CAT_EIG_GRID(T, C, R, G) hipLaunchKernelGGL((k_eig_grid<T, C, R>), dim3(G), dim3(T), 0, st, W, V, ld, D, d, e, tau, copies, patience, fail)
+        if (D <= 128) CAT_EIG_GRID(256, 1, 2, 64);
+        else if (D <= 256) CAT_EIG_GRID(256, 1, 2, 128);
+        else if (D <= 512) CAT_EIG_GRID(512, 1, 4, 128);
+        else CAT_EIG_GRID(512, 2, 8, 128);
+#undef CAT_EIG_GRID
+        CAT_LAUNCH_CHECK("k_eig_grid");
+        hipLaunchKernelGGL(k_eig_whole, dim3(1), dim3(kWholeT), 0, st, W, V, ld, D, d, e, tau, fail);
+        CAT_LAUNCH_CHECK("k_eig_whole");
+    } else {
+        for (int32_t k = 0; k < D; k++) {
+            const int32_t rest = D - (k & ~7);
+            const dim3 grid((unsigned)(rest < 256 ? rest : 256)), block(kEigT);
 #define CAT_EIG_STEP(NI) hipLaunchKernelGGL(k_eig_step<NI>, grid, block, 0, st, W, V, ld, D, k, pb[(k & 1) ^ 1], pb[k & 1], d, e, tau)
-        if (rest <= 256) CAT_EIG_STEP(1);
-        else if (rest <= 512) CAT_EIG_STEP(2);
-        else if (rest <= 768) CAT_EIG_STEP(3);
-        else if (rest <= 1024) CAT_EIG_STEP(4);
-        else if (rest <= 1536) CAT_EIG_STEP(6);
-        else CAT_EIG_STEP(8);
+            if (rest <= 256) CAT_EIG_STEP(1);
+            else if (rest <= 512) CAT_EIG_STEP(2);
+            else if (rest <= 768) CAT_EIG_STEP(3);
+            else if (rest <= 1024) CAT_EIG_STEP(4);
+            else if (rest <= 1536) CAT_EIG_STEP(6);
+            else CAT_EIG_STEP(8);
 #undef CAT_EIG_STEP
-        CAT_LAUNCH_CHECK("k_eig_step");
+            CAT_LAUNCH_CHECK("k_eig_step");
+        }
     }
     hipLaunchKernelGGL(k_eig_bisect, dim3((unsigned)p), dim3(kBisT), (size_t)bisect_terms(D) * 16, st, d, e, D, lambda, tnorm);
     CAT_LAUNCH_CHECK("k_eig_bisect");
@@ -709,3 +1102,8 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
 }
 
 }  // namespace cat
+
+extern "C" cat_status cat_debug_pca_patience(int64_t ticks) {
+    cat::g_grid_patience.store(ticks);
+    return CAT_OK;
+}

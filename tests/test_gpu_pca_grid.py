@@ -1,0 +1,110 @@
+"""Tridiagonalisation in one launch whose workgroups pass their products on through memory: sizes on either side of its range and
+of its numbers of rows and columns per workgroup and thread, the one workgroup that does the work when a wait is given up,
+captured graphs, and calls on several streams at once.
+
+Bounds: an eigenvalue is within a few D eps |C| (the covariance is summed in double); a row of the result satisfies
+C v = lambda v to the rounding of its float32 entries (6e-8 |C|) and the rows are at right angles to the same."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_26277_amd import binding, cat_pca_fit
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(D, seed, N=None):
+    rng = np.random.default_rng(seed)
+    N = N or max(300, D // 2)  # wide rows: a covariance of less than full rank
+    x = rng.standard_normal((N, D)) * np.exp(-3.0 * np.arange(D) / D) + rng.standard_normal((N, 4)) @ rng.standard_normal((4, D))
+    return np.ascontiguousarray(x, dtype=np.float32)
+
+
+def _check(x, mean, comps, evals):
+    D, p = x.shape[1], len(comps)
+    xd = x.astype(np.float64) - x.astype(np.float64).mean(0)
+    C = xd.T @ xd / len(x)
+    w = np.linalg.eigvalsh(C)[::-1]
+    v, lam = comps.cpu().numpy().astype(np.float64), evals.cpu().numpy()
+    norm = np.abs(w).max()
+    slack = 30 * D * np.finfo(np.float64).eps * norm
+    assert np.isfinite(v).all()
+    assert np.abs(lam - w[:p]).max() <= slack
+    assert np.abs(v @ v.T - np.eye(p)).max() <= 1e-6
+    assert np.linalg.norm(v @ C - lam[:, None] * v, axis=1).max() <= 3e-7 * norm + slack
+
+
+@pytest.mark.parametrize("D", [63, 64, 65, 127, 128, 129, 255, 256, 257, 383, 511, 512, 513, 769, 1000, 1023, 1024, 1025])
+def test_sizes(D):
+    x = _rows(D, D)
+    _check(x, *cat_pca_fit(torch.from_numpy(x).cuda(), min(D, 20)))
+
+
+@pytest.mark.parametrize("D", [64, 200, 300, 1001])
+def test_a_wait_given_up(D):
+    x = _rows(D, D + 1)
+    t = torch.from_numpy(x).cuda()
+    want = cat_pca_fit(t, 16)
+    binding.debug_pca_patience(-1)
+    try:
+        got = cat_pca_fit(t, 16)
+        torch.cuda.synchronize()
+    finally:
+        binding.debug_pca_patience(100000000)
+    _check(x, *got)
+    # the covariance is summed with atomics, in another order from call to call
+    assert (got[2] - want[2]).abs().max() <= 60 * D * np.finfo(np.float64).eps * want[2].max()
+
+
+def test_values_that_are_no_numbers_end():
+    x = _rows(130, 3)
+    x[5, 7] = np.nan
+    _, comps, evals = cat_pca_fit(torch.from_numpy(x).cuda(), 4)
+    torch.cuda.synchronize()
+    assert comps.shape == (4, 130)
+
+
+def test_a_constant_matrix():
+    x = torch.full((100, 96), 2.5, device="cuda")
+    _, comps, evals = cat_pca_fit(x, 5)
+    assert evals.abs().max().item() == 0.0
+    v = comps.double()
+    assert (v @ v.T - torch.eye(5, device="cuda", dtype=torch.float64)).abs().max().item() <= 1e-6
+
+
+def test_captures_into_a_hip_graph_and_replays():
+    D, p, N = 320, 12, 2000
+    xs = [_rows(D, s, N) for s in (11, 12, 13)]
+    buf = torch.from_numpy(xs[0]).cuda()
+    ws = torch.empty(binding.load_library().cat_pca_workspace_bytes(N, D, p, binding.CAT_F32), dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        cat_pca_fit(buf, p, workspace=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = cat_pca_fit(buf, p, workspace=ws)
+    for x in xs:
+        buf.copy_(torch.from_numpy(x))
+        graph.replay()
+        torch.cuda.synchronize()
+        _check(x, *out)
+
+
+def test_calls_on_several_streams_at_once():
+    D, p = 1000, 8
+    xs = [_rows(D, 20 + s, 600) for s in range(4)]
+    ts = [torch.from_numpy(x).cuda() for x in xs]
+    ws = [torch.empty(binding.load_library().cat_pca_workspace_bytes(600, D, p, binding.CAT_F32), dtype=torch.uint8, device="cuda")
+          for _ in xs]
+    streams = [torch.cuda.Stream() for _ in xs]
+    torch.cuda.synchronize()
+    outs = [None] * 4
+    for _ in range(3):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                outs[i] = cat_pca_fit(ts[i], p, workspace=ws[i])
+    torch.cuda.synchronize()
+    for x, o in zip(xs, outs):
+        _check(x, *o)
