@@ -10,6 +10,8 @@
 #include "cat_common.h"
 #include "cat_eig.h"
 
+#include <type_traits>
+
 namespace cat {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
@@ -104,36 +106,38 @@ __global__ __launch_bounds__(256) void k_pca_cov(const T* __restrict__ x, int64_
 // (64 x 64 tile of the upper triangle, row range): lane (m, k) = (lane & 15, lane >> 4) loads entry m of a
 // 16-column piece of row i0 + k, centres and widens it, and that is at once the A operand (for the piece of the
 // tile's rows) and the B operand (for the piece of its columns) of a 16 x 16 x 4 product; 4 + 4 pieces feed 16
-// products per step of four rows, 16 rows are requested ahead of their use.  No LDS, no barriers; the 64 x 64
+// products per step of four rows, 8 rows are requested while 8 are multiplied.  No LDS, no barriers; the 64 x 64
 // doubles of a wave stay in registers until they are added to W with atomics.
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
 constexpr int kCovM = 64;     // tile edge of a wave
-constexpr int kCovAhead = 4;  // steps of four rows requested together
+constexpr int kCovAhead = 2;  // steps of four rows requested together, while as many are multiplied
 template <typename T>
-__global__ __launch_bounds__(256) void k_pca_cov_mfma(const T* __restrict__ x, int64_t N, int64_t D, const double* __restrict__ mean,
+__global__ __launch_bounds__(256, 2) void k_pca_cov_mfma(const T* __restrict__ x, int64_t N, int64_t D, const double* __restrict__ mean,
                                                       int64_t rows_per_wave, int32_t ntile, double* __restrict__ W, int64_t ldw) {
-    int t = blockIdx.x, ta = 0;  // tile index -> (ta <= tb)
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    // wave w: tile w mod ntri of row range w / ntri; workgroups go to the eight XCDs in turn, and each takes consecutive waves,
+    // so that an XCD's L2 holds the rows of an eighth of the ranges
+    const int ntri = ntile * (ntile + 1) / 2;
+    const int64_t w = ((int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3)) * (blockDim.x / kWave) + wave;
+    const int64_t range = w / ntri;
+    int t = (int)(w - range * ntri), ta = 0;  // tile index -> (ta <= tb)
     while (t >= ntile - ta) {
         t -= ntile - ta;
         ta++;
     }
     const int tb = ta + t;
     const int64_t a0 = (int64_t)ta * kCovM, b0 = (int64_t)tb * kCovM;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int m = lane & 15, kk = lane >> 4;
-    const int64_t range = (int64_t)blockIdx.y * (blockDim.x / kWave) + wave;
     const int64_t r0 = range * rows_per_wave;
     const int64_t r1 = r0 + rows_per_wave < N ? r0 + rows_per_wave : N;
     if (r0 >= N) return;  // wave-uniform
-    // this lane's eight columns (four of the tile's rows, four of its columns), clamped to valid positions
-    int64_t col[8];
+    // this lane's eight columns (four of the tile's rows, four of its columns); past the last: column 0, whose products are dropped
+    uint32_t col[8];
     double mu[8];
-    bool ok[8];
 #pragma unroll
     for (int s = 0; s < 8; s++) {
         const int64_t c = (s < 4 ? a0 : b0) + 16 * (s & 3) + m;
-        ok[s] = c < D;
-        col[s] = ok[s] ? c : 0;
+        col[s] = c < D ? (uint32_t)c : 0u;
         mu[s] = mean[col[s]];
     }
     f64x4_t acc[4][4];
@@ -141,26 +145,44 @@ __global__ __launch_bounds__(256) void k_pca_cov_mfma(const T* __restrict__ x, i
     for (int i = 0; i < 4; i++)
 #pragma unroll
         for (int j = 0; j < 4; j++) acc[i][j] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
-    for (int64_t rb = r0; rb < r1; rb += 4 * kCovAhead) {
-        float raw[kCovAhead][8];
+    // Two buffers in turn, held to 256 registers: two waves a SIMD (58 TFLOP/s counting whole tiles; as one buffer that the other
+    // wave's products had to hide 55, with 328 registers and one wave a SIMD 44).
+    float ra[kCovAhead][8], rb[kCovAhead][8];
+    auto load = [&](float (&raw)[kCovAhead][8], int64_t row) {
 #pragma unroll
         for (int u = 0; u < kCovAhead; u++) {
-            const int64_t i = rb + 4 * u + kk;
+            const int64_t i = row + 4 * u + kk;
             const T* xr = x + (i < r1 ? i : r0) * D;  // past the range: a valid row, its values dropped below
 #pragma unroll
             for (int s = 0; s < 8; s++) raw[u][s] = ld_elem(xr + col[s]);
         }
+    };
+    auto products = [&](const float (&raw)[kCovAhead][8], int64_t row, auto whole) {
 #pragma unroll
         for (int u = 0; u < kCovAhead; u++) {
-            const bool in = rb + 4 * u + kk < r1;
+            const bool in = whole || row + 4 * u + kk < r1;
             double v[8];
 #pragma unroll
-            for (int s = 0; s < 8; s++) v[s] = (in && ok[s]) ? (double)raw[u][s] - mu[s] : 0.0;
+            for (int s = 0; s < 8; s++) v[s] = in ? (double)raw[u][s] - mu[s] : 0.0;
 #pragma unroll
             for (int i = 0; i < 4; i++)
 #pragma unroll
                 for (int j = 0; j < 4; j++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[i], v[4 + j], acc[i][j], 0, 0, 0);
         }
+    };
+    constexpr int S = 4 * kCovAhead;
+    load(ra, r0);
+    int64_t row = r0;
+    for (; row + 2 * S <= r1; row += 2 * S) {
+        load(rb, row + S);
+        products(ra, row, std::true_type());
+        load(ra, row + 2 * S);
+        products(rb, row + S, std::true_type());
+    }
+    if (row < r1) {  // fewer than 2 S rows
+        load(rb, row + S);
+        products(ra, row, std::false_type());
+        if (row + S < r1) products(rb, row + S, std::false_type());
     }
     // entry r of acc[i][j]: row a0 + 16 i + 4 r + (lane >> 4) of W, column b0 + 16 j + (lane & 15) (the fp64
     // product interleaves its result rows over the lane groups, unlike the fp32 one)
@@ -173,6 +195,27 @@ __global__ __launch_bounds__(256) void k_pca_cov_mfma(const T* __restrict__ x, i
                 const int64_t ia = a0 + 16 * i + 4 * r + kk, ib = b0 + 16 * j + m;
                 if (ia < D && ib < D && ia <= ib) atomicAdd(W + ia * ldw + ib, acc[i][j][r]);
             }
+}
+
+// Rows per wave.  All waves have the same work and 2048 are resident (two to a SIMD, 256 CUs), so their number should be
+// little below a multiple of that: 65536 x 1000 in 15 ranges of 136 tiles, 2040 waves, takes 1.34 ms against 1.49 in 48
+// ranges (6528 waves, 3.2 rounds), and 1.27 with the rows requested ahead of the products.  The fewest rounds that are 97 % full, otherwise the fullest of up to four; a range holds 64
+// rows at least (every wave ends in 4096 atomics).
+static int64_t cov_rows_per_wave(int64_t N, int ntri) {
+    constexpr int64_t kResident = 2048;
+    int64_t split = 1;
+    double best = 0.0;
+    for (int64_t rounds = 1; rounds <= 4 && best < 0.97; rounds++) {
+        const int64_t s = kResident * rounds / ntri;
+        const double full = (double)(s * ntri) / (double)(kResident * rounds);
+        if (s >= 1 && full > best) {
+            best = full;
+            split = s;
+        }
+    }
+    int64_t rpw = (N + split - 1) / split;
+    rpw = (rpw + 15) / 16 * 16;
+    return rpw < 64 ? 64 : rpw;
 }
 
 // scale the upper triangle by 1/N, set the padding row / column (an eigenvalue below every eigenvalue
@@ -1083,15 +1126,12 @@ cat_status cat_pca_fit(const void* lq, int64_t N, int64_t D, int32_t p, cat_dtyp
     }
     {
         if (D >= kCovM) {
-            // matrix cores: 64 x 64 tiles, the rows split so that about 6144 waves are at work, four per workgroup
+            // matrix cores: 64 x 64 tiles, the rows split into ranges
             const int ntile = (int)((D + kCovM - 1) / kCovM);
             const int ntri = ntile * (ntile + 1) / 2;
-            int64_t split = (6144 + ntri - 1) / ntri;
-            split = (split + 3) / 4 * 4;
-            int64_t rpw = (N + split - 1) / split;
-            rpw = (rpw + 15) / 16 * 16;
-            const int64_t nranges = (N + rpw - 1) / rpw;
-            dim3 g((unsigned)ntri, (unsigned)((nranges + 3) / 4)), b(256);
+            const int64_t rpw = cov_rows_per_wave(N, ntri);
+            const int64_t waves = (N + rpw - 1) / rpw * ntri;
+            dim3 g((unsigned)((waves + 31) / 32 * 8)), b(256);
             if (dt == CAT_F32)
                 hipLaunchKernelGGL(k_pca_cov_mfma<float>, g, b, 0, st, (const float*)lq, N, D, w.mean, rpw, ntile, w.W, Dp);
             else
