@@ -74,7 +74,6 @@ struct FitWs {
     float* pivy;              // K x D
     int32_t* counts;          // K
     unsigned long long* rep;  // K           smallest row index of each cluster
-    int64_t* idx;             // K           seeded initial rows
     double* inertia;          // 1
     TileWs tile;              // scratch of the MFMA tile kernels
     LloydWs lloyd;            // changed-row list and counters of the fused Lloyd loop
@@ -97,7 +96,6 @@ static FitWs carve_fit(void* base, int64_t N, int64_t D, int32_t K, cat_dtype dt
     w.pivy = c.take<float>(KD);
     w.counts = c.take<int32_t>(K);
     w.rep = c.take<unsigned long long>(K);
-    w.idx = c.take<int64_t>(K);
     w.inertia = c.take<double>(1);
     w.sort = c.take<uint32_t>(sort_workspace_words(N, K));
     size_t tb = tile_workspace_bytes(D, K, dt);
@@ -265,14 +263,13 @@ static cat_status step_update(const void* lq, cat_dtype dt, const int32_t* assig
 
 static cat_status step_stats(const void* lq, const void* fp, cat_dtype dt, const int32_t* assign, int64_t N, int64_t D,
                              int32_t K, const int32_t* counts, const unsigned long long* rep, const float* hint,
-                             const FitWs& w, float* gamma, float* beta, hipStream_t st) {
-    CAT_TRY(launch_gather_pivots(lq, fp, dt, D, K, rep, hint, w.pivx, w.pivy, st));
-    CAT_TRY(launch_fill_zero(w.acc, (size_t)4 * K * D * sizeof(double), st));
+                             const FitWs& w, float* gamma, float* beta, int32_t* counts_out, hipStream_t st) {
+    CAT_TRY(launch_gather_pivots(lq, fp, dt, D, K, rep, hint, w.pivx, w.pivy, w.acc, st));
     if (segsum_sorted_supported(4, N, D, dt))
         CAT_TRY(launch_segsum_sorted(4, lq, fp, dt, assign, counts, N, D, K, w.pivx, w.pivy, w.acc, w.sort, st));
     else
         CAT_TRY(launch_segsum(4, lq, fp, dt, assign, N, D, K, w.pivx, w.pivy, w.acc, st));
-    return launch_finalize_affine(w.acc, counts, w.pivx, w.pivy, gamma, beta, D, K, st);
+    return launch_finalize_affine(w.acc, counts, w.pivx, w.pivy, gamma, beta, D, K, counts_out, st);
 }
 
 // Initialisation, `iters` Lloyd iterations and the final assignment (everything of cat_fit before the
@@ -292,8 +289,7 @@ static cat_status run_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, 
     if (init_centroids) {
         CAT_TRY(launch_copy_words(init_centroids, c0, (int64_t)KD, st));
     } else {
-        CAT_TRY(launch_init_indices(N, K, seed, w.idx, st));
-        CAT_TRY(launch_gather_rows(lq, dt, D, K, w.idx, c0, st));
+        CAT_TRY(launch_seed_rows(lq, dt, N, D, K, seed, c0, st));
     }
     if (fused) {
         // Long passes leave out the rows whose distance bounds say that they stay (same outputs; no pass needs to be left
@@ -484,8 +480,7 @@ cat_status cat_stats(const void* lq, const void* fp, const int32_t* assignments,
     CAT_TRY(launch_fill_zero(w.counts, (size_t)K * sizeof(int32_t), st));
     CAT_TRY(launch_fill_u64(w.rep, K, ~0ull, st));
     CAT_TRY(launch_count_rep(assignments, N, K, w.counts, w.rep, st));
-    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, w.counts, w.rep, centroids, w, gamma, beta, st));
-    if (counts) CAT_TRY(launch_copy_words(w.counts, counts, K, st));
+    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, w.counts, w.rep, centroids, w, gamma, beta, counts, st));
     return CAT_OK;
 }
 
@@ -553,8 +548,7 @@ static cat_status fit_impl(const char* who, const void* lq, const void* fp, int6
                           with_bounds ? &bw : nullptr));
     }
     // affine fit on that partition, shifted by the centroids
-    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, w.counts, w.rep, centroids, w, gamma, beta, st));
-    if (counts) CAT_TRY(launch_copy_words(w.counts, counts, K, st));
+    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, w.counts, w.rep, centroids, w, gamma, beta, counts, st));
     return CAT_OK;
 }
 
@@ -695,8 +689,7 @@ cat_status cat_fit_restarts(const void* lq, const void* fp, int64_t N, int64_t D
     CAT_TRY(launch_fill_zero(fw.counts, (size_t)K * sizeof(int32_t), st));
     CAT_TRY(launch_fill_u64(fw.rep, K, ~0ull, st));
     CAT_TRY(launch_count_rep(assignments, N, K, fw.counts, fw.rep, st));
-    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, fw.counts, fw.rep, centroids, fw, gamma, beta, st));
-    if (counts) CAT_TRY(launch_copy_words(fw.counts, counts, K, st));
+    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, fw.counts, fw.rep, centroids, fw, gamma, beta, counts, st));
     if (best_run) CAT_TRY(launch_copy_words(w.state + 1, best_run, 1, st));
     return CAT_OK;
 }
@@ -895,8 +888,7 @@ cat_status cat_fit_multi_k(const void* lq, const void* fp, int64_t N, int64_t D,
                 CAT_TRY(run_lloyd(lq, dt, N, D, K, iters, seed, nullptr, cent_i, asg_i, in_i, fw, st));
             }
             CAT_TRY(step_stats(lq, fp, dt, asg_i, N, D, K, fw.counts, fw.rep, cent_i, fw, gamma + row0[i] * D,
-                               beta + row0[i] * D, st));
-            if (counts) CAT_TRY(launch_copy_words(fw.counts, counts + row0[i], K, st));
+                               beta + row0[i] * D, counts ? counts + row0[i] : nullptr, st));
             continue;
         }
         const MultiSets& ms = g.ms;
@@ -904,10 +896,8 @@ cat_status cat_fit_multi_k(const void* lq, const void* fp, int64_t N, int64_t D,
         // seeded rows of every set into its slots; the other slots stay zero rows with zero counts
         CAT_TRY(launch_fill_zero(w.cent, (size_t)gslots * Dl * sizeof(float), st));
         FitWs fw = carve_fit(w.fit, N, Dl, Kmax, dt);
-        for (int j = 0; j < ms.nsets; j++) {
-            CAT_TRY(launch_init_indices(N, ms.k[j], seed, fw.idx, st));
-            CAT_TRY(launch_gather_rows(lql, dt, Dl, ms.k[j], fw.idx, w.cent + (size_t)16 * ms.t0[j] * Dl, st));
-        }
+        for (int j = 0; j < ms.nsets; j++)
+            CAT_TRY(launch_seed_rows(lql, dt, N, Dl, ms.k[j], seed, w.cent + (size_t)16 * ms.t0[j] * Dl, st));
         LloydWs lw = w.lloyd;
         lw.sort_ws = fw.sort;
         CAT_TRY(tile_lloyd_multi(lql, dt, N, Dl, ms, iters, w.cent, w.sums, w.assign16, w.counts, inertia ? w.inertia16 : nullptr,
@@ -924,8 +914,7 @@ cat_status cat_fit_multi_k(const void* lq, const void* fp, int64_t N, int64_t D,
                 CAT_TRY(launch_copy_words(w.cent + (size_t)slot0 * D, cent_i, (int64_t)K * D, st));
             FitWs fk = carve_fit(w.fit, N, D, K, dt);
             CAT_TRY(step_stats(lq, fp, dt, asg_i, N, D, K, w.counts + slot0, w.rep + slot0, cent_i, fk, gamma + row0[i] * D,
-                               beta + row0[i] * D, st));
-            if (counts) CAT_TRY(launch_copy_words(w.counts + slot0, counts + row0[i], K, st));
+                               beta + row0[i] * D, counts ? counts + row0[i] : nullptr, st));
             if (inertia)
                 CAT_TRY(launch_copy_cols((const float*)(w.inertia16 + j), nin, 32, (float*)(inertia + i * nin), 2, 2, st));
         }
@@ -1206,8 +1195,7 @@ cat_status cat_fit_pca(const void* lq, const void* fp, int64_t N, int64_t D, int
     if (pp != p) CAT_TRY(launch_copy_cols(cz, K, pp, centroids_z, p, p, st));
     // ... the affine fit on the full vectors (rows are shared, so the counts and first rows carry over)
     FitWs wx = carve_fit(w.stats, N, D, K, dt);
-    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, wz.counts, wz.rep, nullptr, wx, gamma, beta, st));
-    if (counts) CAT_TRY(launch_copy_words(wz.counts, counts, K, st));
+    CAT_TRY(step_stats(lq, fp, dt, assignments, N, D, K, wz.counts, wz.rep, nullptr, wx, gamma, beta, counts, st));
     return CAT_OK;
 }
 

@@ -105,9 +105,11 @@ struct FoldAlpha {
     float* b;
     int64_t n;
 };
-cat_status launch_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t* idx, hipStream_t st);
 cat_status launch_gather_rows(const void* lq, cat_dtype dt, int64_t D, int32_t K, const int64_t* idx,
                               float* out, hipStream_t st);
+// the K rows that the seed names (cat_init_indices), as K x D floats
+cat_status launch_seed_rows(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, uint64_t seed, float* out,
+                            hipStream_t st);
 // Nearest centroid per row, direct-form double precision.  counts (K), inertia (1 double, added to),
 // rep (K, smallest row index per cluster, min-combined) are optional and must be pre-initialised
 // (zero / zero / ~0ull).  If gamma != NULL also writes corrected = gamma[a] * x + beta[a].
@@ -150,13 +152,13 @@ cat_status launch_segsum_sorted(int nq, const void* lq, const void* fp, cat_dtyp
                                 const float* pivy, double* acc, uint32_t* sort_ws, hipStream_t st, double* sumsq = nullptr);
 cat_status launch_finalize_centroids(const double* sums, const int32_t* counts, const float* prev,
                                      float* cent, int64_t D, int32_t K, hipStream_t st);
-// pivx = hint (if given) else lq[rep[k]]; pivy = fp[rep[k]]; rows of empty clusters are zero
+// pivx = hint (if given) else lq[rep[k]]; pivy = fp[rep[k]]; rows of empty clusters are zero.  acc: 4 K D doubles, cleared
 cat_status launch_gather_pivots(const void* lq, const void* fp, cat_dtype dt, int64_t D, int32_t K,
-                                const unsigned long long* rep, const float* hint, float* pivx, float* pivy,
+                                const unsigned long long* rep, const float* hint, float* pivx, float* pivy, double* acc,
                                 hipStream_t st);
 cat_status launch_finalize_affine(const double* acc, const int32_t* counts, const float* pivx,
                                   const float* pivy, float* gamma, float* beta, int64_t D, int32_t K,
-                                  hipStream_t st);
+                                  int32_t* counts_out, hipStream_t st);  // counts_out: nullable, a copy of counts
 cat_status launch_fold_alpha(const float* gamma, const float* beta, float alpha, float* g_eff, float* b_eff,
                              int64_t KD, hipStream_t st);
 // device-to-device copy of 32-bit words (any 4-byte-aligned buffers)

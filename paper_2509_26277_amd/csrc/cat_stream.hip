@@ -228,9 +228,8 @@ cat_status launch_copy_words(const void* src, void* dst, int64_t nwords, hipStre
 // seeded initial rows: one wave walks the SplitMix64 counter; the 64 lanes share
 // the "already taken?" scan.  The walk has a hard draw cap, so the wave always exits.
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void k_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t* idx) {
-    __shared__ int64_t s_idx[CAT_MAX_K];
-    const int lane = threadIdx.x;
+__device__ __forceinline__ void draw_indices(int64_t N, int32_t K, uint64_t seed, int64_t* s_idx) {  // every wave to one result
+    const int lane = threadIdx.x & (kWave - 1);
     const uint64_t cap = init_draw_cap(N);
     int32_t have = 0;
     uint64_t t = 0;
@@ -264,12 +263,6 @@ __global__ __launch_bounds__(64) void k_init_indices(int64_t N, int32_t K, uint6
         }
         __syncthreads();
     }
-    for (int q = lane; q < K; q += kWave) idx[q] = s_idx[q];
-}
-cat_status launch_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t* idx, hipStream_t st) {
-    hipLaunchKernelGGL(k_init_indices, dim3(1), dim3(64), 0, st, N, K, seed, idx);
-    CAT_LAUNCH_CHECK("k_init_indices");
-    return CAT_OK;
 }
 
 template <typename T>
@@ -285,6 +278,28 @@ cat_status launch_gather_rows(const void* lq, cat_dtype dt, int64_t D, int32_t K
     else
         hipLaunchKernelGGL(k_gather_rows<bf16_t>, dim3(K), dim3(256), 0, st, (const bf16_t*)lq, D, idx, out);
     CAT_LAUNCH_CHECK("k_gather_rows");
+    return CAT_OK;
+}
+
+// The seeded rows as the initial centroids.  Every workgroup draws for itself and copies its row: the draws take as long side by side
+// as once, and a launch less is 3.5 us of a small fit.
+template <typename T>
+__global__ __launch_bounds__(256) void k_seed_rows(const T* __restrict__ lq, int64_t N, int64_t D, int32_t K, uint64_t seed,
+                                                   float* __restrict__ out) {
+    __shared__ int64_t s_idx[CAT_MAX_K];
+    const int k = blockIdx.x;
+    draw_indices(N, K, seed, s_idx);
+    __syncthreads();
+    const T* src = lq + s_idx[k] * D;
+    for (int64_t j = threadIdx.x; j < D; j += blockDim.x) out[(int64_t)k * D + j] = ld_elem(src + j);
+}
+cat_status launch_seed_rows(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, uint64_t seed, float* out,
+                            hipStream_t st) {
+    if (dt == CAT_F32)
+        hipLaunchKernelGGL(k_seed_rows<float>, dim3(K), dim3(256), 0, st, (const float*)lq, N, D, K, seed, out);
+    else
+        hipLaunchKernelGGL(k_seed_rows<bf16_t>, dim3(K), dim3(256), 0, st, (const bf16_t*)lq, N, D, K, seed, out);
+    CAT_LAUNCH_CHECK("k_seed_rows");
     return CAT_OK;
 }
 
@@ -933,9 +948,11 @@ cat_status launch_finalize_centroids(const double* sums, const int32_t* counts, 
 template <typename T>
 __global__ void k_gather_pivots(const T* __restrict__ lq, const T* __restrict__ fp, int64_t D, int64_t KD,
                                 const unsigned long long* __restrict__ rep, const float* __restrict__ hint,
-                                float* __restrict__ pivx, float* __restrict__ pivy) {
+                                float* __restrict__ pivx, float* __restrict__ pivy, double* __restrict__ acc) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= KD) return;
+#pragma unroll
+    for (int q = 0; q < 4; q++) acc[q * KD + i] = 0.0;  // the four sums of the statistics that follow
     int64_t k = i / D, j = i - k * D;
     unsigned long long r = rep[k];
     if (r == ~0ull) {
@@ -947,16 +964,16 @@ __global__ void k_gather_pivots(const T* __restrict__ lq, const T* __restrict__ 
     }
 }
 cat_status launch_gather_pivots(const void* lq, const void* fp, cat_dtype dt, int64_t D, int32_t K,
-                                const unsigned long long* rep, const float* hint, float* pivx, float* pivy,
+                                const unsigned long long* rep, const float* hint, float* pivx, float* pivy, double* acc,
                                 hipStream_t st) {
     int64_t KD = (int64_t)K * D;
     dim3 g((unsigned)((KD + 255) / 256)), b(256);
     if (dt == CAT_F32)
         hipLaunchKernelGGL(k_gather_pivots<float>, g, b, 0, st, (const float*)lq, (const float*)fp, D, KD, rep, hint,
-                           pivx, pivy);
+                           pivx, pivy, acc);
     else
         hipLaunchKernelGGL(k_gather_pivots<bf16_t>, g, b, 0, st, (const bf16_t*)lq, (const bf16_t*)fp, D, KD, rep,
-                           hint, pivx, pivy);
+                           hint, pivx, pivy, acc);
     CAT_LAUNCH_CHECK("k_gather_pivots");
     return CAT_OK;
 }
@@ -964,10 +981,12 @@ cat_status launch_gather_pivots(const void* lq, const void* fp, cat_dtype dt, in
 // gamma = cov / max(var, floor), beta = mean_y - gamma * mean_x, from the shifted raw moments
 __global__ void k_finalize_affine(const double* __restrict__ acc, const int32_t* __restrict__ counts,
                                   const float* __restrict__ pivx, const float* __restrict__ pivy,
-                                  float* __restrict__ gamma, float* __restrict__ beta, int64_t D, int64_t KD) {
+                                  float* __restrict__ gamma, float* __restrict__ beta, int64_t D, int64_t KD,
+                                  int32_t* __restrict__ counts_out) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= KD) return;
     int n = counts[i / D];
+    if (counts_out && i % D == 0) counts_out[i / D] = n;
     if (n <= 0) {
         gamma[i] = 1.f;
         beta[i] = 0.f;
@@ -984,10 +1003,10 @@ __global__ void k_finalize_affine(const double* __restrict__ acc, const int32_t*
 }
 cat_status launch_finalize_affine(const double* acc, const int32_t* counts, const float* pivx,
                                   const float* pivy, float* gamma, float* beta, int64_t D, int32_t K,
-                                  hipStream_t st) {
+                                  int32_t* counts_out, hipStream_t st) {
     int64_t KD = (int64_t)K * D;
     hipLaunchKernelGGL(k_finalize_affine, dim3((unsigned)((KD + 255) / 256)), dim3(256), 0, st, acc, counts, pivx,
-                       pivy, gamma, beta, D, KD);
+                       pivy, gamma, beta, D, KD, counts_out);
     CAT_LAUNCH_CHECK("k_finalize_affine");
     return CAT_OK;
 }

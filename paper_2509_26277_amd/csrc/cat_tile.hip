@@ -13,27 +13,33 @@ namespace cat {
 // scattered into packA, and its squared norm stored.  Last, the outputs of the following pass are
 // reset: its counts (counts_reset, which may be the buffer just read), the objective slot and the
 // first-row table.  (KT is not used for the layout any more: KTs, the cluster tiles per operand array, is.)
+// fold_clear: bit 0 folds as above, bit 1 leaves both sums zero for the full sums that follow the pass.  zero: nzero words that
+// are cleared beside (the control words of a loop).  Launches of their own for these cost a small fit 3.5 us each.
 __global__ __launch_bounds__(256) void k_tile_prep(float* cent, double* base, double* delta,
                                                    const int32_t* counts_read, int32_t* counts_reset,
                                                    int64_t D, int32_t K, int32_t KT, int32_t P, int32_t nchunks, int f32_rows,
                                                    uint16_t* packA, float* cnorm, double* inertia_slot,
-                                                   int32_t inertia_n, unsigned long long* rep, int32_t KTs) {
+                                                   int32_t inertia_n, unsigned long long* rep, int32_t KTs, int32_t fold_clear, uint32_t* zero,
+                                                   uint32_t nzero) {
     __shared__ double s_red[256];
+    const bool fold = fold_clear & 1, clear = fold_clear & 2;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nzero; i += gridDim.x * blockDim.x) zero[i] = 0u;
     const int k = blockIdx.x;
     const int t = k >> 4, m = k & 15;
     double nn = 0.0;
     const int64_t Dpad = (int64_t)nchunks * kChunk;
-    const int cntk = (base && k < K) ? counts_read[k] : 0;
+    const int cntk = (fold && k < K) ? counts_read[k] : 0;
     for (int64_t ch = threadIdx.x; ch < Dpad; ch += blockDim.x) {
         float c = 0.f;
         if (k < K && ch < D) {
             const int64_t i = (int64_t)k * D + ch;
-            if (base) {
-                double S = base[i] + delta[i];
-                base[i] = S;
-                delta[i] = 0.0;
+            if (fold) {
+                const double S = base[i] + delta[i];
                 if (cntk > 0) cent[i] = (float)(S / (double)cntk);
+                if (!clear) base[i] = S;
+                delta[i] = 0.0;
             }
+            if (clear) base[i] = delta[i] = 0.0;
             c = cent[i];
         }
         nn += (double)c * (double)c;
@@ -739,10 +745,11 @@ static cat_status launch_delta_prep(const void* lq, cat_dtype dt, int64_t D, int
 static cat_status launch_prep(cat_dtype dt, float* cent, double* base, double* delta, const int32_t* counts_read,
                               int32_t* counts_reset, int64_t D, int32_t K, const TileCfg& c, const TileWs& ws,
                               double* inertia_slot, unsigned long long* rep, hipStream_t st, int32_t inertia_n = 1,
-                              int32_t split_arrays = 1) {
+                              int32_t split_arrays = 1, bool clear = false, uint32_t* zero = nullptr, uint32_t nzero = 0) {
     dim3 grid(c.KT * 16 * split_arrays), block(256);
     hipLaunchKernelGGL(k_tile_prep, grid, block, 0, st, cent, base, delta, counts_read, counts_reset, D, K, c.KT * split_arrays,
-                       c.P, c.nchunks, dt == CAT_F32 ? 1 : 0, ws.packA, ws.cnorm, inertia_slot, inertia_n, rep, c.KT);
+                       c.P, c.nchunks, dt == CAT_F32 ? 1 : 0, ws.packA, ws.cnorm, inertia_slot, inertia_n, rep, c.KT,
+                       (base && counts_read ? 1 : 0) | (clear ? 2 : 0), zero, nzero);
     CAT_LAUNCH_CHECK("k_tile_prep");
     return CAT_OK;
 }
@@ -930,7 +937,6 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     TileParams p = base_params(lq, N, D, K, c, ws, dt);
     p.cent = cent_io;
     p.assign = assign;
-    if (iters > 2) CAT_T(launch_fill_zero(lw.ctrl, lloyd_ctrl_words(D, bounds) * 4, st));
     if (skipped && skipped != lw.skipped) CAT_T(launch_fill_zero(skipped, sizeof(int32_t), st));  // (that word is one of ctrl's)
     if (bw && bw->evaluated) {
         CAT_T(launch_fill_i32(bw->evaluated, (int64_t)iters + 1, (int32_t)N, st));
@@ -955,8 +961,9 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
         int32_t* cnt_t = cb[(iters - t) & 1];
         const int32_t* cnt_prev = cb[(iters - t + 1) & 1];
         if (t <= kFullPasses)
-            CAT_T(launch_prep(dt, cent_io, t ? base : nullptr, t ? delta : nullptr, t ? cnt_prev : nullptr, cnt_t, D, K, c,
-                              ws, slot, last ? rep : nullptr, st, 1, arrays));
+            CAT_T(launch_prep(dt, cent_io, base, delta, t ? cnt_prev : nullptr, cnt_t, D, K, c, ws, slot, last ? rep : nullptr, st,
+                              1, arrays, t < kFullPasses && !last, t == 0 && iters > 2 ? lw.ctrl : nullptr,
+                              t == 0 && iters > 2 ? (uint32_t)lloyd_ctrl_words(D, bounds) : 0u));
         else
             CAT_T(launch_delta_prep(lq, dt, D, K, c, ws, lw, t & 1, cent_io, base, delta, cnt_prev, cnt_t, slot,
                                     last ? rep : nullptr, last ? nullptr : skipped, st, 1, bounds ? bw : nullptr,
@@ -995,8 +1002,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
             CAT_T(dt == CAT_BF16 ? launch_bounds_bf16(p, c, st) : launch_bounds_f32(p, c, st));
         else
             CAT_T(launch_tile(p, c, dt, st));
-        if (t < kFullPasses && !last) {  // full sums of this pass's partition
-            CAT_T(launch_fill_zero(sums, (t == 0 ? 2 : 1) * KD * sizeof(double), st));
+        if (t < kFullPasses && !last) {  // full sums of this pass's partition (launch_prep has cleared them)
             if (lw.sort_ws && segsum_sorted_supported(1, N, D, dt))
                 CAT_T(launch_segsum_sorted(1, lq, nullptr, dt, assign, cnt_t, N, D, K, nullptr, nullptr, base, lw.sort_ws, st,
                                            bounds && record && inertia && t == 1 ? lw.sumsq : nullptr));
