@@ -7,7 +7,6 @@
 // every load of a round requested before the first is used.  The sums are of squares, so their error is relative and
 // small; clusters within it of the nearest are measured again in double (lowest index on ties), which decides as the other
 // kernels do.  The blending coefficient is folded into the parameters as they are read.
-#include <stdlib.h>
 #include "cat_direct.h"
 
 #include "cat_infer.h"

@@ -9,9 +9,9 @@
 //
 // Against one-sided Jacobi on all D rows (cat_pca.hip, which remains for more than kEigMaxP directions and for callers
 // that ask for a number of sweeps) it does 4/3 D^3 flops instead of about 12 * 6 D^3.
-// Measured at D = 1000, p = 50 (a whole cat_pca_fit on 65536 rows, 1.5 ms of it the covariance): 56.3 ms with the sweeps,
-// 4.5 ms here; of that 2.5 ms the tridiagonalisation (one launch per column: 4.6), 0.16 ms the eigenvalues, 0.06 ms their
-// vectors, 0.28 ms the reflections.
+// Measured at D = 1000, p = 50 (a whole cat_pca_fit on 65536 rows): 56.3 ms with the sweeps,
+// 4.3 ms here, 1.3 of it the covariance and 2.5 the tridiagonalisation (one launch per column: 4.6), 0.16 ms the eigenvalues,
+// 0.05 ms their vectors, 0.29 ms the reflections.
 #include "cat_eig.h"
 
 #include <atomic>
