@@ -40,6 +40,14 @@ def test_sizes(D):
     _check(x, *cat_pca_fit(torch.from_numpy(x).cuda(), min(D, 20)))
 
 
+@pytest.mark.parametrize("N", [2, 15, 17, 63, 64, 65, 71, 72, 73, 129, 2049, 70001])
+@pytest.mark.parametrize("D", [64, 65, 130])
+def test_rows_of_the_covariance(N, D):
+    """remainders of the rows that a wave takes at once, in turn and in all, and one or several ranges of rows"""
+    x = _rows(D, N + D, N)
+    _check(x, *cat_pca_fit(torch.from_numpy(x).cuda(), 8))
+
+
 @pytest.mark.parametrize("D", [64, 200, 300, 1001])
 def test_a_wait_given_up(D):
     x = _rows(D, D + 1)
