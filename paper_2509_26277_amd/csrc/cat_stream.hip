@@ -225,10 +225,15 @@ cat_status launch_copy_words(const void* src, void* dst, int64_t nwords, hipStre
 }
 
 // ---------------------------------------------------------------------------------
-// seeded initial rows: one wave walks the SplitMix64 counter; the 64 lanes share
+// seeded initial rows: one wave walks the SplitMix64 counter; its 64 lanes share
 // the "already taken?" scan.  The walk has a hard draw cap, so the wave always exits.
 // ---------------------------------------------------------------------------------
-__device__ __forceinline__ void draw_indices(int64_t N, int32_t K, uint64_t seed, int64_t* s_idx) {  // every wave to one result
+__device__ __forceinline__ void wave_lds_done() {  // a wave's LDS operations take place in order: only the compiler must keep to it
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+// called by one wave alone: no barrier inside
+__device__ __forceinline__ void draw_indices(int64_t N, int32_t K, uint64_t seed, int64_t* s_idx) {
     const int lane = threadIdx.x & (kWave - 1);
     const uint64_t cap = init_draw_cap(N);
     int32_t have = 0;
@@ -251,7 +256,7 @@ __device__ __forceinline__ void draw_indices(int64_t N, int32_t K, uint64_t seed
         have += __builtin_popcountll(keep);
         have = have < K ? have : K;
         t += kWave;
-        __syncthreads();
+        wave_lds_done();
     }
     // cap reached (not expected): complete with the smallest indices not yet taken
     for (int64_t c = 0; have < K && c < N; c++) {
@@ -261,7 +266,7 @@ __device__ __forceinline__ void draw_indices(int64_t N, int32_t K, uint64_t seed
             if (lane == 0) s_idx[have] = c;
             have++;
         }
-        __syncthreads();
+        wave_lds_done();
     }
 }
 
@@ -281,24 +286,30 @@ cat_status launch_gather_rows(const void* lq, cat_dtype dt, int64_t D, int32_t K
     return CAT_OK;
 }
 
-// The seeded rows as the initial centroids.  Every workgroup draws for itself and copies its row: the draws take as long side by side
-// as once, and a launch less is 3.5 us of a small fit.
+// The seeded rows as the initial centroids.  One wave of every workgroup draws for itself, and the workgroup copies the rows that
+// are its own: the draws take as long side by side as once, and a launch less is 3.5 us of a small fit.  No more workgroups than
+// compute units: with one per row and every wave drawing, the scans shared the LDS of a CU from some 256 rows on (a fit of 0
+// iterations, us; draws and copy as two launches / that / this: 1024 x 16, K = 1024: 2435 / 3340 / 2470; 8192 x 16, K = 1024:
+// 948 / 1038 / 950; 60000 x 16, K = 512: 560 / 569 / 558; 8192 x 64, K = 128: 69 / 64 / 64).
+constexpr int kSeedGroups = 256;
 template <typename T>
 __global__ __launch_bounds__(256) void k_seed_rows(const T* __restrict__ lq, int64_t N, int64_t D, int32_t K, uint64_t seed,
                                                    float* __restrict__ out) {
     __shared__ int64_t s_idx[CAT_MAX_K];
-    const int k = blockIdx.x;
-    draw_indices(N, K, seed, s_idx);
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) == 0) draw_indices(N, K, seed, s_idx);
     __syncthreads();
-    const T* src = lq + s_idx[k] * D;
-    for (int64_t j = threadIdx.x; j < D; j += blockDim.x) out[(int64_t)k * D + j] = ld_elem(src + j);
+    for (int k = blockIdx.x; k < K; k += gridDim.x) {
+        const T* src = lq + s_idx[k] * D;
+        for (int64_t j = threadIdx.x; j < D; j += blockDim.x) out[(int64_t)k * D + j] = ld_elem(src + j);
+    }
 }
 cat_status launch_seed_rows(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, uint64_t seed, float* out,
                             hipStream_t st) {
+    const dim3 grid((unsigned)(K < kSeedGroups ? K : kSeedGroups)), block(256);
     if (dt == CAT_F32)
-        hipLaunchKernelGGL(k_seed_rows<float>, dim3(K), dim3(256), 0, st, (const float*)lq, N, D, K, seed, out);
+        hipLaunchKernelGGL(k_seed_rows<float>, grid, block, 0, st, (const float*)lq, N, D, K, seed, out);
     else
-        hipLaunchKernelGGL(k_seed_rows<bf16_t>, dim3(K), dim3(256), 0, st, (const bf16_t*)lq, N, D, K, seed, out);
+        hipLaunchKernelGGL(k_seed_rows<bf16_t>, grid, block, 0, st, (const bf16_t*)lq, N, D, K, seed, out);
     CAT_LAUNCH_CHECK("k_seed_rows");
     return CAT_OK;
 }
