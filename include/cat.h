@@ -541,6 +541,15 @@ cat_status cat_debug_full_loop(int on);
  */
 cat_status cat_debug_pca_patience(int64_t ticks);
 
+/*
+ * Test hook.  Where in the workspace of cat_pca_fit (bytes from its start) a 32-bit word says, once the call is through, how its
+ * tridiagonalisation went: CAT_PCA_COLUMNS a launch per column, CAT_PCA_GRID the workgroups that wait for each other,
+ * CAT_PCA_ALONE a single workgroup after one of those gave up.  0: no such word (another method, or a shape with a launch per
+ * column whatever the device).
+ */
+enum { CAT_PCA_COLUMNS = 0, CAT_PCA_ALONE = 1, CAT_PCA_GRID = 2 };
+size_t cat_debug_pca_route_offset(int64_t N, int64_t D, int32_t p, cat_dtype dt, int32_t sweeps);
+
 /* Message of the last non-OK status on the calling thread ("" if none).  The
  * pointer stays valid until the next failing call on the same thread. */
 const char *cat_last_error(void);

@@ -28,7 +28,8 @@ EXPORTS = ("cat_select_path", "cat_fit_workspace_bytes", "cat_apply_workspace_by
            "cat_apply_static", "cat_apply_static_max_workspace_bytes", "cat_debug_apply_kernel",
            "cat_fit_multi_k_workspace_bytes", "cat_fit_multi_k", "cat_debug_multi_group_tiles",
            "cat_params_to_bf16", "cat_apply_lp_workspace_bytes", "cat_apply_lp",
-           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_debug_pca_patience", "cat_stream_probe")
+           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_debug_pca_patience",
+           "cat_debug_pca_route_offset", "cat_stream_probe")
 
 
 class CatError(RuntimeError):
@@ -135,6 +136,8 @@ def load_library():
     lib.cat_stream_probe.restype = c.c_int
     lib.cat_debug_pca_patience.argtypes = [c.c_int64]
     lib.cat_debug_pca_patience.restype = c.c_int
+    lib.cat_debug_pca_route_offset.argtypes = [i64, i64, i32, c.c_int, i32]
+    lib.cat_debug_pca_route_offset.restype = sz
     lib.cat_debug_full_loop.argtypes = [c.c_int]
     lib.cat_debug_full_loop.restype = c.c_int
     lib.cat_debug_padded_fit.argtypes = [c.c_int]
@@ -509,6 +512,13 @@ def debug_full_loop(on):
 def debug_pca_patience(ticks):
     """Test hook: how long (ticks of 10 ns; negative: not at all) the workgroups of the tridiagonalisation wait for each other."""
     _check(load_library().cat_debug_pca_patience(int(ticks)))
+
+
+def debug_pca_route(workspace, N, D, p, dt=CAT_F32, sweeps=0):
+    """Test hook: how the tridiagonalisation of the cat_pca_fit that used ``workspace`` went: "columns", "grid" or "alone"
+    (a launch per column, workgroups that wait for each other, one workgroup after one of those gave up).  Synchronises."""
+    at = int(load_library().cat_debug_pca_route_offset(N, D, p, dt, sweeps))
+    return ("columns", "alone", "grid")[int(workspace[at:at + 4].view(torch.int32)) if at else 0]
 
 
 def debug_multi_group_tiles(tiles):

@@ -16,4 +16,8 @@ static inline size_t eig_scratch_doubles(int64_t D) { return 6 * (size_t)D; }
 cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32_t p, double* scratch, float* comps,
                               double* evals, hipStream_t st);
 
+// Where in V (bytes) a word of 32 bits says afterwards how the columns were done (CAT_PCA_*); 0: nowhere, a launch each.  V comes
+// as an identity matrix or with zeros there.
+size_t eig_route_at(int64_t ld, int64_t D);
+
 }  // namespace cat

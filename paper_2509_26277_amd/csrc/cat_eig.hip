@@ -413,7 +413,7 @@ __global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restric
                 if (since == 0) since = now;
                 if (now - since > patience || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
                     if (lane == 0) {
-                        __hip_atomic_store(fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(fail, (uint32_t)CAT_PCA_ALONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         s_fail = 1;
                     }
                     break;
@@ -434,11 +434,17 @@ __global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restric
     }
 }
 
-// The same columns by one workgroup on the matrix in memory, if *fail says that k_eig_grid gave up.
+// The same columns by one workgroup on the matrix in memory, if *fail says that k_eig_grid gave up; otherwise it notes there that
+// the grid has done them (for the tests; nothing reads it).
 constexpr int kWholeT = 1024;
 __global__ __launch_bounds__(kWholeT) void k_eig_whole(double* W, double* __restrict__ V, int64_t ld, int32_t n, double* __restrict__ d,
-                                                       double* __restrict__ e, double* __restrict__ tau, const uint32_t* fail) {
-    if (*fail == 0u) return;
+                                                       double* __restrict__ e, double* __restrict__ tau, uint32_t* fail) {
+    const bool done = *fail == 0u;
+    __syncthreads();  // all have read it
+    if (done) {
+        if (threadIdx.x == 0) *fail = CAT_PCA_GRID;
+        return;
+    }
     constexpr int NW = kWholeT / kWave;
     __shared__ double s_v[kGridMax], s_w[kGridMax], s_red[2][NW];
     __shared__ double s_x0;
@@ -1041,6 +1047,16 @@ static cat_status chip_holds_grid(bool* yes) {
     return CAT_OK;
 }
 
+// the word that says whether a wait was given up: past the words that are passed on, before the diagonal, so that no row of V
+// reaches it
+static inline int64_t grid_fail_entry(int64_t ld, int32_t n) {
+    const int64_t low = n - grid_ring_rows(grid_copies(n));
+    return low * ld + (low - 2);
+}
+size_t eig_route_at(int64_t ld, int64_t D) {
+    return D >= kGridMin && D <= kGridMax ? (size_t)grid_fail_entry(ld, (int32_t)D) * 8 : 0;
+}
+
 cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32_t p, double* scratch, float* comps,
                               double* evals, hipStream_t st) {
     if (D < 1 || D > kEigMaxD || p < 1 || p > D || p > kEigMaxP || ld < D)
@@ -1056,7 +1072,7 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
     if (grid_fits && D >= kGridMin && D <= kGridMax) {
         const int32_t copies = grid_copies(D), low = D - grid_ring_rows(copies);
         if (cat_status s = launch_fill_zero(V + (int64_t)low * ld, (size_t)(D - low) * ld * 8, st); s != CAT_OK) return s;
-        uint32_t* fail = (uint32_t*)(V + (int64_t)low * ld + (low - 2));  // past the words, before the diagonal
+        uint32_t* fail = (uint32_t*)(V + grid_fail_entry(ld, D));
         const int64_t patience = g_grid_patience.load(std::memory_order_relaxed);
 #define CAT_EIG_GRID(T, C, R, G) hipLaunchKernelGGL((k_eig_grid<T, C, R>), dim3(G), dim3(T), 0, st, W, V, ld, D, d, e, tau, copies, patience, fail)
         if (D <= 128) CAT_EIG_GRID(256, 1, 2, 64);

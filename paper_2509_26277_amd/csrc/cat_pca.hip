@@ -1191,6 +1191,12 @@ cat_status cat_pca_fit(const void* lq, int64_t N, int64_t D, int32_t p, cat_dtyp
     return CAT_OK;
 }
 
+size_t cat_debug_pca_route_offset(int64_t N, int64_t D, int32_t p, cat_dtype dt, int32_t sweeps) {
+    if (!pca_shape_ok(N, D, p, dt) || sweeps != 0 || p > kEigMaxP) return 0;
+    const size_t at = eig_route_at(even_up(D), D);
+    return at ? (size_t)((char*)pca_carve(nullptr, D).Vt - (char*)nullptr) + at : 0;
+}
+
 cat_status cat_pca_project(const void* lq, int64_t N, int64_t D, int32_t p, cat_dtype dt, const float* mean,
                            const float* components, float* z, void* hip_stream) {
     return pca_project_ld(lq, N, D, p, dt, mean, components, z, p, (hipStream_t)hip_stream);

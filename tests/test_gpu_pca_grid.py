@@ -1,6 +1,6 @@
 """Tridiagonalisation in one launch whose workgroups pass their products on through memory: sizes on either side of its range and
 of its numbers of rows and columns per workgroup and thread, the one workgroup that does the work when a wait is given up,
-captured graphs, and calls on several streams at once.
+captured graphs, and calls on several streams at once.  Each says by which of the ways its columns went.
 
 Bounds: an eigenvalue is within a few D eps |C| (the covariance is summed in double); a row of the result satisfies
 C v = lambda v to the rounding of its float32 entries (6e-8 |C|) and the rows are at right angles to the same."""
@@ -20,6 +20,14 @@ def _rows(D, seed, N=None):
     return np.ascontiguousarray(x, dtype=np.float32)
 
 
+def _fit(t, p, **kw):
+    """cat_pca_fit with a workspace of its own; the way its columns went, and its outputs"""
+    N, D = t.shape
+    ws = torch.empty(binding.load_library().cat_pca_workspace_bytes(N, D, p, binding.CAT_F32), dtype=torch.uint8, device="cuda")
+    out = cat_pca_fit(t, p, workspace=ws, **kw)
+    return binding.debug_pca_route(ws, N, D, p), out
+
+
 def _check(x, mean, comps, evals):
     D, p = x.shape[1], len(comps)
     xd = x.astype(np.float64) - x.astype(np.float64).mean(0)
@@ -37,7 +45,9 @@ def _check(x, mean, comps, evals):
 @pytest.mark.parametrize("D", [63, 64, 65, 127, 128, 129, 255, 256, 257, 383, 511, 512, 513, 769, 1000, 1023, 1024, 1025])
 def test_sizes(D):
     x = _rows(D, D)
-    _check(x, *cat_pca_fit(torch.from_numpy(x).cuda(), min(D, 20)))
+    route, out = _fit(torch.from_numpy(x).cuda(), min(D, 20))
+    assert route == ("grid" if 64 <= D <= 1024 else "columns")
+    _check(x, *out)
 
 
 @pytest.mark.parametrize("N", [2, 15, 17, 63, 64, 65, 71, 72, 73, 129, 2049, 70001])
@@ -52,13 +62,14 @@ def test_rows_of_the_covariance(N, D):
 def test_a_wait_given_up(D):
     x = _rows(D, D + 1)
     t = torch.from_numpy(x).cuda()
-    want = cat_pca_fit(t, 16)
+    route, want = _fit(t, 16)
+    assert route == "grid"
     binding.debug_pca_patience(-1)
     try:
-        got = cat_pca_fit(t, 16)
-        torch.cuda.synchronize()
+        route, got = _fit(t, 16)
     finally:
         binding.debug_pca_patience(100000000)
+    assert route == "alone"
     _check(x, *got)
     # the covariance is summed with atomics, in another order from call to call
     assert (got[2] - want[2]).abs().max() <= 60 * D * np.finfo(np.float64).eps * want[2].max()
@@ -67,9 +78,8 @@ def test_a_wait_given_up(D):
 def test_values_that_are_no_numbers_end():
     x = _rows(130, 3)
     x[5, 7] = np.nan
-    _, comps, evals = cat_pca_fit(torch.from_numpy(x).cuda(), 4)
-    torch.cuda.synchronize()
-    assert comps.shape == (4, 130)
+    route, (_, comps, evals) = _fit(torch.from_numpy(x).cuda(), 4)
+    assert route == "grid" and comps.shape == (4, 130)  # (values that are none of a number are passed on like others)
 
 
 def test_a_constant_matrix():
@@ -97,6 +107,7 @@ def test_captures_into_a_hip_graph_and_replays():
         buf.copy_(torch.from_numpy(x))
         graph.replay()
         torch.cuda.synchronize()
+        assert binding.debug_pca_route(ws, N, D, p) == "grid"
         _check(x, *out)
 
 
@@ -114,5 +125,6 @@ def test_calls_on_several_streams_at_once():
             with torch.cuda.stream(s):
                 outs[i] = cat_pca_fit(ts[i], p, workspace=ws[i])
     torch.cuda.synchronize()
-    for x, o in zip(xs, outs):
+    for x, o, w in zip(xs, outs, ws):
+        assert binding.debug_pca_route(w, 600, D, p) == "grid"  # four times 128 workgroups were resident together, or in turn
         _check(x, *o)
