@@ -267,7 +267,9 @@ cat_status cat_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t *idx_ou
  * 2048.  sweeps = 0 (default): up to p = 256 by tridiagonalisation, multisection and
  * inverse iteration, beyond that by 12 sweeps of one-sided Jacobi rotations over all
  * pairs; sweeps in 1 .. 64: that number of Jacobi sweeps.  Both agree with LAPACK to
- * a few D times the rounding of a double.
+ * a few D times the rounding of a double.  For 64 <= D <= 1024 on a stream that may use all
+ * CUs of its device (128 or more) the tridiagonalisation is one launch whose workgroups wait
+ * for each other (CUs / 64 such calls fit on the device at once), otherwise a launch per column.
  *   mean         out, D float
  *   components   out, p x D float, row c = direction c
  *   eigenvalues  out, p doubles, nullable

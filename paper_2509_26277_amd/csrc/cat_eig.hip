@@ -161,8 +161,8 @@ __global__ __launch_bounds__(kEigT) void k_eig_step(double* __restrict__ W, doub
 // then.  The owner of the last row stays to the end and writes V, d, e, tau.
 //
 // The workgroups wait for each other, so all of them must be resident: at most 128 of at most 8 waves and 128 registers, two to
-// a CU, so that four calls at once still fit.  Should other work keep some of them out for longer than `patience` ticks of the
-// 100 MHz counter, the waiting ones raise *fail and leave, and k_eig_whole, which the matrix in memory was left unchanged
+// a CU, so that four calls at once still fit on 256 CUs (stream_holds_grid).  Should other work keep some of them out for longer
+// than `patience` ticks of the 100 MHz counter, the waiting ones raise *fail and leave, and k_eig_whole, which the matrix in memory was left unchanged
 // for, does the columns in one workgroup.  Every wait ends.
 constexpr int kGridMin = 64, kGridMax = 1024;
 // rows of V, from the last one up, whose entries before the diagonal carry the words, and how many entries of each
@@ -1033,8 +1033,11 @@ __global__ __launch_bounds__(kWave) void k_eig_back(const double* __restrict__ Z
 
 static std::atomic<int64_t> g_grid_patience{100000000};  // 1 s; cat_debug_pca_patience
 
-// 128 workgroups at two to a CU: with half a chip's worth of CUs there is room for two such calls at once
-static cat_status chip_holds_grid(bool* yes) {
+// Whether the workgroups of k_eig_grid will all be resident on this stream, once others have left: 128 of them at two to a CU
+// take 64 CUs, so CUs / 64 calls fit at once; from 128 CUs on.  A stream that may not use all CUs of its device has a launch per
+// column: which of the XCDs its CUs belong to, to each of which the dispatcher gives an eighth of the workgroups, is not known.
+// (A graph may be replayed on another stream than it was captured on; there the bounded wait has to do.)
+static cat_status stream_holds_grid(hipStream_t st, bool* yes) {
     static std::atomic<int> ncu[16];
     int dev = 0;
     CAT_HIP_TRY(hipGetDevice(&dev));
@@ -1044,6 +1047,13 @@ static cat_status chip_holds_grid(bool* yes) {
         if (dev < 16) ncu[dev].store(v);
     }
     *yes = v >= 128;
+    if (!*yes) return CAT_OK;
+    uint32_t mask[32] = {};  // (the handles of the default streams are no objects of their own: they have the device's mask)
+    const bool named = st != nullptr && st != hipStreamLegacy && st != hipStreamPerThread;
+    CAT_HIP_TRY(hipExtStreamGetCUMask(named ? st : nullptr, 32, mask));
+    int own = 0;
+    for (uint32_t word : mask) own += __builtin_popcount(word);
+    *yes = own >= v;
     return CAT_OK;
 }
 
@@ -1068,8 +1078,9 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
     double* lambda = tau + D;
     double* tnorm = pb[0];  // the products are no longer needed once the last column is done
     bool grid_fits = false;
-    if (cat_status s = chip_holds_grid(&grid_fits); s != CAT_OK) return s;
-    if (grid_fits && D >= kGridMin && D <= kGridMax) {
+    if (D >= kGridMin && D <= kGridMax)
+        if (cat_status s = stream_holds_grid(st, &grid_fits); s != CAT_OK) return s;
+    if (grid_fits) {
         const int32_t copies = grid_copies(D), low = D - grid_ring_rows(copies);
         if (cat_status s = launch_fill_zero(V + (int64_t)low * ld, (size_t)(D - low) * ld * 8, st); s != CAT_OK) return s;
         uint32_t* fail = (uint32_t*)(V + grid_fail_entry(ld, D));

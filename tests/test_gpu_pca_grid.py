@@ -4,6 +4,8 @@ captured graphs, and calls on several streams at once.  Each says by which of th
 
 Bounds: an eigenvalue is within a few D eps |C| (the covariance is summed in double); a row of the result satisfies
 C v = lambda v to the rounding of its float32 entries (6e-8 |C|) and the rows are at right angles to the same."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -128,3 +130,48 @@ def test_calls_on_several_streams_at_once():
     for x, o, w in zip(xs, outs, ws):
         assert binding.debug_pca_route(w, 600, D, p) == "grid"  # four times 128 workgroups were resident together, or in turn
         _check(x, *o)
+
+
+def _hip():
+    """the HIP runtime that torch and the library have loaded"""
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    return ctypes.CDLL(path)
+
+
+@pytest.mark.parametrize("cus", [64, 128, 224])  # (multiples of 32: as many of every shader engine of every XCD)
+def test_a_stream_with_some_of_the_cus_takes_a_launch_per_column(cus):
+    hip, total = _hip(), torch.cuda.get_device_properties(0).multi_processor_count
+    D, p = 200, 8
+    x = _rows(D, 31)
+    t = torch.from_numpy(x).cuda()
+    torch.cuda.synchronize()
+    handle = ctypes.c_void_p()
+    words = (ctypes.c_uint32 * ((total + 31) // 32))(*[0xFFFFFFFF if 32 * (i + 1) <= cus else (1 << max(cus - 32 * i, 0)) - 1
+                                                       for i in range((total + 31) // 32)])
+    if hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), len(words), words) != 0:
+        pytest.skip("no streams with a CU mask here")
+    try:
+        with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+            route, out = _fit(t, p)
+        torch.cuda.synchronize()
+    finally:
+        assert hip.hipStreamDestroy(handle) == 0
+    assert route == "columns"
+    _check(x, *out)
+    assert _fit(t, p)[0] == "grid"  # and the default stream as before
+
+
+def test_the_default_streams_take_the_grid():
+    x = _rows(100, 32)
+    t = torch.from_numpy(x).cuda()
+    mean, comps, evals = torch.empty(100, device="cuda"), torch.empty((5, 100), device="cuda"), torch.empty(5, dtype=torch.float64, device="cuda")
+    lib = binding.load_library()
+    for handle in (0, 1, 2):  # the null stream, hipStreamLegacy, hipStreamPerThread
+        ws = torch.zeros(lib.cat_pca_workspace_bytes(len(x), 100, 5, 0), dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        assert lib.cat_pca_fit(t.data_ptr(), len(x), 100, 5, 0, 0, mean.data_ptr(), comps.data_ptr(), evals.data_ptr(),
+                               ws.data_ptr(), ws.numel(), handle) == 0
+        torch.cuda.synchronize()
+        assert binding.debug_pca_route(ws, len(x), 100, 5) == "grid"
+        _check(x, mean, comps, evals)
