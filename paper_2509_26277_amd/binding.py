@@ -15,6 +15,7 @@ _lib = None
 
 CAT_F32, CAT_BF16 = 0, 1
 CAT_PATH_AUTO, CAT_PATH_STREAM, CAT_PATH_TILE = 0, 1, 2
+CAT_PCA_PATIENCE = 2000000
 _STATUS = {0: "CAT_OK", 1: "CAT_ERR_INVALID_ARG", 2: "CAT_ERR_UNSUPPORTED", 3: "CAT_ERR_WORKSPACE",
            4: "CAT_ERR_DEVICE"}
 

@@ -162,9 +162,13 @@ __global__ __launch_bounds__(kEigT) void k_eig_step(double* __restrict__ W, doub
 //
 // The workgroups wait for each other, so all of them must be resident: at most 128 of at most 8 waves and 128 registers, two to
 // a CU, so that four calls at once still fit on 256 CUs (stream_holds_grid).  Should other work keep some of them out for longer
-// than `patience` ticks of the 100 MHz counter, the waiting ones raise *fail and leave, and k_eig_whole, which the matrix in memory was left unchanged
-// for, does the columns in one workgroup.  Every wait ends.
+// than `patience` ticks of the 100 MHz counter, the waiting ones raise *fail and leave, and k_eig_whole, which the matrix in
+// memory was left unchanged for, does the columns in one workgroup.  Every wait ends.  The patience is 20 ms, 8000 steps: more
+// than this library's longest launches, and not much beside what giving up costs (a whole cat_pca_fit of 2000 rows, ms, the grid /
+// given up at once: D = 256: 0.6 / 3.2; 512: 1.3 / 19; 768: 2.3 / 69; 1000: 3.1 / 190; 1024: 3.1 / 200).  Time between two looks
+// at the counter counts as 1 ms at most: a wave that was taken off the chip meanwhile has not waited for the others.
 constexpr int kGridMin = 64, kGridMax = 1024;
+constexpr int64_t kGridGap = 100000;  // 1 ms; 64 looks take a tenth of that
 // rows of V, from the last one up, whose entries before the diagonal carry the words, and how many entries of each
 __host__ __device__ static inline int32_t grid_ring_rows(int32_t copies) { return 2 * (4 + 4 * copies); }
 __host__ __device__ static inline int32_t grid_ring_width(int32_t n, int32_t copies) { return n - grid_ring_rows(copies) - 4; }
@@ -398,7 +402,7 @@ __global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restric
             }
             return;
         }
-        int64_t since = 0;
+        int64_t seen = 0, waited = 0;
         for (uint32_t spins = 0;; spins++) {
             bool any = false;
 #pragma unroll
@@ -410,8 +414,9 @@ __global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restric
             if (patience >= 0 && !__any(any)) break;
             if (patience < 0 || (spins & 63u) == 63u) {
                 const int64_t now = (int64_t)wall_clock64();
-                if (since == 0) since = now;
-                if (now - since > patience || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
+                if (seen != 0) waited += now - seen < kGridGap ? now - seen : kGridGap;
+                seen = now;
+                if (waited > patience || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
                     if (lane == 0) {
                         __hip_atomic_store(fail, (uint32_t)CAT_PCA_ALONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         s_fail = 1;
@@ -1031,7 +1036,7 @@ __global__ __launch_bounds__(kWave) void k_eig_back(const double* __restrict__ Z
     if (lane == 0 && evals) evals[j] = lambda[j];
 }
 
-static std::atomic<int64_t> g_grid_patience{100000000};  // 1 s; cat_debug_pca_patience
+static std::atomic<int64_t> g_grid_patience{CAT_PCA_PATIENCE};  // cat_debug_pca_patience
 
 // Whether the workgroups of k_eig_grid will all be resident on this stream, once others have left: 128 of them at two to a CU
 // take 64 CUs, so CUs / 64 calls fit at once; from 128 CUs on.  A stream that may not use all CUs of its device has a launch per

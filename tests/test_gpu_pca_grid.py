@@ -4,7 +4,9 @@ captured graphs, and calls on several streams at once.  Each says by which of th
 
 Bounds: an eigenvalue is within a few D eps |C| (the covariance is summed in double); a row of the result satisfies
 C v = lambda v to the rounding of its float32 entries (6e-8 |C|) and the rows are at right angles to the same."""
+import contextlib
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -70,7 +72,7 @@ def test_a_wait_given_up(D):
     try:
         route, got = _fit(t, 16)
     finally:
-        binding.debug_pca_patience(100000000)
+        binding.debug_pca_patience(binding.CAT_PCA_PATIENCE)
     assert route == "alone"
     _check(x, *got)
     # the covariance is summed with atomics, in another order from call to call
@@ -139,27 +141,55 @@ def _hip():
     return ctypes.CDLL(path)
 
 
-@pytest.mark.parametrize("cus", [64, 128, 224])  # (multiples of 32: as many of every shader engine of every XCD)
-def test_a_stream_with_some_of_the_cus_takes_a_launch_per_column(cus):
-    hip, total = _hip(), torch.cuda.get_device_properties(0).multi_processor_count
-    D, p = 200, 8
-    x = _rows(D, 31)
-    t = torch.from_numpy(x).cuda()
-    torch.cuda.synchronize()
+@contextlib.contextmanager
+def _stream_with(cus):
+    """a stream with the first ``cus`` CUs (a multiple of 32: as many of every shader engine of every XCD)"""
+    hip, words = _hip(), torch.cuda.get_device_properties(0).multi_processor_count // 32
+    mask = (ctypes.c_uint32 * words)(*[0xFFFFFFFF if 32 * (i + 1) <= cus else 0 for i in range(words)])
     handle = ctypes.c_void_p()
-    words = (ctypes.c_uint32 * ((total + 31) // 32))(*[0xFFFFFFFF if 32 * (i + 1) <= cus else (1 << max(cus - 32 * i, 0)) - 1
-                                                       for i in range((total + 31) // 32)])
-    if hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), len(words), words) != 0:
+    torch.cuda.synchronize()
+    if hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), words, mask) != 0:
         pytest.skip("no streams with a CU mask here")
     try:
-        with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
-            route, out = _fit(t, p)
+        yield torch.cuda.ExternalStream(handle.value)
         torch.cuda.synchronize()
     finally:
         assert hip.hipStreamDestroy(handle) == 0
+
+
+@pytest.mark.parametrize("cus", [64, 128, 224])
+def test_a_stream_with_some_of_the_cus_takes_a_launch_per_column(cus):
+    x = _rows(200, 31)
+    t = torch.from_numpy(x).cuda()
+    with _stream_with(cus) as s, torch.cuda.stream(s):
+        route, out = _fit(t, 8)
     assert route == "columns"
     _check(x, *out)
-    assert _fit(t, p)[0] == "grid"  # and the default stream as before
+    assert _fit(t, 8)[0] == "grid"  # and the default stream as before
+
+
+def test_workgroups_that_cannot_all_be_resident_give_up_soon():
+    """a graph captured with the whole device and replayed where half of the workgroups have no place: they wait 20 ms, one
+    workgroup does the columns (some 6 ms at this size)"""
+    N, D, p = 600, 300, 8
+    x = _rows(D, 33, N)
+    t = torch.from_numpy(x).cuda()
+    ws = torch.empty(binding.load_library().cat_pca_workspace_bytes(N, D, p, binding.CAT_F32), dtype=torch.uint8, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = cat_pca_fit(t, p, workspace=ws)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert binding.debug_pca_route(ws, N, D, p) == "grid"
+    with _stream_with(32) as s:
+        with torch.cuda.stream(s):
+            start = time.perf_counter()
+            graph.replay()
+            torch.cuda.synchronize()
+            took = time.perf_counter() - start
+    assert binding.debug_pca_route(ws, N, D, p) == "alone"
+    assert 0.02 <= took < 0.3
+    _check(x, *out)
 
 
 def test_the_default_streams_take_the_grid():
