@@ -58,6 +58,14 @@ def test_against_direct_form_doubles(N, D, K, dtype):
         assert torch.equal(out[same], want[same])  # one fused multiply-add per entry on the same folded parameters
 
 
+@pytest.mark.parametrize("N,D,K", [(600, 37, 300), (513, 36, 512), (1100, 36, 513), (1100, 36, 1024)])
+def test_more_clusters_than_the_automatic_selection_sends_it(N, D, K):
+    """the sums of all clusters of a workgroup's rows lie in LDS: fewer rows per workgroup where they would not fit"""
+    x, cent, g, b = _case(N, D, K, torch.float32)
+    out, a, want, wa = _both(x, cent, g, b, 0.6)
+    assert torch.equal(a, wa) and torch.equal(out, want)  # (separated by far more than any rounding)
+
+
 def test_exact_ties_go_to_the_lowest_index():
     cent = torch.randint(-3, 4, (40, 36), device="cuda").float()
     cent[25:] = cent[:15]
