@@ -87,3 +87,21 @@ def full_loop():
         yield
     finally:
         binding.debug_full_loop(False)
+
+
+def without_few_rows_kernel(call, kernels=(2, 3, 1)):
+    """``call()`` with the first of the given inference kernels that has an instance for its shape (cat_debug_apply_kernel; by
+    default the row-tile kernel, the one that streams the centroids, the tile kernel or what takes its place): what a call of so
+    few rows that cat_apply takes its kernel for few rows would not reach.  Returns the kernel and the result."""
+    from paper_2509_26277_amd import binding
+    try:
+        for which in kernels:
+            binding.debug_apply_kernel(which)
+            try:
+                return which, call()
+            except binding.CatError as e:
+                if e.status != 2:
+                    raise
+    finally:
+        binding.debug_apply_kernel(0)
+    raise AssertionError("none of the kernels has an instance")

@@ -97,12 +97,23 @@ def test_overflow_and_no_numbers(D):
 
 def test_default_selection_takes_it_without_a_workspace_and_under_capture():
     x, cent, g, b = _case(300, 1000, 50, torch.float32)
+    binding.select_path(binding.CAT_PATH_STREAM)
     want, wa = cat_apply(x, cent, g, b, alpha=0.6)
+    binding.select_path(binding.CAT_PATH_AUTO)
     out = torch.empty_like(x)
     a = torch.empty(300, dtype=torch.int32, device="cuda")
     cat_apply_static(x, cent, g, b, alpha=0.6, out=out, assignments=a)
     assert torch.equal(out, want) and torch.equal(a, wa)
-    ws = torch.empty(binding.cat_apply_workspace_bytes(300, 1000, 50), dtype=torch.uint8, device="cuda")
+    # the only kernel that leaves the workspace alone: the others fold the coefficient into parameters of their own there
+    ws = torch.full((binding.cat_apply_workspace_bytes(300, 1000, 50),), 0xA5, dtype=torch.uint8, device="cuda")
+    out, a = cat_apply(x, cent, g, b, alpha=0.6, workspace=ws)
+    assert torch.equal(out, want) and torch.equal(a, wa) and bool((ws == 0xA5).all())
+    for which in (1, 2, 3):
+        binding.debug_apply_kernel(which)
+        cat_apply(x, cent, g, b, alpha=0.6, workspace=ws)
+        assert not bool((ws == 0xA5).all())
+        ws.fill_(0xA5)
+    binding.debug_apply_kernel(0)
     s = torch.cuda.Stream()
     s.wait_stream(torch.cuda.current_stream())
     graph = torch.cuda.CUDAGraph()
@@ -112,9 +123,11 @@ def test_default_selection_takes_it_without_a_workspace_and_under_capture():
         x2, _, _, _ = _case(300, 1000, 50, torch.float32, spread=1.0 + seed)
         x.copy_(x2)
         graph.replay()
+        binding.select_path(binding.CAT_PATH_STREAM)
         want, wa = cat_apply(x, cent, g, b, alpha=0.6)
+        binding.select_path(binding.CAT_PATH_AUTO)
         torch.cuda.synchronize()
-        assert torch.equal(go, want) and torch.equal(ga, wa)
+        assert torch.equal(go, want) and torch.equal(ga, wa) and bool((ws == 0xA5).all())
 
 
 def test_a_shape_it_does_not_take_is_an_error():

@@ -54,6 +54,7 @@ def test_rounding_is_the_oracles_bit_for_bit():
     (3000, 64, 6, 1.0, True),
     (3000, 64, 6, 0.6, True),
     (2500, 256, 30, 0.6, False),     # stored parameters, fp32 rows out
+    (700, 256, 30, 0.6, False),      # few rows: the kernel without a preparation
     (4099, 512, 100, 1.0, True),     # one-part operand instance, rows not a multiple of the tile
     (1777, 1000, 16, 0.25, True),    # ragged last vector of a row
     (1500, 37, 4, 0.6, True),        # no instance of the fused kernel: assign first, map by the labels

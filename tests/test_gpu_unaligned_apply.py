@@ -135,12 +135,13 @@ def test_shapes_without_an_instance_still_take_the_streaming_kernel():
         with pytest.raises(binding.CatError):
             binding.debug_apply_kernel(2)
             cat_apply(dev_matrix(x, dt), f(cent), f(gamma), f(beta))
-        binding.debug_apply_kernel(0)
-        out, a = cat_apply(dev_matrix(x, dt), f(cent), f(gamma), f(beta))
         o_out, o_a = oracle.apply(x, cent, gamma, beta, 1.0)
-        a = a.cpu().numpy()
-        check_assignments_lazy(a, o_a, x, cent.astype(np.float64), "streaming kernel")
-        check_values(host_matrix(out)[a == o_a], o_out[a == o_a], RTOL[dt], "corrected")
+        for which in (1, 0):  # the streaming kernel, and as it comes (few rows: a kernel of their own)
+            binding.debug_apply_kernel(which)
+            out, a = cat_apply(dev_matrix(x, dt), f(cent), f(gamma), f(beta))
+            a = a.cpu().numpy()
+            check_assignments_lazy(a, o_a, x, cent.astype(np.float64), "streaming kernel")
+            check_values(host_matrix(out)[a == o_a], o_out[a == o_a], RTOL[dt], "corrected")
 
 
 @pytest.mark.parametrize("N,D,K,dt", [(3000, 1001, 16, "f32"), (4099, 37, 9, "f32"), (800, 255, 128, "f32"), (2100, 1002, 16, "bf16"),

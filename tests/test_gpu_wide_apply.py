@@ -1,10 +1,13 @@
 """Inference with the streamed centroid operand (cat_wide_kernel.h): edges of its instances (steps per wave, cluster tiles,
 rows per tile), rows that are not whole 16-byte groups, near-ties and exact ties, against double-precision torch.  The shapes
-that it has an instance for are run on it whatever cat_apply would choose; the others of each table run as they come."""
+that it has an instance for are run on it whatever cat_apply would choose; the others of each table run as they come, and where
+that is the kernel for few rows, on the one that more rows would take too."""
 import pytest
 import torch
 
 from paper_2509_26277_amd import binding, cat_apply
+
+from parity_util import without_few_rows_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -36,7 +39,17 @@ def _automatic_after():
 def _check(x, cent, g, b, alpha, bf16):
     if _has_instance(x.shape[1], cent.shape[0], bf16):
         binding.debug_apply_kernel(3)
+    else:
+        out, a = without_few_rows_kernel(lambda: cat_apply(x, cent, g, b, alpha=alpha), (2, 1))[1]
+        _check_one(x, cent, g, b, alpha, bf16, out, a)
     out, a = cat_apply(x, cent, g, b, alpha=alpha)
+    a = _check_one(x, cent, g, b, alpha, bf16, out, a)
+    out2, none = cat_apply(x, cent, g, b, alpha=alpha, want_assignments=False)
+    assert none is None and torch.equal(out, out2)
+    return a
+
+
+def _check_one(x, cent, g, b, alpha, bf16, out, a):
     want, d, corr = _exact(x, cent, g, b, alpha)
     a = a.long()
     bad = (a != want).nonzero().flatten()
@@ -48,8 +61,6 @@ def _check(x, cent, g, b, alpha, bf16):
     # one fused multiply-add in float32 with parameters folded in float32; bf16 rows are rounded to bf16 once more
     tol = (2.0 ** -8 if bf16 else 4e-7) * corr.abs()[ok] + 2e-6
     assert (err <= tol).all(), float((err - tol).max())
-    out2, none = cat_apply(x, cent, g, b, alpha=alpha, want_assignments=False)
-    assert none is None and torch.equal(out, out2)
     return a
 
 

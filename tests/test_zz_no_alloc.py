@@ -1,4 +1,5 @@
-"""cat_apply_static (the entry point that allocates nothing) against cat_apply, through the C ABI."""
+"""cat_apply_static (the entry point that allocates nothing) against cat_apply, through the C ABI: as the calls come, and on the
+kernels that use the built-in scratch array where the one for few rows, which needs none, would be taken."""
 import numpy as np
 import pytest
 import torch
@@ -6,6 +7,12 @@ import torch
 from paper_2509_26277_amd import binding, cat_apply, cat_apply_static, workloads
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _automatic_after():
+    yield
+    binding.debug_apply_kernel(0)
 
 
 def _params(K, D, seed):
@@ -26,12 +33,14 @@ def _rows(N, cent, seed, dtype):
     return torch.from_numpy(x).cuda()
 
 
+@pytest.mark.parametrize("kernel", [0, 2])  # automatic; the row-tile kernel, which prepares its operand in the array
 @pytest.mark.parametrize("dtype,D,K", [("f32", 512, 128), ("f32", 1000, 16), ("bf16", 256, 48), ("f32", 37, 5),
                                         ("f32", 1001, 16), ("bf16", 1002, 16)])
-def test_two_calls_in_a_row_match_cat_apply(dtype, D, K):
+def test_two_calls_in_a_row_match_cat_apply(dtype, D, K, kernel):
     """Two calls in a row on the one built-in scratch array, the second on a smaller input with other parameters
     (fewer rows, fewer clusters): each must equal cat_apply with a caller workspace bit for bit."""
     torch.cuda.set_device(0)
+    binding.debug_apply_kernel(kernel)
     shapes = [(6000 + 37, K, 1.0), (1000 + 5, max(1, K // 2), 0.6)]
     for call, (N, k, alpha) in enumerate(shapes):
         cent, gamma, beta = _params(k, D, 100 + call)
@@ -81,8 +90,10 @@ def test_sizes_beyond_the_array_are_refused():
     cent, gamma, beta = _params(k_ok, D, 9)
     c, g, b = (torch.from_numpy(a).cuda() for a in (cent, gamma, beta))
     lq = _rows(N, cent, 10, "f32")
-    want, want_a = cat_apply(lq, c, g, b)
-    a = torch.empty((N,), dtype=torch.int32, device="cuda")
-    got, got_a = cat_apply_static(lq, c, g, b, assignments=a)
-    torch.cuda.synchronize()
-    assert torch.equal(got_a, want_a) and torch.equal(got, want)
+    for kernel in (0, 1):  # (as it comes: few rows; the tile kernel, whose operand nearly fills the array)
+        binding.debug_apply_kernel(kernel)
+        want, want_a = cat_apply(lq, c, g, b)
+        a = torch.empty((N,), dtype=torch.int32, device="cuda")
+        got, got_a = cat_apply_static(lq, c, g, b, assignments=a)
+        torch.cuda.synchronize()
+        assert torch.equal(got_a, want_a) and torch.equal(got, want)
