@@ -271,7 +271,7 @@ cat_status cat_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t *idx_ou
  * CUs of its device (128 or more) the tridiagonalisation is one launch whose workgroups wait
  * for each other (CUs / 64 such calls fit on the device at once), otherwise a launch per column.  Should
  * more such calls, of other processes for instance, keep each other's workgroups off the
- * chip for 20 ms, one workgroup does the columns: 0.2 s at D = 1000.
+ * chip for 20 .. 40 ms, one workgroup does the columns: 0.2 s at D = 1000.
  *   mean         out, D float
  *   components   out, p x D float, row c = direction c
  *   eigenvalues  out, p doubles, nullable
@@ -539,12 +539,12 @@ cat_status cat_debug_apply_kernel(int which);
 cat_status cat_debug_full_loop(int on);
 
 /*
- * Test hook.  The PCA's tridiagonalisation runs in workgroups that wait for each other, no longer than this many ticks of
- * the GPU's 100 MHz counter; when one has waited longer (negative: at its first wait) a single workgroup does the work.
- * Process-wide, default CAT_PCA_PATIENCE; returns CAT_OK.
+ * Test hook.  The PCA's tridiagonalisation runs in workgroups that wait for each other, no longer than this many looks
+ * at the words they pass on, 0.2 .. 0.4 us each; when one has waited longer (negative: at its first wait) a single
+ * workgroup does the work.  Process-wide, default CAT_PCA_PATIENCE; returns CAT_OK.
  */
-#define CAT_PCA_PATIENCE 2000000 /* 20 ms */
-cat_status cat_debug_pca_patience(int64_t ticks);
+#define CAT_PCA_PATIENCE 100000 /* 20 .. 40 ms */
+cat_status cat_debug_pca_patience(int64_t looks);
 
 /*
  * Test hook.  Where in the workspace of cat_pca_fit (bytes from its start) a 32-bit word says, once the call is through, how its

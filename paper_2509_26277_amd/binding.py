@@ -15,7 +15,7 @@ _lib = None
 
 CAT_F32, CAT_BF16 = 0, 1
 CAT_PATH_AUTO, CAT_PATH_STREAM, CAT_PATH_TILE = 0, 1, 2
-CAT_PCA_PATIENCE = 2000000
+CAT_PCA_PATIENCE = 100000
 _STATUS = {0: "CAT_OK", 1: "CAT_ERR_INVALID_ARG", 2: "CAT_ERR_UNSUPPORTED", 3: "CAT_ERR_WORKSPACE",
            4: "CAT_ERR_DEVICE"}
 
@@ -510,9 +510,9 @@ def debug_full_loop(on):
     _check(load_library().cat_debug_full_loop(int(bool(on))))
 
 
-def debug_pca_patience(ticks):
-    """Test hook: how long (ticks of 10 ns; negative: not at all) the workgroups of the tridiagonalisation wait for each other."""
-    _check(load_library().cat_debug_pca_patience(int(ticks)))
+def debug_pca_patience(looks):
+    """Test hook: how long (looks of 0.2 .. 0.4 us; negative: not at all) the workgroups of the tridiagonalisation wait for each other."""
+    _check(load_library().cat_debug_pca_patience(int(looks)))
 
 
 def debug_pca_route(workspace, N, D, p, dt=CAT_F32, sweeps=0):

