@@ -3,7 +3,7 @@ which pivots vanish, couplings are zero, vectors decay past the range of a doubl
 gap below which the pivoted elimination takes over.
 
 Bounds: an eigenvalue is within a few D eps |C| (the covariance is summed in double); a row of the result satisfies
-C v = lambda v to the rounding of its float32 entries (6e-8 |C|) and the rows are at right angles to the same."""
+C v = lambda v to the rounding of its float32 entries (6e-8 |C|) and the rows are at right angles to the same: two of unit length whose entries are each off by 2^-24 of themselves, to 1.2e-7."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +20,7 @@ def _rows(C):
     return np.ascontiguousarray(np.concatenate([r, -r]), dtype=np.float32)
 
 
-def _check(x, p):
+def _check(x, p, right=1e-6):
     D = x.shape[1]
     mean, comps, evals = cat_pca_fit(torch.from_numpy(x).cuda(), p)
     xd = x.astype(np.float64) - x.astype(np.float64).mean(0)
@@ -31,11 +31,11 @@ def _check(x, p):
     slack = 30 * D * np.finfo(np.float64).eps * norm
     assert np.isfinite(v).all()
     assert np.abs(lam - w[:p]).max() <= slack
-    assert np.abs(v @ v.T - np.eye(p)).max() <= 1e-6
+    assert np.abs(v @ v.T - np.eye(p)).max() <= right
     assert np.linalg.norm(v @ C - lam[:, None] * v, axis=1).max() <= 3e-7 * norm + slack
 
 
-@pytest.mark.parametrize("gap", [1e-3, 1e-7, 1e-9, 1e-11, 1e-14, 0.0])
+@pytest.mark.parametrize("gap", [1e-3, 1e-4, 1e-5, 3e-6, 1.2e-6, 1e-7, 1e-9, 1e-11, 1e-14, 0.0])
 def test_pairs_of_close_eigenvalues(gap):
     """rows +-s_j h_j and +-t_j h_j on the columns of a Hadamard matrix, which float32 holds exactly: eigenvalues in pairs whose
     members differ by t^2 alone"""
@@ -45,7 +45,19 @@ def test_pairs_of_close_eigenvalues(gap):
     s = np.repeat(np.linspace(3.0, 1.0, 64), 2).astype(np.float32)
     t = s * np.sqrt(gap) * (np.arange(128) % 2)
     x = np.concatenate([s[:, None] * h, -s[:, None] * h, t[:, None] * h, -t[:, None] * h])
-    _check(np.ascontiguousarray(x, dtype=np.float32), 40)
+    _check(np.ascontiguousarray(x, dtype=np.float32), 40, 2e-7)
+
+
+@pytest.mark.parametrize("step", [2e-5, 5e-6, 2e-6, 5e-7])
+def test_a_run_of_eigenvalues_a_step_apart(step):
+    """every gap among the first vectors near the one (1e-6) below which they are made orthogonal, on either side: rows +-s_j h_j on
+    the columns of a Hadamard matrix, eigenvalues s_j^2"""
+    h = np.ones((1, 1))
+    while len(h) < 256:
+        h = np.block([[h, h], [h, -h]])
+    s = np.float32(1.0) + np.arange(256, dtype=np.float32) * np.float32(step)
+    x = s[:, None] * h
+    _check(np.ascontiguousarray(np.concatenate([x, -x]), dtype=np.float32), 60, 2e-7)
 
 
 @pytest.mark.parametrize("D", [7, 8, 9, 16, 17, 64, 127, 129, 1000])
