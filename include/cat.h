@@ -265,7 +265,7 @@ cat_status cat_init_indices(int64_t N, int32_t K, uint64_t seed, int64_t *idx_ou
  * directions of largest eigenvalue in descending order, each a unit vector whose
  * entry of largest magnitude (the first such entry) is positive.  1 <= p <= D <=
  * 2048.  sweeps = 0 (default): up to p = 256 by tridiagonalisation, multisection and
- * inverse iteration, beyond that by 12 sweeps of one-sided Jacobi rotations over all
+ * two-sided factorisation (inverse iteration where eigenvalues all but coincide), beyond that by 12 sweeps of one-sided Jacobi rotations over all
  * pairs; sweeps in 1 .. 64: that number of Jacobi sweeps.  Both agree with LAPACK to
  * a few D times the rounding of a double.  For 64 <= D <= 1024 on a stream that may use all
  * CUs of its device (128 or more) the tridiagonalisation is one launch whose workgroups wait

@@ -240,7 +240,12 @@ __global__ __launch_bounds__(kDirT) void k_apply_direct(const DirectParams p) {
 //   520 x 301, K = 256: 19.1 / 19.6 and 520 x 102, K = 256: 18.0 / 18.4 (element loads);
 //   shapes neither has an instance for (rows of more than 4 KB above all): 4096 x 1500, K = 5: 49 / 34 (8192 rows: 59 / 65), 4096 x
 //   1500, K = 100: 115 / 71, 4096 x 2048, K = 16: 77 / 44; not whole groups of 4, the LDS kernel: 1024 x 1101, K = 60: 396 / 14,
-//   16384 x 1101, K = 5: 221 / 168 (32768 rows: 226 / 345), 16384 x 1501, K = 30: 400 / 206, 4096 x 2046 bf16, K = 130: 1950 / 138.
+//   16384 x 1101, K = 5: 221 / 168 (32768 rows: 226 / 345), 16384 x 1501, K = 30: 400 / 206, 4096 x 2046 bf16, K = 130: 1950 / 138;
+//   more than 128 clusters on fp32 rows of 769 .. 1024 channels, where the others rank in two launches or on the LDS kernel: 1024 x
+//   900, K = 256: 102 / 30; 1024 x 1000, K = 129: 100 / 18; 512 x 1001, K = 256: 1352 / 25; longer rows of as many: 1024 x 2048: K =
+//   129: 191 / 27, 256: 200 / 44; 1024 x 4096, K = 129: 364 / 51; 1024 x 3002, K = 256: 3931 / 83; the longest rows: 4096 x 4096, K =
+//   5: 153 / 78; 4096 x 8192, K = 5: 296 / 144; 1024 x 8192, K = 50: 371 / 51; 16384 x 3002, K = 5: 614 / 372.  (2218 shapes of 1 ..
+//   16384 rows, 4 .. 8192 channels and 1 .. 256 clusters: none that comes here takes longer than on the others, to 5 %.)
 bool direct_apply_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     if (D > 8192 || K > 256) return false;
     const double work = (double)N * (double)D * (double)K;

@@ -187,8 +187,7 @@ __device__ __forceinline__ void pass_half(u64* at, double v, int half, uint32_t 
 __device__ __forceinline__ u64 peek(const u64* at) { return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ double passed(u64 a, u64 b) { return __longlong_as_double((long long)((b & 0xFFFFFFFF00000000ull) | (a >> 32))); }
 
-// sums of R values over the wave: halves of the lanes take halves of the values while there are several (lane bits 0, 1, ...),
-// full sums over what is left of the wave afterwards.  The lane's value: number `lane & (R - 1)`, bit-reversed (wave_sum_slot).
+// the value that the lane permutation brings (the whole double)
 template <int CTRL>
 __device__ __forceinline__ double dpp_get(double v) {
     const long long b = __double_as_longlong(v);
@@ -513,7 +512,8 @@ __global__ __launch_bounds__(kWholeT) void k_eig_whole(double* W, double* __rest
 // out: lambda[j]; tnorm[0] = a bound of |T| (workgroup 0).
 constexpr int kBisT = 256;
 constexpr int kBisU = 8;  // terms between two rescalings
-static inline int32_t bisect_terms(int32_t n) { return (n + kBisU - 1) / kBisU * kBisU + kBisU; }
+// terms of a chain as its loop reads them: whole groups, and one requested ahead of the last
+__host__ __device__ static inline int32_t minor_terms(int32_t n) { return (n + kBisU - 1) / kBisU * kBisU + kBisU; }
 __global__ __launch_bounds__(kBisT) void k_eig_bisect(const double* __restrict__ d, const double* __restrict__ e, int32_t n,
                                                       double* __restrict__ lambda, double* __restrict__ tnorm) {
     extern __shared__ double2 s_t[];  // diagonal entry, squared off-diagonal one (entry i couples i - 1 and i); whole groups + 1
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(kBisT) void k_eig_bisect(const double* __restrict__
     const double norm = fmax(fabs(lo), fabs(hi));
     if (blockIdx.x == 0 && threadIdx.x == 0) tnorm[0] = norm;
     const int up = norm > 1e-307 && norm < 1e300 ? -ilogb(norm) : 0;  // (a norm of zero, or none at all: as it is)
-    for (int i = threadIdx.x; i < (n + kBisU - 1) / kBisU * kBisU + kBisU; i += kBisT) {  // bisect_terms
+    for (int i = threadIdx.x; i < minor_terms(n); i += kBisT) {
         const double di = i < n ? ldexp(d[i], up) : 8.0;  // past the end: no change of sign
         const double el = i > 0 && i < n ? ldexp(e[i - 1], up) : 0.0;
         s_t[i] = make_double2(di, el * el);
@@ -624,10 +624,9 @@ constexpr double kInvGap = 1e-10;
 __device__ void eig_invit_lu(double* s_lu, const double* __restrict__ d, const double* __restrict__ e, int32_t n, double lam,
                              double norm, int j, double* __restrict__ Z, int64_t ld);
 // bytes: two directions of (diagonal entry, squared coupling), of minors and the minor before each group; two multipliers
-__host__ __device__ static inline int32_t twist_terms(int32_t n) { return (n + kBisU - 1) / kBisU * kBisU + kBisU; }
 __host__ __device__ static inline int32_t twist_at(int32_t i) { return i + (i >> 4); }  // (lanes walk 16 entries apart and more)
 static inline size_t twist_lds_bytes(int32_t n) {
-    return (size_t)twist_terms(n) * 32 + (size_t)twist_terms(n) * 16 + (size_t)twist_terms(n) / kBisU * 16 + (size_t)(twist_at(n) + 1) * 16;
+    return (size_t)minor_terms(n) * 32 + (size_t)minor_terms(n) * 16 + (size_t)minor_terms(n) / kBisU * 16 + (size_t)(twist_at(n) + 1) * 16;
 }
 __global__ __launch_bounds__(kWave) void k_eig_invit(const double* __restrict__ d, const double* __restrict__ e, int32_t n, int32_t p,
                                                      const double* __restrict__ lambda, const double* __restrict__ tnorm,
@@ -638,7 +637,7 @@ __global__ __launch_bounds__(kWave) void k_eig_invit(const double* __restrict__ 
     const double gap = fmin(j > 0 ? lambda[j - 1] - lam : norm, j + 1 < p ? lam - lambda[j + 1] : norm);
     bool done = false;  // uniform
     if (gap > kInvGap * norm && norm > 1e-280 && norm < 1e280) {
-        const int terms = twist_terms(n);
+        const int terms = minor_terms(n);
         double2* T = s_iv;                          // [direction][term]
         double* P = (double*)(T + 2 * terms);       // [direction][term]: minors
         double* B = P + 2 * terms;                  // [direction][group]: the minor before the group, as scaled there
@@ -1112,7 +1111,7 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
             CAT_LAUNCH_CHECK("k_eig_step");
         }
     }
-    hipLaunchKernelGGL(k_eig_bisect, dim3((unsigned)p), dim3(kBisT), (size_t)bisect_terms(D) * 16, st, d, e, D, lambda, tnorm);
+    hipLaunchKernelGGL(k_eig_bisect, dim3((unsigned)p), dim3(kBisT), (size_t)minor_terms(D) * 16, st, d, e, D, lambda, tnorm);
     CAT_LAUNCH_CHECK("k_eig_bisect");
     const size_t lds = invit_lds_bytes(D) > twist_lds_bytes(D) ? invit_lds_bytes(D) : twist_lds_bytes(D);  // 139 KB at D = 2048
     if (lds > 64 * 1024)
