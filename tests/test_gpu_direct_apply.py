@@ -77,6 +77,22 @@ def test_exact_ties_go_to_the_lowest_index():
     assert torch.equal(a.long(), torch.stack([(r == r.min()).nonzero()[0, 0] for r in d]))
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("D", [2, 64, 66, 510, 512, 514, 1024, 1030, 2060])
+def test_near_ties_are_decided_in_doubles(D, dtype):
+    """clusters a rounding error apart, around a round of channels of the exact distance"""
+    K, N = 24, 300
+    x, cent, g, b = _case(N, D, K, dtype)
+    cent = (cent[:1] * (1 + 1e-6 * torch.randn(K, D, device="cuda"))).contiguous()
+    x = (cent[:1] + torch.randn(N, D, device="cuda")).to(dtype).contiguous()
+    out, a, want, wa = _both(x, cent, g, b, 0.6)
+    d = ((x.double()[:, None] - cent.double()[None]) ** 2).sum(2)
+    best, got = d.min(1).values, d.gather(1, a.long()[:, None])[:, 0]
+    assert (got - best <= 2.0 ** -52 * D * best).all()  # the order of the sums of doubles, no more
+    same = a == wa
+    assert same.float().mean() > 0.9 and torch.equal(out[same], want[same])
+
+
 @pytest.mark.parametrize("D", [36, 37])
 def test_overflow_and_no_numbers(D):
     x, cent, g, b = _case(70, D, 11, torch.float32)
