@@ -252,21 +252,31 @@ __global__ __launch_bounds__(kDirT) void k_apply_direct(const DirectParams p) {
 //   9.8 / 9.7, 1024 rows 10.0 / 11.0; 1024 x 512, K = 60: 10.3 / 7.6; 1024 x 1000, K = 16: 11.3 / 8.9; 1024 x 64, K = 100: 8.3 / 9.3;
 //   its one-part instance and the streamed-operand kernel: 256 x 1000, K = 50: 13.9 / 5.9, 1024 rows 14.3 / 9.5; 1024 x 2048 bf16,
 //   K = 64: 26.8 / 13.9; 1024 x 768, K = 256: 25.7 / 22.9; 1024 x 1200 bf16, K = 200: 38.9 / 30.0; 256 x 1001, K = 50: 22.0 / 6.6; but
-//   520 x 301, K = 256: 19.1 / 19.6 and 520 x 102, K = 256: 18.0 / 18.4 (element loads);
+//   520 x 301, K = 256: 19.1 / 19.6 and 520 x 102, K = 256: 18.0 / 18.4 (element loads), and with four rows to a workgroup, many
+//   clusters and a step of 256 channels that is partly empty, against the streamed operand on rows of 1 .. 2 KB: 1024 x 300: K =
+//   160: 18.4 / 16.1, K = 200: 18.5 / 19.9, K = 256: 18.0 / 20.9, 520 rows 18.0 / 19.9, 512 rows 18.1 / 17.2; 1024 x 512, K = 200: 19.4 /
+//   18.3; bf16: 1024 x 640: K = 200: 24.2 / 25.0, K = 256: 24.0 / 25.8; 1024 x 768, K = 200: 25.4 / 23.7; 768 x 1000, K = 256: 26.0 / 27.4.  The
+//   one-part instance for 65 .. 128 clusters varies with the data, since it measures again what lies within 1.6 %: 1024 x 384, K =
+//   128: well separated rows 10.0 / 12.3, a feature map's 11.4 / 12.4, an even mixture's 11.6 / 12.4, a skewed one's 30.2 / 12.4;
+//   the 2 us are given for the 18;
 //   shapes neither has an instance for (rows of more than 4 KB above all): 4096 x 1500, K = 5: 49 / 34 (8192 rows: 59 / 65), 4096 x
 //   1500, K = 100: 115 / 71, 4096 x 2048, K = 16: 77 / 44; not whole groups of 4, the LDS kernel: 1024 x 1101, K = 60: 396 / 14,
 //   16384 x 1101, K = 5: 221 / 168 (32768 rows: 226 / 345), 16384 x 1501, K = 30: 400 / 206, 4096 x 2046 bf16, K = 130: 1950 / 138;
 //   more than 128 clusters on fp32 rows of 769 .. 1024 channels, where the others rank in two launches or on the LDS kernel: 1024 x
 //   900, K = 256: 102 / 30; 1024 x 1000, K = 129: 100 / 18; 512 x 1001, K = 256: 1352 / 25; longer rows of as many: 1024 x 2048: K =
 //   129: 191 / 27, 256: 200 / 44; 1024 x 4096, K = 129: 364 / 51; 1024 x 3002, K = 256: 3931 / 83; the longest rows: 4096 x 4096, K =
-//   5: 153 / 78; 4096 x 8192, K = 5: 296 / 144; 1024 x 8192, K = 50: 371 / 51; 16384 x 3002, K = 5: 614 / 372.  (2218 shapes of 1 ..
-//   16384 rows, 4 .. 8192 channels and 1 .. 256 clusters: none that comes here takes longer than on the others, to 5 %.)
+//   5: 153 / 78; 4096 x 8192, K = 5: 296 / 144; 1024 x 8192, K = 50: 371 / 51; 16384 x 3002, K = 5: 614 / 372.  (3400 shapes of 1 ..
+//   16384 rows, 4 .. 8192 channels and 1 .. 256 clusters: but for that instance none that comes here takes longer, to 4 %.)
 bool direct_apply_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     if (D > 8192 || K > 256) return false;
     const double work = (double)N * (double)D * (double)K;
     const bool rowtile = infer_supported(N, D, K, dt);
     if (rowtile && infer_two_parts(D, K, dt)) return N <= 256 || (N <= 1024 && K <= 64 && work <= 32e6);
-    if (rowtile || wide_supported(N, D, K, dt)) return N <= (D % 4 != 0 && K > 128 ? 512 : 1024) && work <= 256e6;
+    if (rowtile || wide_supported(N, D, K, dt)) {
+        const int64_t kb = D * (dt == CAT_BF16 ? 2 : 4) / 1024;
+        const bool partly = K > 180 && D % 256 != 0 && kb == 1;
+        return N <= ((K > 128 && D % 4 != 0) || partly ? 512 : 1024) && work <= 256e6;
+    }
     if (D <= 1024) return N <= 1024 && work <= 256e6;
     return D % 4 == 0 ? N <= 4096 && work <= 640e6 : N <= 16384 && work <= 1.1e9;
 }
