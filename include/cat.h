@@ -92,7 +92,8 @@ cat_status cat_select_path(cat_path p);
  * fits of fewer than two iterations) run the fused row-tile inference kernel in a form
  * that moves rows, parameters and outputs in 4-byte words (K <= 128; rows of at most
  * 4 KB for fp32, 2 KB for bf16; for 33 .. 64 clusters at most 2 KB), and the LDS
- * streaming kernel beyond that. */
+ * streaming kernel beyond that; inference on few rows has a kernel of its own, whatever
+ * the row length. */
 size_t cat_fit_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt);
 cat_status cat_debug_padded_fit(int on);
 size_t cat_apply_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt);
