@@ -1052,7 +1052,11 @@ static cat_status stream_holds_grid(hipStream_t st, bool* yes) {
     if (!*yes) return CAT_OK;
     uint32_t mask[32] = {};  // (the handles of the default streams are no objects of their own: they have the device's mask)
     const bool named = st != nullptr && st != hipStreamLegacy && st != hipStreamPerThread;
-    CAT_HIP_TRY(hipExtStreamGetCUMask(named ? st : nullptr, 32, mask));
+    if (hipExtStreamGetCUMask(named ? st : nullptr, 32, mask) != hipSuccess) {  // not known: a launch per column will do
+        (void)hipGetLastError();
+        *yes = false;
+        return CAT_OK;
+    }
     int own = 0;
     for (uint32_t word : mask) own += __builtin_popcount(word);
     *yes = own >= v;
