@@ -540,6 +540,14 @@ cat_status cat_debug_apply_kernel(int which);
 cat_status cat_debug_full_loop(int on);
 
 /*
+ * Test hook.  Fits of up to 64 MB whose centroids fit LDS run their whole Lloyd loop in one launch, in which the workgroups
+ * that are there when it starts share the rows; the first one waits some 30 us for the others.  members > 0: it waits for no
+ * more than that many in all; 0: for as many as the launch has (default); negative: such fits run two launches a pass, as the
+ * larger ones do.  Same outputs.  Process-wide; returns CAT_OK.
+ */
+cat_status cat_debug_loop(int members);
+
+/*
  * Test hook.  The PCA's tridiagonalisation runs in workgroups that wait for each other, no longer than this many looks
  * at the words they pass on, 0.2 .. 0.4 us each; when one has waited longer (negative: at its first wait) a single
  * workgroup does the work.  Process-wide, default CAT_PCA_PATIENCE; returns CAT_OK.

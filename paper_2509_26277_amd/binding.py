@@ -29,7 +29,7 @@ EXPORTS = ("cat_select_path", "cat_fit_workspace_bytes", "cat_apply_workspace_by
            "cat_apply_static", "cat_apply_static_max_workspace_bytes", "cat_debug_apply_kernel",
            "cat_fit_multi_k_workspace_bytes", "cat_fit_multi_k", "cat_debug_multi_group_tiles",
            "cat_params_to_bf16", "cat_apply_lp_workspace_bytes", "cat_apply_lp",
-           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_debug_pca_patience",
+           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_debug_loop", "cat_debug_pca_patience",
            "cat_debug_pca_route_offset", "cat_stream_probe")
 
 
@@ -141,6 +141,8 @@ def load_library():
     lib.cat_debug_pca_route_offset.restype = sz
     lib.cat_debug_full_loop.argtypes = [c.c_int]
     lib.cat_debug_full_loop.restype = c.c_int
+    lib.cat_debug_loop.argtypes = [c.c_int]
+    lib.cat_debug_loop.restype = c.c_int
     lib.cat_debug_padded_fit.argtypes = [c.c_int]
     lib.cat_debug_padded_fit.restype = c.c_int
     lib.cat_debug_apply_kernel.argtypes = [c.c_int]
@@ -508,6 +510,11 @@ def debug_padded_fit(on):
 def debug_full_loop(on):
     """Test hook: True runs every pass of the plain fits over every row, without early stop and distance bounds."""
     _check(load_library().cat_debug_full_loop(int(bool(on))))
+
+
+def debug_loop(members):
+    """Test hook: how many workgroups a Lloyd loop in one launch waits for (0: all of them; negative: two launches a pass)."""
+    _check(load_library().cat_debug_loop(int(members)))
 
 
 def debug_pca_patience(looks):

@@ -11,6 +11,7 @@
 #include "cat_common.h"
 #include "cat_direct.h"
 #include "cat_infer.h"
+#include "cat_loop.h"
 #include "cat_tile.h"
 #include "cat_wide.h"
 
@@ -296,12 +297,18 @@ static cat_status run_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, 
         // out as a whole then).  Short ones are left out as a whole once the partition repeats, which costs the others nothing
         // (one word per launch, read beside the first loads): 4096 x 64, K = 4, 20 iterations, settled after a few:
         // 349 -> 232 us.
-        if (!skipped && !bw && !g_full_loop.load()) {
+        const bool plain = !g_full_loop.load();
+        if (!skipped && !bw && plain) {
             if (w.bounds.expire)
                 bw = &w.bounds;
             else
                 skipped = w.lloyd.skipped;
         }
+        // Small matrices: the whole loop in one launch.  (The hooks that concern the launches per pass keep those.)
+        if (!bw && plain && path == CAT_PATH_AUTO && !profile_on() && lloyd_list_capacity() == 1024 && rerank_queue_capacity() == 256 &&
+            loop_pays(N, D, K, iters, dt))
+            return loop_lloyd(lq, dt, N, D, K, iters, centroids, w.acc, assignments, w.counts, inertia, w.rep,
+                              skipped == w.lloyd.skipped ? nullptr : skipped, w.lloyd, st);
         // one assignment launch per Lloyd iteration; only the rows that change cluster touch the sums
         CAT_TRY(tile_lloyd(lq, dt, N, D, K, iters, centroids, w.acc, assignments, w.counts, inertia, w.rep, skipped, w.tile, w.lloyd, st, bw));
     } else {

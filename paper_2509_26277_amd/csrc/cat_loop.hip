@@ -1,0 +1,880 @@
+// All passes of a Lloyd loop in one launch, for matrices whose passes are launches and round trips rather than traffic.
+//
+// As two launches a pass (k_tile, k_delta_prep) a pass over a few megabytes takes 12 .. 25 us, of which the rows are one or two:
+// launches, and in each of them half a dozen dependent trips through memory (operand, rows, list, sums, counters).  Here every
+// workgroup keeps its rows' tiles from the first pass to the last (the rows stay in its L2), holds the centroids in LDS (fp32 and
+// the operand of k_tile), and once a pass the workgroups exchange through memory what changed:
+//   rank the own rows; those that changed cluster are added to their new cluster's sums and taken from the old one's (fp64 atomics
+//   in memory, many of them first combined in an LDS panel);  wait for these;  raise a flag that says which clusters they touched;
+//   wait for everybody's flag;  read the sums of the touched clusters and rebuild those centroids (every workgroup for itself).
+// The loop ends when no row changes any more.  What bounds it: three trips through memory in a row (additions, flags, sums, some
+// 1 us each; 256 flags 2.4 us, 32 flags 0.9), the additions of all workgroups to the same addresses in the first passes, and the
+// instructions of one tile.  us per cat_fit, two launches a pass -> this: 4096 x 64, K = 4, 20 iterations: 361 -> 179 (6.5 a pass);
+// 33816 x 80, K = 37, 30 iterations: 788 -> 371; 3178 x 28, K = 123: 449 -> 220; 11787 x 768, K = 15, 5 iterations: 251 -> 197.
+// Tried: as many copies of the sums as spread those additions (a copy more to read is a trip more: 179 -> 228 with two); a third and
+// fourth chunk of rows in flight (registers spill, 7 .. 20 % slower); a delay before the first look at the flags (alone it makes a
+// barrier of 256 workgroups 1.1 us instead of 2.4, here it is lost beside the waits for the last one to arrive).  The code has to
+// stay small: at 64 KB (loops unrolled) it no longer fits the instruction cache and every phase took half as long again.
+#include <atomic>
+
+#include "cat_loop.h"
+#include "cat_tile_kernel.h"
+
+namespace cat {
+
+constexpr int kLoopT = 512, kLoopW = kLoopT / kWave;
+constexpr int kLoopMax = 256;      // workgroups
+constexpr int kLoopDirect = 16;    // changed rows of a workgroup that may go to the sums without the panel (see loop_lloyd)
+constexpr int kLoopAhead = 8;      // requests of a wave for the sums
+constexpr int kLoopList = 64;      // changed rows of a workgroup whose entries are kept in LDS too
+constexpr uint32_t kLoopClosed = 0x80000000u;
+
+struct LoopParams {
+    const void* lq;
+    int64_t N;
+    int32_t D, K, nsteps, iters, ntiles;
+    float* cent;
+    int32_t* assign;
+    int32_t* counts;
+    double* inertia;          // nullable
+    unsigned long long* rep;
+    int32_t* skipped;         // nullable
+    double* sums;             // 3 x K x D; the first third zero on entry
+    int32_t* dn;              // 3 x K; the first third zero on entry
+    // zero on entry: [0] who has come, [1] how many take part, then by parity of the pass NM words a workgroup (the clusters it
+    // changed, 32 to a word) and two words a workgroup (halves of its share of the objective)
+    unsigned long long* words;
+    unsigned long long* list; // N
+    float tau, tau2;
+    uint32_t off_cent, off_panel, off_small;
+    int32_t W;                // channels of the panel, a multiple of 16
+    int32_t share;            // waves that share the channels of a tile: 1, 2, 4 or 8
+    int32_t direct;           // up to that many changed rows of a workgroup go to the sums without the panel
+    int32_t looks, enough;    // the first workgroup waits that many looks for the others, and for no more than `enough`
+};
+
+template <typename V>
+__device__ __forceinline__ V far_load(const V* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename V>
+__device__ __forceinline__ void far_store(V* p, V v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double lane_double(double v, int l) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// halves of a double, each with the number of the pass: a word says by itself whether it is there
+__device__ __forceinline__ void tagged_store(unsigned long long* at, int next, double v, uint32_t tag) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    far_store(at, (b << 32) | tag);
+    far_store(at + next, (b & 0xFFFFFFFF00000000ull) | tag);
+}
+__device__ __forceinline__ double tagged_load(const unsigned long long* at, int next, uint32_t tag) {
+    unsigned long long a, b;
+    do {
+        a = far_load(at);
+        b = far_load(at + next);
+    } while ((uint32_t)a != tag || (uint32_t)b != tag);
+    return __longlong_as_double((long long)((b & 0xFFFFFFFF00000000ull) | (a >> 32)));
+}
+// the values of a lane and of its partner 16 or 32 lanes on, lower one first: the same pair in both
+__device__ __forceinline__ void halves16(uint32_t v, uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ void halves32(uint32_t v, uint32_t& a, uint32_t& b) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = r[0];
+    b = r[1];
+}
+__device__ __forceinline__ float sum_groups(float v) {  // over the four lanes n, n + 16, n + 32, n + 48
+    uint32_t a, b;
+    halves16(__float_as_uint(v), a, b);
+    halves32(__float_as_uint(__uint_as_float(a) + __uint_as_float(b)), a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+__device__ __forceinline__ void own_memory_done() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
+// Exact squared distances (fp64, direct form) of one row to two centroids in LDS, the whole wave on the row.
+template <bool BF16>
+__device__ __forceinline__ void near_dists(const unsigned char* xrow, int D, const float* c0, const float* c1, int lane, double& d0,
+                                           double& d1) {
+    constexpr int EPL = BF16 ? 8 : 4;
+    double s0 = 0.0, s1 = 0.0;
+    for (int j = lane * EPL; j < D; j += kWave * EPL) {
+        const u32x4 w = *(const u32x4*)(xrow + (size_t)j * (BF16 ? 2 : 4));
+#pragma unroll
+        for (int e = 0; e < EPL; e += 4) {
+            const f32x4 a = *(const f32x4*)(c0 + j + e), b = *(const f32x4*)(c1 + j + e);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const double x = BF16 ? (double)((i & 1) ? hi_half(w[(e + i) >> 1]) : lo_half(w[(e + i) >> 1])) : (double)__uint_as_float(w[i]);
+                const double u = x - (double)a[i], v = x - (double)b[i];
+                s0 = fma(u, u, s0);
+                s1 = fma(v, v, s1);
+            }
+        }
+    }
+    d0 = wave_total(s0);
+    d1 = wave_total(s1);
+}
+
+template <int KT, bool BF16>
+__global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    typedef typename std::conditional<BF16, bf16_t, float>::type T;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int n = lane & 15, q = lane >> 4;
+    constexpr int NM = KT < 4 ? 1 : KT / 2;  // words of 32 clusters
+    const int D = p.D, K = p.K, KD = K * D, W = p.W, Ds = D + 4, G = (int)gridDim.x;
+    float* s_cent = (float*)(smem + p.off_cent);
+    double* s_panel = (double*)(smem + p.off_panel);
+    double* s_in = (double*)(smem + p.off_small);    // kLoopW
+    float* s_cnorm = (float*)(s_in + kLoopW);         // KT * 16
+    int* s_n = (int*)(s_cnorm + KT * 16);             // KT * 16
+    int* s_dn = s_n + KT * 16;                        // KT * 16
+    uint32_t* s_mask = (uint32_t*)(s_dn + KT * 16);   // 4: own changes; 2 x 4: everybody's, by parity of the pass
+    int* s_misc = (int*)(s_mask + 12);                // [0] rank, [1] members, [2] rows that changed
+    unsigned long long* s_list = (unsigned long long*)(s_misc + 4);  // kLoopList
+    float* s_score = (float*)(s_list + kLoopList);    // kLoopW x KT * 16
+
+    // ---- who takes part ----
+    // The workgroups wait for each other, so those that wait must be resident: the members are the workgroups that have come when
+    // the first one closes the door, which it does as soon as all of the grid are there or after `looks` looks (some 30 us: other
+    // kernels hold part of the chip).  A workgroup that starts later finds it closed and leaves.  The rows are shared out over the
+    // members there are, so every wait ends whatever else runs, and nothing has to be known about the stream.
+    if (tid == 0) {
+        s_misc[0] = (int)__hip_atomic_fetch_add((uint32_t*)p.words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_misc[2] = 0;
+    }
+    if (tid < 12) s_mask[tid] = 0;
+    for (int i = tid; i < (int)(p.off_cent / 16); i += kLoopT) ((u32x4*)smem)[i] = (u32x4){0u, 0u, 0u, 0u};
+    for (int i = tid; i < K * W; i += kLoopT) s_panel[i] = 0.0;
+    if (tid < KT * 16) {
+        s_n[tid] = s_dn[tid] = 0;
+        s_cnorm[tid] = kPadNorm;
+    }
+    __syncthreads();
+    const int rank = __builtin_amdgcn_readfirstlane(s_misc[0]);
+    if ((uint32_t)rank & kLoopClosed) return;
+    if (rank == 0) {
+        if (tid < K) {
+            far_store(p.counts + tid, 0);
+            far_store(p.rep + tid, ~0ull);
+        }
+        if (tid == 0 && p.inertia) far_store(p.inertia + p.iters, 0.0);
+        own_memory_done();
+    }
+
+    // Norms and operand of the clusters that the wave owns (wave + kLoopW j, bit j of mine) from their fp32 values.  Of the operand's
+    // 16-byte entries cluster m of a tile and lane group g take number 16 g + (m + 4 g + 2 (step & 1)) mod 16 instead of 16 g + m:
+    // the channels of one cluster then lie in different banks, and what a wave reads stays 1 KB.
+    const int nb = (D + kWave - 1) / kWave;
+    auto emit = [&](unsigned long long mine) {
+        for (; mine; mine &= mine - 1) {
+            const int k = wave + kLoopW * __builtin_amdgcn_readfirstlane(__builtin_ctzll(mine));
+            const float* c = s_cent + k * Ds;
+            unsigned char* at = smem + (k >> 4) * 2048;
+            double nn = 0.0;
+#pragma unroll 2
+            for (int ch = lane; ch < D; ch += kWave) {
+                const float f = c[ch];
+                int g, e;
+                operand_slot(ch & 31, !BF16, g, e);
+                const int step = ch >> 5;
+                uint16_t* a = (uint16_t*)(at + step * KT * 2048 + (g * 16 + ((k + 4 * g + 2 * (step & 1)) & 15)) * 16) + e;
+                const uint32_t hw = pack_bf16(f, 0.f) & 0xFFFFu;
+                a[0] = (uint16_t)hw;
+                a[512] = (uint16_t)(pack_bf16(f - lo_half(hw), 0.f) & 0xFFFFu);
+                nn = fma((double)f, (double)f, nn);
+            }
+            nn = wave_total(nn);
+            if (lane == 0) s_cnorm[k] = (float)nn;
+        }
+    };
+    // The centroids of the clusters in the mask from the sums: a wave takes whole clusters, 64 channels at a time, kLoopAhead
+    // requests before anything waits.
+    auto build = [&](const uint32_t* mask, const double* sums, const int32_t* dn) {
+        const int kd = wave + kLoopW * lane;  // lane j: the wave's cluster j
+        const unsigned long long mine = __ballot(kd < K && (mask[(kd < K ? kd : 0) >> 5] >> (kd & 31) & 1u));
+        if (mine == 0ull) return;
+        int rows = kd < K ? far_load(dn + kd) : 0;
+        double inv = 1.0;
+        unsigned long long left = mine;
+        int blk0 = 0;
+        for (bool first = true; left; first = false) {
+            double v[kLoopAhead];
+            unsigned long long m = left;
+            int blk = blk0;
+#pragma unroll
+            for (int u = 0; u < kLoopAhead; u++) {
+                const int j = m ? __builtin_ctzll(m) : 0, ch = blk * kWave + lane;
+                v[u] = far_load(sums + (wave + kLoopW * j) * D + (ch < D ? ch : 0));
+                if (++blk == nb) {
+                    blk = 0;
+                    m &= m - 1;
+                }
+            }
+            if (first) {
+                if (kd < K) s_n[kd] = rows += s_n[kd];
+                inv = 1.0 / (double)(rows > 0 ? rows : 1);
+            }
+            m = left;
+            blk = blk0;
+#pragma unroll
+            for (int u = 0; u < kLoopAhead; u++) {
+                const int j = m ? __builtin_ctzll(m) : 0, ch = blk * kWave + lane;
+                const int c = __builtin_amdgcn_readlane(rows, j);
+                if (m && c > 0 && ch < D) {  // v / c: the product with the reciprocal, corrected once (Markstein: the rounded quotient)
+                    const double r = lane_double(inv, j), q0 = v[u] * r;
+                    s_cent[(wave + kLoopW * j) * Ds + ch] = (float)fma(fma(-q0, (double)c, v[u]), r, q0);
+                }
+                if (++blk == nb) {
+                    blk = 0;
+                    m &= m - 1;
+                }
+            }
+            left = m;
+            blk0 = blk;
+        }
+        emit(mine);
+    };
+    {
+        int k = tid / D, ch = tid - k * D;
+        const int qd = kLoopT / D, rd = kLoopT - qd * D;
+#pragma unroll 4
+        for (int i = tid; i < KD; i += kLoopT) {
+            s_cent[k * Ds + ch] = p.cent[i];
+            ch += rd;
+            k += qd;
+            if (ch >= D) {
+                ch -= D;
+                k++;
+            }
+        }
+    }
+    __syncthreads();
+    emit(__ballot(wave + kLoopW * lane < K));
+    __syncthreads();
+    if (tid == 0) {
+        uint32_t m = 0;
+        if (rank == 0) {
+            for (int s = 0; s < p.looks; s++) {
+                if ((int)far_load((uint32_t*)p.words) >= p.enough) break;
+                __builtin_amdgcn_s_sleep(2);
+            }
+            m = __hip_atomic_fetch_or((uint32_t*)p.words, kLoopClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            far_store((uint32_t*)(p.words + 1), m);
+        } else {
+            while ((m = far_load((uint32_t*)(p.words + 1))) == 0u) __builtin_amdgcn_s_sleep(1);
+        }
+        s_misc[1] = (int)m;
+    }
+    __syncthreads();
+    const int M = __builtin_amdgcn_readfirstlane(s_misc[1]);
+    const int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * rank / M));
+    const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * (rank + 1) / M));
+    const int64_t row_lo = (int64_t)t_lo * kRows;
+    unsigned long long* list = p.list + row_lo;
+    const int nchunks = (p.nsteps + 3) / 4, share = p.share, slots = kLoopW / share;
+    const int slot = wave / share, part = wave - slot * share;  // the wave's tile in a round, and its chunks of it
+    const int c_lo = nchunks * part / share, c_hi = nchunks * (part + 1) / share;
+    const int z_lo = (int)((int64_t)KD * rank / M), z_hi = (int)((int64_t)KD * (rank + 1) / M);  // the share of the sums to carry on
+    double *sums = p.sums, *sums_next = p.sums + KD, *sums_prev = p.sums + 2 * KD;
+    const int k_start = (rank + wave) % K;
+    double carry = 0.0;
+    int32_t *dn = p.dn, *dn_next = p.dn + K, *dn_prev = p.dn + 2 * K;
+
+    const int at_even = (q * 16 + ((n + 4 * q) & 15)) * 16, at_odd = (q * 16 + ((n + 4 * q + 2) & 15)) * 16;
+    ChunkRegs<BF16> cur, next;
+    f32x4 acc[KT];
+    float nrm = 0.f, cmax = 0.f;
+    double in_acc = 0.0;
+    int t = 0, tl = 0, cl = 0, tc = 0, cc = 0;
+#pragma unroll
+    for (int u = 0; u < KT; u++) acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto issue = [&](ChunkRegs<BF16>& r) {
+        if (tl >= t_hi) return;
+        const int64_t r0 = (int64_t)tl * kRows + n;
+        const int64_t row = r0 < p.N ? r0 : p.N - 1;
+        r.prev = p.assign[row];
+        const T* x = (const T*)p.lq + row * D;
+        const int ch = cl * kChunk + (BF16 ? 8 : 4) * q;
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            const int c = ch + 32 * s;
+            if (BF16) {
+                r.v[s] = *(const u32x4*)(x + (c < D ? c : 0));
+            } else {
+                r.v[2 * s] = *(const u32x4*)(x + (c < D ? c : 0));
+                r.v[2 * s + 1] = *(const u32x4*)(x + (c + 16 < D ? c + 16 : 0));
+            }
+        }
+        if (++cl == c_hi) {
+            cl = c_lo;
+            tl += slots;
+        }
+    };
+    auto restart = [&]() {
+        tl = tc = t_lo + slot;
+        cl = cc = c_lo;
+        issue(cur);
+    };
+    auto contract = [&](const ChunkRegs<BF16>& r) {
+        const int s0 = 4 * cc;
+        const unsigned char* base = smem + s0 * KT * 2048;
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            if (s > 0 && s0 + s >= p.nsteps) break;
+            bf16x8 bh, bl;
+            if (BF16) {
+                const uint32_t m = (s0 + s) * 32 + 8 * q < D ? 0xFFFFFFFFu : 0u;
+                u32x4 w = r.v[s];
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    w[j] &= m;
+                    const float x0 = lo_half(w[j]), x1 = hi_half(w[j]);
+                    nrm = fmaf(x0, x0, fmaf(x1, x1, nrm));
+                }
+                bh = bl = __builtin_bit_cast(bf16x8, w);
+            } else {
+                const int cf = (s0 + s) * 32 + 4 * q;
+                const uint32_t m0 = cf < D ? 0xFFFFFFFFu : 0u, m1 = cf + 16 < D ? 0xFFFFFFFFu : 0u;
+                float x[8];
+                u32x4 h, l;
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    x[j] = __uint_as_float(r.v[2 * s][j] & m0);
+                    x[4 + j] = __uint_as_float(r.v[2 * s + 1][j] & m1);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    nrm = fmaf(x[2 * j], x[2 * j], fmaf(x[2 * j + 1], x[2 * j + 1], nrm));
+                    h[j] = pack_bf16(x[2 * j], x[2 * j + 1]);
+                    l[j] = pack_bf16(x[2 * j] - lo_half(h[j]), x[2 * j + 1] - hi_half(h[j]));
+                }
+                bh = __builtin_bit_cast(bf16x8, h);
+                bl = __builtin_bit_cast(bf16x8, l);
+            }
+#pragma unroll
+            for (int u = 0; u < KT; u++) {
+                const unsigned char* ap = base + (s * KT + u) * 2048 + (s & 1 ? at_odd : at_even);
+                const bf16x8 ah = __builtin_bit_cast(bf16x8, *(const u32x4*)ap);
+                const bf16x8 al = __builtin_bit_cast(bf16x8, *(const u32x4*)(ap + 1024));
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc[u], 0, 0, 0);
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc[u], 0, 0, 0);
+                if (!BF16) acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc[u], 0, 0, 0);
+            }
+        }
+    };
+    auto finish = [&](int prev_in) {
+        const int64_t row0 = (int64_t)tc * kRows;
+        const bool valid = row0 + n < p.N;
+        const float xn2 = sum_groups(nrm);
+        float f1 = __builtin_inff(), f2 = __builtin_inff();
+        int i1 = 0;
+#pragma unroll
+        for (int u = 0; u < KT; u++) {
+            const f32x4 cn = *(const f32x4*)(s_cnorm + 16 * u + 4 * q);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int k = 16 * u + 4 * q + i;
+                const float s = fmaf(-2.f, acc[u][i], cn[i]);
+                f2 = s < f1 ? f1 : (s < f2 ? s : f2);
+                i1 = s < f1 ? k : i1;
+                f1 = s < f1 ? s : f1;
+            }
+        }
+#pragma unroll
+        for (int o = 0; o < 2; o++) {
+            uint32_t a1, c1, a2, c2, ai, ci;
+            if (o == 0) {
+                halves16(__float_as_uint(f1), a1, c1);
+                halves16(__float_as_uint(f2), a2, c2);
+                halves16((uint32_t)i1, ai, ci);
+            } else {
+                halves32(__float_as_uint(f1), a1, c1);
+                halves32(__float_as_uint(f2), a2, c2);
+                halves32((uint32_t)i1, ai, ci);
+            }
+            const float x1 = __uint_as_float(a1), y1 = __uint_as_float(c1);
+            const bool take = y1 < x1 || (y1 == x1 && (int)ci < (int)ai);
+            f1 = take ? y1 : x1;
+            i1 = take ? (int)ci : (int)ai;
+            f2 = fminf(fminf(__uint_as_float(a2), __uint_as_float(c2)), take ? x1 : y1);
+        }
+        i1 = i1 < K ? i1 : K - 1;  // (no real score compares: non-finite input)
+        float dmin = fmaxf(xn2 + f1, 0.f);
+        const float thr_in = p.tau * sqrtf(xn2) * cmax + p.tau2 * cmax * cmax;
+        unsigned long long mask = __ballot(valid && !(f2 - f1 > thr_in) && q == 0);
+        while (mask) {  // rows whose two best are within the error bound: exact distances of all within it
+            const int r = __builtin_amdgcn_readfirstlane(__builtin_ctzll(mask));
+            mask &= mask - 1;
+            const float thr = readlane_f(f1, r) + readlane_f(thr_in, r);
+            float* sc = s_score + wave * (KT * 16);
+#pragma unroll
+            for (int u = 0; u < KT; u++)
+                if (n == r) *(f32x4*)(sc + 16 * u + 4 * q) = acc[u];
+            unsigned long long cand[(KT + 3) / 4];
+#pragma unroll
+            for (int w = 0; w < (KT + 3) / 4; w++) {
+                const int k = 64 * w + lane;
+                cand[w] = __ballot(k < K && fmaf(-2.f, sc[k < K ? k : 0], s_cnorm[k < K ? k : 0]) <= thr);
+            }
+            double dbest = __builtin_inf();
+            int kbest = 0x7fffffff;
+            const unsigned char* xrow = (const unsigned char*)p.lq + (row0 + r) * D * (int64_t)sizeof(T);
+            auto take = [&]() {  // the lowest candidate left; 0x7fffffff: none
+                int k = 0x7fffffff;
+#pragma unroll
+                for (int w = (KT + 3) / 4 - 1; w >= 0; w--)
+                    if (cand[w]) k = 64 * w + __builtin_ctzll(cand[w]);
+#pragma unroll
+                for (int w = 0; w < (KT + 3) / 4; w++)
+                    if (k >> 6 == w) cand[w] &= cand[w] - 1;
+                return __builtin_amdgcn_readfirstlane(k);
+            };
+            for (int ka = take(); ka != 0x7fffffff; ka = take()) {
+                int kb = take();
+                if (kb == 0x7fffffff) kb = ka;
+                double da, db;
+                near_dists<BF16>(xrow, D, s_cent + ka * Ds, s_cent + kb * Ds, lane, da, db);
+                if (da < dbest) {  // (ascending: an equal one later does not win)
+                    dbest = da;
+                    kbest = ka;
+                }
+                if (db < dbest) {
+                    dbest = db;
+                    kbest = kb;
+                }
+            }
+            if (n == r && kbest != 0x7fffffff) {
+                i1 = kbest;
+                dmin = (float)dbest;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < KT; u++) acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        nrm = 0.f;
+        const int prev = t == 0 ? -1 : prev_in;
+        const bool owner = q == 0 && valid;
+        const bool changed = owner && prev != i1;
+        if (owner) in_acc += (double)dmin;
+        const unsigned long long cm = __ballot(changed);
+        if (cm) {
+            int pos = 0;
+            if (lane == 0) pos = atomicAdd(&s_misc[2], (int)__builtin_popcountll(cm));
+            pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(cm & ((1ull << lane) - 1ull));
+            if (changed) {
+                p.assign[row0 + n] = i1;
+                const unsigned long long ent =
+                    ((unsigned long long)(row0 + n) << 16) | ((unsigned long long)(prev + 1) << 8) | (unsigned long long)i1;
+                list[pos] = ent;
+                if (pos < kLoopList) s_list[pos] = ent;
+                atomicAdd(&s_dn[i1], 1);
+                atomicOr(&s_mask[i1 >> 5], 1u << (i1 & 31));
+                if (prev >= 0) {
+                    atomicAdd(&s_dn[prev], -1);
+                    atomicOr(&s_mask[prev >> 5], 1u << (prev & 31));
+                }
+            }
+        }
+    };
+
+    bool settled = false;
+    restart();
+    for (;; t++) {
+        // ---- assignment of the own rows ----
+        {
+            float c2 = 0.f;
+            for (int k = lane; k < K; k += kWave) c2 = fmaxf(c2, s_cnorm[k]);
+            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0xB1, 0xF, 0xF, true)));
+            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x4E, 0xF, 0xF, true)));
+            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x141, 0xF, 0xF, true)));
+            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x140, 0xF, 0xF, true)));
+            cmax = sqrtf(fmaxf(fmaxf(readlane_f(c2, 0), readlane_f(c2, 16)), fmaxf(readlane_f(c2, 32), readlane_f(c2, 48))));
+        }
+        // Three buffers of sums take turns.  Pass t adds to buffer t what moves; its owner adds the sums up to pass t - 1, so that after
+        // the flags of pass t buffer t holds the sums up to t.  Buffer t + 1 was read last after the flags of pass t - 2, which
+        // everybody did before raising the flag of pass t - 1: it is free now, and clear before the flags of pass t.
+        // The share of the sums so far moves on to this pass's, and the buffers of the pass that follows are cleared.
+        for (int i = z_lo + tid; i < z_hi; i += kLoopT) {
+            if (i != z_lo + tid && t > 0) carry = far_load(sums_prev + i);
+            if (carry != 0.0) atomicAdd(sums + i, carry);
+            far_store(sums_next + i, 0.0);
+        }
+        if (rank == 0 && tid < K) far_store(dn_next + tid, 0);
+        in_acc = 0.0;
+        int prev = -1;
+        for (int first = t_lo; first < t_hi; first += slots) {  // a round: every slot one tile
+            if (tc < t_hi) {
+                prev = cur.prev;
+                while (cc < c_hi) {
+                    issue(next);
+                    contract(cur);
+                    cc++;
+                    cur = next;
+                }
+            }
+            if (share > 1) {
+                // the first of the waves that share a tile adds up what the others have (in the panel, which is left zero)
+                if (first > t_lo) __syncthreads();
+                f32x4* parts = (f32x4*)(smem + p.off_panel);
+                if (part > 0) {
+                    const int at = (slot * (share - 1) + part - 1) * (KT * kWave + kWave / 4);
+#pragma unroll
+                    for (int u = 0; u < KT; u++) {
+                        parts[at + u * kWave + lane] = acc[u];
+                        acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    }
+                    ((float*)(parts + at + KT * kWave))[lane] = nrm;
+                    nrm = 0.f;
+                }
+                __syncthreads();
+                if (part == 0) {
+                    for (int i = 0; i < share - 1; i++) {
+                        const int at = (slot * (share - 1) + i) * (KT * kWave + kWave / 4);
+#pragma unroll
+                        for (int u = 0; u < KT; u++) {
+                            acc[u] += parts[at + u * kWave + lane];
+                            parts[at + u * kWave + lane] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        }
+                        nrm += ((float*)(parts + at + KT * kWave))[lane];
+                        ((float*)(parts + at + KT * kWave))[lane] = 0.f;
+                    }
+                }
+            }
+            if (part == 0 && tc < t_hi) finish(prev);
+            cc = c_lo;
+            tc += slots;
+        }
+        in_acc = wave_total(in_acc);
+        if (lane == 0) s_in[wave] = in_acc;
+        own_memory_done();
+        __syncthreads();
+        if (t == p.iters) break;
+
+        // ---- the rows that changed cluster move between the sums ----
+        const int nch = __builtin_amdgcn_readfirstlane(s_misc[2]);
+        if (nch > 0 && nch <= p.direct) {
+            const unsigned long long ent = s_list[lane < nch ? lane : 0];
+            const uint32_t e_lo = (uint32_t)ent, e_hi = (uint32_t)(ent >> 32);
+            const int blocks = (D + kWave - 1) / kWave, items = nch * blocks;
+            constexpr int U = 4;
+            for (int i0 = wave; i0 < items; i0 += U * kLoopW) {
+                float x[U];
+                int ch[U], nw[U], od[U];
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    const int it = i0 + u * kLoopW < items ? i0 + u * kLoopW : i0;
+                    const int e = it / blocks;
+                    ch[u] = (it - e * blocks) * kWave + lane;
+                    const uint32_t lo = __builtin_amdgcn_readlane(e_lo, e), hi = __builtin_amdgcn_readlane(e_hi, e);
+                    const int64_t row = (int64_t)(((unsigned long long)hi << 16) | (lo >> 16));
+                    nw[u] = (int)(lo & 0xFFu);
+                    od[u] = (int)((lo >> 8) & 0xFFu) - 1;
+                    x[u] = ld_elem((const T*)p.lq + row * D + (ch[u] < D ? ch[u] : 0));
+                }
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    if (i0 + u * kLoopW >= items) break;
+                    if (ch[u] < D) {
+                        atomicAdd(sums + nw[u] * D + ch[u], (double)x[u]);
+                        if (od[u] >= 0) atomicAdd(sums + od[u] * D + ch[u], -(double)x[u]);
+                    }
+                }
+            }
+        } else if (nch > 0) {
+            const int pw = (nch + kLoopW - 1) / kLoopW, ws = wave * pw, we = ws + pw < nch ? ws + pw : nch;
+            for (int c0 = 0; c0 < D; c0 += W) {
+                const int wc = D - c0 < W ? D - c0 : W;
+                for (int b = ws; b < we; b += kWave) {
+                    const int nb = we - b < kWave ? we - b : kWave;
+                    const unsigned long long ent = list[b + (lane < nb ? lane : 0)];
+                    const uint32_t e_lo = (uint32_t)ent, e_hi = (uint32_t)(ent >> 32);
+                    constexpr int RB = 8, CB = 2;
+                    for (int i0 = 0; i0 < nb; i0 += RB)
+                        for (int cb = 0; cb < wc; cb += CB * kWave) {
+                            float x[RB][CB];
+                            int nw[RB], od[RB];
+#pragma unroll
+                            for (int u = 0; u < RB; u++) {
+                                const int i = i0 + u < nb ? i0 + u : nb - 1;
+                                const uint32_t lo = __builtin_amdgcn_readlane(e_lo, i), hi = __builtin_amdgcn_readlane(e_hi, i);
+                                const int64_t row = (int64_t)(((unsigned long long)hi << 16) | (lo >> 16));
+                                nw[u] = i0 + u < nb ? (int)(lo & 0xFFu) : -1;
+                                od[u] = i0 + u < nb ? (int)((lo >> 8) & 0xFFu) - 1 : -1;
+                                const T* xr = (const T*)p.lq + row * D + c0;
+#pragma unroll
+                                for (int w = 0; w < CB; w++) {
+                                    const int c = cb + w * kWave + lane;
+                                    if (cb + w * kWave < wc) x[u][w] = ld_elem(xr + (c < wc ? c : 0));
+                                }
+                            }
+#pragma unroll
+                            for (int u = 0; u < RB; u++)
+#pragma unroll
+                                for (int w = 0; w < CB; w++) {
+                                    const int c = cb + w * kWave + lane;
+                                    if (c < wc) {
+                                        if (nw[u] >= 0) atomicAdd(s_panel + nw[u] * W + c, (double)x[u][w]);
+                                        if (od[u] >= 0) atomicAdd(s_panel + od[u] * W + c, -(double)x[u][w]);
+                                    }
+                                }
+                        }
+                }
+                __syncthreads();
+                int k = k_start;  // (the workgroups start at different clusters: not all at one address)
+                for (int i = wave; i < K; i += kLoopW) {
+                    for (int c = lane; c < wc; c += kWave) {
+                        const double v = s_panel[k * W + c];
+                        if (v != 0.0) {
+                            atomicAdd(sums + k * D + c0 + c, v);
+                            s_panel[k * W + c] = 0.0;
+                        }
+                    }
+                    k += kLoopW;
+                    while (k >= K) k -= K;
+                }
+                if (c0 + W < D) __syncthreads();
+            }
+        }
+        if (nch > 0) {
+            if (tid < K) {
+                const int d = s_dn[tid];
+                if (d) {
+                    atomicAdd(dn + tid, d);
+                    s_dn[tid] = 0;
+                }
+            }
+            own_memory_done();
+            __syncthreads();
+        }
+        unsigned long long* flags = p.words + 8 + (t & 1) * (NM + 2) * G;
+        const int par = t & 1;
+        if (tid < NM) {
+            far_store(flags + tid * G + rank, ((unsigned long long)s_mask[tid] << 32) | (uint32_t)(t + 1));
+            s_mask[tid] = 0;
+            s_mask[4 + 4 * (par ^ 1) + tid] = 0;
+        }
+        if (tid == 0) {
+            double v = 0.0;
+#pragma unroll
+            for (int w = 0; w < kLoopW; w++) v += s_in[w];
+            tagged_store(flags + NM * G + rank, G, v, (uint32_t)(t + 1));
+            s_misc[2] = 0;
+        }
+        // ---- wait for the others; the first rows of the next pass travel meanwhile ----
+        restart();
+        for (int i0 = wave * kWave; i0 < NM * kLoopMax; i0 += kLoopT) {
+            const int w = i0 / kLoopMax, m0 = i0 - w * kLoopMax;
+            if (m0 >= M) continue;
+            const unsigned long long* f = flags + w * G + (m0 + lane < M ? m0 + lane : M - 1);
+            unsigned long long v = far_load(f);
+            while (__any((uint32_t)v != (uint32_t)(t + 1))) v = far_load(f);
+            const uint32_t bits = (uint32_t)(v >> 32);
+            if (bits) atomicOr(&s_mask[4 + 4 * par + w], bits);
+        }
+        __syncthreads();
+        if (rank == 0 && wave == kLoopW - 1 && p.inertia) {
+            double v = 0.0;
+            for (int m = lane; m < M; m += kWave) v += tagged_load(flags + NM * G + m, G, (uint32_t)(t + 1));
+            v = wave_total(v);
+            if (lane == 0) p.inertia[t] = v;
+        }
+        const uint32_t* mask = s_mask + 4 + 4 * par;
+        uint32_t any = mask[0];
+#pragma unroll
+        for (int w = 1; w < NM; w++) any |= mask[w];
+        if (__builtin_amdgcn_readfirstlane(any) == 0u) {
+            settled = true;
+            break;
+        }
+        // ---- the next centroids ----
+        if (z_lo + tid < z_hi) carry = far_load(sums + z_lo + tid);
+        build(mask, sums, dn);
+        __syncthreads();
+        {
+            double* s = sums_prev;
+            sums_prev = sums;
+            sums = sums_next;
+            sums_next = s;
+            int32_t* d = dn_prev;
+            dn_prev = dn;
+            dn = dn_next;
+            dn_next = d;
+        }
+    }
+
+    // ---- what is returned ----
+    if (!settled && tid == 0 && p.inertia) {
+        double v = 0.0;
+#pragma unroll
+        for (int w = 0; w < kLoopW; w++) v += s_in[w];
+        atomicAdd(p.inertia + p.iters, v);
+    }
+    if (settled && rank == 0 && wave == kLoopW - 1 && p.inertia) {
+        own_memory_done();  // (the entry of this pass, by this wave)
+        const double v = p.inertia[t];
+        for (int i = t + 1 + lane; i <= p.iters; i += kWave) p.inertia[i] = v;
+    }
+    if (rank == 0 && tid == 0 && p.skipped) *p.skipped = settled && p.iters - 1 > (t > 2 ? t : 2) ? p.iters - 1 - (t > 2 ? t : 2) : 0;
+    int* s_hist = s_dn;
+    unsigned long long* s_rep = (unsigned long long*)s_panel;  // (a panel has at least 16 channels)
+    if (tid < K) {
+        s_hist[tid] = 0;
+        s_rep[tid] = ~0ull;
+    }
+    __syncthreads();
+    const int64_t row_hi = (int64_t)t_hi * kRows < p.N ? (int64_t)t_hi * kRows : p.N;
+    for (int64_t i = row_lo + tid; i < row_hi; i += kLoopT) {
+        const int a = p.assign[i];
+        atomicAdd(&s_hist[a], 1);
+        atomicMin(&s_rep[a], (unsigned long long)i);
+    }
+    __syncthreads();
+    if (tid < K && s_hist[tid]) {
+        atomicAdd(p.counts + tid, s_hist[tid]);
+        atomicMin(p.rep + tid, s_rep[tid]);
+    }
+    for (int k = rank; k < K; k += M)
+        for (int j = tid; j < D; j += kLoopT) p.cent[k * D + j] = s_cent[k * Ds + j];
+}
+
+static std::atomic<int> g_loop_members{0};  // cat_debug_loop
+
+struct LoopCfg {
+    bool ok = false;
+    int KT = 0, nsteps = 0, W = 0;
+    uint32_t off_cent = 0, off_panel = 0, off_small = 0;
+    size_t lds = 0;
+};
+static LoopCfg loop_config(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
+    LoopCfg c;
+    if (N < 256 || N >= ((int64_t)1 << 31) - 16 || K > 128 || D % (dt == CAT_BF16 ? 8 : 4) || (K + 15) / 16 * 16 * D > 16384) return c;
+    c.KT = 1;
+    while (c.KT * 16 < K) c.KT *= 2;
+    c.nsteps = (int)((D + 31) / 32);
+    c.off_cent = (uint32_t)(c.nsteps * c.KT * 2048);
+    c.off_panel = c.off_cent + (uint32_t)(K * (D + 4) * 4);
+    const size_t small = (size_t)c.KT * 16 * (4 + 4 + 4) + kLoopW * 8 + 16 * 4 + kLoopList * 8 + (size_t)kLoopW * c.KT * 16 * 4;
+    if (c.off_panel + small + (size_t)K * 16 * 8 > kLdsLimit) return c;
+    int64_t W = (int64_t)((kLdsLimit - small - c.off_panel) / ((size_t)K * 8)) / 16 * 16;
+    const int64_t Dr = (D + 15) / 16 * 16;
+    if (W > Dr) W = Dr;
+    if (W > 64 && W < Dr) W = W / 64 * 64;
+    c.W = (int)W;
+    c.off_small = c.off_panel + (uint32_t)(K * W * 8);
+    c.lds = c.off_small + small;
+    c.ok = true;
+    return c;
+}
+
+// Below 64 MB, where the passes keep no distance bounds (cat_tile.hip): faster than two launches a pass in all of 260 fits measured
+// there (256 .. 560000 rows of 24 .. 1000 channels, K = 1 .. 128, 1 .. 30 iterations; 1.0 .. 4.0, 1.63 on average; the least at one to
+// three iterations with 50 clusters and more).  The centroids have to fit LDS twice, see loop_config.
+bool loop_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
+    return (double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) < 64.0 * 1024 * 1024 && iters >= 1 && g_loop_members.load() >= 0 &&
+           loop_config(N, D, K, dt).ok;
+}
+
+// clears the words and the sums of the first pass
+__global__ __launch_bounds__(256) void k_loop_clear(unsigned long long* a, int na, double* b, int nb) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < na) a[i] = 0ull;
+    if (i < nb) b[i] = 0.0;
+}
+
+template <int KT, bool BF16>
+static cat_status launch_loop(const LoopParams& p, const LoopCfg& c, int groups, hipStream_t st) {
+    auto kern = k_lloyd_loop<KT, BF16>;
+    CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kLoopT), c.lds, st, p);
+    CAT_LAUNCH_CHECK("k_lloyd_loop");
+    return CAT_OK;
+}
+
+cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,
+                      int32_t* assign, int32_t* counts, double* inertia, unsigned long long* rep, int32_t* skipped,
+                      const LloydWs& lw, hipStream_t st) {
+    const LoopCfg c = loop_config(N, D, K, dt);
+    if (!c.ok) return set_error(CAT_ERR_UNSUPPORTED, "loop in one launch: N=%lld D=%lld K=%d", (long long)N, (long long)D, (int)K);
+    LoopParams p = {};
+    p.lq = lq;
+    p.N = N;
+    p.D = (int32_t)D;
+    p.K = K;
+    p.nsteps = c.nsteps;
+    p.iters = iters;
+    p.ntiles = (int32_t)((N + kRows - 1) / kRows);
+    p.cent = cent_io;
+    p.assign = assign;
+    p.counts = counts;
+    p.inertia = inertia;
+    p.rep = rep;
+    p.skipped = skipped;
+    p.sums = sums;
+    p.list = lw.list;
+    p.tau2 = 4.0e-7f;
+    p.off_cent = c.off_cent;
+    p.off_panel = c.off_panel;
+    p.off_small = c.off_small;
+    p.W = c.W;
+    int dev = 0, v = 0;
+    static std::atomic<int> ncu[16];
+    CAT_HIP_TRY(hipGetDevice(&dev));
+    v = dev < 16 ? ncu[dev].load() : 0;
+    if (v == 0) {
+        CAT_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
+        if (dev < 16) ncu[dev].store(v);
+    }
+    // Few tiles of long rows: several waves share the channels of a tile (what the others have goes through the panel).  us per cat_fit,
+    // one wave a tile / as here: 2958 x 984 bf16, K = 14: 159 / 115 (8 waves); 2652 x 640, K = 11: 279 / 187 (4); 7294 x 776, K = 3: 133 / 115 (4);
+    // 14629 x 998 bf16, K = 4: 273 / 230 (2)
+    p.share = 1;
+    while (p.share < kLoopW && 2 * p.share <= (c.nsteps + 3) / 4 && (int64_t)p.ntiles * 2 * p.share <= (int64_t)v * kLoopW &&
+           (size_t)(kLoopW - kLoopW / (2 * p.share)) * (c.KT * 1024 + 256) <= (size_t)K * c.W * 8)
+        p.share *= 2;
+    // the error bound of the split arithmetic as in the tile kernels (cat_tile.hip: base_params); shared channels are added up once more
+    const int n_acc = (dt == CAT_BF16 ? 2 : 3) * ((c.nsteps + 3) / 4 * 4) + 8 + (p.share - 1);
+    p.tau = (dt == CAT_BF16 ? 3.1e-5f : 9.4e-5f) + 4.f * (float)n_acc * 5.96e-8f;
+    int groups = (p.ntiles * p.share + kLoopW - 1) / kLoopW;
+    if (groups > v) groups = v;
+    if (groups > kLoopMax) groups = kLoopMax;
+    // Rows that go to the sums directly come to 2 rows / K additions an address and workgroup, through the panel to one at most; all
+    // workgroups add to the same addresses.  us per cat_fit with up to 2 / 4 / 16 rows directly: 89551 x 128 bf16, K = 7 (256 workgroups)
+    // 242 / 268 / 308; 7294 x 776, K = 3 (228) 115 / 115 / 150; 14629 x 998 bf16, K = 4 (229) 249 / 228 / 233; 4096 x 64, K = 4 (32)
+    // 194 / 189 / 188; 2652 x 640, K = 11 192 / 185 / 186.
+    p.direct = 64 * K / groups;
+    if (p.direct < 3) p.direct = 3;
+    if (p.direct > kLoopDirect) p.direct = kLoopDirect;
+    const int members = g_loop_members.load();
+    p.enough = members > 0 && members < groups ? members : groups;
+    p.looks = 40;
+    // The words lie in the scratch of the counting sort, 4 N + 8 K + 8 bytes: 64 + 32 (NM + 2) groups + 12 K are needed, NM <= 4
+    const int nm = c.KT < 4 ? 1 : c.KT / 2;
+    p.words = (unsigned long long*)lw.sort_ws;
+    p.dn = (int32_t*)(p.words + 8 + 2 * (nm + 2) * groups);
+    const int nwords = 8 + 2 * (nm + 2) * groups + (K + 1) / 2, nsums = K * (int)D;
+    hipLaunchKernelGGL(k_loop_clear, dim3((unsigned)(((nwords > nsums ? nwords : nsums) + 255) / 256)), dim3(256), 0, st, p.words, nwords, sums, nsums);
+    CAT_LAUNCH_CHECK("k_loop_clear");
+    const bool bf = dt == CAT_BF16;
+    switch (c.KT) {
+        case 1: return bf ? launch_loop<1, true>(p, c, groups, st) : launch_loop<1, false>(p, c, groups, st);
+        case 2: return bf ? launch_loop<2, true>(p, c, groups, st) : launch_loop<2, false>(p, c, groups, st);
+        case 4: return bf ? launch_loop<4, true>(p, c, groups, st) : launch_loop<4, false>(p, c, groups, st);
+        default: return bf ? launch_loop<8, true>(p, c, groups, st) : launch_loop<8, false>(p, c, groups, st);
+    }
+}
+
+}  // namespace cat
+
+extern "C" cat_status cat_debug_loop(int members) {
+    cat::g_loop_members.store(members < 0 ? -1 : members);
+    return CAT_OK;
+}

@@ -1,0 +1,151 @@
+"""Lloyd loops in one launch (cat_loop.hip): the fits of up to 64 MB whose centroids fit LDS.
+
+Compared with the loop of two launches a pass, which the oracle tests pin, and with the oracle itself.  Both sides rank the rows
+exactly and keep their sums in double precision, in another order: centroids agree to a rounding of fp32, and a row may only
+differ where its two nearest centroids do to that rounding.  The objective's terms are fp32 (|x|^2 + score, see cat_fit)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2509_26277_amd import binding, cat_fit
+
+from parity_util import CENTROID_RTOL, check_assignments_lazy, check_values, dev_matrix, f32_round, host_matrix
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _defaults():
+    yield
+    binding.debug_loop(0)
+
+
+def _rows(N, D, comps, dtype, seed, spread=2.0):
+    rng = np.random.default_rng(seed)
+    mu = rng.standard_normal((comps, D)) * spread
+    x = mu[rng.integers(0, comps, N)] + rng.standard_normal((N, D))
+    y = 1.1 * x + 0.3 + 0.05 * rng.standard_normal((N, D))
+    if dtype == "bf16":
+        x, y = (torch.from_numpy(a).bfloat16().float().numpy() for a in (x, y))
+    return x.astype(np.float32), y.astype(np.float32)
+
+
+def _fits(x, y, K, iters, dtype, members=0, **kw):
+    lq, fp = dev_matrix(x, dtype), dev_matrix(y, dtype)
+    binding.debug_loop(members)
+    got = cat_fit(lq, fp, K, iters, seed=5, **kw)
+    binding.debug_loop(-1)
+    want = cat_fit(lq, fp, K, iters, seed=5, **kw)
+    return got, want
+
+
+def _same(got, want, x, dtype):
+    cent = host_matrix(want["centroids"])
+    differ = check_assignments_lazy(got["assignments"].cpu().numpy(),
+                                    oracle.assign(x, f32_round(cent)) if (got["assignments"] != want["assignments"]).any()
+                                    else got["assignments"].cpu().numpy(), x, f32_round(cent), "labels")
+    counts = torch.bincount(got["assignments"].long(), minlength=cent.shape[0])
+    assert (counts == got["counts"]).all()
+    np.testing.assert_allclose(got["inertia"].cpu().numpy(), want["inertia"].cpu().numpy(), rtol=1e-4)
+    if differ == 0:
+        check_values(host_matrix(got["centroids"]), cent, CENTROID_RTOL, "centroids")
+        for name in ("gamma", "beta"):
+            check_values(host_matrix(got[name]), host_matrix(want[name]), 1e-5, name)
+    if "passes_skipped" in got and differ == 0:
+        assert int(got["passes_skipped"].item()) == int(want["passes_skipped"].item())
+
+
+SHAPES = [
+    # N, D, K, iterations, type: fewest rows, one channel group, one cluster
+    (256, 4, 1, 3, "f32"), (256, 8, 3, 5, "bf16"),
+    # remainders of tiles and of clusters, both sides of each cluster tile count
+    (1000, 28, 15, 8, "f32"), (2049, 36, 16, 8, "f32"), (2047, 36, 17, 8, "f32"), (3001, 64, 32, 6, "bf16"),
+    (3001, 64, 33, 6, "f32"), (4099, 60, 65, 6, "f32"), (5000, 128, 128, 5, "f32"), (5000, 120, 127, 5, "bf16"),
+    # long rows: two, four and eight waves share the channels of a tile, the panel takes part of the channels
+    (300, 1000, 16, 6, "f32"), (2500, 1024, 16, 5, "f32"), (5000, 512, 30, 5, "f32"), (9001, 520, 9, 5, "bf16"), (600, 1000, 3, 9, "bf16"),
+    # more tiles than waves on the chip, rows that are not whole 16-byte groups
+    (70000, 32, 7, 6, "f32"), (40000, 45, 2, 6, "f32"),
+    # one iteration; a loop that settles
+    (900, 40, 6, 1, "f32"), (4096, 64, 4, 40, "f32"),
+]
+
+
+@pytest.mark.parametrize("N,D,K,iters,dtype", SHAPES)
+def test_same_outputs_as_two_launches_a_pass(N, D, K, iters, dtype):
+    x, y = _rows(N, D, max(2, K - 1), dtype, N + D)
+    got, want = _fits(x, y, K, iters, dtype)
+    _same(got, want, x, dtype)
+
+
+@pytest.mark.parametrize("members", [1, 2, 5, 0])
+def test_any_number_of_workgroups(members):
+    """the rows are shared out over the workgroups that are there when the first one closes the door"""
+    x, y = _rows(9000, 96, 12, "f32", 3, spread=0.5)
+    got, want = _fits(x, y, 20, 12, "f32", members=members, early_stop=True)
+    _same(got, want, x, "f32")
+
+
+def test_ties_and_empty_clusters():
+    """integer rows on few points: exact ties between centroids, clusters without rows (they keep their centroid)"""
+    rng = np.random.default_rng(1)
+    pts = rng.integers(-3, 4, (6, 32)).astype(np.float32)
+    x = pts[rng.integers(0, 6, 3000)]
+    y = (x * 2 + 1).astype(np.float32)
+    o = oracle.fit(x, y, 9, iters=6, seed=5)
+    got, _ = _fits(x, y, 9, 6, "f32")
+    assert (got["assignments"].cpu().numpy() == o["assignments"]).all()
+    assert (got["counts"].cpu().numpy() == 0).any()
+    check_values(host_matrix(got["centroids"]), o["centroids"], CENTROID_RTOL, "centroids")
+
+
+def test_given_centroids_far_from_the_rows():
+    """all rows in one cluster first, the others empty; |x| large beside the spread (most rows measured exactly)"""
+    x, y = _rows(3000, 64, 5, "f32", 9)
+    x = (x + 100.0).astype(np.float32)
+    init = torch.from_numpy(np.concatenate([x[:1], x[:4] + 1000.0]).astype(np.float32)).cuda()
+    got, want = _fits(x, y, 5, 7, "f32", init_centroids=init)
+    _same(got, want, x, "f32")
+
+
+def test_calls_side_by_side_on_streams():
+    """loops of several streams share the chip: each with the members that were there in time"""
+    cases = [(_rows(n, d, 8, "f32", n), k) for n, d, k in ((20000, 64, 9), (33000, 80, 37), (5000, 600, 8), (12000, 100, 64))]
+    want = []
+    for (x, y), k in cases:
+        binding.debug_loop(-1)
+        want.append(cat_fit(dev_matrix(x, "f32"), dev_matrix(y, "f32"), k, 10, seed=5))
+    binding.debug_loop(0)
+    ins = [(dev_matrix(x, "f32"), dev_matrix(y, "f32"), k) for (x, y), k in cases]
+    streams = [torch.cuda.Stream() for _ in cases]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        got = []
+        for s, (lq, fp, k) in zip(streams, ins):
+            with torch.cuda.stream(s):
+                got.append(cat_fit(lq, fp, k, 10, seed=5))
+        torch.cuda.synchronize()
+        for g, w, ((x, _), _) in zip(got, want, cases):
+            _same(g, w, x, "f32")
+
+
+def test_replayed_from_a_graph():
+    x, y = _rows(8000, 72, 10, "f32", 4, spread=0.7)
+    lq, fp = dev_matrix(x, "f32"), dev_matrix(y, "f32")
+    ws = torch.empty(binding.cat_fit_workspace_bytes(8000, 72, 12, binding.CAT_F32), dtype=torch.uint8, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        cat_fit(lq, fp, 12, 8, seed=5, workspace=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = cat_fit(lq, fp, 12, 8, seed=5, workspace=ws)
+    for scale in (1.0, 0.5, 2.0):
+        lq.copy_(dev_matrix((x * scale).astype(np.float32), "f32"))
+        graph.replay()
+        torch.cuda.synchronize()
+        binding.debug_loop(-1)
+        want = cat_fit(lq, fp, 12, 8, seed=5)
+        binding.debug_loop(0)
+        _same(got, want, (x * scale).astype(np.float32), "f32")
