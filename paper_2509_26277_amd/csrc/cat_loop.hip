@@ -11,6 +11,12 @@
 // 1 us each; 256 flags 2.4 us, 32 flags 0.9), the additions of all workgroups to the same addresses in the first passes, and the
 // instructions of one tile.  us per cat_fit, two launches a pass -> this: 4096 x 64, K = 4, 20 iterations: 361 -> 179 (6.5 a pass);
 // 33816 x 80, K = 37, 30 iterations: 788 -> 371; 3178 x 28, K = 123: 449 -> 220; 11787 x 768, K = 15, 5 iterations: 251 -> 197.
+// From 64 MB on (BOUNDS) the passes that leave rows out by distance bounds run here too: tile_lloyd's passes 0 .. 2 read every row, the
+// last of them lists the rows that changed and leaves the bounds; then every workgroup selects the due ones of its own rows, and
+// the waves share the channels of a tile where a pass has few tiles.  A row within the error bound is measured at the end of the
+// workgroup's tiles, by any wave.  36 random fits of 64 .. 490 MB: 0.99 .. 1.47 times as fast, 1.09 on average; 65536 x 1000, K = 16:
+// 546 -> 441 us where the loop settles after 25 passes (18 us a pass: bounds and rows 6, what few workgroups have to measure and
+// to move 5, flags 1, 32 sums a thread 5).
 // Tried: as many copies of the sums as spread those additions (a copy more to read is a trip more: 179 -> 228 with two); a third and
 // fourth chunk of rows in flight (registers spill, 7 .. 20 % slower); a delay before the first look at the flags (alone it makes a
 // barrier of 256 workgroups 1.1 us instead of 2.4, here it is lost beside the waits for the last one to arrive).  The code has to
@@ -25,7 +31,6 @@ namespace cat {
 constexpr int kLoopT = 512, kLoopW = kLoopT / kWave;
 constexpr int kLoopMax = 256;      // workgroups
 constexpr int kLoopDirect = 16;    // changed rows of a workgroup that may go to the sums without the panel (see loop_lloyd)
-constexpr int kLoopAhead = 8;      // requests of a wave for the sums
 constexpr int kLoopList = 64;      // changed rows of a workgroup whose entries are kept in LDS too
 constexpr uint32_t kLoopClosed = 0x80000000u;
 
@@ -48,10 +53,23 @@ struct LoopParams {
     float tau, tau2;
     uint32_t off_cent, off_panel, off_small;
     int32_t W;                // channels of the panel, a multiple of 16
-    int32_t share;            // waves that share the channels of a tile: 1, 2, 4 or 8
+    int32_t share;            // waves that share the channels of a tile: 1, 2, 4 or 8 (BOUNDS: at most)
     int32_t direct;           // up to that many changed rows of a workgroup go to the sums without the panel
     int32_t looks, enough;    // the first workgroup waits that many looks for the others, and for no more than `enough`
+    // BOUNDS: the loop goes on after pass kLoopBounds of tile_lloyd, from that pass's sums but for the rows it listed
+    double* expire;           // N: the drift at which a row has to be looked at again (see TileParams)
+    int32_t* rows;            // N + 63: the members' lists of due rows
+    const uint32_t* list_count;
+    const int32_t* counts0;   // rows per cluster in that pass
+    const double* sumsq;      // kSumSqSlots shares of the sum of |x|^2
 };
+constexpr int kLoopBounds = 2;
+struct LoopQueued {  // a row that is measured when the workgroup has run out of tiles
+    uint32_t row;
+    int prev;
+    unsigned long long cand[2];
+};
+constexpr int kLoopQueue = 32;
 
 template <typename V>
 __device__ __forceinline__ V far_load(const V* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -93,6 +111,29 @@ __device__ __forceinline__ float sum_groups(float v) {  // over the four lanes n
     halves32(__float_as_uint(__uint_as_float(a) + __uint_as_float(b)), a, b);
     return __uint_as_float(a) + __uint_as_float(b);
 }
+// the two largest of what the lanes hold (v1 >= v2 >= 0 each), in all lanes
+template <int CTRL>
+__device__ __forceinline__ double dpp_value(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ void two_more(double& v1, double& v2, double o1, double o2) {
+    v2 = fmax(fmin(v1, o1), fmax(v2, o2));
+    v1 = fmax(v1, o1);
+}
+__device__ __forceinline__ void two_largest(double& v1, double& v2) {
+    two_more(v1, v2, dpp_value<0xB1>(v1), dpp_value<0xB1>(v2));
+    two_more(v1, v2, dpp_value<0x4E>(v1), dpp_value<0x4E>(v2));
+    two_more(v1, v2, dpp_value<0x141>(v1), dpp_value<0x141>(v2));
+    two_more(v1, v2, dpp_value<0x140>(v1), dpp_value<0x140>(v2));
+    double r1 = lane_double(v1, 0), r2 = lane_double(v2, 0);
+#pragma unroll
+    for (int l = 16; l < kWave; l += 16) two_more(r1, r2, lane_double(v1, l), lane_double(v2, l));
+    v1 = r1;
+    v2 = r2;
+}
 __device__ __forceinline__ void own_memory_done() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0);
@@ -123,7 +164,7 @@ __device__ __forceinline__ void near_dists(const unsigned char* xrow, int D, con
     d1 = wave_total(s1);
 }
 
-template <int KT, bool BF16>
+template <int KT, bool BF16, bool BOUNDS>
 __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     typedef typename std::conditional<BF16, bf16_t, float>::type T;
@@ -139,9 +180,12 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     int* s_n = (int*)(s_cnorm + KT * 16);             // KT * 16
     int* s_dn = s_n + KT * 16;                        // KT * 16
     uint32_t* s_mask = (uint32_t*)(s_dn + KT * 16);   // 4: own changes; 2 x 4: everybody's, by parity of the pass
-    int* s_misc = (int*)(s_mask + 12);                // [0] rank, [1] members, [2] rows that changed
-    unsigned long long* s_list = (unsigned long long*)(s_misc + 4);  // kLoopList
-    float* s_score = (float*)(s_list + kLoopList);    // kLoopW x KT * 16
+    int* s_misc = (int*)(s_mask + 12);                // [0] rank, [1] members, [2] rows that changed, [3] queued rows, [4] due rows
+    unsigned long long* s_list = (unsigned long long*)(s_misc + 8);  // kLoopList
+    LoopQueued* s_queue = (LoopQueued*)(s_list + kLoopList);  // kLoopQueue
+    float* s_score = (float*)(s_queue + kLoopQueue);  // kLoopW x KT * 16
+    double* s_mv = (double*)(s_score + kLoopW * KT * 16);  // BOUNDS, KT * 16 each: squared movements; the first member: the clusters'
+    double *s_obj = s_mv + KT * 16, *s_term = s_obj + KT * 16;  // terms of the objective as the centroids stand, and of the pass
 
     // ---- who takes part ----
     // The workgroups wait for each other, so those that wait must be resident: the members are the workgroups that have come when
@@ -150,24 +194,28 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     // members there are, so every wait ends whatever else runs, and nothing has to be known about the stream.
     if (tid == 0) {
         s_misc[0] = (int)__hip_atomic_fetch_add((uint32_t*)p.words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_misc[2] = 0;
+        s_misc[2] = s_misc[3] = s_misc[4] = 0;
     }
     if (tid < 12) s_mask[tid] = 0;
     for (int i = tid; i < (int)(p.off_cent / 16); i += kLoopT) ((u32x4*)smem)[i] = (u32x4){0u, 0u, 0u, 0u};
     for (int i = tid; i < K * W; i += kLoopT) s_panel[i] = 0.0;
     if (tid < KT * 16) {
-        s_n[tid] = s_dn[tid] = 0;
+        s_n[tid] = BOUNDS && tid < K ? p.counts0[tid] : 0;
+        s_dn[tid] = 0;
         s_cnorm[tid] = kPadNorm;
     }
     __syncthreads();
     const int rank = __builtin_amdgcn_readfirstlane(s_misc[0]);
     if ((uint32_t)rank & kLoopClosed) return;
-    if (rank == 0) {
+    auto clear_counts = [&]() {
         if (tid < K) {
             far_store(p.counts + tid, 0);
             far_store(p.rep + tid, ~0ull);
         }
-        if (tid == 0 && p.inertia) far_store(p.inertia + p.iters, 0.0);
+    };
+    if (rank == 0 && !BOUNDS) {
+        clear_counts();
+        if (!BOUNDS && tid == 0 && p.inertia) far_store(p.inertia + p.iters, 0.0);
         own_memory_done();
     }
 
@@ -197,22 +245,23 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             if (lane == 0) s_cnorm[k] = (float)nn;
         }
     };
-    // The centroids of the clusters in the mask from the sums: a wave takes whole clusters, 64 channels at a time, kLoopAhead
-    // requests before anything waits.
-    auto build = [&](const uint32_t* mask, const double* sums, const int32_t* dn) {
+    // The centroids of the clusters in the mask from the sums: a wave takes whole clusters, 64 channels at a time, AHEAD requests before anything waits.
+    constexpr int AHEAD = 8;
+    auto build = [&](const uint32_t* mask, const double* sums, const int32_t* dn, bool terms, bool last) {
         const int kd = wave + kLoopW * lane;  // lane j: the wave's cluster j
         const unsigned long long mine = __ballot(kd < K && (mask[(kd < K ? kd : 0) >> 5] >> (kd & 31) & 1u));
+        if (BOUNDS && kd < K) s_mv[kd] = 0.0;
         if (mine == 0ull) return;
         int rows = kd < K ? far_load(dn + kd) : 0;
-        double inv = 1.0;
+        double inv = 1.0, mv = 0.0, was = 0.0, now = 0.0;
         unsigned long long left = mine;
         int blk0 = 0;
         for (bool first = true; left; first = false) {
-            double v[kLoopAhead];
+            double v[AHEAD];
             unsigned long long m = left;
             int blk = blk0;
 #pragma unroll
-            for (int u = 0; u < kLoopAhead; u++) {
+            for (int u = 0; u < AHEAD; u++) {
                 const int j = m ? __builtin_ctzll(m) : 0, ch = blk * kWave + lane;
                 v[u] = far_load(sums + (wave + kLoopW * j) * D + (ch < D ? ch : 0));
                 if (++blk == nb) {
@@ -227,14 +276,39 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             m = left;
             blk = blk0;
 #pragma unroll
-            for (int u = 0; u < kLoopAhead; u++) {
-                const int j = m ? __builtin_ctzll(m) : 0, ch = blk * kWave + lane;
+            for (int u = 0; u < AHEAD; u++) {
+                const int j = m ? __builtin_ctzll(m) : 0, ch = blk * kWave + lane, k = wave + kLoopW * j;
                 const int c = __builtin_amdgcn_readlane(rows, j);
-                if (m && c > 0 && ch < D) {  // v / c: the product with the reciprocal, corrected once (Markstein: the rounded quotient)
-                    const double r = lane_double(inv, j), q0 = v[u] * r;
-                    s_cent[(wave + kLoopW * j) * Ds + ch] = (float)fma(fma(-q0, (double)c, v[u]), r, q0);
+                if (m && ch < D) {
+                    const float old = BOUNDS ? s_cent[k * Ds + ch] : 0.f;
+                    float f = old;
+                    if (c > 0 && !(BOUNDS && last)) {  // v / c: the product with the reciprocal, corrected once (Markstein: the rounded quotient)
+                        const double r = lane_double(inv, j), q0 = v[u] * r;
+                        s_cent[k * Ds + ch] = f = (float)fma(fma(-q0, (double)c, v[u]), r, q0);
+                    }
+                    if (BOUNDS) {
+                        const double d = (double)f - (double)old;
+                        mv = fma(d, d, mv);
+                        if (terms) {
+                            was += (double)old * ((double)c * (double)old - 2.0 * v[u]);
+                            now += (double)f * ((double)c * (double)f - 2.0 * v[u]);
+                        }
+                    }
                 }
                 if (++blk == nb) {
+                    if (BOUNDS && m) {
+                        mv = wave_total(mv);
+                        if (lane == 0) s_mv[k] = mv;
+                        if (terms) {
+                            was = wave_total(was);
+                            now = wave_total(now);
+                            if (lane == 0) {
+                                s_term[k] = was;
+                                s_obj[k] = now;
+                            }
+                        }
+                        mv = was = now = 0.0;
+                    }
                     blk = 0;
                     m &= m - 1;
                 }
@@ -242,7 +316,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             left = m;
             blk0 = blk;
         }
-        emit(mine);
+        if (!(BOUNDS && last)) emit(mine);
     };
     {
         int k = tid / D, ch = tid - k * D;
@@ -277,13 +351,27 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     }
     __syncthreads();
     const int M = __builtin_amdgcn_readfirstlane(s_misc[1]);
-    const int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * rank / M));
-    const int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * (rank + 1) / M));
-    const int64_t row_lo = (int64_t)t_lo * kRows;
-    unsigned long long* list = p.list + row_lo;
-    const int nchunks = (p.nsteps + 3) / 4, share = p.share, slots = kLoopW / share;
-    const int slot = wave / share, part = wave - slot * share;  // the wave's tile in a round, and its chunks of it
-    const int c_lo = nchunks * part / share, c_hi = nchunks * (part + 1) / share;
+    // The member's rows: consecutive tiles; BOUNDS: every M-th block of 64 (rows that are due lie together where the matrix is
+    // sorted), of which a pass takes those that are due.  Its part of the list holds as many entries as it has rows.
+    int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * rank / M));
+    int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * (rank + 1) / M));
+    int64_t row_lo = (int64_t)t_lo * kRows;
+    const uint32_t blocks64 = (uint32_t)((p.N + kWave - 1) / kWave);
+    const uint32_t per = blocks64 / (uint32_t)M, extra = blocks64 % (uint32_t)M, mine64 = per + ((uint32_t)rank < extra ? 1u : 0u);
+    int32_t* due = nullptr;
+    if (BOUNDS) {
+        row_lo = (int64_t)kWave * ((int64_t)rank * per + ((uint32_t)rank < extra ? (uint32_t)rank : extra));
+        due = p.rows + row_lo;
+        if ((p.N & (kWave - 1)) && (blocks64 - 1) % (uint32_t)M < (uint32_t)rank) row_lo -= kWave - (p.N & (kWave - 1));
+    }
+    unsigned long long* const own_list = p.list + row_lo;
+    const unsigned long long* list = own_list;
+    const int nchunks = (p.nsteps + 3) / 4;
+    int share = p.share, slots = kLoopW / share;
+    int slot = wave / share, part = wave - slot * share;  // the wave's tile in a round, and its chunks of it
+    int c_lo = nchunks * part / share, c_hi = nchunks * (part + 1) / share;
+    int n_due = 0, lrow = 0;
+    double gnow = 0.0, sq_total = 0.0;
     const int z_lo = (int)((int64_t)KD * rank / M), z_hi = (int)((int64_t)KD * (rank + 1) / M);  // the share of the sums to carry on
     double *sums = p.sums, *sums_next = p.sums + KD, *sums_prev = p.sums + 2 * KD;
     const int k_start = (rank + wave) % K;
@@ -295,13 +383,25 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     f32x4 acc[KT];
     float nrm = 0.f, cmax = 0.f;
     double in_acc = 0.0;
-    int t = 0, tl = 0, cl = 0, tc = 0, cc = 0;
+    int t = BOUNDS ? kLoopBounds : 0, tl = 0, cl = 0, tc = 0, cc = 0;
 #pragma unroll
     for (int u = 0; u < KT; u++) acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
     auto issue = [&](ChunkRegs<BF16>& r) {
         if (tl >= t_hi) return;
-        const int64_t r0 = (int64_t)tl * kRows + n;
-        const int64_t row = r0 < p.N ? r0 : p.N - 1;
+        int64_t row;
+        if (BOUNDS) {
+            if (cl == c_lo) {  // the number of the tile's row, and that of the tile after it
+                r.row = lrow;
+                const int e = (tl + slots) * kRows + n;
+                lrow = due[e < n_due ? e : n_due - 1];
+            } else {
+                r.row = cur.row;
+            }
+            row = r.row;
+        } else {
+            const int64_t r0 = (int64_t)tl * kRows + n;
+            row = r0 < p.N ? r0 : p.N - 1;
+        }
         r.prev = p.assign[row];
         const T* x = (const T*)p.lq + row * D;
         const int ch = cl * kChunk + (BF16 ? 8 : 4) * q;
@@ -323,6 +423,10 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     auto restart = [&]() {
         tl = tc = t_lo + slot;
         cl = cc = c_lo;
+        if (BOUNDS && tl < t_hi) {
+            const int e = tl * kRows + n;
+            lrow = due[e < n_due ? e : n_due - 1];
+        }
         issue(cur);
     };
     auto contract = [&](const ChunkRegs<BF16>& r) {
@@ -372,9 +476,65 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             }
         }
     };
-    auto finish = [&](int prev_in) {
+    // a row's cluster (the lanes with `on` hold one each): the label, and the lists of what changed
+    auto book = [&](bool on, int64_t row, int prev, int k) {
+        const bool changed = on && prev != k;
+        const unsigned long long cm = __ballot(changed);
+        if (!cm) return;
+        int pos = 0;
+        if (lane == 0) pos = atomicAdd(&s_misc[2], (int)__builtin_popcountll(cm));
+        pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(cm & ((1ull << lane) - 1ull));
+        if (changed) {
+            p.assign[row] = k;
+            const unsigned long long ent = ((unsigned long long)row << 24) | ((unsigned long long)(prev + 1) << 12) | (unsigned long long)k;
+            own_list[pos] = ent;
+            if (pos < kLoopList) s_list[pos] = ent;
+            atomicAdd(&s_dn[k], 1);
+            atomicOr(&s_mask[k >> 5], 1u << (k & 31));
+            if (prev >= 0) {
+                atomicAdd(&s_dn[prev], -1);
+                atomicOr(&s_mask[prev >> 5], 1u << (prev & 31));
+            }
+        }
+    };
+    // exact distances of a row to the clusters of `cand`, by the whole wave: the nearest, the lowest one on ties (0x7fffffff: no
+    // distance compares)
+    constexpr int NC = (KT + 3) / 4;
+    auto measure = [&](int64_t row, unsigned long long (&cand)[NC], double& dbest) {
+        dbest = __builtin_inf();
+        int kbest = 0x7fffffff;
+        const unsigned char* xrow = (const unsigned char*)p.lq + row * D * (int64_t)sizeof(T);
+        auto take = [&]() {  // the lowest candidate left; 0x7fffffff: none
+            int k = 0x7fffffff;
+#pragma unroll
+            for (int w = NC - 1; w >= 0; w--)
+                if (cand[w]) k = 64 * w + __builtin_ctzll(cand[w]);
+#pragma unroll
+            for (int w = 0; w < NC; w++)
+                if (k >> 6 == w) cand[w] &= cand[w] - 1;
+            return __builtin_amdgcn_readfirstlane(k);
+        };
+        for (int ka = take(); ka != 0x7fffffff; ka = take()) {
+            int kb = take();
+            if (kb == 0x7fffffff) kb = ka;
+            double da, db;
+            near_dists<BF16>(xrow, D, s_cent + ka * Ds, s_cent + kb * Ds, lane, da, db);
+            if (da < dbest) {  // (ascending: an equal one later does not win)
+                dbest = da;
+                kbest = ka;
+            }
+            if (db < dbest) {
+                dbest = db;
+                kbest = kb;
+            }
+        }
+        return kbest;
+    };
+    auto finish = [&](int prev_in, int row_in) {
         const int64_t row0 = (int64_t)tc * kRows;
-        const bool valid = row0 + n < p.N;
+        const int64_t row = BOUNDS ? (int64_t)row_in : row0 + n;
+        const bool valid = BOUNDS ? tc * kRows + n < n_due : row < p.N;
+        const int prev = !BOUNDS && t == 0 ? -1 : prev_in;
         const float xn2 = sum_groups(nrm);
         float f1 = __builtin_inff(), f2 = __builtin_inff();
         int i1 = 0;
@@ -411,8 +571,10 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         i1 = i1 < K ? i1 : K - 1;  // (no real score compares: non-finite input)
         float dmin = fmaxf(xn2 + f1, 0.f);
         const float thr_in = p.tau * sqrtf(xn2) * cmax + p.tau2 * cmax * cmax;
-        unsigned long long mask = __ballot(valid && !(f2 - f1 > thr_in) && q == 0);
-        while (mask) {  // rows whose two best are within the error bound: exact distances of all within it
+        const bool near = valid && !(f2 - f1 > thr_in);
+        bool queued = false;
+        unsigned long long mask = __ballot(near && q == 0);
+        while (mask) {  // rows whose two best are within the error bound: all within it are measured
             const int r = __builtin_amdgcn_readfirstlane(__builtin_ctzll(mask));
             mask &= mask - 1;
             const float thr = readlane_f(f1, r) + readlane_f(thr_in, r);
@@ -420,39 +582,31 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
 #pragma unroll
             for (int u = 0; u < KT; u++)
                 if (n == r) *(f32x4*)(sc + 16 * u + 4 * q) = acc[u];
-            unsigned long long cand[(KT + 3) / 4];
+            unsigned long long cand[NC];
 #pragma unroll
-            for (int w = 0; w < (KT + 3) / 4; w++) {
+            for (int w = 0; w < NC; w++) {
                 const int k = 64 * w + lane;
                 cand[w] = __ballot(k < K && fmaf(-2.f, sc[k < K ? k : 0], s_cnorm[k < K ? k : 0]) <= thr);
             }
-            double dbest = __builtin_inf();
-            int kbest = 0x7fffffff;
-            const unsigned char* xrow = (const unsigned char*)p.lq + (row0 + r) * D * (int64_t)sizeof(T);
-            auto take = [&]() {  // the lowest candidate left; 0x7fffffff: none
-                int k = 0x7fffffff;
-#pragma unroll
-                for (int w = (KT + 3) / 4 - 1; w >= 0; w--)
-                    if (cand[w]) k = 64 * w + __builtin_ctzll(cand[w]);
-#pragma unroll
-                for (int w = 0; w < (KT + 3) / 4; w++)
-                    if (k >> 6 == w) cand[w] &= cand[w] - 1;
-                return __builtin_amdgcn_readfirstlane(k);
-            };
-            for (int ka = take(); ka != 0x7fffffff; ka = take()) {
-                int kb = take();
-                if (kb == 0x7fffffff) kb = ka;
-                double da, db;
-                near_dists<BF16>(xrow, D, s_cent + ka * Ds, s_cent + kb * Ds, lane, da, db);
-                if (da < dbest) {  // (ascending: an equal one later does not win)
-                    dbest = da;
-                    kbest = ka;
+            const int64_t xr = ((int64_t)__builtin_amdgcn_readlane((int)(row >> 32), r) << 32) | (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)row, r);
+            int pos = kLoopQueue;
+            if (BOUNDS && lane == 0 && (cand[0] | cand[NC - 1]) != 0ull) pos = atomicAdd(&s_misc[3], 1);
+            pos = __builtin_amdgcn_readfirstlane(pos);
+            if (BOUNDS && pos < kLoopQueue) {  // by any wave, when all tiles are done
+                const int pv = __builtin_amdgcn_readlane(prev, r);
+                if (lane == 0) {
+                    LoopQueued e;
+                    e.row = (uint32_t)xr;
+                    e.prev = pv;
+                    e.cand[0] = cand[0];
+                    e.cand[1] = NC > 1 ? cand[NC - 1] : 0ull;
+                    s_queue[pos] = e;
                 }
-                if (db < dbest) {
-                    dbest = db;
-                    kbest = kb;
-                }
+                if (n == r) queued = true;
+                continue;
             }
+            double dbest;
+            const int kbest = measure(xr, cand, dbest);
             if (n == r && kbest != 0x7fffffff) {
                 i1 = kbest;
                 dmin = (float)dbest;
@@ -461,35 +615,92 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
 #pragma unroll
         for (int u = 0; u < KT; u++) acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
         nrm = 0.f;
-        const int prev = t == 0 ? -1 : prev_in;
-        const bool owner = q == 0 && valid;
-        const bool changed = owner && prev != i1;
-        if (owner) in_acc += (double)dmin;
-        const unsigned long long cm = __ballot(changed);
-        if (cm) {
-            int pos = 0;
-            if (lane == 0) pos = atomicAdd(&s_misc[2], (int)__builtin_popcountll(cm));
-            pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(cm & ((1ull << lane) - 1ull));
-            if (changed) {
-                p.assign[row0 + n] = i1;
-                const unsigned long long ent =
-                    ((unsigned long long)(row0 + n) << 16) | ((unsigned long long)(prev + 1) << 8) | (unsigned long long)i1;
-                list[pos] = ent;
-                if (pos < kLoopList) s_list[pos] = ent;
-                atomicAdd(&s_dn[i1], 1);
-                atomicOr(&s_mask[i1 >> 5], 1u << (i1 & 31));
-                if (prev >= 0) {
-                    atomicAdd(&s_dn[prev], -1);
-                    atomicOr(&s_mask[prev >> 5], 1u << (prev & 31));
-                }
+        const bool owner = q == 0 && valid && !queued;
+        if (!BOUNDS && owner) in_acc += (double)dmin;
+        if (BOUNDS && owner) {
+            // as in finish_tile (cat_tile_kernel.h): the drift that leaves the nearest centroid the nearest
+            double m = 0.0;
+            if (!near) {
+                const double e = (double)thr_in + (double)xn2 * (double)D * 1.5e-8;
+                const double hi1 = (double)xn2 + (double)f1 + e, lo2 = (double)xn2 + (double)f2 - e;
+                if (lo2 > hi1) m = (sqrt(lo2) - sqrt(hi1 > 0.0 ? hi1 : 0.0)) * (1.0 - 1e-9);
             }
+            p.expire[row] = gnow + m;
+        }
+        book(owner, row, prev, i1);
+    };
+
+    constexpr uint32_t U = 4;  // blocks of a wave whose rows' bounds are requested at once
+    double ex[U];
+    auto bounds_of = [&](uint32_t i0) {
+#pragma unroll
+        for (uint32_t u = 0; u < U; u++) {
+            const uint32_t i = i0 + kLoopW * u;
+            const int64_t r = (int64_t)kWave * ((int64_t)rank + (int64_t)M * (i < mine64 ? i : mine64 - 1)) + lane;
+            ex[u] = p.expire[r < p.N ? r : p.N - 1];
         }
     };
 
     bool settled = false;
-    restart();
+    int e0 = 0, e1 = 0;  // BOUNDS: the member's share of the rows that the pass before the first listed
+    if (BOUNDS) {
+        const int64_t len = (int64_t)*p.list_count;
+        e0 = (int)(len * rank / M);
+        e1 = (int)(len * (rank + 1) / M);
+        list = p.list + e0;
+        if (tid < 4) s_mask[tid] = ~0u;
+        if (rank == 0) sq_total = wave_total(p.sumsq[lane * kSumSqStride]);
+        static_assert(kSumSqSlots == kWave, "one share a lane");
+        if (tid == 0) s_misc[2] = e1 - e0;
+        __syncthreads();
+    } else {
+        restart();
+    }
     for (;; t++) {
         // ---- assignment of the own rows ----
+        if (BOUNDS && t > kLoopBounds) {
+            // how far the centroids have moved in all (select_rows in cat_tile_kernel.h), and the rows that are due
+            double v1 = lane < K ? s_mv[lane] : 0.0, v2 = 0.0;
+            if (KT > 4) {
+                const double o = lane + kWave < K ? s_mv[lane + kWave] : 0.0;
+                v2 = fmin(v1, o);
+                v1 = fmax(v1, o);
+            }
+            v1 = fmax(sqrt(v1), 0.0);
+            v2 = fmax(sqrt(v2), 0.0);
+            two_largest(v1, v2);
+            const double g0 = gnow;
+            gnow = g0 + (v1 + v2) * (1.0 + 1e-9);
+            if (v1 + v2 > 0.0 && gnow == g0) gnow = __longlong_as_double(__double_as_longlong(g0) + 1);  // (drifts are >= 0)
+            for (uint32_t i0 = (uint32_t)wave; i0 < mine64; i0 += U * kLoopW) {
+                if (i0 != (uint32_t)wave) bounds_of(i0);
+#pragma unroll
+                for (uint32_t u = 0; u < U; u++) {
+                    const uint32_t i = i0 + kLoopW * u;
+                    const int64_t r = (int64_t)kWave * ((int64_t)rank + (int64_t)M * i) + lane;
+                    const bool is_due = i < mine64 && r < p.N && !(gnow <= ex[u]);
+                    const unsigned long long m = __ballot(is_due);
+                    if (!m) continue;
+                    int pos = 0;
+                    if (lane == 0) pos = atomicAdd(&s_misc[4], (int)__builtin_popcountll(m));
+                    pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+                    if (is_due) due[pos] = (int32_t)r;
+                }
+            }
+            __syncthreads();
+            n_due = __builtin_amdgcn_readfirstlane(s_misc[4]);
+            t_lo = 0;
+            t_hi = (n_due + kRows - 1) / kRows;
+            share = 1;
+            while (2 * share <= p.share && t_hi * 2 * share <= kLoopW) share *= 2;
+            slots = kLoopW / share;
+            slot = wave / share;
+            part = wave - slot * share;
+            c_lo = nchunks * part / share;
+            c_hi = nchunks * (part + 1) / share;
+            list = own_list;
+            restart();
+        }
         {
             float c2 = 0.f;
             for (int k = lane; k < K; k += kWave) c2 = fmaxf(c2, s_cnorm[k]);
@@ -504,16 +715,18 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         // everybody did before raising the flag of pass t - 1: it is free now, and clear before the flags of pass t.
         // The share of the sums so far moves on to this pass's, and the buffers of the pass that follows are cleared.
         for (int i = z_lo + tid; i < z_hi; i += kLoopT) {
-            if (i != z_lo + tid && t > 0) carry = far_load(sums_prev + i);
+            if (i != z_lo + tid) carry = t > (BOUNDS ? kLoopBounds : 0) ? far_load(sums_prev + i) : 0.0;
             if (carry != 0.0) atomicAdd(sums + i, carry);
             far_store(sums_next + i, 0.0);
         }
         if (rank == 0 && tid < K) far_store(dn_next + tid, 0);
+        if (BOUNDS && rank == 0 && t == kLoopBounds + 1) clear_counts();  // (counts0 may be the same array: everybody has read it)
         in_acc = 0.0;
-        int prev = -1;
-        for (int first = t_lo; first < t_hi; first += slots) {  // a round: every slot one tile
+        int prev = -1, row = 0;
+        for (int first = t_lo; first < (BOUNDS && t == kLoopBounds ? t_lo : t_hi); first += slots) {  // a round: every slot one tile
             if (tc < t_hi) {
                 prev = cur.prev;
+                row = cur.row;
                 while (cc < c_hi) {
                     issue(next);
                     contract(cur);
@@ -549,23 +762,41 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                     }
                 }
             }
-            if (part == 0 && tc < t_hi) finish(prev);
+            if (part == 0 && tc < t_hi) finish(prev, row);
             cc = c_lo;
             tc += slots;
         }
-        in_acc = wave_total(in_acc);
-        if (lane == 0) s_in[wave] = in_acc;
+        if (BOUNDS) {
+            __syncthreads();
+            const int pushed = __builtin_amdgcn_readfirstlane(s_misc[3]), qn = pushed < kLoopQueue ? pushed : kLoopQueue;
+            for (int e = wave; e < qn; e += kLoopW) {
+                const LoopQueued w = s_queue[e];
+                unsigned long long cand[NC];
+                cand[0] = w.cand[0];
+                if (NC > 1) cand[NC - 1] = w.cand[1];
+                const int first = cand[0] ? __builtin_ctzll(cand[0]) : kWave + __builtin_ctzll(cand[NC - 1]);
+                double dbest;
+                int k = measure((int64_t)w.row, cand, dbest);
+                if (k == 0x7fffffff) k = first;  // (non-finite input: any of them)
+                if (lane == 0) p.expire[w.row] = gnow;  // two centroids within the bound of each other: no margin
+                book(lane == 0, (int64_t)w.row, w.prev, k);
+            }
+        }
+        if (!BOUNDS) {
+            in_acc = wave_total(in_acc);
+            if (lane == 0) s_in[wave] = in_acc;
+        }
         own_memory_done();
         __syncthreads();
-        if (t == p.iters) break;
+        if (!BOUNDS && t == p.iters) break;
 
         // ---- the rows that changed cluster move between the sums ----
         const int nch = __builtin_amdgcn_readfirstlane(s_misc[2]);
         if (nch > 0 && nch <= p.direct) {
-            const unsigned long long ent = s_list[lane < nch ? lane : 0];
+            const unsigned long long ent = BOUNDS && t == kLoopBounds ? list[lane < nch ? lane : 0] : s_list[lane < nch ? lane : 0];
             const uint32_t e_lo = (uint32_t)ent, e_hi = (uint32_t)(ent >> 32);
             const int blocks = (D + kWave - 1) / kWave, items = nch * blocks;
-            constexpr int U = 4;
+            constexpr int U = BOUNDS ? 8 : 4;  // rows and blocks requested at once
             for (int i0 = wave; i0 < items; i0 += U * kLoopW) {
                 float x[U];
                 int ch[U], nw[U], od[U];
@@ -575,9 +806,9 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                     const int e = it / blocks;
                     ch[u] = (it - e * blocks) * kWave + lane;
                     const uint32_t lo = __builtin_amdgcn_readlane(e_lo, e), hi = __builtin_amdgcn_readlane(e_hi, e);
-                    const int64_t row = (int64_t)(((unsigned long long)hi << 16) | (lo >> 16));
-                    nw[u] = (int)(lo & 0xFFu);
-                    od[u] = (int)((lo >> 8) & 0xFFu) - 1;
+                    const int64_t row = (int64_t)(((unsigned long long)hi << 8) | (lo >> 24));
+                    nw[u] = (int)(lo & 0xFFFu);
+                    od[u] = (int)((lo >> 12) & 0xFFFu) - 1;
                     x[u] = ld_elem((const T*)p.lq + row * D + (ch[u] < D ? ch[u] : 0));
                 }
 #pragma unroll
@@ -606,9 +837,9 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                             for (int u = 0; u < RB; u++) {
                                 const int i = i0 + u < nb ? i0 + u : nb - 1;
                                 const uint32_t lo = __builtin_amdgcn_readlane(e_lo, i), hi = __builtin_amdgcn_readlane(e_hi, i);
-                                const int64_t row = (int64_t)(((unsigned long long)hi << 16) | (lo >> 16));
-                                nw[u] = i0 + u < nb ? (int)(lo & 0xFFu) : -1;
-                                od[u] = i0 + u < nb ? (int)((lo >> 8) & 0xFFu) - 1 : -1;
+                                const int64_t row = (int64_t)(((unsigned long long)hi << 8) | (lo >> 24));
+                                nw[u] = i0 + u < nb ? (int)(lo & 0xFFFu) : -1;
+                                od[u] = i0 + u < nb ? (int)((lo >> 12) & 0xFFFu) - 1 : -1;
                                 const T* xr = (const T*)p.lq + row * D + c0;
 #pragma unroll
                                 for (int w = 0; w < CB; w++) {
@@ -644,14 +875,14 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                 if (c0 + W < D) __syncthreads();
             }
         }
-        if (nch > 0) {
-            if (tid < K) {
-                const int d = s_dn[tid];
-                if (d) {
-                    atomicAdd(dn + tid, d);
-                    s_dn[tid] = 0;
-                }
+        if (nch > 0 && tid < K) {
+            const int d = s_dn[tid];
+            if (d) {
+                atomicAdd(dn + tid, d);
+                s_dn[tid] = 0;
             }
+        }
+        if (nch > 0) {
             own_memory_done();
             __syncthreads();
         }
@@ -663,14 +894,17 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             s_mask[4 + 4 * (par ^ 1) + tid] = 0;
         }
         if (tid == 0) {
-            double v = 0.0;
+            if (!BOUNDS) {
+                double v = 0.0;
 #pragma unroll
-            for (int w = 0; w < kLoopW; w++) v += s_in[w];
-            tagged_store(flags + NM * G + rank, G, v, (uint32_t)(t + 1));
-            s_misc[2] = 0;
+                for (int w = 0; w < kLoopW; w++) v += s_in[w];
+                tagged_store(flags + NM * G + rank, G, v, (uint32_t)(t + 1));
+            }
+            s_misc[2] = s_misc[3] = s_misc[4] = 0;
         }
-        // ---- wait for the others; the first rows of the next pass travel meanwhile ----
-        restart();
+        // ---- wait for the others; the first rows (bounds) of the next pass travel meanwhile ----
+        if (BOUNDS) bounds_of((uint32_t)wave);
+        else restart();
         for (int i0 = wave * kWave; i0 < NM * kLoopMax; i0 += kLoopT) {
             const int w = i0 / kLoopMax, m0 = i0 - w * kLoopMax;
             if (m0 >= M) continue;
@@ -681,7 +915,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             if (bits) atomicOr(&s_mask[4 + 4 * par + w], bits);
         }
         __syncthreads();
-        if (rank == 0 && wave == kLoopW - 1 && p.inertia) {
+        if (!BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia) {
             double v = 0.0;
             for (int m = lane; m < M; m += kWave) v += tagged_load(flags + NM * G + m, G, (uint32_t)(t + 1));
             v = wave_total(v);
@@ -696,9 +930,19 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             break;
         }
         // ---- the next centroids ----
+        const bool last = BOUNDS && t == p.iters;
+        if (last && rank != 0) break;
         if (z_lo + tid < z_hi) carry = far_load(sums + z_lo + tid);
-        build(mask, sums, dn);
+        build(mask, sums, dn, BOUNDS && rank == 0 && p.inertia, last);
         __syncthreads();
+        if (BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia && t > kLoopBounds) {
+            // sum |x|^2 + sum_k c_k . (n_k c_k - 2 S_k), the centroids as they were in this pass
+            double v = 0.0;
+            for (int k = lane; k < K; k += kWave) v += mask[k >> 5] >> (k & 31) & 1u ? s_term[k] : s_obj[k];
+            v = wave_total(v) + sq_total;
+            if (lane == 0) p.inertia[t] = v > 0.0 ? v : (v == v ? 0.0 : v);
+        }
+        if (last) break;
         {
             double* s = sums_prev;
             sums_prev = sums;
@@ -712,16 +956,23 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     }
 
     // ---- what is returned ----
-    if (!settled && tid == 0 && p.inertia) {
+    if (!BOUNDS && !settled && tid == 0 && p.inertia) {
         double v = 0.0;
 #pragma unroll
         for (int w = 0; w < kLoopW; w++) v += s_in[w];
         atomicAdd(p.inertia + p.iters, v);
     }
     if (settled && rank == 0 && wave == kLoopW - 1 && p.inertia) {
-        own_memory_done();  // (the entry of this pass, by this wave)
-        const double v = p.inertia[t];
-        for (int i = t + 1 + lane; i <= p.iters; i += kWave) p.inertia[i] = v;
+        double v = 0.0;
+        if (BOUNDS) {
+            for (int k = lane; k < K; k += kWave) v += s_obj[k];
+            v = wave_total(v) + sq_total;
+            v = v > 0.0 ? v : (v == v ? 0.0 : v);
+        } else {
+            own_memory_done();  // (the entry of this pass, by this wave)
+            v = p.inertia[t];
+        }
+        for (int i = t + (BOUNDS ? 0 : 1) + lane; i <= p.iters; i += kWave) p.inertia[i] = v;
     }
     if (rank == 0 && tid == 0 && p.skipped) *p.skipped = settled && p.iters - 1 > (t > 2 ? t : 2) ? p.iters - 1 - (t > 2 ? t : 2) : 0;
     int* s_hist = s_dn;
@@ -731,11 +982,22 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         s_rep[tid] = ~0ull;
     }
     __syncthreads();
-    const int64_t row_hi = (int64_t)t_hi * kRows < p.N ? (int64_t)t_hi * kRows : p.N;
-    for (int64_t i = row_lo + tid; i < row_hi; i += kLoopT) {
-        const int a = p.assign[i];
-        atomicAdd(&s_hist[a], 1);
-        atomicMin(&s_rep[a], (unsigned long long)i);
+    if (BOUNDS) {
+        for (uint32_t i = (uint32_t)wave; i < mine64; i += kLoopW) {
+            const int64_t r = (int64_t)kWave * ((int64_t)rank + (int64_t)M * i) + lane;
+            if (r < p.N) {
+                const int a = p.assign[r];
+                atomicAdd(&s_hist[a], 1);
+                atomicMin(&s_rep[a], (unsigned long long)r);
+            }
+        }
+    } else {
+        const int64_t row_hi = (int64_t)t_hi * kRows < p.N ? (int64_t)t_hi * kRows : p.N;
+        for (int64_t i = row_lo + tid; i < row_hi; i += kLoopT) {
+            const int a = p.assign[i];
+            atomicAdd(&s_hist[a], 1);
+            atomicMin(&s_rep[a], (unsigned long long)i);
+        }
     }
     __syncthreads();
     if (tid < K && s_hist[tid]) {
@@ -754,7 +1016,7 @@ struct LoopCfg {
     uint32_t off_cent = 0, off_panel = 0, off_small = 0;
     size_t lds = 0;
 };
-static LoopCfg loop_config(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
+static LoopCfg loop_config(int64_t N, int64_t D, int32_t K, cat_dtype dt, bool bounds = false) {
     LoopCfg c;
     if (N < 256 || N >= ((int64_t)1 << 31) - 16 || K > 128 || D % (dt == CAT_BF16 ? 8 : 4) || (K + 15) / 16 * 16 * D > 16384) return c;
     c.KT = 1;
@@ -762,7 +1024,8 @@ static LoopCfg loop_config(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     c.nsteps = (int)((D + 31) / 32);
     c.off_cent = (uint32_t)(c.nsteps * c.KT * 2048);
     c.off_panel = c.off_cent + (uint32_t)(K * (D + 4) * 4);
-    const size_t small = (size_t)c.KT * 16 * (4 + 4 + 4) + kLoopW * 8 + 16 * 4 + kLoopList * 8 + (size_t)kLoopW * c.KT * 16 * 4;
+    const size_t small = (size_t)c.KT * 16 * (4 + 4 + 4) + kLoopW * 8 + 20 * 4 + kLoopList * 8 + kLoopQueue * sizeof(LoopQueued) +
+                         (size_t)kLoopW * c.KT * 16 * 4 + (bounds ? 3 * (size_t)c.KT * 16 * 8 : 0);
     if (c.off_panel + small + (size_t)K * 16 * 8 > kLdsLimit) return c;
     int64_t W = (int64_t)((kLdsLimit - small - c.off_panel) / ((size_t)K * 8)) / 16 * 16;
     const int64_t Dr = (D + 15) / 16 * 16;
@@ -790,19 +1053,19 @@ __global__ __launch_bounds__(256) void k_loop_clear(unsigned long long* a, int n
     if (i < nb) b[i] = 0.0;
 }
 
-template <int KT, bool BF16>
+template <int KT, bool BF16, bool BOUNDS>
 static cat_status launch_loop(const LoopParams& p, const LoopCfg& c, int groups, hipStream_t st) {
-    auto kern = k_lloyd_loop<KT, BF16>;
+    auto kern = k_lloyd_loop<KT, BF16, BOUNDS>;
     CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
     hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kLoopT), c.lds, st, p);
     CAT_LAUNCH_CHECK("k_lloyd_loop");
     return CAT_OK;
 }
 
-cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,
-                      int32_t* assign, int32_t* counts, double* inertia, unsigned long long* rep, int32_t* skipped,
-                      const LloydWs& lw, hipStream_t st) {
-    const LoopCfg c = loop_config(N, D, K, dt);
+static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,
+                           int32_t* assign, int32_t* counts, double* inertia, unsigned long long* rep, int32_t* skipped,
+                           const LloydWs& lw, const LoopBounds* lb, hipStream_t st) {
+    const LoopCfg c = loop_config(N, D, K, dt, lb != nullptr);
     if (!c.ok) return set_error(CAT_ERR_UNSUPPORTED, "loop in one launch: N=%lld D=%lld K=%d", (long long)N, (long long)D, (int)K);
     LoopParams p = {};
     p.lq = lq;
@@ -820,6 +1083,13 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     p.skipped = skipped;
     p.sums = sums;
     p.list = lw.list;
+    if (lb) {
+        p.expire = lb->expire;
+        p.rows = lb->rows;
+        p.list_count = lb->list_count;
+        p.counts0 = lb->counts;
+        p.sumsq = lw.sumsq;
+    }
     p.tau2 = 4.0e-7f;
     p.off_cent = c.off_cent;
     p.off_panel = c.off_panel;
@@ -837,20 +1107,21 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     // one wave a tile / as here: 2958 x 984 bf16, K = 14: 159 / 115 (8 waves); 2652 x 640, K = 11: 279 / 187 (4); 7294 x 776, K = 3: 133 / 115 (4);
     // 14629 x 998 bf16, K = 4: 273 / 230 (2)
     p.share = 1;
-    while (p.share < kLoopW && 2 * p.share <= (c.nsteps + 3) / 4 && (int64_t)p.ntiles * 2 * p.share <= (int64_t)v * kLoopW &&
+    while (p.share < kLoopW && 2 * p.share <= (c.nsteps + 3) / 4 && (lb || (int64_t)p.ntiles * 2 * p.share <= (int64_t)v * kLoopW) &&
            (size_t)(kLoopW - kLoopW / (2 * p.share)) * (c.KT * 1024 + 256) <= (size_t)K * c.W * 8)
         p.share *= 2;
     // the error bound of the split arithmetic as in the tile kernels (cat_tile.hip: base_params); shared channels are added up once more
     const int n_acc = (dt == CAT_BF16 ? 2 : 3) * ((c.nsteps + 3) / 4 * 4) + 8 + (p.share - 1);
     p.tau = (dt == CAT_BF16 ? 3.1e-5f : 9.4e-5f) + 4.f * (float)n_acc * 5.96e-8f;
-    int groups = (p.ntiles * p.share + kLoopW - 1) / kLoopW;
+    int groups = lb ? v : (p.ntiles * p.share + kLoopW - 1) / kLoopW;
+    if (lb && groups > (N + kWave - 1) / kWave) groups = (int)((N + kWave - 1) / kWave);
     if (groups > v) groups = v;
     if (groups > kLoopMax) groups = kLoopMax;
     // Rows that go to the sums directly come to 2 rows / K additions an address and workgroup, through the panel to one at most; all
     // workgroups add to the same addresses.  us per cat_fit with up to 2 / 4 / 16 rows directly: 89551 x 128 bf16, K = 7 (256 workgroups)
     // 242 / 268 / 308; 7294 x 776, K = 3 (228) 115 / 115 / 150; 14629 x 998 bf16, K = 4 (229) 249 / 228 / 233; 4096 x 64, K = 4 (32)
     // 194 / 189 / 188; 2652 x 640, K = 11 192 / 185 / 186.
-    p.direct = 64 * K / groups;
+    p.direct = 64 * K / groups * (int)((D + c.W - 1) / c.W);
     if (p.direct < 3) p.direct = 3;
     if (p.direct > kLoopDirect) p.direct = kLoopDirect;
     const int members = g_loop_members.load();
@@ -860,16 +1131,37 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     const int nm = c.KT < 4 ? 1 : c.KT / 2;
     p.words = (unsigned long long*)lw.sort_ws;
     p.dn = (int32_t*)(p.words + 8 + 2 * (nm + 2) * groups);
-    const int nwords = 8 + 2 * (nm + 2) * groups + (K + 1) / 2, nsums = K * (int)D;
+    const int nwords = 8 + 2 * (nm + 2) * groups + (K + 1) / 2, nsums = lb ? 0 : K * (int)D;
     hipLaunchKernelGGL(k_loop_clear, dim3((unsigned)(((nwords > nsums ? nwords : nsums) + 255) / 256)), dim3(256), 0, st, p.words, nwords, sums, nsums);
     CAT_LAUNCH_CHECK("k_loop_clear");
     const bool bf = dt == CAT_BF16;
+#define CAT_LOOP(KT)                                                                                                          \
+    (lb ? bf ? launch_loop<KT, true, true>(p, c, groups, st) : launch_loop<KT, false, true>(p, c, groups, st)                  \
+        : bf ? launch_loop<KT, true, false>(p, c, groups, st) : launch_loop<KT, false, false>(p, c, groups, st))
     switch (c.KT) {
-        case 1: return bf ? launch_loop<1, true>(p, c, groups, st) : launch_loop<1, false>(p, c, groups, st);
-        case 2: return bf ? launch_loop<2, true>(p, c, groups, st) : launch_loop<2, false>(p, c, groups, st);
-        case 4: return bf ? launch_loop<4, true>(p, c, groups, st) : launch_loop<4, false>(p, c, groups, st);
-        default: return bf ? launch_loop<8, true>(p, c, groups, st) : launch_loop<8, false>(p, c, groups, st);
+        case 1: return CAT_LOOP(1);
+        case 2: return CAT_LOOP(2);
+        case 4: return CAT_LOOP(4);
+        default: return CAT_LOOP(8);
     }
+#undef CAT_LOOP
+}
+
+cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,
+                      int32_t* assign, int32_t* counts, double* inertia, unsigned long long* rep, int32_t* skipped,
+                      const LloydWs& lw, hipStream_t st) {
+    return run_loop(lq, dt, N, D, K, iters, cent_io, sums, assign, counts, inertia, rep, skipped, lw, nullptr, st);
+}
+
+bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
+    return g_loop_members.load() >= 0 && lloyd_list_capacity() == kListCap && rerank_queue_capacity() == kQueueCap && !profile_on() &&
+           loop_config(N, D, K, dt, true).ok;
+}
+
+cat_status loop_lloyd_bounds(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,
+                             int32_t* assign, int32_t* counts, double* inertia, unsigned long long* rep, const LloydWs& lw,
+                             const LoopBounds& lb, hipStream_t st) {
+    return run_loop(lq, dt, N, D, K, iters, cent_io, sums, assign, counts, inertia, rep, nullptr, lw, &lb, st);
 }
 
 }  // namespace cat

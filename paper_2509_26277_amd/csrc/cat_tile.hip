@@ -2,6 +2,7 @@
 // driver) and the centroid preparation kernel.  The tile kernel itself is in cat_tile_kernel.h.
 #include "cat_tile_kernel.h"
 #include "cat_infer.h"
+#include "cat_loop.h"
 #include "cat_wide.h"
 
 namespace cat {
@@ -1002,6 +1003,10 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
             CAT_T(dt == CAT_BF16 ? launch_bounds_bf16(p, c, st) : launch_bounds_f32(p, c, st));
         else
             CAT_T(launch_tile(p, c, dt, st));
+        if (t == kFullPasses && bounds && record && one_launch && loop_bounds_pays(N, D, K, dt)) {
+            const LoopBounds lb = {bw->expire, bw->rows, p.list_count, cnt_t};
+            return loop_lloyd_bounds(lq, dt, N, D, K, iters, cent_io, sums, assign, counts, inertia, rep, lw, lb, st);
+        }
         if (t < kFullPasses && !last) {  // full sums of this pass's partition (launch_prep has cleared them)
             if (lw.sort_ws && segsum_sorted_supported(1, N, D, dt))
                 CAT_T(launch_segsum_sorted(1, lq, nullptr, dt, assign, cnt_t, N, D, K, nullptr, nullptr, base, lw.sort_ws, st,
