@@ -16,11 +16,11 @@ _ROOT = os.path.dirname(_HERE)
 CSRC = os.path.join(_HERE, "csrc")
 # (the files that take longest to compile come first: they start at once and the rest fills in beside them)
 SOURCES = ["cat_tile_k16_f32.hip", "cat_tile_k16_bf16.hip", "cat_tile_k16_f32_p1.hip", "cat_tile_k16_bf16_p1.hip",
-           "cat_tile_bounds_f32.hip", "cat_tile_bounds_bf16.hip", "cat_infer.hip", "cat_wide.hip", "cat_direct.hip", "cat_loop.hip", "cat_api.hip", "cat_stream.hip", "cat_tile.hip",
+           "cat_tile_bounds_f32.hip", "cat_tile_bounds_bf16.hip", "cat_infer.hip", "cat_wide.hip", "cat_direct.hip", "cat_loop.hip", "cat_short.hip", "cat_api.hip", "cat_stream.hip", "cat_tile.hip",
            "cat_pca.hip", "cat_eig.hip", "cat_sweep.hip", "cat_seed.hip", "cat_lds.hip", "cat_lp.hip", "cat_tile_multi_f32.hip",
            "cat_tile_multi_bf16.hip", "cat_tile_split.hip", "cat_tile_split_rows.hip"] + [
     f"cat_tile_k{kt}_{dt}.hip" for kt in (8, 4, 2, 1) for dt in ("f32", "bf16")]
-HEADERS = ["cat_common.h", "cat_tile.h", "cat_tile_kernel.h", "cat_infer.h", "cat_infer_kernel.h", "cat_wide.h", "cat_wide_kernel.h", "cat_direct.h", "cat_loop.h", "cat_eig.h"]
+HEADERS = ["cat_common.h", "cat_tile.h", "cat_tile_kernel.h", "cat_infer.h", "cat_infer_kernel.h", "cat_wide.h", "cat_wide_kernel.h", "cat_direct.h", "cat_loop.h", "cat_short.h", "cat_eig.h"]
 OUT = os.path.join(_HERE, "libcat_hip.so")
 OBJ_DIR = os.path.join(_HERE, "_build")
 

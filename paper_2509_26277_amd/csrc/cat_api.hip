@@ -12,6 +12,7 @@
 #include "cat_direct.h"
 #include "cat_infer.h"
 #include "cat_loop.h"
+#include "cat_short.h"
 #include "cat_tile.h"
 #include "cat_wide.h"
 
@@ -964,6 +965,8 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     const int which = g_apply_kernel.load();
     if (path == CAT_PATH_AUTO && (which == 4 || (which == 0 && direct_apply_pays(N, D, K, dt))))
         return direct_apply(lq, dt, N, D, K, centroids, gamma, beta, alpha, corrected, assignments, st);
+    if (path == CAT_PATH_AUTO && which == 0 && short_apply_pays(N, D, K, dt))
+        return short_apply(lq, dt, N, D, K, centroids, gamma, beta, alpha, corrected, assignments, st);
     const bool tile_ok = tile_supports(TILE_APPLY, N, D, K, dt);
     if (path == CAT_PATH_TILE && !tile_ok)
         return set_error(CAT_ERR_UNSUPPORTED, "tile path forced but D=%lld K=%d dt=%d does not fit it", (long long)D,

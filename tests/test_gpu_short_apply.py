@@ -1,0 +1,89 @@
+"""Inference over short rows (cat_short.hip): rows of at most 512 bytes, moved as pieces of 16 rows.
+
+Against the oracle in double precision: the ranking is exact (rows whose two nearest centroids tie to 1e-5 are exempt), the map one
+fused multiply-add per entry on parameters folded in fp32, bfloat16 results rounded once.  The shapes have more rows than the kernel
+for few rows takes."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2509_26277_amd import binding, cat_apply
+
+from parity_util import check_assignments_lazy, check_values, dev_matrix, f32_round, host_matrix
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(N, D, K, dtype, seed, spread=2.0):
+    rng = np.random.default_rng(seed)
+    cent = rng.standard_normal((K, D)) * spread
+    x = cent[rng.integers(0, K, N)] + rng.standard_normal((N, D))
+    if dtype == "bf16":
+        x = torch.from_numpy(x).bfloat16().float().numpy()
+    g, b = rng.uniform(0.5, 1.5, (K, D)), rng.standard_normal((K, D))
+    return x.astype(np.float32), f32_round(cent), f32_round(g), f32_round(b)
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+
+
+def _check(x, cent, g, b, alpha, dtype):
+    out, a = cat_apply(dev_matrix(x, dtype), _dev(cent), _dev(g), _dev(b), alpha=alpha)
+    a = a.cpu().numpy()
+    want, label = oracle.apply(x, cent, g, b, alpha)
+    check_assignments_lazy(a, label, x, cent, "labels")
+    same = a == label
+    # fp32: folding rounds gamma' and beta' (6e-8 each, of 1 + alpha |gamma - 1|), the product once more; bf16: half a unit of 2^-8
+    check_values(host_matrix(out)[same], want[same], 1e-6 if dtype == "f32" else 4e-3, "corrected")
+    return a
+
+
+SHAPES = [
+    # N, D, K: fewest channels, remainders of 16 rows, whole 16-byte groups and not, each number of groups per lane
+    (1025, 4, 1, "f32"), (1030, 5, 2, "f32"), (1039, 7, 16, "f32"), (1040, 31, 17, "f32"), (1100, 32, 33, "f32"), (1337, 33, 5, "f32"),
+    (1041, 63, 20, "f32"), (1042, 64, 65, "f32"), (1043, 65, 9, "f32"), (1044, 127, 3, "f32"), (1045, 128, 30, "f32"), (40001, 127, 100, "f32"),
+    (40003, 128, 128, "f32"), (33333, 20, 128, "f32"),
+    (1025, 8, 1, "bf16"), (1030, 10, 2, "bf16"), (1039, 62, 16, "bf16"), (1040, 64, 17, "bf16"), (1041, 66, 33, "bf16"), (1337, 126, 5, "bf16"),
+    (1042, 128, 65, "bf16"), (1043, 130, 9, "bf16"), (1044, 254, 3, "bf16"), (1045, 256, 20, "bf16"), (20001, 250, 40, "bf16"),
+]
+
+
+@pytest.mark.parametrize("alpha", [1.0, 0.6])
+@pytest.mark.parametrize("N,D,K,dtype", SHAPES)
+def test_against_the_oracle(N, D, K, dtype, alpha):
+    _check(*_case(N, D, K, dtype, N + D + K), alpha, dtype)
+
+
+def test_near_ties_are_measured():
+    """clusters that overlap, far from the origin: many rows within the error bound of the split arithmetic; equal centroids"""
+    x, cent, g, b = _case(3000, 45, 12, "f32", 3, spread=0.05)
+    x = (x + 30.0).astype(np.float32)
+    cent = f32_round(cent + 30.0)
+    cent[7] = cent[2]
+    a = _check(x, cent, g, b, 0.6, "f32")
+    assert not (a == 7).any()  # the lowest of two equal centroids
+
+
+def test_without_labels_and_other_rows_beside_non_finite_ones():
+    x, cent, g, b = _case(2000, 50, 6, "f32", 8)
+    x[5] = np.nan
+    x[700, 3] = np.inf
+    lq = dev_matrix(x, "f32")
+    out, a = cat_apply(lq, _dev(cent), _dev(g), _dev(b))
+    a = a.cpu().numpy()
+    assert ((a >= 0) & (a < 6)).all()
+    fine = np.ones(2000, dtype=bool)
+    fine[[5, 700]] = False
+    want, label = oracle.apply(x[fine], cent, g, b, 1.0)
+    assert (a[fine] == label).all()
+    check_values(host_matrix(out)[fine], want, 1e-6, "corrected")
+    lib = binding.load_library()
+    again = torch.full_like(out, 7.0)
+    ws = torch.empty(binding.cat_apply_workspace_bytes(2000, 50, 6), dtype=torch.uint8, device="cuda")
+    c, gg, bb = _dev(cent), _dev(g), _dev(b)
+    assert lib.cat_apply(lq.data_ptr(), 2000, 50, 6, binding.CAT_F32, c.data_ptr(), gg.data_ptr(), bb.data_ptr(), 1.0, again.data_ptr(),
+                         None, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(again[:5], out[:5]) and torch.equal(again[701:], out[701:])
