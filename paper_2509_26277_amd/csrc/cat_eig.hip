@@ -1,7 +1,8 @@
 // The leading eigenpairs of a symmetric D x D matrix in double precision, for the PCA front-end (p of D directions).
 //
-//   1. Householder tridiagonalisation: for 64 <= D <= 1024 one launch whose workgroups pass the products of a column on through
-//      memory (k_eig_grid), otherwise one launch per column (k_eig_step).  Either is a chain of D steps bound by latencies.
+//   1. Householder tridiagonalisation: below 64 one workgroup with the matrix in registers (k_eig_small), for 64 <= D <= 1024 one
+//      launch whose workgroups pass the products of a column on through memory (k_eig_grid), otherwise one launch per column
+//      (k_eig_step).  Each is a chain of D steps bound by latencies.
 //   2. The p largest eigenvalues of the tridiagonal matrix T by multisection on Sturm counts (k_eig_bisect).
 //   3. Their vectors from the two-sided factorisation of T - lambda I, or by inverse iteration from pseudo-random starts where
 //      eigenvalues all but coincide (k_eig_invit), made orthogonal where they lie close together (k_eig_ortho).
@@ -498,6 +499,68 @@ __global__ __launch_bounds__(kWholeT) void k_eig_whole(double* W, double* __rest
             for (int j = k + 1 + lane; j < n; j += kWave) W[(int64_t)i * ld + j] -= vi * s_w[j] + wi * s_v[j];
         }
         __syncthreads();
+    }
+}
+
+// All columns by one workgroup that holds the matrix in registers, below the sizes the grid is for: lane i of wave q has columns
+// 16 q .. 16 q + 15 of row i.  The matrix is symmetric, so column k is row k, which its lane lays in LDS; every wave makes the
+// reflection for itself, the waves' shares of the products A v meet in LDS.  Two barriers a column: a chain of latencies, LDS and
+// the divisions of the reflection: 72 us at n = 60 (a launch per column 226; A x requested before the norm is known, 76).
+constexpr int kSmallT = 256, kSmallC = kGridMin / (kSmallT / kWave);
+__global__ __launch_bounds__(kSmallT) void k_eig_small(const double* __restrict__ W, double* __restrict__ V, int64_t ld, int32_t n,
+                                                       double* __restrict__ d, double* __restrict__ e, double* __restrict__ tau) {
+    constexpr int NW = kSmallT / kWave, C = kSmallC;
+    __shared__ __align__(16) double s_x[kGridMin], s_p[NW][kGridMin], s_v[NW][kGridMin], s_w[NW][kGridMin];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    double a[C];
+#pragma unroll
+    for (int j = 0; j < C; j++) a[j] = lane < n && C * wave + j < n ? W[(int64_t)lane * ld + C * wave + j] : 0.0;
+    for (int k = 0; k < n; k++) {
+        if (lane == k) {
+#pragma unroll
+            for (int j = 0; j < C; j++) s_x[C * wave + j] = a[j];
+        }
+        __syncthreads();
+        const double x = s_x[lane];
+        if (tid == k) d[k] = x;
+        if (k + 1 >= n) return;
+        const double x0 = s_x[k + 1];
+        const double ss = wave_total(lane > k + 1 ? x * x : 0.0);
+        double beta = x0, tk = 0.0, scale = 0.0;
+        if (ss > 0.0) {
+            const double nrm = sqrt(fma(x0, x0, ss));
+            beta = x0 >= 0.0 ? -nrm : nrm;
+            tk = (beta - x0) / beta;
+            scale = 1.0 / (x0 - beta);
+        }
+        const double v = lane == k + 1 ? 1.0 : lane > k + 1 ? x * scale : 0.0;
+        if (wave == 0 && lane > k && lane < n) V[(int64_t)k * ld + lane] = v;
+        if (tid == 0) {
+            e[k] = beta;
+            tau[k] = tk;
+        }
+        s_v[wave][lane] = v;
+        __builtin_amdgcn_wave_barrier();  // (a wave's own copy; LDS serves it in order)
+        double vj[C], s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int j = 0; j < C; j++) vj[j] = s_v[wave][C * wave + j];
+#pragma unroll
+        for (int j = 0; j < C; j += 2) {
+            s0 = fma(a[j], vj[j], s0);
+            s1 = fma(a[j + 1], vj[j + 1], s1);
+        }
+        s_p[wave][lane] = s0 + s1;
+        __syncthreads();
+        double p = 0.0;
+#pragma unroll
+        for (int h = 0; h < NW; h++) p += s_p[h][lane];
+        p = lane > k ? p : 0.0;
+        const double pv = wave_total(p * v);
+        const double w = tk * p - 0.5 * tk * tk * pv * v;
+        s_w[wave][lane] = w;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < C; j++) a[j] -= v * s_w[wave][C * wave + j] + w * vj[j];
     }
 }
 
@@ -1100,6 +1163,9 @@ cat_status launch_eig_leading(double* W, double* V, int64_t ld, int32_t D, int32
         CAT_LAUNCH_CHECK("k_eig_grid");
         hipLaunchKernelGGL(k_eig_whole, dim3(1), dim3(kWholeT), 0, st, W, V, ld, D, d, e, tau, fail);
         CAT_LAUNCH_CHECK("k_eig_whole");
+    } else if (D < kGridMin) {
+        hipLaunchKernelGGL(k_eig_small, dim3(1), dim3(kSmallT), 0, st, W, V, ld, D, d, e, tau);
+        CAT_LAUNCH_CHECK("k_eig_small");
     } else {
         for (int32_t k = 0; k < D; k++) {
             const int32_t rest = D - (k & ~7);

@@ -40,6 +40,33 @@ __global__ __launch_bounds__(256) void k_pca_colsum(const T* __restrict__ x, int
     for (; i < r1; i++) s += (double)ld_elem(x + i * D + j);
     atomicAdd(sum + j, s);
 }
+// Up to 256 columns (G of 64, 128 or 256): the groups of G threads of a workgroup take its rows in turn and meet in LDS.  Additions to
+// one address follow each other, about 25 ns each, so there are 256 workgroups at most.
+// 700001 x 60: 77 us as above (1024 workgroups), 48 here.
+constexpr int kSumT = 1024, kSumU = 8;
+template <typename T, int G>
+__global__ __launch_bounds__(kSumT) void k_pca_colsum_short(const T* __restrict__ x, int64_t N, int64_t D, int64_t rows_per_block,
+                                                            double* __restrict__ sum) {
+    constexpr int S = kSumT / G;
+    __shared__ double s_sum[S][G];
+    const int g = threadIdx.x / G, j = threadIdx.x % G, jc = j < D ? j : 0;
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
+    const int64_t r1 = r0 + rows_per_block < N ? r0 + rows_per_block : N;
+    double s = 0.0;
+    for (int64_t i = r0 + g; i < r1; i += kSumU * S) {
+        float v[kSumU];
+#pragma unroll
+        for (int u = 0; u < kSumU; u++) v[u] = ld_elem(x + (i + u * S < r1 ? i + u * S : i) * D + jc);
+#pragma unroll
+        for (int u = 0; u < kSumU; u++) s += i + u * S < r1 ? (double)v[u] : 0.0;
+    }
+    s_sum[g][j] = s;
+    __syncthreads();
+    if (g != 0 || j >= D) return;
+#pragma unroll
+    for (int h = 1; h < S; h++) s += s_sum[h][j];
+    atomicAdd(sum + j, s);
+}
 
 __global__ void k_pca_mean(const double* __restrict__ sum, int64_t N, int64_t D, double* __restrict__ mean_d,
                            float* __restrict__ mean_f) {
@@ -50,59 +77,10 @@ __global__ void k_pca_mean(const double* __restrict__ sum, int64_t N, int64_t D,
     mean_f[j] = (float)m;
 }
 
-// ---- covariance: one workgroup per (32 x 32 tile of the upper triangle, row range) ----------------
-// 256 threads, each owns a 2 x 2 block of the tile; 64 centred rows of both column blocks are staged
-// in LDS as doubles per round.  W (ld = ldw) receives sum (x_a - m_a)(x_b - m_b); scaled and mirrored
-// afterwards.
-constexpr int kCovTile = 32, kCovRows = 64;
-template <typename T>
-__global__ __launch_bounds__(256) void k_pca_cov(const T* __restrict__ x, int64_t N, int64_t D, const double* __restrict__ mean,
-                                                 int64_t rows_per_block, int32_t ntile, double* __restrict__ W, int64_t ldw) {
-    __shared__ double sa[kCovRows][kCovTile + 1], sb[kCovRows][kCovTile + 1];
-    // tile index -> (ta <= tb)
-    int t = blockIdx.x, ta = 0;
-    while (t >= ntile - ta) {
-        t -= ntile - ta;
-        ta++;
-    }
-    const int tb = ta + t;
-    const int64_t a0 = (int64_t)ta * kCovTile, b0 = (int64_t)tb * kCovTile;
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per_block;
-    const int64_t r1 = r0 + rows_per_block < N ? r0 + rows_per_block : N;
-    const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;  // 16 x 16 threads, 2 x 2 outputs each
-    double c00 = 0.0, c01 = 0.0, c10 = 0.0, c11 = 0.0;
-    for (int64_t rb = r0; rb < r1; rb += kCovRows) {
-        __syncthreads();
-        for (int i = threadIdx.x; i < kCovRows * kCovTile; i += blockDim.x) {
-            const int r = i / kCovTile, c = i - r * kCovTile;
-            const int64_t row = rb + r;
-            double va = 0.0, vb = 0.0;
-            if (row < r1) {
-                if (a0 + c < D) va = (double)ld_elem(x + row * D + a0 + c) - mean[a0 + c];
-                if (b0 + c < D) vb = (double)ld_elem(x + row * D + b0 + c) - mean[b0 + c];
-            }
-            sa[r][c] = va;
-            sb[r][c] = vb;
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int r = 0; r < kCovRows; r++) {
-            const double a_0 = sa[r][2 * ty], a_1 = sa[r][2 * ty + 1];
-            const double b_0 = sb[r][2 * tx], b_1 = sb[r][2 * tx + 1];
-            c00 = fma(a_0, b_0, c00);
-            c01 = fma(a_0, b_1, c01);
-            c10 = fma(a_1, b_0, c10);
-            c11 = fma(a_1, b_1, c11);
-        }
-    }
-    const int64_t ia = a0 + 2 * ty, ib = b0 + 2 * tx;
-    if (ia < D && ib < D) atomicAdd(W + ia * ldw + ib, c00);
-    if (ia < D && ib + 1 < D) atomicAdd(W + ia * ldw + ib + 1, c01);
-    if (ia + 1 < D && ib < D) atomicAdd(W + (ia + 1) * ldw + ib, c10);
-    if (ia + 1 < D && ib + 1 < D) atomicAdd(W + (ia + 1) * ldw + ib + 1, c11);
-}
-
-// The same sums on the fp64 matrix cores (v_mfma_f64_16x16x4_f64), used from D = 64 on.  One wave per
+// ---- covariance ----------------------------------------------------------------------------------
+// W (ld = ldw) receives sum (x_a - m_a)(x_b - m_b) over the upper triangle; scaled and mirrored afterwards.
+//
+// On the fp64 matrix cores (v_mfma_f64_16x16x4_f64); above 64 columns one wave per
 // (64 x 64 tile of the upper triangle, row range): lane (m, k) = (lane & 15, lane >> 4) loads entry m of a
 // 16-column piece of row i0 + k, centres and widens it, and that is at once the A operand (for the piece of the
 // tile's rows) and the B operand (for the piece of its columns) of a 16 x 16 x 4 product; 4 + 4 pieces feed 16
@@ -195,6 +173,87 @@ __global__ __launch_bounds__(256, 2) void k_pca_cov_mfma(const T* __restrict__ x
                 const int64_t ia = a0 + 16 * i + 4 * r + kk, ib = b0 + 16 * j + m;
                 if (ia < D && ib < D && ia <= ib) atomicAdd(W + ia * ldw + ib, acc[i][j][r]);
             }
+}
+
+// Up to 64 columns: the tile is the whole triangle, so its rows and its columns are the same NP pieces, loaded once, and NP (NP + 1) / 2
+// products a step are all there is.  The eight waves of a workgroup take a range of rows each and meet in LDS, so that one of them
+// adds to W, where the additions to one address follow each other: 256 workgroups at most.
+// 700001 x 60: 975 us by 32 x 32 tiles of doubles from LDS, 76 here.
+constexpr int kCovShortT = 512, kCovShortMax = 64;
+template <typename T, int NP>
+__global__ __launch_bounds__(kCovShortT) void k_pca_cov_short(const T* __restrict__ x, int64_t N, int64_t D, const double* __restrict__ mean,
+                                                              int64_t rows_per_wave, double* __restrict__ W, int64_t ldw) {
+    constexpr int NT = NP * (NP + 1) / 2, S = 4 * kCovAhead;
+    __shared__ double s_acc[NT * 256];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int m = lane & 15, kk = lane >> 4;
+    for (int i = tid; i < NT * 256; i += kCovShortT) s_acc[i] = 0.0;
+    __syncthreads();
+    const int64_t r0 = ((int64_t)blockIdx.x * (kCovShortT / kWave) + wave) * rows_per_wave;
+    const int64_t r1 = r0 + rows_per_wave < N ? r0 + rows_per_wave : N;
+    if (r0 < r1) {
+        uint32_t col[NP];  // past the last: column 0, whose products are dropped
+        double mu[NP];
+#pragma unroll
+        for (int s = 0; s < NP; s++) {
+            const int c = 16 * s + m;
+            col[s] = c < D ? (uint32_t)c : 0u;
+            mu[s] = mean[col[s]];
+        }
+        f64x4_t acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; t++) acc[t] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+        float ra[kCovAhead][NP], rb[kCovAhead][NP];
+        auto load = [&](float (&raw)[kCovAhead][NP], int64_t row) {
+#pragma unroll
+            for (int u = 0; u < kCovAhead; u++) {
+                const int64_t i = row + 4 * u + kk;
+                const T* xr = x + (i < r1 ? i : r0) * D;  // past the range: a valid row, its values dropped below
+#pragma unroll
+                for (int s = 0; s < NP; s++) raw[u][s] = ld_elem(xr + col[s]);
+            }
+        };
+        auto products = [&](const float (&raw)[kCovAhead][NP], int64_t row) {
+#pragma unroll
+            for (int u = 0; u < kCovAhead; u++) {
+                const bool in = row + 4 * u + kk < r1;
+                double v[NP];
+#pragma unroll
+                for (int s = 0; s < NP; s++) v[s] = in ? (double)raw[u][s] - mu[s] : 0.0;
+                int t = 0;
+#pragma unroll
+                for (int i = 0; i < NP; i++)
+#pragma unroll
+                    for (int j = i; j < NP; j++, t++) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[i], v[j], acc[t], 0, 0, 0);
+            }
+        };
+        load(ra, r0);
+        for (int64_t row = r0; row < r1; row += 2 * S) {
+            load(rb, row + S);
+            products(ra, row);
+            load(ra, row + 2 * S);
+            products(rb, row + S);
+        }
+#pragma unroll
+        for (int t = 0; t < NT; t++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) atomicAdd(s_acc + t * 256 + (4 * r + kk) * 16 + m, acc[t][r]);
+    }
+    __syncthreads();
+    for (int i = tid; i < NT * 256; i += kCovShortT) {
+        int t = i >> 8, pi = 0;  // tile -> its pieces (pi <= pj)
+        while (t >= NP - pi) {
+            t -= NP - pi;
+            pi++;
+        }
+        const int a = 16 * pi + ((i >> 4) & 15), b = 16 * (pi + t) + (i & 15);
+        if (a <= b && b < D) atomicAdd(W + (int64_t)a * ldw + b, s_acc[i]);
+    }
+}
+// Rows of a wave of it: 2048 waves in all, and 32 rows at least.
+static int64_t cov_short_rows(int64_t N) {
+    const int64_t rows = ((N + 2047) / 2048 + 15) / 16 * 16;
+    return rows < 32 ? 32 : rows;
 }
 
 // Rows per wave.  All waves have the same work and 2048 are resident (two to a SIMD, 256 CUs), so their number should be
@@ -1104,45 +1163,59 @@ cat_status cat_pca_fit(const void* lq, int64_t N, int64_t D, int32_t p, cat_dtyp
     cat_status s;
     if ((s = launch_fill_zero(w.sum, (size_t)D * 8, st)) != CAT_OK) return s;
     if ((s = launch_fill_zero(w.W, (size_t)Dp * Dp * 8, st)) != CAT_OK) return s;
-    // about 64 row ranges: enough workgroups for the covariance without drowning it in atomics
-    int64_t rpb = (N + 63) / 64;
-    rpb = (rpb + kCovRows - 1) / kCovRows * kCovRows;
-    const unsigned nrb = (unsigned)((N + rpb - 1) / rpb);
     {
-        // about 1024 workgroups: 256 or more row ranges (256 atomics per column at most)
-        const int64_t cblocks = (D + 255) / 256;
-        int64_t ranges = (1024 + cblocks - 1) / cblocks;
-        ranges = ranges < 256 ? 256 : ranges;
-        int64_t rps = (N + ranges - 1) / ranges;
-        rps = (rps + 7) & ~(int64_t)7;
-        dim3 g((unsigned)cblocks, (unsigned)((N + rps - 1) / rps)), b(256);
-        if (dt == CAT_F32)
-            hipLaunchKernelGGL(k_pca_colsum<float>, g, b, 0, st, (const float*)lq, N, D, rps, w.sum);
-        else
-            hipLaunchKernelGGL(k_pca_colsum<bf16_t>, g, b, 0, st, (const bf16_t*)lq, N, D, rps, w.sum);
+        if (D <= 256) {
+            const int64_t G = D <= 64 ? 64 : D <= 128 ? 128 : 256, whole = kSumU * (kSumT / G);  // rows that its threads load at once
+            const int64_t rps = ((N + 255) / 256 + whole - 1) / whole * whole;
+            const dim3 g((unsigned)((N + rps - 1) / rps)), b(kSumT);
+#define CAT_COLSUM(G_)                                                                                               \
+    if (dt == CAT_F32)                                                                                               \
+        hipLaunchKernelGGL((k_pca_colsum_short<float, G_>), g, b, 0, st, (const float*)lq, N, D, rps, w.sum);         \
+    else                                                                                                             \
+        hipLaunchKernelGGL((k_pca_colsum_short<bf16_t, G_>), g, b, 0, st, (const bf16_t*)lq, N, D, rps, w.sum);
+            if (G == 64) { CAT_COLSUM(64) } else if (G == 128) { CAT_COLSUM(128) } else { CAT_COLSUM(256) }
+#undef CAT_COLSUM
+        } else {
+            // about 1024 workgroups: 256 or more row ranges (256 atomics per column at most)
+            const int64_t cblocks = (D + 255) / 256;
+            int64_t ranges = (1024 + cblocks - 1) / cblocks;
+            ranges = ranges < 256 ? 256 : ranges;
+            int64_t rps = (N + ranges - 1) / ranges;
+            rps = (rps + 7) & ~(int64_t)7;
+            dim3 g((unsigned)cblocks, (unsigned)((N + rps - 1) / rps)), b(256);
+            if (dt == CAT_F32)
+                hipLaunchKernelGGL(k_pca_colsum<float>, g, b, 0, st, (const float*)lq, N, D, rps, w.sum);
+            else
+                hipLaunchKernelGGL(k_pca_colsum<bf16_t>, g, b, 0, st, (const bf16_t*)lq, N, D, rps, w.sum);
+        }
         CAT_LAUNCH_CHECK("k_pca_colsum");
         hipLaunchKernelGGL(k_pca_mean, dim3((unsigned)((D + 255) / 256)), dim3(256), 0, st, w.sum, N, D, w.mean, mean);
         CAT_LAUNCH_CHECK("k_pca_mean");
     }
     {
-        if (D >= kCovM) {
-            // matrix cores: 64 x 64 tiles, the rows split into ranges
+        const dim3 b(256);
+        if (D <= kCovShortMax) {
+            const int64_t rpw = cov_short_rows(N);
+            constexpr int64_t kWaves = kCovShortT / kWave;
+            const dim3 g((unsigned)((N + rpw * kWaves - 1) / (rpw * kWaves))), bs(kCovShortT);
+#define CAT_COV_SHORT(NP)                                                                                                             \
+    if (dt == CAT_F32)                                                                                                                \
+        hipLaunchKernelGGL((k_pca_cov_short<float, NP>), g, bs, 0, st, (const float*)lq, N, D, w.mean, rpw, w.W, Dp);                  \
+    else                                                                                                                              \
+        hipLaunchKernelGGL((k_pca_cov_short<bf16_t, NP>), g, bs, 0, st, (const bf16_t*)lq, N, D, w.mean, rpw, w.W, Dp);
+            if (D <= 16) { CAT_COV_SHORT(1) } else if (D <= 32) { CAT_COV_SHORT(2) } else if (D <= 48) { CAT_COV_SHORT(3) } else { CAT_COV_SHORT(4) }
+#undef CAT_COV_SHORT
+        } else {
+            // 64 x 64 tiles, the rows split into ranges
             const int ntile = (int)((D + kCovM - 1) / kCovM);
             const int ntri = ntile * (ntile + 1) / 2;
             const int64_t rpw = cov_rows_per_wave(N, ntri);
             const int64_t waves = (N + rpw - 1) / rpw * ntri;
-            dim3 g((unsigned)((waves + 31) / 32 * 8)), b(256);
+            const dim3 g((unsigned)((waves + 31) / 32 * 8));
             if (dt == CAT_F32)
                 hipLaunchKernelGGL(k_pca_cov_mfma<float>, g, b, 0, st, (const float*)lq, N, D, w.mean, rpw, ntile, w.W, Dp);
             else
                 hipLaunchKernelGGL(k_pca_cov_mfma<bf16_t>, g, b, 0, st, (const bf16_t*)lq, N, D, w.mean, rpw, ntile, w.W, Dp);
-        } else {
-            const int ntile = (int)((D + kCovTile - 1) / kCovTile);
-            dim3 g((unsigned)(ntile * (ntile + 1) / 2), nrb), b(256);
-            if (dt == CAT_F32)
-                hipLaunchKernelGGL(k_pca_cov<float>, g, b, 0, st, (const float*)lq, N, D, w.mean, rpb, ntile, w.W, Dp);
-            else
-                hipLaunchKernelGGL(k_pca_cov<bf16_t>, g, b, 0, st, (const bf16_t*)lq, N, D, w.mean, rpb, ntile, w.W, Dp);
         }
         CAT_LAUNCH_CHECK("k_pca_cov");
         dim3 g2((unsigned)((Dp + 255) / 256), (unsigned)Dp);
