@@ -15,6 +15,7 @@
 namespace cat {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 
 constexpr int kPcaMaxD = 2048;  // eigen workspace is 2 (D+1)^2 doubles; the selection kernel keeps D values in LDS
 static_assert(kPcaMaxD % 2 == 0 && kPcaMaxD <= 8 * 256, "a Jacobi step keeps a row in 8 x 256 registers at most");
@@ -767,30 +768,42 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
             load_x(jc, xcur);  // this chunk's rows first (the other waves of the SIMD cover their latency), then the next chunk's directions
             load_w(c0, jn, wreg);
             mreg = load_m(jn);
+            // 16 channels of the row against the directions; the steps past the end of a last, shorter chunk are left out.  us
+            // with all / here: projection of 700001 x 60, p = 50: 178 / 112; fused inference, K = 50: 700001 x 60, p = 50: 328 / 292;
+            // 200003 x 160, p = 50: 159 / 141; 65536 x 1000 bf16, p = 30: 134 / 119.  One tile of directions takes them all: its four
+            // products a step are no more than the branch holds up (300000 x 64, p = 16: 87 / 96; 600000 x 104 bf16: 158 / 174).
+            auto step = [&](int s_) {
+                const int64_t ch = (int64_t)jc * kProjChunk + 16 * s_ + 4 * g;
+                float e[4];
+                if (sizeof(T) == 4) {
+                    e[0] = __uint_as_float(xcur[s_][0]), e[1] = __uint_as_float(xcur[s_][1]);
+                    e[2] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 2 : 0]), e[3] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 3 : 1]);
+                } else {
+                    e[0] = __uint_as_float(xcur[s_][0] << 16), e[1] = __uint_as_float(xcur[s_][0] & 0xFFFF0000u);
+                    e[2] = __uint_as_float(xcur[s_][1] << 16), e[3] = __uint_as_float(xcur[s_][1] & 0xFFFF0000u);
+                }
+                const f32x4_t mv = *(const f32x4_t*)&s_m[cur][16 * s_ + 4 * g];
+                const bool in = ch < D;  // D is a multiple of 4: a group is inside the row or wholly outside
+                const f32x4_t xv = (f32x4_t){in ? e[0] - mv.x : 0.f, in ? e[1] - mv.y : 0.f, in ? e[2] - mv.z : 0.f,
+                                             in ? e[3] - mv.w : 0.f};
+#pragma unroll
+                for (int t = 0; t < NT; t++) {
+                    const f32x4_t wv = *(const f32x4_t*)&s_w[cur][(((s_ * NT + t) * kWave) + lane) * 4];
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc[t], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc[t], 0, 0, 0);
+                }
+            };
             if (tile < ntiles) {
+                const int64_t rest = D - (int64_t)jc * kProjChunk;
+                if (NT == 1 || rest >= kProjChunk) {
 #pragma unroll
-                for (int s_ = 0; s_ < XS; s_++) {
-                    const int64_t ch = (int64_t)jc * kProjChunk + 16 * s_ + 4 * g;
-                    float e[4];
-                    if (sizeof(T) == 4) {
-                        e[0] = __uint_as_float(xcur[s_][0]), e[1] = __uint_as_float(xcur[s_][1]);
-                        e[2] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 2 : 0]), e[3] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 3 : 1]);
-                    } else {
-                        e[0] = __uint_as_float(xcur[s_][0] << 16), e[1] = __uint_as_float(xcur[s_][0] & 0xFFFF0000u);
-                        e[2] = __uint_as_float(xcur[s_][1] << 16), e[3] = __uint_as_float(xcur[s_][1] & 0xFFFF0000u);
-                    }
-                    const f32x4_t mv = *(const f32x4_t*)&s_m[cur][16 * s_ + 4 * g];
-                    const bool in = ch < D;  // D is a multiple of 4: a group is inside the row or wholly outside
-                    const f32x4_t xv = (f32x4_t){in ? e[0] - mv.x : 0.f, in ? e[1] - mv.y : 0.f, in ? e[2] - mv.z : 0.f,
-                                                 in ? e[3] - mv.w : 0.f};
+                    for (int s_ = 0; s_ < XS; s_++) step(s_);
+                } else {
 #pragma unroll
-                    for (int t = 0; t < NT; t++) {
-                        const f32x4_t wv = *(const f32x4_t*)&s_w[cur][(((s_ * NT + t) * kWave) + lane) * 4];
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc[t], 0, 0, 0);
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc[t], 0, 0, 0);
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc[t], 0, 0, 0);
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc[t], 0, 0, 0);
-                    }
+                    for (int s_ = 0; s_ < XS; s_++)
+                        if (16 * s_ < rest) step(s_);
                 }
             }
             // the other buffer was last read one chunk ago, before the barrier that ended that chunk
@@ -807,6 +820,9 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
                     float* o = z + row * ldz + c;
                     if (c + 3 < ldz && ((ldz & 3) == 0)) {
                         *(f32x4_t*)o = acc[t];
+                    } else if (c + 3 < ldz && (ldz & 1) == 0 && ((uintptr_t)z & 7u) == 0) {
+                        ((f32x2_t*)o)[0] = (f32x2_t){acc[t].x, acc[t].y};
+                        ((f32x2_t*)o)[1] = (f32x2_t){acc[t].z, acc[t].w};
                     } else {
                         if (c < ldz) o[0] = acc[t].x;
                         if (c + 1 < ldz) o[1] = acc[t].y;
