@@ -16,8 +16,10 @@
 // Two barriers per tile.  Bound by memory (one read, one write of the rows); per tile the operand costs K D 4 bytes of L2
 // traffic and the parameters 8 bytes per entry.
 //
-// UA: rows that are not whole 16-byte groups: rows, parameters and outputs move in 4-byte words, 64 consecutive words per
-// wave instruction; LDS rows start on 16 bytes, so only these accesses differ.
+// UA: rows that are not whole 16-byte groups (LDS rows start on 16 bytes all the same).  bf16 rows and their parameters move in 16-byte
+// vectors on word boundaries, fp32 ones in words, 64 consecutive words per wave instruction.  us per cat_apply by words / by vectors:
+// bf16 60001 x 1030, K = 100: 195 / 146; 50021 x 2046, K = 30: 169 / 150; 50021 x 1002, K = 64: 85 / 81; fp32, whose parameters then lie on
+// 4 instead of 8 bytes: 50021 x 1001, K = 50: 124 / 145; 100003 x 769, K = 40: 183 / 221.
 #pragma once
 #include "cat_infer_kernel.h"
 #include "cat_wide.h"
@@ -37,6 +39,9 @@ struct WideParams {
     const float* beta;
     float tau, tau2;
 };
+
+typedef iu32x4 __attribute__((aligned(4))) iu32x4_w;  // vectors on a word boundary
+typedef if32x4 __attribute__((aligned(4))) if32x4_w;
 
 constexpr int wide_row_stride(int vpr) { return vpr * 1024 + 16; }  // bytes; 16 rows apart in banks
 constexpr int wide_dots_stride(int kt, int sc) { return infer_dots_stride(sc * kt * 16); }
@@ -58,6 +63,7 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
     constexpr int NB = (SPW + U - 1) / U;
     constexpr int NSLOT = (K16 + kWave - 1) / kWave;
     constexpr int NL = RPW * VPR;                          // row vectors of a wave
+    constexpr bool UV = UA && BF16, UW = UA && !BF16;      // unaligned rows in vectors, in words
     typedef typename std::conditional<BF16, bf16_t, float>::type T;
 
     float* s_dots = (float*)(smem + (size_t)ROWS * XS);  // [row][channel share][cluster], rows DS apart
@@ -78,17 +84,36 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
         }
         cmax = sqrtf(wave_all(cm2, [](float a, float b) { return fmaxf(a, b); }));
     }
-    // positions of this lane in a row: vectors, or (UA) words, clamped to a valid one so that no load is conditional
+    // positions of this lane in a row: elements, or (UA) words; past the row a valid one, so that no load is conditional
     const int W = (int)(UA ? (BF16 ? p.D / 2 : p.D) : p.D);
-    auto pos = [&](int v, int e) { return UA ? 256 * v + 64 * e + lane : (v * kWave + lane) * EPL; };
+    auto pos = [&](int v, int e) { return UV ? 4 * (v * kWave + lane) + e : UW ? 256 * v + 64 * e + lane : (v * kWave + lane) * EPL; };
     auto ok = [&](int v, int e) { return pos(v, e) < W; };
+    // UV: the vector that a row ends in runs on into the next row, which it drops; in the last row (of the rows, or of the parameters) it
+    // is loaded as the row's last four words and moved down where it is used
+    auto whole = [&](int v) { return pos(v, 0) + 4 <= W; };
+    auto at = [&](int v, bool last) { return whole(v) ? pos(v, 0) : ok(v, 0) ? (last ? W - 4 : pos(v, 0)) : 0; };
+    auto split = [&](int v, bool last) { return last && (W & 3) != 0 && !whole(v) && ok(v, 0); };
+    auto settle = [&](iu32x4& t, int v, bool last) {
+        if (!split(v, last)) return;
+        const int left = W & 3;  // words of the row in it
+        t = left == 1 ? (iu32x4){t.w, 0u, 0u, 0u} : left == 2 ? (iu32x4){t.z, t.w, 0u, 0u} : (iu32x4){t.y, t.z, t.w, 0u};
+    };
+    auto settle_params = [&](if32x4& lo4, if32x4& hi4, int v, bool last) {  // (two channels a word)
+        if (!split(v, last)) return;
+        const int left = W & 3;
+        const if32x4 a = lo4, b = hi4;
+        lo4 = left == 1 ? (if32x4){b.z, b.w, 0.f, 0.f} : left == 2 ? b : (if32x4){a.z, a.w, b.x, b.y};
+        hi4 = left == 3 ? (if32x4){b.z, b.w, 0.f, 0.f} : (if32x4){0.f, 0.f, 0.f, 0.f};
+    };
 
     iu32x4 X[RPW][VPR];
     auto load_vec = [&](int64_t tile, int r, int v) {
         int64_t row = tile * ROWS + wave * RPW + r;
         row = row < p.N ? row : p.N - 1;  // rows past N (and tiles past the last) repeat the last row
         const T* x = (const T*)p.lq + row * p.D;
-        if (UA) {
+        if (UV) {
+            X[r][v] = *(const iu32x4_w*)((const uint32_t*)x + at(v, row == p.N - 1));
+        } else if (UW) {
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 const int w = pos(v, e);
@@ -100,13 +125,15 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
         }
     };
     float xn2[RPW];  // |x|^2 of the wave's rows of the tile in LDS
-    auto stage = [&]() {
+    auto stage = [&](int64_t tile) {
 #pragma unroll
         for (int r = 0; r < RPW; r++) {
+            const bool last = tile * ROWS + wave * RPW + r >= p.N - 1;
             unsigned char* xr = smem + (size_t)(wave * RPW + r) * XS;
             float s = 0.f;
 #pragma unroll
             for (int v = 0; v < VPR; v++) {
+                if (UV) settle(X[r][v], v, last);
 #pragma unroll
                 for (int e = 0; e < 4; e++) {
                     if (!ok(v, UA ? e : 0)) continue;
@@ -116,37 +143,29 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
                     } else {
                         s = fmaf(__uint_as_float(w), __uint_as_float(w), s);
                     }
-                    if (UA) *(uint32_t*)(xr + 4 * pos(v, e)) = w;
+                    if (UW || (UV && !whole(v))) *(uint32_t*)(xr + 4 * pos(v, e)) = w;
                 }
-                if (!UA && ok(v, 0)) *(iu32x4*)(xr + 16 * (v * kWave + lane)) = X[r][v];
+                if (UV ? whole(v) : !UA && ok(v, 0)) *(iu32x4*)(xr + 16 * (v * kWave + lane)) = X[r][v];
             }
             xn2[r] = wave_sum_all(s);
         }
     };
     // the fp32 parameters under vector v of a parameter row
-    auto params = [&](const float* row, int v, if32x4& lo4, if32x4& hi4) {
+    auto params = [&](const float* row, int v, bool last, if32x4& lo4, if32x4& hi4) {
         if (!UA) {
             const int c = pos(v, 0);
             const float* q = row + (c < W ? c : 0);
             lo4 = *(const if32x4*)q;
             if (BF16) hi4 = *(const if32x4*)(q + 4);
+        } else if (UV) {  // (to be settled where it is used)
+            const float* q = row + 2 * at(v, last);
+            lo4 = *(const if32x4_w*)q;
+            hi4 = *(const if32x4_w*)(q + 4);
         } else {
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                int w = pos(v, e);
-                w = w < W ? w : W - 1;
-                if (BF16) {  // two channels per word; D is even, so the pairs are 8-byte aligned
-                    const if32x2 t = *(const if32x2*)(row + 2 * w);
-                    if (e < 2) {
-                        lo4[2 * e] = t.x;
-                        lo4[2 * e + 1] = t.y;
-                    } else {
-                        hi4[2 * e - 4] = t.x;
-                        hi4[2 * e - 3] = t.y;
-                    }
-                } else {
-                    lo4[e] = row[w];
-                }
+                const int w = pos(v, e);
+                lo4[e] = row[w < W ? w : W - 1];
             }
         }
     };
@@ -154,11 +173,11 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
     auto lds_vec = [&](int trow, int v) {
         const unsigned char* xr = smem + (size_t)trow * XS;
         iu32x4 w;
-        if (UA) {
+        if (UW) {
 #pragma unroll
             for (int e = 0; e < 4; e++) w[e] = *(const uint32_t*)(xr + 4 * pos(v, e));
         } else {
-            w = *(const iu32x4*)(xr + 16 * (v * kWave + lane));
+            w = *(const iu32x4*)(xr + 16 * (v * kWave + lane));  // (past the row: zeros)
         }
         return w;
     };
@@ -182,7 +201,7 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
 #pragma unroll
         for (int v = 0; v < VPR; v++) load_vec(tile, r, v);
     __syncthreads();  // the zeroed rows
-    stage();
+    stage(tile);
     __syncthreads();
     for (; tile < p.ntiles; tile += gridDim.x) {
         const int64_t next = tile + gridDim.x;
@@ -317,13 +336,18 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
             for (int k0 = pop(); k0 >= 0; k0 = pop()) {
                 const int k1 = pop();
                 const float* c0 = p.cent + (int64_t)k0 * p.D;
-                const float* c1 = p.cent + (int64_t)(k1 >= 0 ? k1 : k0) * p.D;
+                const int ke = k1 >= 0 ? k1 : k0;
+                const float* c1 = p.cent + (int64_t)ke * p.D;
                 double d0 = 0.0, d1 = 0.0;
 #pragma unroll
                 for (int v = 0; v < VPR; v++) {
                     if32x4 a[2], b[2];
-                    params(c0, v, a[0], a[1]);
-                    params(c1, v, b[0], b[1]);
+                    params(c0, v, k0 == p.K - 1, a[0], a[1]);
+                    params(c1, v, ke == p.K - 1, b[0], b[1]);
+                    if (UV) {
+                        settle_params(a[0], a[1], v, k0 == p.K - 1);
+                        settle_params(b[0], b[1], v, ke == p.K - 1);
+                    }
                     const iu32x4 w = lds_vec(trow, v);
 #pragma unroll
                     for (int e = 0; e < 4; e++) {
@@ -365,8 +389,8 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
         if32x4 P[AHEAD + 1][4];
         auto fetch = [&](int q) {
             const int64_t a = idx[q / VPR];
-            params(p.gamma + a * p.D, q % VPR, P[q % (AHEAD + 1)][0], P[q % (AHEAD + 1)][1]);
-            params(p.beta + a * p.D, q % VPR, P[q % (AHEAD + 1)][2], P[q % (AHEAD + 1)][3]);
+            params(p.gamma + a * p.D, q % VPR, a == p.K - 1, P[q % (AHEAD + 1)][0], P[q % (AHEAD + 1)][1]);
+            params(p.beta + a * p.D, q % VPR, a == p.K - 1, P[q % (AHEAD + 1)][2], P[q % (AHEAD + 1)][3]);
         };
 #pragma unroll
         for (int q = 0; q < AHEAD; q++)
@@ -376,7 +400,11 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
             const int r = q / VPR, v = q % VPR;
             __builtin_amdgcn_sched_barrier(0);
             if (q + AHEAD < NL) fetch(q + AHEAD);
-            const if32x4(&t)[4] = P[q % (AHEAD + 1)];
+            if32x4(&t)[4] = P[q % (AHEAD + 1)];
+            if (UV) {
+                settle_params(t[0], t[1], v, idx[r] == p.K - 1);
+                settle_params(t[2], t[3], v, idx[r] == p.K - 1);
+            }
             const int64_t row = tile * ROWS + wave * RPW + r;
             const iu32x4 w = lds_vec(wave * RPW + r, v);
             iu32x4 y;
@@ -391,7 +419,9 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
             }
             T* o = (T*)p.out + row * p.D;
             if (row < p.N) {
-                if (UA) {
+                if (UV && whole(v)) {
+                    __builtin_nontemporal_store(y, (iu32x4_w*)((uint32_t*)o + pos(v, 0)));
+                } else if (UA) {
 #pragma unroll
                     for (int e = 0; e < 4; e++)
                         if (ok(v, e)) __builtin_nontemporal_store(y[e], (uint32_t*)o + pos(v, e));
@@ -401,7 +431,7 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
             }
         }
         // the rows of this tile are this wave's alone since the barrier: the next ones take their place
-        stage();
+        stage(next);
         __syncthreads();
     }
 }
