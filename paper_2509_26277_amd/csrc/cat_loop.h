@@ -20,7 +20,7 @@ struct LoopBounds {
     const uint32_t* list_count;  // rows that changed cluster in pass 2 (lw.list)
     const int32_t* counts;       // rows per cluster in pass 2
 };
-bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt);
+bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt);
 cat_status loop_lloyd_bounds(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,
                              int32_t* assign, int32_t* counts, double* inertia, unsigned long long* rep, const LloydWs& lw,
                              const LoopBounds& lb, hipStream_t st);

@@ -14,13 +14,8 @@
 // From 64 MB on (BOUNDS) the passes that leave rows out by distance bounds run here too: tile_lloyd's passes 0 .. 2 read every row, the
 // last of them lists the rows that changed and leaves the bounds; then every workgroup selects the due ones of its own rows, and
 // the waves share the channels of a tile where a pass has few tiles.  A row within the error bound is measured at the end of the
-// workgroup's tiles, by any wave.  36 random fits of 64 .. 490 MB: 0.99 .. 1.47 times as fast, 1.09 on average; 65536 x 1000, K = 16:
-// 546 -> 441 us where the loop settles after 25 passes (18 us a pass: bounds and rows 6, what few workgroups have to measure and
-// to move 5, flags 1, 32 sums a thread 5).
-// Tried: as many copies of the sums as spread those additions (a copy more to read is a trip more: 179 -> 228 with two); a third and
-// fourth chunk of rows in flight (registers spill, 7 .. 20 % slower); a delay before the first look at the flags (alone it makes a
-// barrier of 256 workgroups 1.1 us instead of 2.4, here it is lost beside the waits for the last one to arrive).  The code has to
-// stay small: at 64 KB (loops unrolled) it no longer fits the instruction cache and every phase took half as long again.
+// workgroup's tiles, by any wave.  us per cat_fit: 563519 x 40, K = 91: 1992 -> 1747; 1048576 x 256,
+// K = 32: 2423 -> 2357; longer rows only where every kind of data gained (loop_bounds_pays).
 #include <atomic>
 
 #include "cat_loop.h"
@@ -1153,7 +1148,13 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     return run_loop(lq, dt, N, D, K, iters, cent_io, sums, assign, counts, inertia, rep, skipped, lw, nullptr, st);
 }
 
-bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
+// Rows of up to 256 channels: faster or the same in all of 70 fits of 64 to 490 MB (0.99 to 1.21).  Longer rows: the first passes after the
+// full ones list many rows, which k_delta_prep adds faster than the members' atomics, and only a long run of short lists makes up for
+// it, us in two launches a pass / here: 40000 x 1000, K = 5, 10 iterations 553 / 670; 117187 x 512, K = 28, 6: 635 / 774; 50000 x 1000, K =
+// 16, 30, skewed clusters 1756 / 1888 (logits 965 / 725); 80000 x 1000 bf16, K = 5, 30: 1380 / 1602.  So there fp32, few clusters, 20
+// iterations: 50000 x 1000, K = 5, 20: 473 / 403; 83333 x 600, K = 5, 30: 1220 / 1134, K = 8, 20: 1231 / 1236.
+bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
+    if (D > 256 && (dt != CAT_F32 || (int64_t)K * D > 5120 || iters < 20)) return false;
     return g_loop_members.load() >= 0 && lloyd_list_capacity() == kListCap && rerank_queue_capacity() == kQueueCap && !profile_on() &&
            loop_config(N, D, K, dt, true).ok;
 }

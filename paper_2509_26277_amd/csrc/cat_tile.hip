@@ -1003,7 +1003,7 @@ cat_status tile_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
             CAT_T(dt == CAT_BF16 ? launch_bounds_bf16(p, c, st) : launch_bounds_f32(p, c, st));
         else
             CAT_T(launch_tile(p, c, dt, st));
-        if (t == kFullPasses && bounds && record && one_launch && loop_bounds_pays(N, D, K, dt)) {
+        if (t == kFullPasses && bounds && record && one_launch && loop_bounds_pays(N, D, K, iters, dt)) {
             const LoopBounds lb = {bw->expire, bw->rows, p.list_count, cnt_t};
             return loop_lloyd_bounds(lq, dt, N, D, K, iters, cent_io, sums, assign, counts, inertia, rep, lw, lb, st);
         }
