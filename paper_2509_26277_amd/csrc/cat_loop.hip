@@ -16,6 +16,10 @@
 // the waves share the channels of a tile where a pass has few tiles.  A row within the error bound is measured at the end of the
 // workgroup's tiles, by any wave.  us per cat_fit: 563519 x 40, K = 91: 1992 -> 1747; 1048576 x 256,
 // K = 32: 2423 -> 2357; longer rows only where every kind of data gained (loop_bounds_pays).
+// Tried: as many copies of the sums as spread those additions (a copy more to read is a trip more: 179 -> 228 with two); a third and
+// fourth chunk of rows in flight (registers spill, 7 .. 20 % slower); a delay before the first look at the flags (alone it makes a
+// barrier of 256 workgroups 1.1 us instead of 2.4, here it is lost beside the waits for the last one to arrive).  The code has to
+// stay small: at 64 KB (loops unrolled) it no longer fits the instruction cache and every phase took half as long again.
 #include <atomic>
 
 #include "cat_loop.h"
