@@ -63,6 +63,11 @@ struct LoopParams {
     const double* sumsq;      // kSumSqSlots shares of the sum of |x|^2
 };
 constexpr int kLoopBounds = 2;
+// Passes whose sums are made afresh from all rows, as with two launches a pass.  Most rows still move in pass 1; and what a row of
+// large entries leaves behind where it is added and taken away again (a rounding of the sum it was in) would stay in that cluster's
+// sum.  us per cat_fit, pass 1 by differences / afresh: 4096 x 64, K = 4, 20 iterations: 129 / 131; 41590 x 40 bf16, K = 21, 18: 246 / 252;
+// 562555 x 38 bf16, K = 3, 30: 446 / 507.
+constexpr int kLoopFull = 2;
 struct LoopQueued {  // a row that is measured when the workgroup has run out of tiles
     uint32_t row;
     int prev;
@@ -475,19 +480,21 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             }
         }
     };
-    // a row's cluster (the lanes with `on` hold one each): the label, and the lists of what changed
+    // a row's cluster (the lanes with `on` hold one each): the label, and the lists of what changed (the first passes: of all rows)
     auto book = [&](bool on, int64_t row, int prev, int k) {
-        const bool changed = on && prev != k;
-        const unsigned long long cm = __ballot(changed);
+        const bool changed = on && prev != k, afresh = !BOUNDS && t < kLoopFull && (t == 0 || K > 1), listed = changed || (on && afresh);
+        const unsigned long long cm = __ballot(listed);
         if (!cm) return;
         int pos = 0;
         if (lane == 0) pos = atomicAdd(&s_misc[2], (int)__builtin_popcountll(cm));
         pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(cm & ((1ull << lane) - 1ull));
-        if (changed) {
-            p.assign[row] = k;
-            const unsigned long long ent = ((unsigned long long)row << 24) | ((unsigned long long)(prev + 1) << 12) | (unsigned long long)k;
+        if (listed) {
+            const unsigned long long ent = ((unsigned long long)row << 24) | ((unsigned long long)(afresh ? 0 : prev + 1) << 12) | (unsigned long long)k;
             own_list[pos] = ent;
             if (pos < kLoopList) s_list[pos] = ent;
+        }
+        if (changed) {
+            p.assign[row] = k;
             atomicAdd(&s_dn[k], 1);
             atomicOr(&s_mask[k >> 5], 1u << (k & 31));
             if (prev >= 0) {
@@ -712,9 +719,9 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         // Three buffers of sums take turns.  Pass t adds to buffer t what moves; its owner adds the sums up to pass t - 1, so that after
         // the flags of pass t buffer t holds the sums up to t.  Buffer t + 1 was read last after the flags of pass t - 2, which
         // everybody did before raising the flag of pass t - 1: it is free now, and clear before the flags of pass t.
-        // The share of the sums so far moves on to this pass's, and the buffers of the pass that follows are cleared.
+        // The share of the sums so far moves on to this pass's (unless that adds up all rows), and the buffers of the pass that follows are cleared.
         for (int i = z_lo + tid; i < z_hi; i += kLoopT) {
-            if (i != z_lo + tid) carry = t > (BOUNDS ? kLoopBounds : 0) ? far_load(sums_prev + i) : 0.0;
+            if (i != z_lo + tid) carry = t > (BOUNDS ? kLoopBounds : kLoopFull - 1) ? far_load(sums_prev + i) : 0.0;
             if (carry != 0.0) atomicAdd(sums + i, carry);
             far_store(sums_next + i, 0.0);
         }
@@ -931,7 +938,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         // ---- the next centroids ----
         const bool last = BOUNDS && t == p.iters;
         if (last && rank != 0) break;
-        if (z_lo + tid < z_hi) carry = far_load(sums + z_lo + tid);
+        if (z_lo + tid < z_hi && (BOUNDS || t >= kLoopFull - 1)) carry = far_load(sums + z_lo + tid);
         build(mask, sums, dn, BOUNDS && rank == 0 && p.inertia, last);
         __syncthreads();
         if (BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia && t > kLoopBounds) {

@@ -129,6 +129,31 @@ def test_given_centroids_far_from_the_rows():
     _same(got, want, x, "f32")
 
 
+def test_rows_of_very_different_magnitude():
+    """a few rows 1e17 times as long as the others leave those rows' clusters after pass 0: nothing of them may stay in the sums
+    (passes 0 and 1 make the sums afresh, as two launches a pass do)"""
+    rng = np.random.default_rng(2)
+    u = rng.standard_normal(64)
+    x = rng.standard_normal((3000, 64)) + 2.0
+    for i, far in ((100, 1.0e17), (200, -1.0e17)):  # (the two groups all but cancel: the short rows keep their cluster)
+        x[i:i + 20] = far * u
+        x[i + 20:i + 80] = 1.8 * far * u
+        x[i + 80:i + 84] = 3.0 * far * u
+    x = x.astype(np.float32)
+    y = (0.5 * x + 1.0).astype(np.float32)
+    init = np.stack([np.zeros(64), 3.0e17 * u, -3.0e17 * u]).astype(np.float32)
+    # what the case is about, by the oracle: the long rows lie with the short ones in pass 0 and leave them in pass 1
+    first = oracle.assign(x, init)
+    second = oracle.assign(x, oracle.fit(x, y, 3, 1, init_centroids=init)["centroids"])
+    assert (first[100:120] == 0).all() and (second[100:120] == 1).all() and (second == 0).sum() == 2832
+    want = oracle.fit(x, y, 3, 6, init_centroids=init)
+    got, two = _fits(x, y, 3, 6, "f32", init_centroids=torch.from_numpy(init).cuda())
+    for r in (two, got):
+        assert (r["assignments"].cpu().numpy() == want["assignments"]).all()
+        for k in range(3):
+            check_values(host_matrix(r["centroids"])[k], want["centroids"][k], CENTROID_RTOL, f"centroid {k}")
+
+
 def test_calls_side_by_side_on_streams():
     """loops of several streams share the chip: each with the members that were there in time"""
     cases = [(_rows(n, d, 8, "f32", n), k) for n, d, k in ((20000, 64, 9), (33000, 80, 37), (5000, 600, 8), (12000, 100, 64))]
