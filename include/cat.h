@@ -541,11 +541,20 @@ cat_status cat_debug_full_loop(int on);
 
 /*
  * Test hook.  Fits of up to 64 MB whose centroids fit LDS run their whole Lloyd loop in one launch, in which the workgroups
- * that are there when it starts share the rows; the first one waits some 30 us for the others.  members > 0: it waits for no
- * more than that many in all; 0: for as many as the launch has (default); negative: such fits run two launches a pass, as the
- * larger ones do.  Same outputs.  Process-wide; returns CAT_OK.
+ * that are there when it starts share the rows; the first one waits some 30 us for the others.  So do the passes from the fourth on of
+ * larger fits, which leave rows out by distance bounds.  Either only where that is the faster way.  members > 0: the first one
+ * waits for no more than that many in all, and every shape that fits runs this way; 0: as described (default); negative: no fit does,
+ * all run two launches a pass.  Same outputs.  Process-wide; returns CAT_OK.
  */
 cat_status cat_debug_loop(int members);
+
+/*
+ * Test hook.  Where in the workspace of cat_fit (bytes from its start, iters >= 2) a 32-bit word says, once the call is through, how its Lloyd
+ * loop ran: CAT_LOOP_RAN + m if passes of it ran in one launch, m workgroups sharing the last of them; otherwise it is
+ * below CAT_LOOP_RAN, provided the caller cleared the workspace before.  0: no such word (a shape without a loop on matrix cores).
+ */
+#define CAT_LOOP_RAN 0x40000000
+size_t cat_debug_loop_route_offset(int64_t N, int64_t D, int32_t K, cat_dtype dt);
 
 /*
  * Test hook.  The PCA's tridiagonalisation runs in workgroups that wait for each other, no longer than this many looks

@@ -16,6 +16,7 @@ _lib = None
 CAT_F32, CAT_BF16 = 0, 1
 CAT_PATH_AUTO, CAT_PATH_STREAM, CAT_PATH_TILE = 0, 1, 2
 CAT_PCA_PATIENCE = 100000
+CAT_LOOP_RAN = 0x40000000
 _STATUS = {0: "CAT_OK", 1: "CAT_ERR_INVALID_ARG", 2: "CAT_ERR_UNSUPPORTED", 3: "CAT_ERR_WORKSPACE",
            4: "CAT_ERR_DEVICE"}
 
@@ -29,7 +30,7 @@ EXPORTS = ("cat_select_path", "cat_fit_workspace_bytes", "cat_apply_workspace_by
            "cat_apply_static", "cat_apply_static_max_workspace_bytes", "cat_debug_apply_kernel",
            "cat_fit_multi_k_workspace_bytes", "cat_fit_multi_k", "cat_debug_multi_group_tiles",
            "cat_params_to_bf16", "cat_apply_lp_workspace_bytes", "cat_apply_lp",
-           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_debug_loop", "cat_debug_pca_patience",
+           "cat_fit_bounds_workspace_bytes", "cat_fit_bounds", "cat_debug_padded_fit", "cat_debug_full_loop", "cat_debug_loop", "cat_debug_loop_route_offset", "cat_debug_pca_patience",
            "cat_debug_pca_route_offset", "cat_stream_probe")
 
 
@@ -143,6 +144,8 @@ def load_library():
     lib.cat_debug_full_loop.restype = c.c_int
     lib.cat_debug_loop.argtypes = [c.c_int]
     lib.cat_debug_loop.restype = c.c_int
+    lib.cat_debug_loop_route_offset.argtypes = [i64, i64, i32, c.c_int]
+    lib.cat_debug_loop_route_offset.restype = sz
     lib.cat_debug_padded_fit.argtypes = [c.c_int]
     lib.cat_debug_padded_fit.restype = c.c_int
     lib.cat_debug_apply_kernel.argtypes = [c.c_int]
@@ -513,8 +516,17 @@ def debug_full_loop(on):
 
 
 def debug_loop(members):
-    """Test hook: how many workgroups a Lloyd loop in one launch waits for (0: all of them; negative: two launches a pass)."""
+    """Test hook: a Lloyd loop in one launch waits for no more than ``members`` workgroups, and takes every shape that it fits
+    (0: for all of them, where it is the faster one; negative: two launches a pass)."""
     _check(load_library().cat_debug_loop(int(members)))
+
+
+def debug_loop_members(N, D, K, dtype, workspace):
+    """Test hook: how many workgroups shared the last pass of the Lloyd loop in one launch of the ``cat_fit`` that used ``workspace``
+    (cleared before); 0: all its passes were launches of their own.  Synchronises."""
+    at = int(load_library().cat_debug_loop_route_offset(N, D, K, dtype))
+    word = int(workspace[at:at + 4].view(torch.int32)) if at else 0
+    return max(0, word - CAT_LOOP_RAN)
 
 
 def debug_pca_patience(looks):

@@ -413,6 +413,19 @@ size_t cat_fit_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     return b;
 }
 
+size_t cat_debug_loop_route_offset(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
+    if (!shape_ok(N, D, K, dt)) return 0;
+    char* const base = (char*)256;  // (any address: only distances from it count)
+    char* fit = base;
+    if (pad_applies(N, D, K, dt)) {
+        PadWs pw = carve_pad(base + align256(carve_fit(nullptr, N, D, K, dt, true).bytes), N, D, K, dt, false, true);
+        fit = (char*)pw.fit;
+        D = pw.Dp;
+    }
+    const FitWs w = carve_fit(fit, N, D, K, dt, true);
+    return w.lloyd.skipped ? (size_t)((char*)w.lloyd.skipped - base) : 0;
+}
+
 size_t cat_apply_workspace_bytes(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     if (!shape_ok(N, D, K, dt)) return 0;
     return carve_apply(nullptr, D, K, dt, N).bytes;

@@ -43,6 +43,7 @@ struct LoopParams {
     double* inertia;          // nullable
     unsigned long long* rep;
     int32_t* skipped;         // nullable
+    int32_t* route;           // CAT_LOOP_RAN + members, for cat_debug_loop_route_offset
     double* sums;             // 3 x K x D; the first third zero on entry
     int32_t* dn;              // 3 x K; the first third zero on entry
     // zero on entry: [0] who has come, [1] how many take part, then by parity of the pass NM words a workgroup (the clusters it
@@ -981,6 +982,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         for (int i = t + (BOUNDS ? 0 : 1) + lane; i <= p.iters; i += kWave) p.inertia[i] = v;
     }
     if (rank == 0 && tid == 0 && p.skipped) *p.skipped = settled && p.iters - 1 > (t > 2 ? t : 2) ? p.iters - 1 - (t > 2 ? t : 2) : 0;
+    if (rank == 0 && tid == 0) *p.route = CAT_LOOP_RAN + M;
     int* s_hist = s_dn;
     unsigned long long* s_rep = (unsigned long long*)s_panel;  // (a panel has at least 16 channels)
     if (tid < K) {
@@ -1087,6 +1089,7 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
     p.inertia = inertia;
     p.rep = rep;
     p.skipped = skipped;
+    p.route = lw.skipped;  // (none of the loops here uses that word otherwise)
     p.sums = sums;
     p.list = lw.list;
     if (lb) {
@@ -1165,7 +1168,7 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
 // 16, 30, skewed clusters 1756 / 1888 (logits 965 / 725); 80000 x 1000 bf16, K = 5, 30: 1380 / 1602.  So there fp32, few clusters, 20
 // iterations: 50000 x 1000, K = 5, 20: 473 / 403; 83333 x 600, K = 5, 30: 1220 / 1134, K = 8, 20: 1231 / 1236.
 bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
-    if (D > 256 && (dt != CAT_F32 || (int64_t)K * D > 5120 || iters < 20)) return false;
+    if (g_loop_members.load() <= 0 && D > 256 && (dt != CAT_F32 || (int64_t)K * D > 5120 || iters < 20)) return false;
     return g_loop_members.load() >= 0 && lloyd_list_capacity() == kListCap && rerank_queue_capacity() == kQueueCap && !profile_on() &&
            loop_config(N, D, K, dt, true).ok;
 }

@@ -31,12 +31,25 @@ def _rows(N, D, comps, dtype, seed, spread=2.0):
     return x.astype(np.float32), y.astype(np.float32)
 
 
-def _fits(x, y, K, iters, dtype, members=0, **kw):
-    lq, fp = dev_matrix(x, dtype), dev_matrix(y, dtype)
+ALL = 256  # the most workgroups a loop has: waits for all of them, and every shape that fits runs in one launch
+
+
+def _fit_on(members, lq, fp, K, iters, **kw):
+    """cat_fit with the hook set, and how many workgroups shared its last pass (0: two launches a pass)"""
+    N, D = lq.shape
+    dt = binding.CAT_BF16 if lq.dtype == torch.bfloat16 else binding.CAT_F32
+    ws = torch.zeros(binding.cat_fit_workspace_bytes(N, D, K, dt), dtype=torch.uint8, device="cuda")
     binding.debug_loop(members)
-    got = cat_fit(lq, fp, K, iters, seed=5, **kw)
-    binding.debug_loop(-1)
-    want = cat_fit(lq, fp, K, iters, seed=5, **kw)
+    r = cat_fit(lq, fp, K, iters, seed=5, workspace=ws, **kw)
+    binding.debug_loop(0)
+    return r, binding.debug_loop_members(N, D, K, dt, ws)
+
+
+def _fits(x, y, K, iters, dtype, members=ALL, **kw):
+    lq, fp = dev_matrix(x, dtype), dev_matrix(y, dtype)
+    got, shared = _fit_on(members, lq, fp, K, iters, **kw)
+    want, none = _fit_on(-1, lq, fp, K, iters, **kw)
+    assert shared > 0 and none == 0
     return got, want
 
 
@@ -78,20 +91,32 @@ def test_same_outputs_as_two_launches_a_pass(N, D, K, iters, dtype):
     _same(got, want, x, dtype)
 
 
-@pytest.mark.parametrize("members", [0, 3])
+@pytest.mark.parametrize("members", [ALL, 3])
 @pytest.mark.parametrize("N,D,K,iters,dtype", [(70001, 240, 5, 9, "f32"), (66003, 512, 17, 6, "bf16"), (131101, 128, 128, 5, "f32"),
                                                (17001, 1000, 16, 12, "f32"), (280001, 60, 1, 4, "f32"), (400031, 45, 33, 8, "f32")])
 def test_passes_that_leave_rows_out(N, D, K, iters, dtype, members):
     """from 64 MB on: the bounds of two launches a pass, which test_gpu_fit_default_bounds compares with the full loop"""
+    _bounded(N, D, K, iters, dtype, members)
+
+
+@pytest.mark.parametrize("N,D,K,iters,dtype", [
+    # bf16, each number of cluster tiles, whole 16-byte groups and not
+    (150001, 256, 5, 7, "bf16"), (300001, 128, 17, 6, "bf16"), (400003, 90, 33, 6, "bf16"), (270001, 128, 100, 6, "bf16"),
+    # fp32, two tiles of clusters; long rows, whose channels four or eight waves share
+    (200003, 100, 20, 6, "f32"), (33001, 600, 8, 20, "f32"), (17001, 1000, 5, 20, "f32")])
+def test_shapes_that_are_dispatched_there(N, D, K, iters, dtype):
+    _bounded(N, D, K, iters, dtype, 0)
+
+
+def _bounded(N, D, K, iters, dtype, members):
     g = torch.Generator(device="cuda").manual_seed(N)
     mu = torch.randn(max(2, K - 1), D, generator=g, device="cuda") * 0.7
     lq = mu[torch.randint(0, mu.shape[0], (N,), generator=g, device="cuda")] + torch.randn(N, D, generator=g, device="cuda")
     lq = lq.to(torch.bfloat16 if dtype == "bf16" else torch.float32).contiguous()
     fp = (lq * 1.1).contiguous()
-    binding.debug_loop(members)
-    got = cat_fit(lq, fp, K, iters, seed=5)
-    binding.debug_loop(-1)
-    want = cat_fit(lq, fp, K, iters, seed=5)
+    got, shared = _fit_on(members, lq, fp, K, iters)
+    want, none = _fit_on(-1, lq, fp, K, iters)
+    assert shared > 0 and none == 0
     # both rank exactly against centroids that agree to a rounding: a handful of rows between two of them may differ
     assert int((got["assignments"] != want["assignments"]).sum()) <= 3
     assert (torch.bincount(got["assignments"].long(), minlength=K) == got["counts"]).all()
@@ -99,7 +124,7 @@ def test_passes_that_leave_rows_out(N, D, K, iters, dtype, members):
     check_values(host_matrix(got["centroids"]), host_matrix(want["centroids"]), 1e-4, "centroids")
 
 
-@pytest.mark.parametrize("members", [1, 2, 5, 0])
+@pytest.mark.parametrize("members", [1, 2, 5, ALL])
 def test_any_number_of_workgroups(members):
     """the rows are shared out over the workgroups that are there when the first one closes the door"""
     x, y = _rows(9000, 96, 12, "f32", 3, spread=0.5)
@@ -161,7 +186,7 @@ def test_calls_side_by_side_on_streams():
     for (x, y), k in cases:
         binding.debug_loop(-1)
         want.append(cat_fit(dev_matrix(x, "f32"), dev_matrix(y, "f32"), k, 10, seed=5))
-    binding.debug_loop(0)
+    binding.debug_loop(ALL)
     ins = [(dev_matrix(x, "f32"), dev_matrix(y, "f32"), k) for (x, y), k in cases]
     streams = [torch.cuda.Stream() for _ in cases]
     torch.cuda.synchronize()
@@ -179,6 +204,7 @@ def test_replayed_from_a_graph():
     x, y = _rows(8000, 72, 10, "f32", 4, spread=0.7)
     lq, fp = dev_matrix(x, "f32"), dev_matrix(y, "f32")
     ws = torch.empty(binding.cat_fit_workspace_bytes(8000, 72, 12, binding.CAT_F32), dtype=torch.uint8, device="cuda")
+    binding.debug_loop(ALL)
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
@@ -193,5 +219,4 @@ def test_replayed_from_a_graph():
         torch.cuda.synchronize()
         binding.debug_loop(-1)
         want = cat_fit(lq, fp, 12, 8, seed=5)
-        binding.debug_loop(0)
         _same(got, want, (x * scale).astype(np.float32), "f32")
