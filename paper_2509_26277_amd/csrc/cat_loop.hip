@@ -1046,12 +1046,42 @@ static LoopCfg loop_config(int64_t N, int64_t D, int32_t K, cat_dtype dt, bool b
     return c;
 }
 
-// Below 64 MB, where the passes keep no distance bounds (cat_tile.hip): faster than two launches a pass in all of 260 fits measured
-// there (256 .. 560000 rows of 24 .. 1000 channels, K = 1 .. 128, 1 .. 30 iterations; 1.0 .. 4.0, 1.63 on average; the least at one to
-// three iterations with 50 clusters and more).  The centroids have to fit LDS twice, see loop_config.
+// Few tiles of long rows: several waves share the channels of a tile (what the others have goes through the panel).  us per cat_fit,
+// one wave a tile / as here: 2958 x 984 bf16, K = 14: 159 / 115 (8 waves); 2652 x 640, K = 11: 279 / 187 (4); 7294 x 776, K = 3: 133 / 115 (4);
+// 14629 x 998 bf16, K = 4: 273 / 230 (2)
+static int loop_share(const LoopCfg& c, int64_t N, int32_t K, int cus, bool bounds) {
+    int share = 1;
+    while (share < kLoopW && 2 * share <= (c.nsteps + 3) / 4 && (bounds || (N + kRows - 1) / kRows * 2 * share <= (int64_t)cus * kLoopW) &&
+           (size_t)(kLoopW - kLoopW / (2 * share)) * (c.KT * 1024 + 256) <= (size_t)K * c.W * 8)
+        share *= 2;
+    return share;
+}
+static int loop_groups(int64_t N, int share, int cus, bool bounds) {
+    int64_t groups = bounds ? (N + kWave - 1) / kWave : ((N + kRows - 1) / kRows * share + kLoopW - 1) / kLoopW;
+    if (groups > cus) groups = cus;
+    return (int)(groups < kLoopMax ? groups : kLoopMax);
+}
+
+// Below 64 MB, where the passes keep no distance bounds (cat_tile.hip), and the centroids fit LDS twice (loop_config): where one launch
+// saves more than it costs.  Against two launches a pass, us per fit, by least squares over 1300 fits (256 .. 700000 rows of 16 .. 1024
+// channels, K = 1 .. 128, 1 .. 32 iterations, four kinds of data):
+//   saved: 6 a pass (launches, trips) and 4 more in the first four, and 400 per million rows (no sort by cluster for the full sums);
+//   lost: 16 per million additions to the sums in memory if every workgroup adds to all of them, once a full pass; 70 per thousand rows
+//   of a workgroup for each part of the channels that the panel takes at a time; 2.5 per million entries of bf16 rows (the rows of
+//   a tile kernel come faster, and there are twice as many to 64 MB).
+// Both sides, two launches / one: 28835 x 1000 bf16, K = 16, 4 iterations 230 / 420 (two here); 60074 x 480 bf16, K = 16, 10: 430 / 525
+// (two); 14417 x 1000, K = 16, 4: 222 / 281 (two); 1715 x 136 bf16, K = 98, 2: 116 / 206 (two); 30037 x 480, K = 16, 10: 359 / 283 (one);
+// 6291 x 1000 bf16, K = 3, 10: 174 / 132 (one).  Over 1200 other fits of the same ranges: 1.43 times as fast on average, 5 of them slower
+// than 0.98 of two launches a pass, the least 0.92.
 bool loop_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
-    return (double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) < 64.0 * 1024 * 1024 && iters >= 1 && g_loop_members.load() >= 0 &&
-           loop_config(N, D, K, dt).ok;
+    if ((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) >= 64.0 * 1024 * 1024 || iters < 1 || g_loop_members.load() < 0) return false;
+    const LoopCfg c = loop_config(N, D, K, dt);
+    if (!c.ok || g_loop_members.load() > 0) return c.ok;
+    const double groups = loop_groups(N, loop_share(c, N, K, kLoopMax, false), kLoopMax, false);
+    const double saved = 6.0 * iters + 4.0 * (iters < 4 ? iters : 4) + 400e-6 * (double)N;
+    const double lost = 16e-6 * groups * (double)K * (double)D + 70e-3 * (double)N / groups * (double)((D + c.W - 1) / c.W) +
+                        (dt == CAT_BF16 ? 2.5e-6 * (double)N * (double)D : 0.0);
+    return saved - lost > 10.0;
 }
 
 // clears the words and the sums of the first pass
@@ -1112,20 +1142,11 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
         CAT_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
         if (dev < 16) ncu[dev].store(v);
     }
-    // Few tiles of long rows: several waves share the channels of a tile (what the others have goes through the panel).  us per cat_fit,
-    // one wave a tile / as here: 2958 x 984 bf16, K = 14: 159 / 115 (8 waves); 2652 x 640, K = 11: 279 / 187 (4); 7294 x 776, K = 3: 133 / 115 (4);
-    // 14629 x 998 bf16, K = 4: 273 / 230 (2)
-    p.share = 1;
-    while (p.share < kLoopW && 2 * p.share <= (c.nsteps + 3) / 4 && (lb || (int64_t)p.ntiles * 2 * p.share <= (int64_t)v * kLoopW) &&
-           (size_t)(kLoopW - kLoopW / (2 * p.share)) * (c.KT * 1024 + 256) <= (size_t)K * c.W * 8)
-        p.share *= 2;
+    p.share = loop_share(c, N, K, v, lb != nullptr);
     // the error bound of the split arithmetic as in the tile kernels (cat_tile.hip: base_params); shared channels are added up once more
     const int n_acc = (dt == CAT_BF16 ? 2 : 3) * ((c.nsteps + 3) / 4 * 4) + 8 + (p.share - 1);
     p.tau = (dt == CAT_BF16 ? 3.1e-5f : 9.4e-5f) + 4.f * (float)n_acc * 5.96e-8f;
-    int groups = lb ? v : (p.ntiles * p.share + kLoopW - 1) / kLoopW;
-    if (lb && groups > (N + kWave - 1) / kWave) groups = (int)((N + kWave - 1) / kWave);
-    if (groups > v) groups = v;
-    if (groups > kLoopMax) groups = kLoopMax;
+    const int groups = loop_groups(N, p.share, v, lb != nullptr);
     // Rows that go to the sums directly come to 2 rows / K additions an address and workgroup, through the panel to one at most; all
     // workgroups add to the same addresses.  us per cat_fit with up to 2 / 4 / 16 rows directly: 89551 x 128 bf16, K = 7 (256 workgroups)
     // 242 / 268 / 308; 7294 x 776, K = 3 (228) 115 / 115 / 150; 14629 x 998 bf16, K = 4 (229) 249 / 228 / 233; 4096 x 64, K = 4 (32)
