@@ -1183,15 +1183,21 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     return run_loop(lq, dt, N, D, K, iters, cent_io, sums, assign, counts, inertia, rep, skipped, lw, nullptr, st);
 }
 
-// Rows of up to 256 channels: faster or the same in all of 70 fits of 64 to 490 MB (0.99 to 1.21).  Longer rows: the first passes after the
-// full ones list many rows, which k_delta_prep adds faster than the members' atomics, and only a long run of short lists makes up for
-// it, us in two launches a pass / here: 40000 x 1000, K = 5, 10 iterations 553 / 670; 117187 x 512, K = 28, 6: 635 / 774; 50000 x 1000, K =
-// 16, 30, skewed clusters 1756 / 1888 (logits 965 / 725); 80000 x 1000 bf16, K = 5, 30: 1380 / 1602.  So there fp32, few clusters, 20
-// iterations: 50000 x 1000, K = 5, 20: 473 / 403; 83333 x 600, K = 5, 30: 1220 / 1134, K = 8, 20: 1231 / 1236.
+// Fits of 64 to 500 MB, two launches a pass against this, 720 random ones (24 .. 256 channels, K = 1 .. 128, 4 .. 32 iterations, four
+// kinds of data).  The panel has to take whole rows at once: there 0.97 to 1.3, 1.07 on average from five iterations on (with four, the one
+// pass in between gains nothing: 0.97 to 1.03); in parts, rows are read again for each, and 12 of 55 fits lost 3 .. 13 % (us: 636254 x 144 bf16, K = 91, 5
+// iterations: 1039 / 1190; 761995 x 145, K = 90, 10: 2918 / 3188).  Longer rows: the first passes after the full ones list many rows,
+// which k_delta_prep adds faster than the members' atomics, and only a long run of short lists makes up for it: 40000 x 1000, K = 5, 10
+// iterations 553 / 670; 117187 x 512, K = 28, 6: 635 / 774; 50000 x 1000, K = 16, 30, skewed clusters 1756 / 1888 (logits 965 / 725); 80000 x
+// 1000 bf16, K = 5, 30: 1380 / 1602.  So there fp32, few clusters, 20 iterations: 88 fits of 50 million entries in rows of 300, 600 and
+// 1000 channels with K = 2, 3, 5, 8 and 20 or 30 iterations, skewed clusters among them: 1.00 to 1.30, the least 83333 x 600, K = 8, 20, skewed
+// 1230 / 1235; 123 random ones 0.98 to 1.51.
 bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
-    if (g_loop_members.load() <= 0 && D > 256 && (dt != CAT_F32 || (int64_t)K * D > 5120 || iters < 20)) return false;
-    return g_loop_members.load() >= 0 && lloyd_list_capacity() == kListCap && rerank_queue_capacity() == kQueueCap && !profile_on() &&
-           loop_config(N, D, K, dt, true).ok;
+    if (g_loop_members.load() < 0 || lloyd_list_capacity() != kListCap || rerank_queue_capacity() != kQueueCap || profile_on()) return false;
+    const LoopCfg c = loop_config(N, D, K, dt, true);
+    if (!c.ok || g_loop_members.load() > 0) return c.ok;
+    if (D > 256) return dt == CAT_F32 && (int64_t)K * D <= 5120 && iters >= 20;
+    return c.W >= D && iters >= 5;
 }
 
 cat_status loop_lloyd_bounds(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,
