@@ -16,10 +16,8 @@
 // Two barriers per tile.  Bound by memory (one read, one write of the rows); per tile the operand costs K D 4 bytes of L2
 // traffic and the parameters 8 bytes per entry.
 //
-// UA: rows that are not whole 16-byte groups (LDS rows start on 16 bytes all the same).  bf16 rows and their parameters move in 16-byte
-// vectors on word boundaries, fp32 ones in words, 64 consecutive words per wave instruction.  us per cat_apply by words / by vectors:
-// bf16 60001 x 1030, K = 100: 195 / 146; 50021 x 2046, K = 30: 169 / 150; 50021 x 1002, K = 64: 85 / 81; fp32, whose parameters then lie on
-// 4 instead of 8 bytes: 50021 x 1001, K = 50: 124 / 145; 100003 x 769, K = 40: 183 / 221.
+// UA: rows that are not whole 16-byte groups (LDS rows start on 16 bytes all the same).  They and their parameters move in words, 64
+// consecutive words per wave instruction, or in 16-byte vectors on word boundaries (wide_in_vectors).
 #pragma once
 #include "cat_infer_kernel.h"
 #include "cat_wide.h"
@@ -43,6 +41,15 @@ struct WideParams {
 typedef iu32x4 __attribute__((aligned(4))) iu32x4_w;  // vectors on a word boundary
 typedef if32x4 __attribute__((aligned(4))) if32x4_w;
 
+// Unaligned rows in vectors: bf16 ones, in the instances that gain.  us per cat_apply by words / by vectors, from a graph, KT and VPR as
+// there: KT = 8, VPR = 3: 112771 x 1114, K = 116: 346 / 246; 8, 4: 65554 x 1846, K = 80: 343 / 270; 8, 2: 90085 x 986, K = 85: 143 / 132 (a single tile a
+// workgroup loses a little: 1950 x 594, K = 89: 24.5 / 25.6); 4, 4:
+// 79833 x 1702, K = 34: 270 / 201; 2, 4: 73117 x 2044, K = 8: 213 / 182; 16, 2: 237423 x 550, K = 225: 530 / 454; 16, 3: 42587 x 1490, K = 186:
+// 221 / 184.  Not 2, 3: 2282 x 1126, K = 8: 21.5 / 24.0, 44001 x 1038, K = 3: 80 / 85; 4, 3: 2825 x 1074, K = 52: 23.3 / 25.8, 37634 x
+// 1042, K = 47: 78 / 81; 4, 2: 1247 x 526, K = 36: 21.3 / 23.3, 52013 x 586, K = 36: 72 / 74 (121776 x 930: 151 / 142); 8, 1: 2783 x 294, K = 77:
+// 19.4 / 20.4, 144248 x 268, K = 95: 107 / 109.  And not fp32, whose parameters then lie on 4 instead of 8 bytes: 50021 x 1001, K = 50: 124 / 145;
+// 100003 x 769, K = 40: 183 / 221.
+constexpr bool wide_in_vectors(bool bf16, int kt, int vpr) { return bf16 && (vpr == 4 || kt == 16 || (kt == 8 && vpr >= 2)); }
 constexpr int wide_row_stride(int vpr) { return vpr * 1024 + 16; }  // bytes; 16 rows apart in banks
 constexpr int wide_dots_stride(int kt, int sc) { return infer_dots_stride(sc * kt * 16); }
 constexpr size_t wide_lds_bytes(int kt, int sc, int rg, int vpr) {
@@ -63,7 +70,7 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
     constexpr int NB = (SPW + U - 1) / U;
     constexpr int NSLOT = (K16 + kWave - 1) / kWave;
     constexpr int NL = RPW * VPR;                          // row vectors of a wave
-    constexpr bool UV = UA && BF16, UW = UA && !BF16;      // unaligned rows in vectors, in words
+    constexpr bool UV = UA && wide_in_vectors(BF16, KT, VPR), UW = UA && !UV;      // unaligned rows in vectors, in words
     typedef typename std::conditional<BF16, bf16_t, float>::type T;
 
     float* s_dots = (float*)(smem + (size_t)ROWS * XS);  // [row][channel share][cluster], rows DS apart
@@ -164,8 +171,20 @@ __global__ __launch_bounds__(kInferWaves * kWave) void k_wide(const WideParams p
         } else {
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                const int w = pos(v, e);
-                lo4[e] = row[w < W ? w : W - 1];
+                int w = pos(v, e);
+                w = w < W ? w : W - 1;
+                if (BF16) {  // two channels per word; D is even, so the pairs are 8-byte aligned
+                    const if32x2 t = *(const if32x2*)(row + 2 * w);
+                    if (e < 2) {
+                        lo4[2 * e] = t.x;
+                        lo4[2 * e + 1] = t.y;
+                    } else {
+                        hi4[2 * e - 4] = t.x;
+                        hi4[2 * e - 3] = t.y;
+                    }
+                } else {
+                    lo4[e] = row[w];
+                }
             }
         }
     };

@@ -1,5 +1,5 @@
-"""The inference kernel with the streamed operand on bfloat16 rows that are not whole 16-byte groups: they move in 16-byte vectors on word
-boundaries, and the vector a row ends in is another one in the last row and the last cluster.
+"""The inference kernel with the streamed operand on bfloat16 rows that are not whole 16-byte groups: they move in words or, some
+instances, in 16-byte vectors on word boundaries, where the vector a row ends in is another one in the last row and the last cluster.
 
 Against the oracle: exact ranking (ties to 1e-5 exempt), one rounding of the result to bfloat16 (half a unit of 2^-8)."""
 import numpy as np
@@ -23,7 +23,8 @@ def _streamed_operand():
 
 # words of a row past the last whole vector: 1, 2, 3 and none; rows that end in the first, a middle and the last vector of the lanes
 @pytest.mark.parametrize("N,D,K", [(129, 522, 100), (128, 524, 110), (70, 526, 70), (130, 770, 40), (97, 1022, 64), (200, 1026, 33), (145, 1534, 128),
-                                   (33, 1538, 17), (100, 2042, 50), (31, 2044, 30), (112, 2046, 100), (230, 1010, 200), (255, 1502, 250)])
+                                   (33, 1538, 17), (100, 2042, 50), (31, 2044, 30), (112, 2046, 100), (230, 1010, 200), (255, 1502, 250),
+                                   (131, 294, 77), (100, 1126, 8), (65, 1126, 40)])
 @pytest.mark.parametrize("alpha", [1.0, 0.6])
 def test_against_the_oracle(N, D, K, alpha):
     rng = np.random.default_rng(N + D + K)
