@@ -523,12 +523,12 @@ cat_status cat_debug_list_capacity(int entries);
 cat_status cat_debug_rerank_queue(int entries);
 
 /*
- * Test hook.  cat_apply (and cat_apply_static) on the fused path has four kernels: one that keeps a tile of rows
+ * Test hook.  cat_apply (and cat_apply_static) on the fused path has five kernels: one that keeps a tile of rows
  * on the chip between the ranking and the affine map and the centroids in registers, one that keeps the rows and
- * streams the centroids (larger products of clusters and channels), one for few rows that needs no preparation, and
- * the tile kernel shared with cat_assign.
+ * streams the centroids (larger products of clusters and channels), one for few rows that needs no preparation, one for rows of up to
+ * 512 bytes that takes 16 of them at a time, and the tile kernel shared with cat_assign.
  * 0 = automatic (default), 1 = the tile kernel (or what takes its place), 2 = only the first, 3 = only the second, 4 = only
- * the third (2, 3 and 4: CAT_ERR_UNSUPPORTED on a shape it has no instance for; they hold where cat_select_path is automatic).  Results never depend on it beyond rounding-equivalent ties.  Process-wide.  CAT_ERR_INVALID_ARG for other values.
+ * the third, 5 = only the fourth (2 .. 5: CAT_ERR_UNSUPPORTED on a shape it has no instance for; they hold where cat_select_path is automatic).  Results never depend on it beyond rounding-equivalent ties.  Process-wide.  CAT_ERR_INVALID_ARG for other values.
  */
 cat_status cat_debug_apply_kernel(int which);
 

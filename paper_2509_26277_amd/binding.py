@@ -210,7 +210,7 @@ def debug_rerank_queue(entries):
 
 def debug_apply_kernel(which):
     """Test hook: 0 automatic, 1 none of the inference kernels, 2 only the row-tile kernel, 3 only the one that streams
-    the centroids, 4 only the one for few rows."""
+    the centroids, 4 only the one for few rows, 5 only the one for short rows."""
     _check(load_library().cat_debug_apply_kernel(int(which)))
 
 

@@ -379,7 +379,7 @@ cat_status cat_debug_rerank_queue(int entries) {
 }
 
 cat_status cat_debug_apply_kernel(int which) {
-    if (which < 0 || which > 4) return set_error(CAT_ERR_INVALID_ARG, "cat_debug_apply_kernel: 0 .. 4, got %d", which);
+    if (which < 0 || which > 5) return set_error(CAT_ERR_INVALID_ARG, "cat_debug_apply_kernel: 0 .. 5, got %d", which);
     g_apply_kernel.store(which);
     return CAT_OK;
 }
@@ -978,7 +978,7 @@ static cat_status apply_impl(const char* who, const void* lq, int64_t N, int64_t
     const int which = g_apply_kernel.load();
     if (path == CAT_PATH_AUTO && (which == 4 || (which == 0 && direct_apply_pays(N, D, K, dt))))
         return direct_apply(lq, dt, N, D, K, centroids, gamma, beta, alpha, corrected, assignments, st);
-    if (path == CAT_PATH_AUTO && which == 0 && short_apply_pays(N, D, K, dt))
+    if (path == CAT_PATH_AUTO && (which == 5 || (which == 0 && short_apply_pays(N, D, K, dt))))
         return short_apply(lq, dt, N, D, K, centroids, gamma, beta, alpha, corrected, assignments, st);
     const bool tile_ok = tile_supports(TILE_APPLY, N, D, K, dt);
     if (path == CAT_PATH_TILE && !tile_ok)

@@ -50,6 +50,7 @@ __device__ __forceinline__ void short_pair32(uint32_t v, uint32_t& a, uint32_t& 
 // PL: the folded parameters lie in LDS, gamma and beta of a channel side by side.  KT: cluster tiles.  VV: 16-byte groups of a tile per lane (rows of up to 64 VV bytes).  UA: rows that are not whole 16-byte groups.
 template <bool BF16, int KT, int VV, bool UA, bool PL>
 __global__ __launch_bounds__(kShortT) void k_apply_short(const ShortParams p) {
+    static_assert(PL || !UA, "unaligned rows take their parameters from LDS");
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int CPW = BF16 ? 2 : 1;  // channels of a word
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
@@ -308,18 +309,6 @@ __global__ __launch_bounds__(kShortT) void k_apply_short(const ShortParams p) {
                             y[e] = __float_as_uint(fmaf(t.x, __uint_as_float(x[j][e]), t.y));
                         }
                     }
-                } else if (UA) {
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const bool over = w + e >= W;
-                        const int o = ((over ? kb : ka) * W + w + e - (over ? W : 0)) * CPW;
-                        if (BF16) {
-                            const f32x2 g = *(const f32x2*)(p.gamma + o), c = *(const f32x2*)(p.beta + o);
-                            y[e] = pack_bf16(fmaf(fold_g(g.x), lo_half(x[j][e]), fold_b(c.x)), fmaf(fold_g(g.y), hi_half(x[j][e]), fold_b(c.y)));
-                        } else {
-                            y[e] = __float_as_uint(fmaf(fold_g(p.gamma[o]), __uint_as_float(x[j][e]), fold_b(p.beta[o])));
-                        }
-                    }
                 } else {
                     const int o = (ka * W + w) * CPW;
 #pragma unroll
@@ -375,19 +364,19 @@ static ShortCfg short_config(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     c.off_params = (uint32_t)c.lds;
     c.params = c.lds + (size_t)K * D * 8 <= kLdsLimit;
     if (c.params) c.lds += (size_t)K * D * 8;
-    c.ok = c.lds <= kLdsLimit;
+    // (unaligned rows word by word from L2: 500001 x 101, K = 100: 310 us on the other kernels, 316 here)
+    c.ok = c.lds <= kLdsLimit && (c.params || D % (16 / b) == 0);
     return c;
 }
 
 // Wherever the kernel fits, us per cat_apply before / here: 700001 x 60, K = 16: 198 / 66, K = 120: 244 / 103; 700001 x 61, K = 50: 237 / 80;
 // 500001 x 101, K = 50: 187 / 93; 500001 x 128, K = 50: 192 / 112; bf16: 700001 x 60, K = 16: 214 / 33; 758816 x 128, K = 5: 354 / 73; 400001 x
 // 250, K = 30: 243 / 91; 4000 x 32, K = 5: 15.1 / 12.1 (a launch less).  But not
-//   - rows that are not whole 16-byte groups whose parameters do not fit LDS: word by word from L2 (500001 x 101, K = 100: 310 / 316);
 //   - few fp32 rows against large operands, which every workgroup prepares for itself: 2002 x 87, K = 94: 15.6 / 18.9; 15579 x 96, K = 82:
 //     16.9 / 20.0; 1703 x 70, K = 70: 15.2 / 15.8 (bf16 rows: 1175 x 80, K = 70: 24.2 / 12.6).
 bool short_apply_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     const ShortCfg c = short_config(N, D, K, dt);
-    if (!c.ok || (!c.params && D % (dt == CAT_BF16 ? 8 : 4) != 0)) return false;
+    if (!c.ok) return false;
     return dt == CAT_BF16 || (int64_t)K * D <= 4500 || N >= 32768;
 }
 
@@ -417,9 +406,14 @@ static cat_status launch_short(const ShortParams& p, const ShortCfg& c, hipStrea
 }
 template <bool BF16, int KT, bool UA>
 static cat_status launch_short_vv(const ShortParams& p, const ShortCfg& c, hipStream_t st) {
-#define CAT_SHORT(VV) (c.params ? launch_short<BF16, KT, VV, UA, true>(p, c, st) : launch_short<BF16, KT, VV, UA, false>(p, c, st))
-    return c.VV == 2 ? CAT_SHORT(2) : c.VV == 4 ? CAT_SHORT(4) : CAT_SHORT(8);
-#undef CAT_SHORT
+    if constexpr (!UA)
+        if (!c.params)
+            return c.VV == 2   ? launch_short<BF16, KT, 2, false, false>(p, c, st)
+                   : c.VV == 4 ? launch_short<BF16, KT, 4, false, false>(p, c, st)
+                               : launch_short<BF16, KT, 8, false, false>(p, c, st);
+    return c.VV == 2   ? launch_short<BF16, KT, 2, UA, true>(p, c, st)
+           : c.VV == 4 ? launch_short<BF16, KT, 4, UA, true>(p, c, st)
+                       : launch_short<BF16, KT, 8, UA, true>(p, c, st);
 }
 template <bool BF16, bool UA>
 static cat_status launch_short_kt(const ShortParams& p, const ShortCfg& c, hipStream_t st) {

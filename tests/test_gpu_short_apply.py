@@ -1,8 +1,7 @@
 """Inference over short rows (cat_short.hip): rows of at most 512 bytes, moved as pieces of 16 rows.
 
 Against the oracle in double precision: the ranking is exact (rows whose two nearest centroids tie to 1e-5 are exempt), the map one
-fused multiply-add per entry on parameters folded in fp32, bfloat16 results rounded once.  The shapes have more rows than the kernel
-for few rows takes."""
+fused multiply-add per entry on parameters folded in fp32, bfloat16 results rounded once."""
 import numpy as np
 import pytest
 import torch
@@ -13,6 +12,13 @@ from paper_2509_26277_amd import binding, cat_apply
 from parity_util import check_assignments_lazy, check_values, dev_matrix, f32_round, host_matrix
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _short_rows():
+    binding.debug_apply_kernel(5)  # this kernel or an error
+    yield
+    binding.debug_apply_kernel(0)
 
 
 def _case(N, D, K, dtype, seed, spread=2.0):
@@ -43,10 +49,10 @@ def _check(x, cent, g, b, alpha, dtype):
 SHAPES = [
     # N, D, K: fewest channels, remainders of 16 rows, whole 16-byte groups and not, each number of groups per lane
     (1025, 4, 1, "f32"), (1030, 5, 2, "f32"), (1039, 7, 16, "f32"), (1040, 31, 17, "f32"), (1100, 32, 33, "f32"), (1337, 33, 5, "f32"),
-    (1041, 63, 20, "f32"), (1042, 64, 65, "f32"), (1043, 65, 9, "f32"), (1044, 127, 3, "f32"), (1045, 128, 30, "f32"), (40001, 127, 100, "f32"),
+    (1041, 63, 20, "f32"), (1042, 64, 65, "f32"), (1043, 65, 9, "f32"), (1044, 127, 3, "f32"), (1045, 128, 30, "f32"), (40001, 127, 60, "f32"),
     (40003, 128, 128, "f32"), (33333, 20, 128, "f32"),
     (1025, 8, 1, "bf16"), (1030, 10, 2, "bf16"), (1039, 62, 16, "bf16"), (1040, 64, 17, "bf16"), (1041, 66, 33, "bf16"), (1337, 126, 5, "bf16"),
-    (1042, 128, 65, "bf16"), (1043, 130, 9, "bf16"), (1044, 254, 3, "bf16"), (1045, 256, 20, "bf16"), (20001, 250, 40, "bf16"),
+    (1042, 128, 65, "bf16"), (1043, 130, 9, "bf16"), (1044, 254, 3, "bf16"), (1045, 256, 20, "bf16"), (20001, 250, 16, "bf16"), (20002, 248, 60, "bf16"),
 ]
 
 
@@ -87,3 +93,12 @@ def test_without_labels_and_other_rows_beside_non_finite_ones():
                          None, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
     torch.cuda.synchronize()
     assert torch.equal(again[:5], out[:5]) and torch.equal(again[701:], out[701:])
+
+
+@pytest.mark.parametrize("N,D,K,dtype", [(1100, 129, 5, "f32"), (1100, 3, 5, "f32"), (1100, 258, 5, "bf16"), (1100, 6, 5, "bf16"), (1100, 64, 129, "f32"),
+                                         (1100, 127, 100, "f32"), (1100, 250, 40, "bf16")])
+def test_shapes_outside_are_refused(N, D, K, dtype):
+    """longer than 512 bytes, shorter than 16, more than 128 clusters; unaligned rows whose parameters do not fit LDS"""
+    x, cent, g, b = _case(N, D, K, dtype, 1)
+    with pytest.raises(binding.CatError, match="CAT_ERR_UNSUPPORTED"):
+        cat_apply(dev_matrix(x, dtype), _dev(cent), _dev(g), _dev(b))
