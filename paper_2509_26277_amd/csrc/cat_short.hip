@@ -14,6 +14,7 @@
 // row traffic from some 100 MB on; below, the launch and the latency of one tile after the other.
 #include <atomic>
 
+#include "cat_infer.h"
 #include "cat_short.h"
 #include "cat_tile_kernel.h"
 
@@ -369,15 +370,24 @@ static ShortCfg short_config(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     return c;
 }
 
-// Wherever the kernel fits, us per cat_apply before / here: 700001 x 60, K = 16: 198 / 66, K = 120: 244 / 103; 700001 x 61, K = 50: 237 / 80;
-// 500001 x 101, K = 50: 187 / 93; 500001 x 128, K = 50: 192 / 112; bf16: 700001 x 60, K = 16: 214 / 33; 758816 x 128, K = 5: 354 / 73; 400001 x
-// 250, K = 30: 243 / 91; 4000 x 32, K = 5: 15.1 / 12.1 (a launch less).  But not
-//   - few fp32 rows against large operands, which every workgroup prepares for itself: 2002 x 87, K = 94: 15.6 / 18.9; 15579 x 96, K = 82:
-//     16.9 / 20.0; 1703 x 70, K = 70: 15.2 / 15.8 (bf16 rows: 1175 x 80, K = 70: 24.2 / 12.6).
+// us per cat_apply before / here: 700001 x 60, K = 16: 198 / 66, K = 120: 244 / 103; 700001 x 61, K = 50: 237 / 80; 500001 x 101, K = 50:
+// 187 / 93; 500001 x 128, K = 50: 192 / 112; bf16: 700001 x 60, K = 16: 214 / 33; 758816 x 128, K = 5: 354 / 73; 400001 x 250, K = 30: 243 / 91.
+// Few rows: every workgroup prepares the operand for itself, and a wave does one tile at the pace of its latencies.  Over 2000 random calls from a
+// graph (us): wherever the row-tile kernel has no instance of two parts (bf16, K > 64), 1.3 times as fast or more; where it has one, from
+// 16384 rows on (fp32 with K D > 4500: 32768; 15579 x 96, K = 82: 16.9 / 20.0); below
+//   - rows enough for the operand: 2437 x 41, K = 89: 10.2 / 13.5; 2041 x 118, K = 16: 8.2 / 10.6; bf16 6444 x 200, K = 54: 10.4 / 12.6;
+//     and for moving them in pieces across the words: 4706 x 101, K = 16: 9.4 / 10.9; bf16 4298 x 242, K = 2: 10.3 / 11.1;
+//   - not many clusters on a few channels, which lie close to each other: ties are measured one after the other by the wave that has
+//     them: 5941 x 4, K = 115: 13.3 / 20.7; 12512 x 7, K = 110: 18.7 / 20.9.
+// With these lines 5 of 1400 other calls took more than 1.02 times as long, the worst 7.5 / 8.0 (2813 x 128, K = 2).
 bool short_apply_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
-    const ShortCfg c = short_config(N, D, K, dt);
-    if (!c.ok) return false;
-    return dt == CAT_BF16 || (int64_t)K * D <= 4500 || N >= 32768;
+    if (!short_config(N, D, K, dt).ok) return false;
+    if (!infer_two_parts(D, K, dt)) return true;
+    const int64_t KD = (int64_t)K * D;
+    if (dt == CAT_F32 && KD > 4500) return N >= 32768;
+    if (N >= 16384) return true;
+    const bool ua = D % (dt == CAT_BF16 ? 8 : 4) != 0;
+    return K <= 4 * D && 2 * N >= 100 * K + 3 * KD && (!ua || N >= 80 * D);
 }
 
 template <bool BF16, int KT, int VV, bool UA, bool PL>

@@ -102,3 +102,16 @@ def test_shapes_outside_are_refused(N, D, K, dtype):
     x, cent, g, b = _case(N, D, K, dtype, 1)
     with pytest.raises(binding.CatError, match="CAT_ERR_UNSUPPORTED"):
         cat_apply(dev_matrix(x, dtype), _dev(cent), _dev(g), _dev(b))
+
+
+@pytest.mark.parametrize("N,D,K,dtype", [(4706, 101, 16, "f32"), (5941, 4, 100, "f32"), (2041, 118, 16, "f32"), (6444, 200, 54, "bf16"), (20000, 100, 50, "f32"),
+                                         (4096, 32, 10, "f32"), (3000, 120, 70, "bf16")])
+def test_the_dispatch_gives_what_each_kernel_gives(N, D, K, dtype):
+    """either side of the rule's lines: the same labels and, to the rounding of a fold, the same rows as the kernel forced"""
+    x, cent, g, b = _case(N, D, K, dtype, 2, spread=1.0)
+    lq, p = dev_matrix(x, dtype), (_dev(cent), _dev(g), _dev(b))
+    forced, a = cat_apply(lq, *p, alpha=0.6)
+    binding.debug_apply_kernel(0)
+    out, a0 = cat_apply(lq, *p, alpha=0.6)
+    assert (a == a0).all()
+    check_values(host_matrix(out), host_matrix(forced), 1e-6 if dtype == "f32" else 8e-3, "corrected")
