@@ -702,6 +702,30 @@ struct ProjFuse {
     int32_t K;
     float alpha;
 };
+// 16 channels of the row against the directions (step s_ of a chunk; D is a multiple of 4: a group of 4 channels is inside the row or wholly
+// outside).  A macro, because the compiler schedules the loop around it differently from one around a function (k_pca_project_pipe).
+#define CAT_PROJECT_STEP                                                                                                    \
+    const int64_t ch = (int64_t)jc * kProjChunk + 16 * s_ + 4 * g;                                                          \
+    float e[4];                                                                                                             \
+    if (sizeof(T) == 4) {                                                                                                   \
+        e[0] = __uint_as_float(xcur[s_][0]), e[1] = __uint_as_float(xcur[s_][1]);                                           \
+        e[2] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 2 : 0]), e[3] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 3 : 1]); \
+    } else {                                                                                                                \
+        e[0] = __uint_as_float(xcur[s_][0] << 16), e[1] = __uint_as_float(xcur[s_][0] & 0xFFFF0000u);                       \
+        e[2] = __uint_as_float(xcur[s_][1] << 16), e[3] = __uint_as_float(xcur[s_][1] & 0xFFFF0000u);                       \
+    }                                                                                                                       \
+    const f32x4_t mv = *(const f32x4_t*)&s_m[cur][16 * s_ + 4 * g];                                                         \
+    const bool in = ch < D;                                                                                                 \
+    const f32x4_t xv = (f32x4_t){in ? e[0] - mv.x : 0.f, in ? e[1] - mv.y : 0.f, in ? e[2] - mv.z : 0.f,                    \
+                                 in ? e[3] - mv.w : 0.f};                                                                   \
+    _Pragma("unroll")                                                                                                       \
+    for (int t = 0; t < NT; t++) {                                                                                          \
+        const f32x4_t wv = *(const f32x4_t*)&s_w[cur][(((s_ * NT + t) * kWave) + lane) * 4];                                \
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc[t], 0, 0, 0);                                         \
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc[t], 0, 0, 0);                                         \
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc[t], 0, 0, 0);                                         \
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc[t], 0, 0, 0);                                         \
+    }
 template <typename T, int NT, bool FUSED>
 __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(const T* __restrict__ x, int64_t N, int64_t D, int32_t p,
                                                                          const float* __restrict__ mean,
@@ -768,42 +792,36 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
             load_x(jc, xcur);  // this chunk's rows first (the other waves of the SIMD cover their latency), then the next chunk's directions
             load_w(c0, jn, wreg);
             mreg = load_m(jn);
-            // 16 channels of the row against the directions; the steps past the end of a last, shorter chunk are left out.  us
-            // with all / here: projection of 700001 x 60, p = 50: 178 / 112; fused inference, K = 50: 700001 x 60, p = 50: 328 / 292;
-            // 200003 x 160, p = 50: 159 / 141; 65536 x 1000 bf16, p = 30: 134 / 119.  One tile of directions takes them all: its four
-            // products a step are no more than the branch holds up (300000 x 64, p = 16: 87 / 96; 600000 x 104 bf16: 158 / 174).
-            auto step = [&](int s_) {
-                const int64_t ch = (int64_t)jc * kProjChunk + 16 * s_ + 4 * g;
-                float e[4];
-                if (sizeof(T) == 4) {
-                    e[0] = __uint_as_float(xcur[s_][0]), e[1] = __uint_as_float(xcur[s_][1]);
-                    e[2] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 2 : 0]), e[3] = __uint_as_float(xcur[s_][sizeof(T) == 4 ? 3 : 1]);
-                } else {
-                    e[0] = __uint_as_float(xcur[s_][0] << 16), e[1] = __uint_as_float(xcur[s_][0] & 0xFFFF0000u);
-                    e[2] = __uint_as_float(xcur[s_][1] << 16), e[3] = __uint_as_float(xcur[s_][1] & 0xFFFF0000u);
-                }
-                const f32x4_t mv = *(const f32x4_t*)&s_m[cur][16 * s_ + 4 * g];
-                const bool in = ch < D;  // D is a multiple of 4: a group is inside the row or wholly outside
-                const f32x4_t xv = (f32x4_t){in ? e[0] - mv.x : 0.f, in ? e[1] - mv.y : 0.f, in ? e[2] - mv.z : 0.f,
-                                             in ? e[3] - mv.w : 0.f};
-#pragma unroll
-                for (int t = 0; t < NT; t++) {
-                    const f32x4_t wv = *(const f32x4_t*)&s_w[cur][(((s_ * NT + t) * kWave) + lane) * 4];
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.x, xv.x, acc[t], 0, 0, 0);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.y, xv.y, acc[t], 0, 0, 0);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc[t], 0, 0, 0);
-                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc[t], 0, 0, 0);
-                }
-            };
+            // The steps past the end of a last, shorter chunk are left out, in a loop of its own.  us with all / here: projection of 700001 x
+            // 60, p = 50: 178 / 112; fused inference, K = 50: 700001 x 60, p = 50: 328 / 292; 200003 x 160, p = 50: 159 / 141.  One tile of
+            // directions takes them all: its four products a step are no more than the branch holds up (300000 x 64, p = 16: 87 / 96; 600000 x
+            // 104 bf16: 158 / 174); so do two in the fused kernel, where a second loop leaves registers for four waves a SIMD instead of six
+            // (440200 x 120 bf16, p = 17: 97 / 112; 1083963 x 68 bf16, p = 22: 375 / 424).  The step as a function of its own or in the loop, whichever
+            // the compiler schedules better there, us: projection, p <= 16: 16427 x 964 bf16 31 / 20; 12033 x 504 17.4 / 13.3; bf16, p <= 32:
+            // 10294 x 320 13.4 / 12.5; fp32, p <= 32: 1213600 x 32 126 / 139; fused, fp32, p <= 16: 4846 x 712 30.3 / 32.6.
             if (tile < ntiles) {
+                constexpr bool kAll = NT == 1 || (FUSED && NT == 2), kInLoop = !FUSED && (NT == 1 || sizeof(T) == 2);
                 const int64_t rest = D - (int64_t)jc * kProjChunk;
-                if (NT == 1 || rest >= kProjChunk) {
+                if constexpr (kInLoop) {
 #pragma unroll
-                    for (int s_ = 0; s_ < XS; s_++) step(s_);
+                    for (int form = 0; form < (kAll ? 1 : 2); form++) {
+                        if (!kAll && (form == 0) != (rest >= kProjChunk)) continue;
+#pragma unroll
+                        for (int s_ = 0; s_ < XS; s_++) {
+                            if (form == 1 && 16 * s_ >= rest) continue;
+                            CAT_PROJECT_STEP
+                        }
+                    }
                 } else {
+                    auto step = [&](int s_) { CAT_PROJECT_STEP };
+                    if (kAll || rest >= kProjChunk) {
 #pragma unroll
-                    for (int s_ = 0; s_ < XS; s_++)
-                        if (16 * s_ < rest) step(s_);
+                        for (int s_ = 0; s_ < XS; s_++) step(s_);
+                    } else {
+#pragma unroll
+                        for (int s_ = 0; s_ < XS; s_++)
+                            if (16 * s_ < rest) step(s_);
+                    }
                 }
             }
             // the other buffer was last read one chunk ago, before the barrier that ended that chunk
@@ -820,7 +838,7 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
                     float* o = z + row * ldz + c;
                     if (c + 3 < ldz && ((ldz & 3) == 0)) {
                         *(f32x4_t*)o = acc[t];
-                    } else if (c + 3 < ldz && (ldz & 1) == 0 && ((uintptr_t)z & 7u) == 0) {
+                    } else if (NT > 1 && c + 3 < ldz && (ldz & 1) == 0 && ((uintptr_t)z & 7u) == 0) {
                         ((f32x2_t*)o)[0] = (f32x2_t){acc[t].x, acc[t].y};
                         ((f32x2_t*)o)[1] = (f32x2_t){acc[t].z, acc[t].w};
                     } else {
@@ -972,6 +990,7 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
         }
     }
 }
+#undef CAT_PROJECT_STEP
 
 // ---- affine map by given labels ------------------------------------------------------------------
 // One wave per row.  WIDE: 16-byte loads and stores, all of a lane's requests for the row issued before the
