@@ -541,10 +541,11 @@ cat_status cat_debug_full_loop(int on);
 
 /*
  * Test hook.  Fits of up to 64 MB whose centroids fit LDS run their whole Lloyd loop in one launch, in which the workgroups
- * that are there when it starts share the rows; the first one waits some 30 us for the others.  So do the passes from the fourth on of
- * larger fits, which leave rows out by distance bounds.  Either only where that is the faster way.  members > 0: the first one
- * waits for no more than that many in all, and every shape that fits runs this way; 0: as described (default); negative: no fit does,
- * all run two launches a pass.  Same outputs.  Process-wide; returns CAT_OK.
+ * that are there when it starts share the rows, and anew at the end of a pass when others have come: beside another kernel a fit begins
+ * with what that leaves of the chip.  So do the passes from the fourth on of larger fits, which leave rows out by distance bounds.  Either
+ * only where that is the faster way.  members > 0: the loop begins with no more than that many, each further group has up to four times as
+ * many as the one before, and every shape that fits runs this way; 0: as described (default); negative: no fit does, all run two
+ * launches a pass.  Same outputs.  Process-wide; returns CAT_OK.
  */
 cat_status cat_debug_loop(int members);
 

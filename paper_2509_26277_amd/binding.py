@@ -516,8 +516,8 @@ def debug_full_loop(on):
 
 
 def debug_loop(members):
-    """Test hook: a Lloyd loop in one launch waits for no more than ``members`` workgroups, and takes every shape that it fits
-    (0: for all of them, where it is the faster one; negative: two launches a pass)."""
+    """Test hook: a Lloyd loop in one launch begins with no more than ``members`` workgroups, and takes every shape that it fits
+    (0: with all of them, where it is the faster one; negative: two launches a pass)."""
     _check(load_library().cat_debug_loop(int(members)))
 
 

@@ -31,7 +31,9 @@ constexpr int kLoopT = 512, kLoopW = kLoopT / kWave;
 constexpr int kLoopMax = 256;      // workgroups
 constexpr int kLoopDirect = 16;    // changed rows of a workgroup that may go to the sums without the panel (see loop_lloyd)
 constexpr int kLoopList = 64;      // changed rows of a workgroup whose entries are kept in LDS too
-constexpr uint32_t kLoopClosed = 0x80000000u;
+constexpr uint32_t kLoopClosed = 0x80000000u;        // in the word that counts who has come: the loop is through
+constexpr uint32_t kLoopRegroup = 0x80000000u;       // in the tag of the first workgroup's flag: the rows are shared out anew after this pass
+constexpr unsigned long long kLoopOver = ~0ull;      // in place of the number of a group: the loop is through
 
 struct LoopParams {
     const void* lq;
@@ -46,8 +48,9 @@ struct LoopParams {
     int32_t* route;           // CAT_LOOP_RAN + members, for cat_debug_loop_route_offset
     double* sums;             // 3 x K x D; the first third zero on entry
     int32_t* dn;              // 3 x K; the first third zero on entry
-    // zero on entry: [0] who has come, [1] how many take part, then by parity of the pass NM words a workgroup (the clusters it
-    // changed, 32 to a word) and two words a workgroup (halves of its share of the objective)
+    // zero on entry: [0] who has come, [1] number of the group << 32 | its members, [2] .. [5] for a change of groups: the pass to go on
+    // with, the drift so far, who has handed over, who has taken over; from [8] on by parity of the pass NM words a workgroup (the
+    // clusters it changed, 32 to a word) and two words a workgroup (halves of its share of the objective)
     unsigned long long* words;
     unsigned long long* list; // N
     float tau, tau2;
@@ -55,7 +58,9 @@ struct LoopParams {
     int32_t W;                // channels of the panel, a multiple of 16
     int32_t share;            // waves that share the channels of a tile: 1, 2, 4 or 8 (BOUNDS: at most)
     int32_t direct;           // up to that many changed rows of a workgroup go to the sums without the panel
-    int32_t looks, enough;    // the first workgroup waits that many looks for the others, and for no more than `enough`
+    int32_t looks, enough;    // the first workgroup waits that many looks for the others (and see `patience`), and for no more than `enough`
+    int64_t patience;         // looks it waits on while few are there, times those
+    int32_t step;             // a group has at most that many times the members of the one before
     // BOUNDS: the loop goes on after pass kLoopBounds of tile_lloyd, from that pass's sums but for the rows it listed
     double* expire;           // N: the drift at which a row has to be looked at again (see TileParams)
     int32_t* rows;            // N + 63: the members' lists of due rows
@@ -185,7 +190,8 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     int* s_n = (int*)(s_cnorm + KT * 16);             // KT * 16
     int* s_dn = s_n + KT * 16;                        // KT * 16
     uint32_t* s_mask = (uint32_t*)(s_dn + KT * 16);   // 4: own changes; 2 x 4: everybody's, by parity of the pass
-    int* s_misc = (int*)(s_mask + 12);                // [0] rank, [1] members, [2] rows that changed, [3] queued rows, [4] due rows
+    // [0] rank, [1] members, [2] rows that changed, [3] queued rows, [4] due rows, [5] whether the group changes, [6] its number
+    int* s_misc = (int*)(s_mask + 12);
     unsigned long long* s_list = (unsigned long long*)(s_misc + 8);  // kLoopList
     LoopQueued* s_queue = (LoopQueued*)(s_list + kLoopList);  // kLoopQueue
     float* s_score = (float*)(s_queue + kLoopQueue);  // kLoopW x KT * 16
@@ -193,13 +199,14 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     double *s_obj = s_mv + KT * 16, *s_term = s_obj + KT * 16;  // terms of the objective as the centroids stand, and of the pass
 
     // ---- who takes part ----
-    // The workgroups wait for each other, so those that wait must be resident: the members are the workgroups that have come when
-    // the first one closes the door, which it does as soon as all of the grid are there or after `looks` looks (some 30 us: other
-    // kernels hold part of the chip).  A workgroup that starts later finds it closed and leaves.  The rows are shared out over the
-    // members there are, so every wait ends whatever else runs, and nothing has to be known about the stream.
+    // The workgroups wait for each other, so those that wait must be resident: the members of the first group are the workgroups that
+    // have come when the first one closes the door, which it does as soon as all of the grid are there or has waited long enough (see
+    // run_loop: other kernels hold part of the chip).  The rows are shared out over the members there are, so every wait ends
+    // whatever else runs, and nothing has to be known about the stream.  A workgroup that starts later waits for the next group: once an
+    // eighth more are there, or all, the rows are shared out anew at the end of the pass.  One that starts when all is done leaves.
     if (tid == 0) {
         s_misc[0] = (int)__hip_atomic_fetch_add((uint32_t*)p.words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_misc[2] = s_misc[3] = s_misc[4] = 0;
+        s_misc[2] = s_misc[3] = s_misc[4] = s_misc[5] = 0;
     }
     if (tid < 12) s_mask[tid] = 0;
     for (int i = tid; i < (int)(p.off_cent / 16); i += kLoopT) ((u32x4*)smem)[i] = (u32x4){0u, 0u, 0u, 0u};
@@ -323,7 +330,8 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         }
         if (!(BOUNDS && last)) emit(mine);
     };
-    {
+    // the centroids in memory, all of them (a workgroup that comes late may read some that are being written, and reads them again later)
+    auto load_centroids = [&]() {
         int k = tid / D, ch = tid - k * D;
         const int qd = kLoopT / D, rd = kLoopT - qd * D;
 #pragma unroll 4
@@ -336,48 +344,59 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                 k++;
             }
         }
-    }
-    __syncthreads();
-    emit(__ballot(wave + kLoopW * lane < K));
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t m = 0;
-        if (rank == 0) {
-            for (int s = 0; s < p.looks; s++) {
-                if ((int)far_load((uint32_t*)p.words) >= p.enough) break;
-                __builtin_amdgcn_s_sleep(2);
+        __syncthreads();
+        emit(__ballot(wave + kLoopW * lane < K));
+        __syncthreads();
+    };
+    // waits for a group after the one of that number which the workgroup belongs to; false: there will be none
+    int M = 0;
+    uint32_t group = 0;
+    auto admitted = [&]() {
+        if (tid == 0) {
+            unsigned long long g;
+            for (;;) {
+                g = far_load(p.words + 1);
+                if (g == kLoopOver || ((uint32_t)(g >> 32) > group && (uint32_t)rank < (uint32_t)g)) break;
+                __builtin_amdgcn_s_sleep(1);
             }
-            m = __hip_atomic_fetch_or((uint32_t*)p.words, kLoopClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            far_store((uint32_t*)(p.words + 1), m);
-        } else {
-            while ((m = far_load((uint32_t*)(p.words + 1))) == 0u) __builtin_amdgcn_s_sleep(1);
+            s_misc[1] = g == kLoopOver ? 0 : (int)(uint32_t)g;
+            s_misc[6] = (int)(g >> 32);
         }
-        s_misc[1] = (int)m;
-    }
-    __syncthreads();
-    const int M = __builtin_amdgcn_readfirstlane(s_misc[1]);
+        __syncthreads();
+        M = __builtin_amdgcn_readfirstlane(s_misc[1]);
+        group = (uint32_t)__builtin_amdgcn_readfirstlane(s_misc[6]);
+        return M > 0;
+    };
     // The member's rows: consecutive tiles; BOUNDS: every M-th block of 64 (rows that are due lie together where the matrix is
     // sorted), of which a pass takes those that are due.  Its part of the list holds as many entries as it has rows.
-    int t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * rank / M));
-    int t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * (rank + 1) / M));
-    int64_t row_lo = (int64_t)t_lo * kRows;
     const uint32_t blocks64 = (uint32_t)((p.N + kWave - 1) / kWave);
-    const uint32_t per = blocks64 / (uint32_t)M, extra = blocks64 % (uint32_t)M, mine64 = per + ((uint32_t)rank < extra ? 1u : 0u);
+    int t_lo = 0, t_hi = 0, z_lo = 0, z_hi = 0;  // tiles; the share of the sums to carry on
+    uint32_t mine64 = 0;
     int32_t* due = nullptr;
-    if (BOUNDS) {
-        row_lo = (int64_t)kWave * ((int64_t)rank * per + ((uint32_t)rank < extra ? (uint32_t)rank : extra));
-        due = p.rows + row_lo;
-        if ((p.N & (kWave - 1)) && (blocks64 - 1) % (uint32_t)M < (uint32_t)rank) row_lo -= kWave - (p.N & (kWave - 1));
-    }
-    unsigned long long* const own_list = p.list + row_lo;
-    const unsigned long long* list = own_list;
+    int64_t row_lo = 0;
+    unsigned long long* own_list = nullptr;
+    auto share_out = [&]() {
+        t_lo = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * rank / M));
+        t_hi = __builtin_amdgcn_readfirstlane((int)((int64_t)p.ntiles * (rank + 1) / M));
+        row_lo = (int64_t)t_lo * kRows;
+        const uint32_t per = blocks64 / (uint32_t)M, extra = blocks64 % (uint32_t)M;
+        mine64 = per + ((uint32_t)rank < extra ? 1u : 0u);
+        if (BOUNDS) {
+            row_lo = (int64_t)kWave * ((int64_t)rank * per + ((uint32_t)rank < extra ? (uint32_t)rank : extra));
+            due = p.rows + row_lo;
+            if ((p.N & (kWave - 1)) && (blocks64 - 1) % (uint32_t)M < (uint32_t)rank) row_lo -= kWave - (p.N & (kWave - 1));
+        }
+        own_list = p.list + row_lo;
+        z_lo = (int)((int64_t)KD * rank / M);
+        z_hi = (int)((int64_t)KD * (rank + 1) / M);
+    };
+    const unsigned long long* list = nullptr;
     const int nchunks = (p.nsteps + 3) / 4;
     int share = p.share, slots = kLoopW / share;
     int slot = wave / share, part = wave - slot * share;  // the wave's tile in a round, and its chunks of it
     int c_lo = nchunks * part / share, c_hi = nchunks * (part + 1) / share;
     int n_due = 0, lrow = 0;
     double gnow = 0.0, sq_total = 0.0;
-    const int z_lo = (int)((int64_t)KD * rank / M), z_hi = (int)((int64_t)KD * (rank + 1) / M);  // the share of the sums to carry on
     double *sums = p.sums, *sums_next = p.sums + KD, *sums_prev = p.sums + 2 * KD;
     const int k_start = (rank + wave) % K;
     double carry = 0.0;
@@ -648,318 +667,407 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         }
     };
 
-    bool settled = false;
+    bool settled = false, in = false, regroup = false;
     int e0 = 0, e1 = 0;  // BOUNDS: the member's share of the rows that the pass before the first listed
-    if (BOUNDS) {
-        const int64_t len = (int64_t)*p.list_count;
-        e0 = (int)(len * rank / M);
-        e1 = (int)(len * (rank + 1) / M);
-        list = p.list + e0;
-        if (tid < 4) s_mask[tid] = ~0u;
-        if (rank == 0) sq_total = wave_total(p.sumsq[lane * kSumSqStride]);
-        static_assert(kSumSqSlots == kWave, "one share a lane");
-        if (tid == 0) s_misc[2] = e1 - e0;
-        __syncthreads();
-    } else {
-        restart();
-    }
-    for (;; t++) {
-        // ---- assignment of the own rows ----
-        if (BOUNDS && t > kLoopBounds) {
-            // how far the centroids have moved in all (select_rows in cat_tile_kernel.h), and the rows that are due
-            double v1 = lane < K ? s_mv[lane] : 0.0, v2 = 0.0;
-            if (KT > 4) {
-                const double o = lane + kWave < K ? s_mv[lane + kWave] : 0.0;
-                v2 = fmin(v1, o);
-                v1 = fmax(v1, o);
-            }
-            v1 = fmax(sqrt(v1), 0.0);
-            v2 = fmax(sqrt(v2), 0.0);
-            two_largest(v1, v2);
-            const double g0 = gnow;
-            gnow = g0 + (v1 + v2) * (1.0 + 1e-9);
-            if (v1 + v2 > 0.0 && gnow == g0) gnow = __longlong_as_double(__double_as_longlong(g0) + 1);  // (drifts are >= 0)
-            for (uint32_t i0 = (uint32_t)wave; i0 < mine64; i0 += U * kLoopW) {
-                if (i0 != (uint32_t)wave) bounds_of(i0);
-#pragma unroll
-                for (uint32_t u = 0; u < U; u++) {
-                    const uint32_t i = i0 + kLoopW * u;
-                    const int64_t r = (int64_t)kWave * ((int64_t)rank + (int64_t)M * i) + lane;
-                    const bool is_due = i < mine64 && r < p.N && !(gnow <= ex[u]);
-                    const unsigned long long m = __ballot(is_due);
-                    if (!m) continue;
-                    int pos = 0;
-                    if (lane == 0) pos = atomicAdd(&s_misc[4], (int)__builtin_popcountll(m));
-                    pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
-                    if (is_due) due[pos] = (int32_t)r;
+    for (;;) {  // groups; almost always one
+        load_centroids();
+        if (!in) {
+            if (rank == 0 && tid == 0) {
+                int come = 0;
+                for (int64_t s = 0;; s++) {
+                    come = (int)far_load((uint32_t*)p.words);
+                    if (come >= p.enough || (s >= p.looks && s * come >= p.patience)) break;
+                    __builtin_amdgcn_s_sleep(2);
                 }
+                far_store(p.words + 1, (1ull << 32) | (uint32_t)(come < p.enough ? come : p.enough));
             }
-            __syncthreads();
-            n_due = __builtin_amdgcn_readfirstlane(s_misc[4]);
-            t_lo = 0;
-            t_hi = (n_due + kRows - 1) / kRows;
-            share = 1;
-            while (2 * share <= p.share && t_hi * 2 * share <= kLoopW) share *= 2;
-            slots = kLoopW / share;
-            slot = wave / share;
-            part = wave - slot * share;
-            c_lo = nchunks * part / share;
-            c_hi = nchunks * (part + 1) / share;
-            list = own_list;
-            restart();
-        }
-        {
-            float c2 = 0.f;
-            for (int k = lane; k < K; k += kWave) c2 = fmaxf(c2, s_cnorm[k]);
-            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0xB1, 0xF, 0xF, true)));
-            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x4E, 0xF, 0xF, true)));
-            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x141, 0xF, 0xF, true)));
-            c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x140, 0xF, 0xF, true)));
-            cmax = sqrtf(fmaxf(fmaxf(readlane_f(c2, 0), readlane_f(c2, 16)), fmaxf(readlane_f(c2, 32), readlane_f(c2, 48))));
-        }
-        // Three buffers of sums take turns.  Pass t adds to buffer t what moves; its owner adds the sums up to pass t - 1, so that after
-        // the flags of pass t buffer t holds the sums up to t.  Buffer t + 1 was read last after the flags of pass t - 2, which
-        // everybody did before raising the flag of pass t - 1: it is free now, and clear before the flags of pass t.
-        // The share of the sums so far moves on to this pass's (unless that adds up all rows), and the buffers of the pass that follows are cleared.
-        for (int i = z_lo + tid; i < z_hi; i += kLoopT) {
-            if (i != z_lo + tid) carry = t > (BOUNDS ? kLoopBounds : kLoopFull - 1) ? far_load(sums_prev + i) : 0.0;
-            if (carry != 0.0) atomicAdd(sums + i, carry);
-            far_store(sums_next + i, 0.0);
-        }
-        if (rank == 0 && tid < K) far_store(dn_next + tid, 0);
-        if (BOUNDS && rank == 0 && t == kLoopBounds + 1) clear_counts();  // (counts0 may be the same array: everybody has read it)
-        in_acc = 0.0;
-        int prev = -1, row = 0;
-        for (int first = t_lo; first < (BOUNDS && t == kLoopBounds ? t_lo : t_hi); first += slots) {  // a round: every slot one tile
-            if (tc < t_hi) {
-                prev = cur.prev;
-                row = cur.row;
-                while (cc < c_hi) {
-                    issue(next);
-                    contract(cur);
-                    cc++;
-                    cur = next;
-                }
-            }
-            if (share > 1) {
-                // the first of the waves that share a tile adds up what the others have (in the panel, which is left zero)
-                if (first > t_lo) __syncthreads();
-                f32x4* parts = (f32x4*)(smem + p.off_panel);
-                if (part > 0) {
-                    const int at = (slot * (share - 1) + part - 1) * (KT * kWave + kWave / 4);
-#pragma unroll
-                    for (int u = 0; u < KT; u++) {
-                        parts[at + u * kWave + lane] = acc[u];
-                        acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                    }
-                    ((float*)(parts + at + KT * kWave))[lane] = nrm;
-                    nrm = 0.f;
-                }
-                __syncthreads();
-                if (part == 0) {
-                    for (int i = 0; i < share - 1; i++) {
-                        const int at = (slot * (share - 1) + i) * (KT * kWave + kWave / 4);
-#pragma unroll
-                        for (int u = 0; u < KT; u++) {
-                            acc[u] += parts[at + u * kWave + lane];
-                            parts[at + u * kWave + lane] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                        }
-                        nrm += ((float*)(parts + at + KT * kWave))[lane];
-                        ((float*)(parts + at + KT * kWave))[lane] = 0.f;
-                    }
-                }
-            }
-            if (part == 0 && tc < t_hi) finish(prev, row);
-            cc = c_lo;
-            tc += slots;
-        }
-        if (BOUNDS) {
-            __syncthreads();
-            const int pushed = __builtin_amdgcn_readfirstlane(s_misc[3]), qn = pushed < kLoopQueue ? pushed : kLoopQueue;
-            for (int e = wave; e < qn; e += kLoopW) {
-                const LoopQueued w = s_queue[e];
-                unsigned long long cand[NC];
-                cand[0] = w.cand[0];
-                if (NC > 1) cand[NC - 1] = w.cand[1];
-                const int first = cand[0] ? __builtin_ctzll(cand[0]) : kWave + __builtin_ctzll(cand[NC - 1]);
-                double dbest;
-                int k = measure((int64_t)w.row, cand, dbest);
-                if (k == 0x7fffffff) k = first;  // (non-finite input: any of them)
-                if (lane == 0) p.expire[w.row] = gnow;  // two centroids within the bound of each other: no margin
-                book(lane == 0, (int64_t)w.row, w.prev, k);
+            if (!admitted()) return;
+            in = true;
+            if (group > 1) {
+                __threadfence();
+                continue;
             }
         }
-        if (!BOUNDS) {
-            in_acc = wave_total(in_acc);
-            if (lane == 0) s_in[wave] = in_acc;
-        }
-        own_memory_done();
-        __syncthreads();
-        if (!BOUNDS && t == p.iters) break;
-
-        // ---- the rows that changed cluster move between the sums ----
-        const int nch = __builtin_amdgcn_readfirstlane(s_misc[2]);
-        if (nch > 0 && nch <= p.direct) {
-            const unsigned long long ent = BOUNDS && t == kLoopBounds ? list[lane < nch ? lane : 0] : s_list[lane < nch ? lane : 0];
-            const uint32_t e_lo = (uint32_t)ent, e_hi = (uint32_t)(ent >> 32);
-            const int blocks = (D + kWave - 1) / kWave, items = nch * blocks;
-            constexpr int U = BOUNDS ? 8 : 4;  // rows and blocks requested at once
-            for (int i0 = wave; i0 < items; i0 += U * kLoopW) {
-                float x[U];
-                int ch[U], nw[U], od[U];
-#pragma unroll
-                for (int u = 0; u < U; u++) {
-                    const int it = i0 + u * kLoopW < items ? i0 + u * kLoopW : i0;
-                    const int e = it / blocks;
-                    ch[u] = (it - e * blocks) * kWave + lane;
-                    const uint32_t lo = __builtin_amdgcn_readlane(e_lo, e), hi = __builtin_amdgcn_readlane(e_hi, e);
-                    const int64_t row = (int64_t)(((unsigned long long)hi << 8) | (lo >> 24));
-                    nw[u] = (int)(lo & 0xFFFu);
-                    od[u] = (int)((lo >> 12) & 0xFFFu) - 1;
-                    x[u] = ld_elem((const T*)p.lq + row * D + (ch[u] < D ? ch[u] : 0));
-                }
-#pragma unroll
-                for (int u = 0; u < U; u++) {
-                    if (i0 + u * kLoopW >= items) break;
-                    if (ch[u] < D) {
-                        atomicAdd(sums + nw[u] * D + ch[u], (double)x[u]);
-                        if (od[u] >= 0) atomicAdd(sums + od[u] * D + ch[u], -(double)x[u]);
-                    }
-                }
-            }
-        } else if (nch > 0) {
-            const int pw = (nch + kLoopW - 1) / kLoopW, ws = wave * pw, we = ws + pw < nch ? ws + pw : nch;
-            for (int c0 = 0; c0 < D; c0 += W) {
-                const int wc = D - c0 < W ? D - c0 : W;
-                for (int b = ws; b < we; b += kWave) {
-                    const int nb = we - b < kWave ? we - b : kWave;
-                    const unsigned long long ent = list[b + (lane < nb ? lane : 0)];
-                    const uint32_t e_lo = (uint32_t)ent, e_hi = (uint32_t)(ent >> 32);
-                    constexpr int RB = 8, CB = 2;
-                    for (int i0 = 0; i0 < nb; i0 += RB)
-                        for (int cb = 0; cb < wc; cb += CB * kWave) {
-                            float x[RB][CB];
-                            int nw[RB], od[RB];
-#pragma unroll
-                            for (int u = 0; u < RB; u++) {
-                                const int i = i0 + u < nb ? i0 + u : nb - 1;
-                                const uint32_t lo = __builtin_amdgcn_readlane(e_lo, i), hi = __builtin_amdgcn_readlane(e_hi, i);
-                                const int64_t row = (int64_t)(((unsigned long long)hi << 8) | (lo >> 24));
-                                nw[u] = i0 + u < nb ? (int)(lo & 0xFFFu) : -1;
-                                od[u] = i0 + u < nb ? (int)((lo >> 12) & 0xFFFu) - 1 : -1;
-                                const T* xr = (const T*)p.lq + row * D + c0;
-#pragma unroll
-                                for (int w = 0; w < CB; w++) {
-                                    const int c = cb + w * kWave + lane;
-                                    if (cb + w * kWave < wc) x[u][w] = ld_elem(xr + (c < wc ? c : 0));
-                                }
-                            }
-#pragma unroll
-                            for (int u = 0; u < RB; u++)
-#pragma unroll
-                                for (int w = 0; w < CB; w++) {
-                                    const int c = cb + w * kWave + lane;
-                                    if (c < wc) {
-                                        if (nw[u] >= 0) atomicAdd(s_panel + nw[u] * W + c, (double)x[u][w]);
-                                        if (od[u] >= 0) atomicAdd(s_panel + od[u] * W + c, -(double)x[u][w]);
-                                    }
-                                }
-                        }
-                }
-                __syncthreads();
-                int k = k_start;  // (the workgroups start at different clusters: not all at one address)
-                for (int i = wave; i < K; i += kLoopW) {
-                    for (int c = lane; c < wc; c += kWave) {
-                        const double v = s_panel[k * W + c];
-                        if (v != 0.0) {
-                            atomicAdd(sums + k * D + c0 + c, v);
-                            s_panel[k * W + c] = 0.0;
-                        }
-                    }
-                    k += kLoopW;
-                    while (k >= K) k -= K;
-                }
-                if (c0 + W < D) __syncthreads();
-            }
-        }
-        if (nch > 0 && tid < K) {
-            const int d = s_dn[tid];
-            if (d) {
-                atomicAdd(dn + tid, d);
-                s_dn[tid] = 0;
-            }
-        }
-        if (nch > 0) {
+        share_out();
+        list = own_list;
+        if (group > 1) {  // goes on where the last group has stopped
+            t = __builtin_amdgcn_readfirstlane((int)far_load(p.words + 2));
+            regroup = true;  // (BOUNDS: the bounds of its rows have not been requested yet)
+            gnow = __longlong_as_double((long long)far_load(p.words + 3));
+            const int turn = (t - (BOUNDS ? kLoopBounds : 0)) % 3, after = turn == 2 ? 0 : turn + 1, before = turn == 0 ? 2 : turn - 1;
+            sums = p.sums + turn * KD;
+            sums_next = p.sums + after * KD;
+            sums_prev = p.sums + before * KD;
+            dn = p.dn + turn * K;
+            dn_next = p.dn + after * K;
+            dn_prev = p.dn + before * K;
+            if (tid < K) s_n[tid] = (int)far_load(p.rep + tid);
             own_memory_done();
             __syncthreads();
-        }
-        unsigned long long* flags = p.words + 8 + (t & 1) * (NM + 2) * G;
-        const int par = t & 1;
-        if (tid < NM) {
-            far_store(flags + tid * G + rank, ((unsigned long long)s_mask[tid] << 32) | (uint32_t)(t + 1));
-            s_mask[tid] = 0;
-            s_mask[4 + 4 * (par ^ 1) + tid] = 0;
-        }
-        if (tid == 0) {
-            if (!BOUNDS) {
-                double v = 0.0;
-#pragma unroll
-                for (int w = 0; w < kLoopW; w++) v += s_in[w];
-                tagged_store(flags + NM * G + rank, G, v, (uint32_t)(t + 1));
+            if (tid == 0) {
+                __hip_atomic_fetch_add(p.words + 5, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                while (far_load(p.words + 5) != (unsigned long long)M) __builtin_amdgcn_s_sleep(1);
             }
-            s_misc[2] = s_misc[3] = s_misc[4] = 0;
+            __syncthreads();
+            if (rank == 0 && tid < K) far_store(p.rep + tid, ~0ull);
+            carry = z_lo + tid < z_hi && (BOUNDS || t >= kLoopFull) ? far_load(sums_prev + z_lo + tid) : 0.0;
+        } else if (BOUNDS) {
+            const int64_t len = (int64_t)*p.list_count;
+            e0 = (int)(len * rank / M);
+            e1 = (int)(len * (rank + 1) / M);
+            list = p.list + e0;
+            if (tid < 4) s_mask[tid] = ~0u;
+            if (rank == 0) sq_total = wave_total(p.sumsq[lane * kSumSqStride]);
+            static_assert(kSumSqSlots == kWave, "one share a lane");
+            if (tid == 0) s_misc[2] = e1 - e0;
+            __syncthreads();
         }
-        // ---- wait for the others; the first rows (bounds) of the next pass travel meanwhile ----
-        if (BOUNDS) bounds_of((uint32_t)wave);
-        else restart();
-        for (int i0 = wave * kWave; i0 < NM * kLoopMax; i0 += kLoopT) {
-            const int w = i0 / kLoopMax, m0 = i0 - w * kLoopMax;
-            if (m0 >= M) continue;
-            const unsigned long long* f = flags + w * G + (m0 + lane < M ? m0 + lane : M - 1);
-            unsigned long long v = far_load(f);
-            while (__any((uint32_t)v != (uint32_t)(t + 1))) v = far_load(f);
-            const uint32_t bits = (uint32_t)(v >> 32);
-            if (bits) atomicOr(&s_mask[4 + 4 * par + w], bits);
-        }
-        __syncthreads();
-        if (!BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia) {
-            double v = 0.0;
-            for (int m = lane; m < M; m += kWave) v += tagged_load(flags + NM * G + m, G, (uint32_t)(t + 1));
-            v = wave_total(v);
-            if (lane == 0) p.inertia[t] = v;
-        }
-        const uint32_t* mask = s_mask + 4 + 4 * par;
-        uint32_t any = mask[0];
+        if (!BOUNDS) restart();
+        for (;;) {
+            // ---- assignment of the own rows ----
+            if (BOUNDS && t > kLoopBounds) {  // the rows that are due
+                for (uint32_t i0 = (uint32_t)wave; i0 < mine64; i0 += U * kLoopW) {
+                    if (regroup || i0 != (uint32_t)wave) bounds_of(i0);
 #pragma unroll
-        for (int w = 1; w < NM; w++) any |= mask[w];
-        if (__builtin_amdgcn_readfirstlane(any) == 0u) {
-            settled = true;
-            break;
+                    for (uint32_t u = 0; u < U; u++) {
+                        const uint32_t i = i0 + kLoopW * u;
+                        const int64_t r = (int64_t)kWave * ((int64_t)rank + (int64_t)M * i) + lane;
+                        const bool is_due = i < mine64 && r < p.N && !(gnow <= ex[u]);
+                        const unsigned long long m = __ballot(is_due);
+                        if (!m) continue;
+                        int pos = 0;
+                        if (lane == 0) pos = atomicAdd(&s_misc[4], (int)__builtin_popcountll(m));
+                        pos = __builtin_amdgcn_readfirstlane(pos) + (int)__builtin_popcountll(m & ((1ull << lane) - 1ull));
+                        if (is_due) due[pos] = (int32_t)r;
+                    }
+                }
+                __syncthreads();
+                n_due = __builtin_amdgcn_readfirstlane(s_misc[4]);
+                t_lo = 0;
+                t_hi = (n_due + kRows - 1) / kRows;
+                share = 1;
+                while (2 * share <= p.share && t_hi * 2 * share <= kLoopW) share *= 2;
+                slots = kLoopW / share;
+                slot = wave / share;
+                part = wave - slot * share;
+                c_lo = nchunks * part / share;
+                c_hi = nchunks * (part + 1) / share;
+                list = own_list;
+                restart();
+            }
+            regroup = false;
+            {
+                float c2 = 0.f;
+                for (int k = lane; k < K; k += kWave) c2 = fmaxf(c2, s_cnorm[k]);
+                c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0xB1, 0xF, 0xF, true)));
+                c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x4E, 0xF, 0xF, true)));
+                c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x141, 0xF, 0xF, true)));
+                c2 = fmaxf(c2, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(c2), 0x140, 0xF, 0xF, true)));
+                cmax = sqrtf(fmaxf(fmaxf(readlane_f(c2, 0), readlane_f(c2, 16)), fmaxf(readlane_f(c2, 32), readlane_f(c2, 48))));
+            }
+            // Three buffers of sums take turns.  Pass t adds to buffer t what moves; its owner adds the sums up to pass t - 1, so that after
+            // the flags of pass t buffer t holds the sums up to t.  Buffer t + 1 was read last after the flags of pass t - 2, which
+            // everybody did before raising the flag of pass t - 1: it is free now, and clear before the flags of pass t.
+            // The share of the sums so far moves on to this pass's (unless that adds up all rows), and the buffers of the pass that follows are cleared.
+            for (int i = z_lo + tid; i < z_hi; i += kLoopT) {
+                if (i != z_lo + tid) carry = t > (BOUNDS ? kLoopBounds : kLoopFull - 1) ? far_load(sums_prev + i) : 0.0;
+                if (carry != 0.0) atomicAdd(sums + i, carry);
+                far_store(sums_next + i, 0.0);
+            }
+            if (rank == 0 && tid < K) far_store(dn_next + tid, 0);
+            if (BOUNDS && rank == 0 && t == kLoopBounds + 1) clear_counts();  // (counts0 may be the same array: everybody has read it)
+            in_acc = 0.0;
+            int prev = -1, row = 0;
+            for (int first = t_lo; first < (BOUNDS && t == kLoopBounds ? t_lo : t_hi); first += slots) {  // a round: every slot one tile
+                if (tc < t_hi) {
+                    prev = cur.prev;
+                    row = cur.row;
+                    while (cc < c_hi) {
+                        issue(next);
+                        contract(cur);
+                        cc++;
+                        cur = next;
+                    }
+                }
+                if (share > 1) {
+                    // the first of the waves that share a tile adds up what the others have (in the panel, which is left zero)
+                    if (first > t_lo) __syncthreads();
+                    f32x4* parts = (f32x4*)(smem + p.off_panel);
+                    if (part > 0) {
+                        const int at = (slot * (share - 1) + part - 1) * (KT * kWave + kWave / 4);
+#pragma unroll
+                        for (int u = 0; u < KT; u++) {
+                            parts[at + u * kWave + lane] = acc[u];
+                            acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                        }
+                        ((float*)(parts + at + KT * kWave))[lane] = nrm;
+                        nrm = 0.f;
+                    }
+                    __syncthreads();
+                    if (part == 0) {
+                        for (int i = 0; i < share - 1; i++) {
+                            const int at = (slot * (share - 1) + i) * (KT * kWave + kWave / 4);
+#pragma unroll
+                            for (int u = 0; u < KT; u++) {
+                                acc[u] += parts[at + u * kWave + lane];
+                                parts[at + u * kWave + lane] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                            }
+                            nrm += ((float*)(parts + at + KT * kWave))[lane];
+                            ((float*)(parts + at + KT * kWave))[lane] = 0.f;
+                        }
+                    }
+                }
+                if (part == 0 && tc < t_hi) finish(prev, row);
+                cc = c_lo;
+                tc += slots;
+            }
+            if (BOUNDS) {
+                __syncthreads();
+                const int pushed = __builtin_amdgcn_readfirstlane(s_misc[3]), qn = pushed < kLoopQueue ? pushed : kLoopQueue;
+                for (int e = wave; e < qn; e += kLoopW) {
+                    const LoopQueued w = s_queue[e];
+                    unsigned long long cand[NC];
+                    cand[0] = w.cand[0];
+                    if (NC > 1) cand[NC - 1] = w.cand[1];
+                    const int first = cand[0] ? __builtin_ctzll(cand[0]) : kWave + __builtin_ctzll(cand[NC - 1]);
+                    double dbest;
+                    int k = measure((int64_t)w.row, cand, dbest);
+                    if (k == 0x7fffffff) k = first;  // (non-finite input: any of them)
+                    if (lane == 0) p.expire[w.row] = gnow;  // two centroids within the bound of each other: no margin
+                    book(lane == 0, (int64_t)w.row, w.prev, k);
+                }
+            }
+            if (!BOUNDS) {
+                in_acc = wave_total(in_acc);
+                if (lane == 0) s_in[wave] = in_acc;
+            }
+            own_memory_done();
+            __syncthreads();
+            if (!BOUNDS && t == p.iters) break;
+
+            // ---- the rows that changed cluster move between the sums ----
+            const int nch = __builtin_amdgcn_readfirstlane(s_misc[2]);
+            if (nch > 0 && nch <= p.direct) {
+                const unsigned long long ent = BOUNDS && t == kLoopBounds ? list[lane < nch ? lane : 0] : s_list[lane < nch ? lane : 0];
+                const uint32_t e_lo = (uint32_t)ent, e_hi = (uint32_t)(ent >> 32);
+                const int blocks = (D + kWave - 1) / kWave, items = nch * blocks;
+                constexpr int U = BOUNDS ? 8 : 4;  // rows and blocks requested at once
+                for (int i0 = wave; i0 < items; i0 += U * kLoopW) {
+                    float x[U];
+                    int ch[U], nw[U], od[U];
+#pragma unroll
+                    for (int u = 0; u < U; u++) {
+                        const int it = i0 + u * kLoopW < items ? i0 + u * kLoopW : i0;
+                        const int e = it / blocks;
+                        ch[u] = (it - e * blocks) * kWave + lane;
+                        const uint32_t lo = __builtin_amdgcn_readlane(e_lo, e), hi = __builtin_amdgcn_readlane(e_hi, e);
+                        const int64_t row = (int64_t)(((unsigned long long)hi << 8) | (lo >> 24));
+                        nw[u] = (int)(lo & 0xFFFu);
+                        od[u] = (int)((lo >> 12) & 0xFFFu) - 1;
+                        x[u] = ld_elem((const T*)p.lq + row * D + (ch[u] < D ? ch[u] : 0));
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; u++) {
+                        if (i0 + u * kLoopW >= items) break;
+                        if (ch[u] < D) {
+                            atomicAdd(sums + nw[u] * D + ch[u], (double)x[u]);
+                            if (od[u] >= 0) atomicAdd(sums + od[u] * D + ch[u], -(double)x[u]);
+                        }
+                    }
+                }
+            } else if (nch > 0) {
+                const int pw = (nch + kLoopW - 1) / kLoopW, ws = wave * pw, we = ws + pw < nch ? ws + pw : nch;
+                for (int c0 = 0; c0 < D; c0 += W) {
+                    const int wc = D - c0 < W ? D - c0 : W;
+                    for (int b = ws; b < we; b += kWave) {
+                        const int nb = we - b < kWave ? we - b : kWave;
+                        const unsigned long long ent = list[b + (lane < nb ? lane : 0)];
+                        const uint32_t e_lo = (uint32_t)ent, e_hi = (uint32_t)(ent >> 32);
+                        constexpr int RB = 8, CB = 2;
+                        for (int i0 = 0; i0 < nb; i0 += RB)
+                            for (int cb = 0; cb < wc; cb += CB * kWave) {
+                                float x[RB][CB];
+                                int nw[RB], od[RB];
+#pragma unroll
+                                for (int u = 0; u < RB; u++) {
+                                    const int i = i0 + u < nb ? i0 + u : nb - 1;
+                                    const uint32_t lo = __builtin_amdgcn_readlane(e_lo, i), hi = __builtin_amdgcn_readlane(e_hi, i);
+                                    const int64_t row = (int64_t)(((unsigned long long)hi << 8) | (lo >> 24));
+                                    nw[u] = i0 + u < nb ? (int)(lo & 0xFFFu) : -1;
+                                    od[u] = i0 + u < nb ? (int)((lo >> 12) & 0xFFFu) - 1 : -1;
+                                    const T* xr = (const T*)p.lq + row * D + c0;
+#pragma unroll
+                                    for (int w = 0; w < CB; w++) {
+                                        const int c = cb + w * kWave + lane;
+                                        if (cb + w * kWave < wc) x[u][w] = ld_elem(xr + (c < wc ? c : 0));
+                                    }
+                                }
+#pragma unroll
+                                for (int u = 0; u < RB; u++)
+#pragma unroll
+                                    for (int w = 0; w < CB; w++) {
+                                        const int c = cb + w * kWave + lane;
+                                        if (c < wc) {
+                                            if (nw[u] >= 0) atomicAdd(s_panel + nw[u] * W + c, (double)x[u][w]);
+                                            if (od[u] >= 0) atomicAdd(s_panel + od[u] * W + c, -(double)x[u][w]);
+                                        }
+                                    }
+                            }
+                    }
+                    __syncthreads();
+                    int k = k_start;  // (the workgroups start at different clusters: not all at one address)
+                    for (int i = wave; i < K; i += kLoopW) {
+                        for (int c = lane; c < wc; c += kWave) {
+                            const double v = s_panel[k * W + c];
+                            if (v != 0.0) {
+                                atomicAdd(sums + k * D + c0 + c, v);
+                                s_panel[k * W + c] = 0.0;
+                            }
+                        }
+                        k += kLoopW;
+                        while (k >= K) k -= K;
+                    }
+                    if (c0 + W < D) __syncthreads();
+                }
+            }
+            if (nch > 0 && tid < K) {
+                const int d = s_dn[tid];
+                if (d) {
+                    atomicAdd(dn + tid, d);
+                    s_dn[tid] = 0;
+                }
+            }
+            if (nch > 0) {
+                own_memory_done();
+                __syncthreads();
+            }
+            unsigned long long* flags = p.words + 8 + (t & 1) * (NM + 2) * G;
+            const int par = t & 1;
+            if (tid < NM) {
+                uint32_t tag = (uint32_t)(t + 1);
+                // others have come since (not before the last pass, which nothing follows that would wait for the first workgroup)
+                if (tid == 0 && rank == 0 && M < G && t + 1 < p.iters) {
+                    const int come = (int)far_load((uint32_t*)p.words);
+                    if (come == G || come > M + M / 8) tag |= kLoopRegroup;
+                }
+                far_store(flags + tid * G + rank, ((unsigned long long)s_mask[tid] << 32) | tag);
+                s_mask[tid] = 0;
+                s_mask[4 + 4 * (par ^ 1) + tid] = 0;
+            }
+            if (tid == 0) {
+                if (!BOUNDS) {
+                    double v = 0.0;
+#pragma unroll
+                    for (int w = 0; w < kLoopW; w++) v += s_in[w];
+                    tagged_store(flags + NM * G + rank, G, v, (uint32_t)(t + 1));
+                }
+                s_misc[2] = s_misc[3] = s_misc[4] = 0;
+            }
+            // ---- wait for the others; the first rows (bounds) of the next pass travel meanwhile ----
+            if (BOUNDS) bounds_of((uint32_t)wave);
+            else restart();
+            for (int i0 = wave * kWave; i0 < NM * kLoopMax; i0 += kLoopT) {
+                const int w = i0 / kLoopMax, m0 = i0 - w * kLoopMax;
+                if (m0 >= M) continue;
+                const unsigned long long* f = flags + w * G + (m0 + lane < M ? m0 + lane : M - 1);
+                unsigned long long v = far_load(f);
+                while (__any(((uint32_t)v & ~kLoopRegroup) != (uint32_t)(t + 1))) v = far_load(f);
+                if (i0 == 0 && lane == 0 && ((uint32_t)v & kLoopRegroup)) s_misc[5] = 1;
+                const uint32_t bits = (uint32_t)(v >> 32);
+                if (bits) atomicOr(&s_mask[4 + 4 * par + w], bits);
+            }
+            __syncthreads();
+            if (!BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia) {
+                double v = 0.0;
+                for (int m = lane; m < M; m += kWave) v += tagged_load(flags + NM * G + m, G, (uint32_t)(t + 1));
+                v = wave_total(v);
+                if (lane == 0) p.inertia[t] = v;
+            }
+            const uint32_t* mask = s_mask + 4 + 4 * par;
+            uint32_t any = mask[0];
+#pragma unroll
+            for (int w = 1; w < NM; w++) any |= mask[w];
+            if (__builtin_amdgcn_readfirstlane(any) == 0u) {
+                settled = true;
+                break;
+            }
+            // ---- the next centroids ----
+            const bool last = BOUNDS && t == p.iters;
+            if (last && rank != 0) break;
+            if (z_lo + tid < z_hi && (BOUNDS || t >= kLoopFull - 1)) carry = far_load(sums + z_lo + tid);
+            build(mask, sums, dn, BOUNDS && rank == 0 && p.inertia, last);
+            __syncthreads();
+            if (BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia && t > kLoopBounds) {
+                // sum |x|^2 + sum_k c_k . (n_k c_k - 2 S_k), the centroids as they were in this pass
+                double v = 0.0;
+                for (int k = lane; k < K; k += kWave) v += mask[k >> 5] >> (k & 31) & 1u ? s_term[k] : s_obj[k];
+                v = wave_total(v) + sq_total;
+                if (lane == 0) p.inertia[t] = v > 0.0 ? v : (v == v ? 0.0 : v);
+            }
+            if (last) break;
+            if (BOUNDS) {
+                // how far the centroids have moved in all (select_rows in cat_tile_kernel.h), and the rows that are due
+                double v1 = lane < K ? s_mv[lane] : 0.0, v2 = 0.0;
+                if (KT > 4) {
+                    const double o = lane + kWave < K ? s_mv[lane + kWave] : 0.0;
+                    v2 = fmin(v1, o);
+                    v1 = fmax(v1, o);
+                }
+                v1 = fmax(sqrt(v1), 0.0);
+                v2 = fmax(sqrt(v2), 0.0);
+                two_largest(v1, v2);
+                const double g0 = gnow;
+                gnow = g0 + (v1 + v2) * (1.0 + 1e-9);
+                if (v1 + v2 > 0.0 && gnow == g0) gnow = __longlong_as_double(__double_as_longlong(g0) + 1);  // (drifts are >= 0)
+            }
+            {
+                double* s = sums_prev;
+                sums_prev = sums;
+                sums = sums_next;
+                sums_next = s;
+                int32_t* d = dn_prev;
+                dn_prev = dn;
+                dn = dn_next;
+                dn_next = d;
+            }
+            t++;
+            regroup = __builtin_amdgcn_readfirstlane(s_misc[5]) != 0;
+            if (regroup) break;
         }
-        // ---- the next centroids ----
-        const bool last = BOUNDS && t == p.iters;
-        if (last && rank != 0) break;
-        if (z_lo + tid < z_hi && (BOUNDS || t >= kLoopFull - 1)) carry = far_load(sums + z_lo + tid);
-        build(mask, sums, dn, BOUNDS && rank == 0 && p.inertia, last);
+        if (!regroup) break;
+        // ---- another group: those who are there now share the rows out anew ----
+        // What a row's owner keeps of it (label, bound) is in memory, and the sums are; the first workgroup leaves the rest there: the
+        // centroids where they are returned, the rows per cluster in the words of `rep`.
+        if (rank == 0) {
+            for (int k = wave; k < K; k += kLoopW)
+                for (int ch = lane; ch < D; ch += kWave) far_store(p.cent + k * D + ch, s_cent[k * Ds + ch]);
+            if (tid < K) far_store(p.rep + tid, (unsigned long long)(uint32_t)s_n[tid]);
+            if (tid == 0) {
+                far_store(p.words + 2, (unsigned long long)t);
+                far_store(p.words + 3, (unsigned long long)__double_as_longlong(gnow));
+            }
+        }
+        __threadfence();
+        own_memory_done();
         __syncthreads();
-        if (BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia && t > kLoopBounds) {
-            // sum |x|^2 + sum_k c_k . (n_k c_k - 2 S_k), the centroids as they were in this pass
-            double v = 0.0;
-            for (int k = lane; k < K; k += kWave) v += mask[k >> 5] >> (k & 31) & 1u ? s_term[k] : s_obj[k];
-            v = wave_total(v) + sq_total;
-            if (lane == 0) p.inertia[t] = v > 0.0 ? v : (v == v ? 0.0 : v);
+        if (tid == 0) {
+            s_misc[5] = 0;
+            __hip_atomic_fetch_add(p.words + 4, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (rank == 0) {
+                while (far_load(p.words + 4) != (unsigned long long)M) __builtin_amdgcn_s_sleep(1);
+                far_store(p.words + 4, 0ull);
+                far_store(p.words + 5, 0ull);
+                own_memory_done();
+                const int come = (int)far_load((uint32_t*)p.words), most = M * p.step;
+                far_store(p.words + 1, ((unsigned long long)(group + 1) << 32) | (uint32_t)(come < most ? come : most));
+            }
         }
-        if (last) break;
-        {
-            double* s = sums_prev;
-            sums_prev = sums;
-            sums = sums_next;
-            sums_next = s;
-            int32_t* d = dn_prev;
-            dn_prev = dn;
-            dn = dn_next;
-            dn_next = d;
-        }
+        admitted();
+        __threadfence();
+    }
+    if (rank == 0 && tid == 0) {
+        __hip_atomic_fetch_or((uint32_t*)p.words, kLoopClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        far_store(p.words + 1, kLoopOver);
     }
 
     // ---- what is returned ----
@@ -1156,7 +1264,15 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
     if (p.direct > kLoopDirect) p.direct = kLoopDirect;
     const int members = g_loop_members.load();
     p.enough = members > 0 && members < groups ? members : groups;
-    p.looks = 40;
+    p.step = members > 0 ? 4 : kLoopMax;
+    // A look takes some 0.75 us.  On an idle chip all are there within three; a group that lacks some waits for ten, and for as long as
+    // its members would take for a pass (about 40 GB/s each) while that is longer: then the end of another kernel is as likely
+    // as not to come first.  us, two launches a pass / this / this with the first group for good: two fits side by side on two streams: 30037 x 480,
+    // K = 16, 10 iterations 613 / 662 / 1508 (alone 400 / 345); 1048576 x 256, K = 32, 15: 7555 / 7740 / 14434 (3950 / 3880); 14629 x 998
+    // bf16, K = 4, 20: 564 / 700 / 846 (335 / 287); 4096 x 64, K = 4, 20: 542 / 268 / 290 (385 / 208); a fit beside three products of 8192 x 8192 matrices
+    // in bf16: 33816 x 80, K = 37, 30: 3409 / 2586 / 3056.
+    p.looks = 10;
+    p.patience = (int64_t)((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) / 30000.0);
     // The words lie in the scratch of the counting sort, 4 N + 8 K + 8 bytes: 64 + 32 (NM + 2) groups + 12 K are needed, NM <= 4
     const int nm = c.KT < 4 ? 1 : c.KT / 2;
     p.words = (unsigned long long*)lw.sort_ws;

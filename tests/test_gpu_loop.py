@@ -134,10 +134,58 @@ def _bounded(N, D, K, iters, dtype, members):
 
 @pytest.mark.parametrize("members", [1, 2, 5, ALL])
 def test_any_number_of_workgroups(members):
-    """the rows are shared out over the workgroups that are there when the first one closes the door"""
+    """the rows are shared out over the workgroups that are there when the first one closes the door, and anew (the hook: over up to four times
+    as many) when others have come"""
     x, y = _rows(9000, 96, 12, "f32", 3, spread=0.5)
     got, want = _fits(x, y, 20, 12, "f32", members=members, early_stop=True)
     _same(got, want, x, "f32")
+
+
+@pytest.mark.parametrize("N,D,K,iters,dtype", [(9000, 96, 20, 12, "f32"), (5003, 520, 30, 9, "f32"), (30001, 40, 128, 9, "bf16"), (12000, 64, 5, 10, "bf16"),
+                                               (50001, 1000, 5, 20, "f32"), (300001, 128, 17, 12, "bf16"), (420001, 80, 100, 12, "bf16")])
+def test_workgroups_that_come_later_join(N, D, K, iters, dtype):
+    """a loop that begins with one workgroup (others hold the chip) is shared by all before its last pass"""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    mu = torch.randn(max(2, K - 1), D, generator=g, device="cuda") * 0.3
+    lq = mu[torch.randint(0, mu.shape[0], (N,), generator=g, device="cuda")] + torch.randn(N, D, generator=g, device="cuda")
+    lq = lq.to(torch.bfloat16 if dtype == "bf16" else torch.float32).contiguous()
+    fp = (lq * 1.1).contiguous()
+    (got, shared), (want, every) = _fit_on(1, lq, fp, K, iters), _fit_on(ALL, lq, fp, K, iters)
+    assert shared == every
+    # both rank exactly against centroids that agree to a rounding: a handful of rows between two of them may differ
+    assert int((got["assignments"] != want["assignments"]).sum()) <= 3
+    assert (torch.bincount(got["assignments"].long(), minlength=K) == got["counts"]).all()
+    np.testing.assert_allclose(got["inertia"].cpu().numpy(), want["inertia"].cpu().numpy(), rtol=1e-9)
+    check_values(host_matrix(got["centroids"]), host_matrix(want["centroids"]), 1e-4, "centroids")
+
+
+@pytest.mark.parametrize("N,D,K,dtype", [(30037, 480, 16, "f32"), (400031, 64, 33, "f32")])
+def test_a_fit_begun_beside_another_kernel_gets_the_whole_chip(N, D, K, dtype):
+    """the second of two fits begins with what the first one leaves of the chip, and is shared by all workgroups once that has ended"""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    mu = torch.randn(K, D, generator=g, device="cuda") * 0.1
+    lq = mu[torch.randint(0, K, (N,), generator=g, device="cuda")] + torch.randn(N, D, generator=g, device="cuda")
+    fp = (lq * 1.1).contiguous()
+    want, every = _fit_on(ALL, lq, fp, K, 60)
+    assert every > 200
+    at = binding.cat_fit_workspace_bytes(N, D, K, binding.CAT_F32)
+    ws = [torch.zeros(at, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    binding.debug_loop(ALL)
+    for _ in range(3):  # (the first calls on a stream take long)
+        ws[1].zero_()
+        go = torch.cuda.Event()
+        torch.cuda._sleep(3000000)  # both are queued when they start
+        go.record()
+        got = []
+        for s, w, iters in zip(streams, ws, (15, 60)):
+            s.wait_event(go)
+            with torch.cuda.stream(s):
+                got.append(cat_fit(lq, fp, K, iters, seed=5, workspace=w))
+        torch.cuda.synchronize()
+        assert binding.debug_loop_members(N, D, K, binding.CAT_F32, ws[1]) == every
+    assert int((got[1]["assignments"] != want["assignments"]).sum()) <= N // 1000
+    np.testing.assert_allclose(got[1]["inertia"].cpu().numpy(), want["inertia"].cpu().numpy(), rtol=1e-4)
 
 
 def test_ties_and_empty_clusters():
