@@ -163,8 +163,10 @@ cat_status infer_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32
         int nb = 0, v = 0;
         const void* f0 = c.ua ? in.fn_ua : in.fn;
         const void* f1 = c.ua ? in.fn_ua_dyn : in.fn_dyn;
-        CAT_HIP_TRY(hipFuncSetAttribute(f0, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
-        CAT_HIP_TRY(hipFuncSetAttribute(f1, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
+        // (the most there is beside the queue of k_infer, not what this call needs: another thread may launch the same kernel with more meanwhile)
+        const int most = 160 * 1024 - 64;
+        CAT_HIP_TRY(hipFuncSetAttribute(f0, hipFuncAttributeMaxDynamicSharedMemorySize, most));
+        CAT_HIP_TRY(hipFuncSetAttribute(f1, hipFuncAttributeMaxDynamicSharedMemorySize, most));
         CAT_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, f0, kInferWaves * kWave, c.lds));
         CAT_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
         per_cu = nb < 1 ? 1 : nb;

@@ -1202,7 +1202,8 @@ __global__ __launch_bounds__(256) void k_loop_clear(unsigned long long* a, int n
 template <int KT, bool BF16, bool BOUNDS>
 static cat_status launch_loop(const LoopParams& p, const LoopCfg& c, int groups, hipStream_t st) {
     auto kern = k_lloyd_loop<KT, BF16, BOUNDS>;
-    CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
+    // (the most there is, not what this call needs: another thread may launch the same kernel with more meanwhile)
+    CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit));
     hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kLoopT), c.lds, st, p);
     CAT_LAUNCH_CHECK("k_lloyd_loop");
     return CAT_OK;

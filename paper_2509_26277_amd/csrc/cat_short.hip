@@ -398,7 +398,8 @@ static cat_status launch_short(const ShortParams& p, const ShortCfg& c, hipStrea
     CAT_HIP_TRY(hipGetDevice(&dev));
     if (cached_lds != (int)c.lds || cached_dev != dev) {
         int nb = 0, v = 0;
-        CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds));
+        // (the most there is, not what this call needs: another thread may launch the same kernel for a larger K D meanwhile)
+        CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit));
         CAT_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, (const void*)kern, kShortT, c.lds));
         CAT_HIP_TRY(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev));
         per_cu = nb < 1 ? 1 : nb;

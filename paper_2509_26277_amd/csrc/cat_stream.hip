@@ -605,7 +605,7 @@ cat_status launch_segsum(int nq, const void* lq, const void* fp, cat_dtype dt, c
 #define CAT_SEG(T, NQ_)                                                                                          \
     do {                                                                                                         \
         CAT_HIP_TRY(hipFuncSetAttribute((const void*)k_segsum<T, NQ_>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                                        (int)lds));                                                              \
+                                        budget)); /* (not lds: other threads may launch it with more meanwhile) */ \
         hipLaunchKernelGGL((k_segsum<T, NQ_>), grid, block, lds, st, (const T*)lq, (const T*)fp, assign, N, D, K, KC, \
                            SW, (int32_t)panel_rows, pivx, pivy, acc);                                                                 \
     } while (0)

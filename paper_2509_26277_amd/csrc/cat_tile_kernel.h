@@ -1236,7 +1236,8 @@ static inline cat_status launch_one(const TileParams& p, const TileCfg& c, hipSt
     if (CA && c.waves != kMaxWaves) {
         return set_error(CAT_ERR_INVALID_ARG, "k_tile: the chunked-operand variant needs %d waves, got %d", kMaxWaves, c.waves);
     }
-    CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds_total));
+    // (the most there is, not what this call needs: another thread may launch the same kernel with more meanwhile)
+    CAT_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit));
     // persistent grid: as many workgroups as are resident at once (registers and LDS decide), each
     // walking its share of the tiles; asked from the runtime once per kernel variant, LDS size and device
     static thread_local int cached_lds = -1, cached_dev = -1, cached_per_cu = 1, ncu = 256;

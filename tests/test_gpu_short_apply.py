@@ -2,6 +2,8 @@
 
 Against the oracle in double precision: the ranking is exact (rows whose two nearest centroids tie to 1e-5 are exempt), the map one
 fused multiply-add per entry on parameters folded in fp32, bfloat16 results rounded once."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -115,3 +117,30 @@ def test_the_dispatch_gives_what_each_kernel_gives(N, D, K, dtype):
     out, a0 = cat_apply(lq, *p, alpha=0.6)
     assert (a == a0).all()
     check_values(host_matrix(out), host_matrix(forced), 1e-6 if dtype == "f32" else 8e-3, "corrected")
+
+
+def test_threads_that_use_one_kernel_with_different_amounts_of_lds():
+    """one instance, parameters of few and of many channels: what a launch may take is not lowered by a smaller one beside it"""
+    cases = [_case(3000, D, K, "f32", D, spread=1.0) for D, K in ((36, 17), (64, 32))]
+    dev = [(dev_matrix(x, "f32"), _dev(c), _dev(g), _dev(b)) for x, c, g, b in cases]
+    want = [cat_apply(*d) for d in dev]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(i):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(50):
+                    out, a = cat_apply(*dev[i])
+                    torch.cuda.current_stream().synchronize()
+                    if not (torch.equal(out, want[i][0]) and torch.equal(a, want[i][1])):
+                        raise AssertionError("other results")
+        except Exception as e:
+            wrong.append((i, e))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong
