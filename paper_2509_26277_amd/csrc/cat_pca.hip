@@ -726,7 +726,8 @@ struct ProjFuse {
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.z, xv.z, acc[t], 0, 0, 0);                                         \
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv.w, xv.w, acc[t], 0, 0, 0);                                         \
     }
-template <typename T, int NT, bool FUSED>
+// ALL: the steps past the end of a row are done too, on zeros.
+template <typename T, int NT, bool FUSED, bool ALL = NT == 1>
 __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(const T* __restrict__ x, int64_t N, int64_t D, int32_t p,
                                                                          const float* __restrict__ mean,
                                                                          const float* __restrict__ comps, float* __restrict__ z,
@@ -795,17 +796,16 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
             // The steps past the end of a last, shorter chunk are left out, in a loop of its own.  us with all / here: projection of 700001 x
             // 60, p = 50: 178 / 112; fused inference, K = 50: 700001 x 60, p = 50: 328 / 292; 200003 x 160, p = 50: 159 / 141.  One tile of
             // directions takes them all: its four products a step are no more than the branch holds up (300000 x 64, p = 16: 87 / 96; 600000 x
-            // 104 bf16: 158 / 174); so do two in the fused kernel, where a second loop leaves registers for four waves a SIMD instead of six
-            // (440200 x 120 bf16, p = 17: 97 / 112; 1083963 x 68 bf16, p = 22: 375 / 424).  The step as a function of its own or in the loop, whichever
+            // 104 bf16: 158 / 174); two in the fused kernel do where it has so many rows that registers count (project_all_steps).  The step as a function of its own or in the loop, whichever
             // the compiler schedules better there, us: projection, p <= 16: 16427 x 964 bf16 31 / 20; 12033 x 504 17.4 / 13.3; bf16, p <= 32:
             // 10294 x 320 13.4 / 12.5; fp32, p <= 32: 1213600 x 32 126 / 139; fused, fp32, p <= 16: 4846 x 712 30.3 / 32.6.
             if (tile < ntiles) {
-                constexpr bool kAll = NT == 1 || (FUSED && NT == 2), kInLoop = !FUSED && (NT == 1 || sizeof(T) == 2);
+                constexpr bool kInLoop = !FUSED && (NT == 1 || sizeof(T) == 2);
                 const int64_t rest = D - (int64_t)jc * kProjChunk;
                 if constexpr (kInLoop) {
 #pragma unroll
-                    for (int form = 0; form < (kAll ? 1 : 2); form++) {
-                        if (!kAll && (form == 0) != (rest >= kProjChunk)) continue;
+                    for (int form = 0; form < (ALL ? 1 : 2); form++) {
+                        if (!ALL && (form == 0) != (rest >= kProjChunk)) continue;
 #pragma unroll
                         for (int s_ = 0; s_ < XS; s_++) {
                             if (form == 1 && 16 * s_ >= rest) continue;
@@ -814,7 +814,7 @@ __global__ __launch_bounds__(kProjWaves * kWave, 4) void k_pca_project_pipe(cons
                     }
                 } else {
                     auto step = [&](int s_) { CAT_PROJECT_STEP };
-                    if (kAll || rest >= kProjChunk) {
+                    if (ALL || rest >= kProjChunk) {
 #pragma unroll
                         for (int s_ = 0; s_ < XS; s_++) step(s_);
                     } else {
@@ -1148,6 +1148,17 @@ bool apply_pca_fused_supported(const void* lq, int64_t D, int32_t K, int32_t p, 
                             (uintptr_t)corrected;
     return (D & 3) == 0 && (bases & 15u) == 0 && p <= 64 && K <= 256;
 }
+// 17 .. 32 directions: a second loop for the steps of a row's last chunk leaves registers for four waves a SIMD instead of six, which hold
+// 65536 and 98304 rows.  Up to 65536 it is the faster one or the same, above that for fp32 rows but the short ones and, in between, those
+// of up to 384 channels.  us, without / with it: 7223 x 1712, p = 27: 100 / 84; 10482 x 2040 bf16, p = 21: 118 / 101; 82158 x 640, p =
+// 17: 154 / 128; 145618 x 336, p = 31: 125 / 115; 237125 x 40, p = 26: 57.8 / 55.4; 76306 x 96, p = 25: 30.0 / 34.5; 86893 x 336, p = 32: 64.1 /
+// 68.5; 311291 x 112, p = 20: 128 / 142; bf16: 83338 x 240, p = 26: 42.4 / 48.5; 97899 x 624, p = 30: 85 / 99; 799341 x 72, p = 24: 253 / 284.
+static bool project_all_steps(int64_t N, int64_t D, cat_dtype dt) {
+    constexpr int64_t kFour = 65536, kSix = 98304;
+    if (N <= kFour) return false;
+    return dt == CAT_BF16 || (D <= 128 && (D > 48 || N > 8 * kFour)) || (D <= 384 && N <= kSix);
+}
+
 cat_status launch_apply_pca_fused(const void* lq, int64_t N, int64_t D, int32_t K, int32_t p, cat_dtype dt, const float* mean,
                                   const float* components, const float* centroids_z, const float* gamma, const float* beta,
                                   float alpha, void* corrected, int32_t* assignments, hipStream_t st) {
@@ -1156,13 +1167,19 @@ cat_status launch_apply_pca_fused(const void* lq, int64_t N, int64_t D, int32_t 
     ProjFuse f{centroids_z, gamma, beta, corrected, assignments, K, alpha};
     const int64_t rows_per_block = kProjWaves * 16;
     dim3 g((unsigned)((N + rows_per_block - 1) / rows_per_block)), b(kProjWaves * kWave);
-#define CAT_FUSE(T, NT) \
-    hipLaunchKernelGGL((k_pca_project_pipe<T, NT, true>), g, b, 0, st, (const T*)lq, N, D, p, mean, components, nullptr, 0, f)
+#define CAT_FUSE(T, NT, ALL) \
+    hipLaunchKernelGGL((k_pca_project_pipe<T, NT, true, ALL>), g, b, 0, st, (const T*)lq, N, D, p, mean, components, nullptr, 0, f)
+#define CAT_FUSE_P(T)                                                        \
+    if (p <= 16) CAT_FUSE(T, 1, true);                                       \
+    else if (p > 32) CAT_FUSE(T, 4, false);                                  \
+    else if (project_all_steps(N, D, dt)) CAT_FUSE(T, 2, true);              \
+    else CAT_FUSE(T, 2, false)
     if (dt == CAT_F32) {
-        if (p <= 16) CAT_FUSE(float, 1); else if (p <= 32) CAT_FUSE(float, 2); else CAT_FUSE(float, 4);
+        CAT_FUSE_P(float);
     } else {
-        if (p <= 16) CAT_FUSE(bf16_t, 1); else if (p <= 32) CAT_FUSE(bf16_t, 2); else CAT_FUSE(bf16_t, 4);
+        CAT_FUSE_P(bf16_t);
     }
+#undef CAT_FUSE_P
 #undef CAT_FUSE
     CAT_LAUNCH_CHECK("k_pca_project_pipe (fused inference)");
     return CAT_OK;

@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import oracle
-from paper_2509_26277_amd import cat_pca_fit, cat_pca_project
+from paper_2509_26277_amd import binding, cat_apply_pca, cat_pca_fit, cat_pca_project
 
 pytestmark = pytest.mark.gpu
 EPS = np.finfo(np.float64).eps
@@ -54,3 +54,23 @@ def test_scores_of_rows_that_end_inside_a_chunk(N, D, p, dtype):
     d = x.astype(np.float64) - mean
     bound = (D + 2) * 2.0**-24 * (np.abs(d) @ np.abs(comps.astype(np.float64)).T)
     assert (np.abs(z - d @ comps.T.astype(np.float64)) <= bound).all()
+
+
+@pytest.mark.parametrize("D,p,dtype", [(72, 20, "f32"), (136, 32, "f32"), (344, 25, "f32"), (124, 17, "bf16"), (640, 30, "bf16")])
+def test_fused_inference_with_many_rows(D, p, dtype):
+    """17 .. 32 directions: above 65536 rows the steps past a row's end may be done, on zeros: the same bits as without them"""
+    g = torch.Generator(device="cuda").manual_seed(D)
+    N, K = 66003, 7
+    lq = torch.randn(N, D, generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    mean, comps = torch.randn(D, generator=g, device="cuda"), torch.randn(p, D, generator=g, device="cuda") / D ** 0.5
+    cz = torch.randn(K, p, generator=g, device="cuda")
+    gamma, beta = torch.rand(K, D, generator=g, device="cuda") + 0.5, torch.randn(K, D, generator=g, device="cuda")
+    out, a = cat_apply_pca(lq, mean, comps, cz, gamma, beta, alpha=0.7)
+    few, b = cat_apply_pca(lq[:65536], mean, comps, cz, gamma, beta, alpha=0.7)
+    assert torch.equal(a[:65536], b) and torch.equal(out[:65536], few)
+    try:
+        binding.select_path(binding.CAT_PATH_STREAM)
+        steps, c = cat_apply_pca(lq, mean, comps, cz, gamma, beta, alpha=0.7)
+    finally:
+        binding.select_path(binding.CAT_PATH_AUTO)
+    assert torch.equal(a, c) and torch.equal(out, steps)
