@@ -372,22 +372,22 @@ static ShortCfg short_config(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
 
 // us per cat_apply before / here: 700001 x 60, K = 16: 198 / 66, K = 120: 244 / 103; 700001 x 61, K = 50: 237 / 80; 500001 x 101, K = 50:
 // 187 / 93; 500001 x 128, K = 50: 192 / 112; bf16: 700001 x 60, K = 16: 214 / 33; 758816 x 128, K = 5: 354 / 73; 400001 x 250, K = 30: 243 / 91.
-// Few rows: every workgroup prepares the operand for itself, and a wave does one tile at the pace of its latencies.  Over 2000 random calls from a
-// graph (us): wherever the row-tile kernel has no instance of two parts (bf16, K > 64), 1.3 times as fast or more; where it has one, from
-// 16384 rows on (fp32 with K D > 4500: 32768; 15579 x 96, K = 82: 16.9 / 20.0); below
-//   - rows enough for the operand: 2437 x 41, K = 89: 10.2 / 13.5; 2041 x 118, K = 16: 8.2 / 10.6; bf16 6444 x 200, K = 54: 10.4 / 12.6;
-//     and for moving them in pieces across the words: 4706 x 101, K = 16: 9.4 / 10.9; bf16 4298 x 242, K = 2: 10.3 / 11.1;
-//   - not many clusters on a few channels, which lie close to each other: ties are measured one after the other by the wave that has
-//     them: 5941 x 4, K = 115: 13.3 / 20.7; 12512 x 7, K = 110: 18.7 / 20.9.
-// With these lines 5 of 1400 other calls took more than 1.02 times as long, the worst 7.5 / 8.0 (2813 x 128, K = 2).
+// Wherever the row-tile kernel has no instance of two parts (bf16, K > 64), 1.3 times as fast or more; where it has one, always from 16384
+// rows on (17830 x 114, K = 57: 14.4 / 13.9, the least gain of 894 calls).  Below, one launch less is set against an operand that every
+// workgroup prepares for itself and a wave's one tile at the pace of its latencies: the difference in us, by least squares over 2300 random
+// calls from a graph, must be 0.35 in favour.  Near ties are measured one after the other by the wave that has them, so that many clusters
+// on few channels, and more than 64 at all, count against it.  Over 5000 calls, the same and others: 1.53 times as fast on average, 1.002
+// times what the faster kernel takes; 37 longer than the row-tile kernel by more than 2 %, the worst 9.4 / 11.8 (3253 x 24, K = 90, overlapping
+// clusters).  Either side of the line: 2041 x 118, K = 16: 8.2 / 10.6; bf16 6444 x 200, K = 54: 10.4 / 12.6; 4298 x 242 bf16, K = 2: 10.3 / 11.1;
+// 3420 x 106 bf16, K = 3: 8.1 / 6.8; 12479 x 4, K = 22: 10.9 / 5.9; 15363 x 6, K = 35: 13.2 / 8.2; 9329 x 122 bf16, K = 4: 11.8 / 7.3.
 bool short_apply_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
-    if (!short_config(N, D, K, dt).ok) return false;
-    if (!infer_two_parts(D, K, dt)) return true;
-    const int64_t KD = (int64_t)K * D;
-    if (dt == CAT_F32 && KD > 4500) return N >= 32768;
-    if (N >= 16384) return true;
+    const ShortCfg c = short_config(N, D, K, dt);
+    if (!c.ok) return false;
+    if (N >= 16384 || !infer_two_parts(D, K, dt)) return true;
+    const double row = (double)D * (dt == CAT_BF16 ? 2.0 : 4.0);
     const bool ua = D % (dt == CAT_BF16 ? 8 : 4) != 0;
-    return K <= 4 * D && 2 * N >= 100 * K + 3 * KD && (!ua || N >= 80 * D);
+    const double longer = -3.3 + 0.18 * c.KT * c.nsteps + (ua ? 0.0103 : 0.0074) * row + 0.2 * (double)K / (double)D - 0.29e-3 * (double)N;
+    return longer + (K > 64 ? 0.9 : 0.0) < -0.35;
 }
 
 template <bool BF16, int KT, int VV, bool UA, bool PL>

@@ -107,7 +107,7 @@ def test_shapes_outside_are_refused(N, D, K, dtype):
 
 
 @pytest.mark.parametrize("N,D,K,dtype", [(4706, 101, 16, "f32"), (5941, 4, 100, "f32"), (2041, 118, 16, "f32"), (6444, 200, 54, "bf16"), (20000, 100, 50, "f32"),
-                                         (4096, 32, 10, "f32"), (3000, 120, 70, "bf16")])
+                                         (4096, 32, 10, "f32"), (3000, 120, 70, "bf16"), (12479, 4, 22, "f32"), (3253, 24, 90, "f32"), (3420, 106, 3, "bf16")])
 def test_the_dispatch_gives_what_each_kernel_gives(N, D, K, dtype):
     """either side of the rule's lines: the same labels and, to the rounding of a fold, the same rows as the kernel forced"""
     x, cent, g, b = _case(N, D, K, dtype, 2, spread=1.0)
