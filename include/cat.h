@@ -478,11 +478,12 @@ cat_status cat_fit_restarts(const void *lq, const void *fp, int64_t N, int64_t D
 
 /*
  * Timing of the dominant kernel, for benchmarks.  While enabled, every launch of the tile
- * kernel (the assignment / Lloyd / inference pass) made by the calling process is bracketed by
+ * kernel (an assignment or Lloyd pass) and of an inference kernel made by the calling process is bracketed by
  * two HIP events recorded on the launch stream.  cat_profile_read waits for those events and
  * copies up to `cap` durations (milliseconds, launch order) to the HOST array ms_out; it
  * returns the number of launches recorded since cat_profile_enable(1) (which also clears the
- * record), or -1 on a HIP error.  Event objects are created on first use and kept; nothing is
+ * record), or -1 on a HIP error.  A fit that would run several passes in one launch runs two launches a pass while this is
+ * enabled, so that each has its time: the same outputs, but another duration of the whole fit.  Event objects are created on first use and kept; nothing is
  * recorded, created or waited for while profiling is disabled (the default).  Not thread-safe.
  */
 cat_status cat_profile_enable(int on);

@@ -20,7 +20,7 @@ SOURCES = ["cat_tile_k16_f32.hip", "cat_tile_k16_bf16.hip", "cat_tile_k16_f32_p1
            "cat_pca.hip", "cat_eig.hip", "cat_sweep.hip", "cat_seed.hip", "cat_lds.hip", "cat_lp.hip", "cat_tile_multi_f32.hip",
            "cat_tile_multi_bf16.hip", "cat_tile_split.hip", "cat_tile_split_rows.hip"] + [
     f"cat_tile_k{kt}_{dt}.hip" for kt in (8, 4, 2, 1) for dt in ("f32", "bf16")]
-HEADERS = ["cat_common.h", "cat_tile.h", "cat_tile_kernel.h", "cat_infer.h", "cat_infer_kernel.h", "cat_wide.h", "cat_wide_kernel.h", "cat_direct.h", "cat_loop.h", "cat_short.h", "cat_eig.h"]
+HEADERS = ["cat_common.h", "cat_tile.h", "cat_tile_kernel.h", "cat_infer.h", "cat_infer_kernel.h", "cat_wide.h", "cat_wide_kernel.h", "cat_direct.h", "cat_loop.h", "cat_short.h", "cat_rank.h", "cat_eig.h"]
 OUT = os.path.join(_HERE, "libcat_hip.so")
 OBJ_DIR = os.path.join(_HERE, "_build")
 

@@ -296,8 +296,8 @@ static cat_status run_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, 
     if (fused) {
         // Long passes leave out the rows whose distance bounds say that they stay (same outputs; no pass needs to be left
         // out as a whole then).  Short ones are left out as a whole once the partition repeats, which costs the others nothing
-        // (one word per launch, read beside the first loads): 4096 x 64, K = 4, 20 iterations, settled after a few:
-        // 349 -> 232 us.
+        // (one word per launch, read beside the first loads): 4096 x 64, K = 4, 20 iterations, settled after a few, in two
+        // launches a pass: 349 -> 232 us.
         const bool plain = !g_full_loop.load();
         if (!skipped && !bw && plain) {
             if (w.bounds.expire)
@@ -305,9 +305,8 @@ static cat_status run_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, 
             else
                 skipped = w.lloyd.skipped;
         }
-        // Small matrices: the whole loop in one launch.  (The hooks that concern the launches per pass keep those.)
-        if (!bw && plain && path == CAT_PATH_AUTO && !profile_on() && lloyd_list_capacity() == 1024 && rerank_queue_capacity() == 256 &&
-            loop_pays(N, D, K, iters, dt))
+        // Small matrices: the whole loop in one launch.
+        if (!bw && plain && path == CAT_PATH_AUTO && loop_pays(N, D, K, iters, dt))
             return loop_lloyd(lq, dt, N, D, K, iters, centroids, w.acc, assignments, w.counts, inertia, w.rep,
                               skipped == w.lloyd.skipped ? nullptr : skipped, w.lloyd, st);
         // one assignment launch per Lloyd iteration; only the rows that change cluster touch the sums

@@ -23,6 +23,7 @@
 #include <atomic>
 
 #include "cat_loop.h"
+#include "cat_rank.h"
 #include "cat_tile_kernel.h"
 
 namespace cat {
@@ -103,23 +104,6 @@ __device__ __forceinline__ double tagged_load(const unsigned long long* at, int 
         b = far_load(at + next);
     } while ((uint32_t)a != tag || (uint32_t)b != tag);
     return __longlong_as_double((long long)((b & 0xFFFFFFFF00000000ull) | (a >> 32)));
-}
-// the values of a lane and of its partner 16 or 32 lanes on, lower one first: the same pair in both
-__device__ __forceinline__ void halves16(uint32_t v, uint32_t& a, uint32_t& b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    a = r[0];
-    b = r[1];
-}
-__device__ __forceinline__ void halves32(uint32_t v, uint32_t& a, uint32_t& b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    a = r[0];
-    b = r[1];
-}
-__device__ __forceinline__ float sum_groups(float v) {  // over the four lanes n, n + 16, n + 32, n + 48
-    uint32_t a, b;
-    halves16(__float_as_uint(v), a, b);
-    halves32(__float_as_uint(__uint_as_float(a) + __uint_as_float(b)), a, b);
-    return __uint_as_float(a) + __uint_as_float(b);
 }
 // the two largest of what the lanes hold (v1 >= v2 >= 0 each), in all lanes
 template <int CTRL>
@@ -576,24 +560,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                 f1 = s < f1 ? s : f1;
             }
         }
-#pragma unroll
-        for (int o = 0; o < 2; o++) {
-            uint32_t a1, c1, a2, c2, ai, ci;
-            if (o == 0) {
-                halves16(__float_as_uint(f1), a1, c1);
-                halves16(__float_as_uint(f2), a2, c2);
-                halves16((uint32_t)i1, ai, ci);
-            } else {
-                halves32(__float_as_uint(f1), a1, c1);
-                halves32(__float_as_uint(f2), a2, c2);
-                halves32((uint32_t)i1, ai, ci);
-            }
-            const float x1 = __uint_as_float(a1), y1 = __uint_as_float(c1);
-            const bool take = y1 < x1 || (y1 == x1 && (int)ci < (int)ai);
-            f1 = take ? y1 : x1;
-            i1 = take ? (int)ci : (int)ai;
-            f2 = fminf(fminf(__uint_as_float(a2), __uint_as_float(c2)), take ? x1 : y1);
-        }
+        best_two_groups(f1, i1, f2);
         i1 = i1 < K ? i1 : K - 1;  // (no real score compares: non-finite input)
         float dmin = fmaxf(xn2 + f1, 0.f);
         const float thr_in = p.tau * sqrtf(xn2) * cmax + p.tau2 * cmax * cmax;
@@ -1126,6 +1093,11 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
 
 static std::atomic<int> g_loop_members{0};  // cat_debug_loop
 
+// (what concerns the launches of a pass, hooks and the record of their times, keeps two launches a pass)
+static bool loops_on() {
+    return g_loop_members.load() >= 0 && lloyd_list_capacity() == kListCap && rerank_queue_capacity() == kQueueCap && !profile_on();
+}
+
 struct LoopCfg {
     bool ok = false;
     int KT = 0, nsteps = 0, W = 0;
@@ -1182,7 +1154,7 @@ static int loop_groups(int64_t N, int share, int cus, bool bounds) {
 // 6291 x 1000 bf16, K = 3, 10: 174 / 132 (one).  Over 1200 other fits of the same ranges: 1.43 times as fast on average, 5 of them slower
 // than 0.98 of two launches a pass, the least 0.92.
 bool loop_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
-    if ((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) >= 64.0 * 1024 * 1024 || iters < 1 || g_loop_members.load() < 0) return false;
+    if ((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) >= 64.0 * 1024 * 1024 || iters < 1 || !loops_on()) return false;
     const LoopCfg c = loop_config(N, D, K, dt);
     if (!c.ok || g_loop_members.load() > 0) return c.ok;
     const double groups = loop_groups(N, loop_share(c, N, K, kLoopMax, false), kLoopMax, false);
@@ -1238,7 +1210,7 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
         p.counts0 = lb->counts;
         p.sumsq = lw.sumsq;
     }
-    p.tau2 = 4.0e-7f;
+    p.tau2 = kSplitTau2;
     p.off_cent = c.off_cent;
     p.off_panel = c.off_panel;
     p.off_small = c.off_small;
@@ -1252,9 +1224,9 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
         if (dev < 16) ncu[dev].store(v);
     }
     p.share = loop_share(c, N, K, v, lb != nullptr);
-    // the error bound of the split arithmetic as in the tile kernels (cat_tile.hip: base_params); shared channels are added up once more
+    // (shared channels are added up once more)
     const int n_acc = (dt == CAT_BF16 ? 2 : 3) * ((c.nsteps + 3) / 4 * 4) + 8 + (p.share - 1);
-    p.tau = (dt == CAT_BF16 ? 3.1e-5f : 9.4e-5f) + 4.f * (float)n_acc * 5.96e-8f;
+    p.tau = split_tau(dt, n_acc);
     const int groups = loop_groups(N, p.share, v, lb != nullptr);
     // Rows that go to the sums directly come to 2 rows / K additions an address and workgroup, through the panel to one at most; all
     // workgroups add to the same addresses.  us per cat_fit with up to 2 / 4 / 16 rows directly: 89551 x 128 bf16, K = 7 (256 workgroups)
@@ -1274,8 +1246,11 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
     // in bf16: 33816 x 80, K = 37, 30: 3409 / 2586 / 3056.
     p.looks = 10;
     p.patience = (int64_t)((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) / 30000.0);
-    // The words lie in the scratch of the counting sort, 4 N + 8 K + 8 bytes: 64 + 32 (NM + 2) groups + 12 K are needed, NM <= 4
+    // The words lie in the scratch of the counting sort, 4 N + 8 K + 8 bytes: 64 + 16 (NM + 2) groups + 12 K are needed, NM <= 4, and there are
+    // at most N share / 128 + 1 groups of rows that `share` <= 8 waves work on (272 x 112, K = 104: five, 1796 of 1928 bytes, the narrowest)
     const int nm = c.KT < 4 ? 1 : c.KT / 2;
+    if (64 + 16 * (int64_t)(nm + 2) * groups + 12 * (int64_t)K > 4 * N + 8 * (int64_t)K + 8)
+        return set_error(CAT_ERR_WORKSPACE, "loop in one launch: the scratch of %lld rows does not hold the words of %d workgroups", (long long)N, groups);
     p.words = (unsigned long long*)lw.sort_ws;
     p.dn = (int32_t*)(p.words + 8 + 2 * (nm + 2) * groups);
     const int nwords = 8 + 2 * (nm + 2) * groups + (K + 1) / 2, nsums = lb ? 0 : K * (int)D;
@@ -1300,21 +1275,24 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
     return run_loop(lq, dt, N, D, K, iters, cent_io, sums, assign, counts, inertia, rep, skipped, lw, nullptr, st);
 }
 
-// Fits of 64 to 500 MB, two launches a pass against this, 720 random ones (24 .. 256 channels, K = 1 .. 128, 4 .. 32 iterations, four
-// kinds of data).  The panel has to take whole rows at once: there 0.97 to 1.3, 1.07 on average from five iterations on (with four, the one
-// pass in between gains nothing: 0.97 to 1.03); in parts, rows are read again for each, and 12 of 55 fits lost 3 .. 13 % (us: 636254 x 144 bf16, K = 91, 5
-// iterations: 1039 / 1190; 761995 x 145, K = 90, 10: 2918 / 3188).  Longer rows: the first passes after the full ones list many rows,
-// which k_delta_prep adds faster than the members' atomics, and only a long run of short lists makes up for it: 40000 x 1000, K = 5, 10
-// iterations 553 / 670; 117187 x 512, K = 28, 6: 635 / 774; 50000 x 1000, K = 16, 30, skewed clusters 1756 / 1888 (logits 965 / 725); 80000 x
-// 1000 bf16, K = 5, 30: 1380 / 1602.  So there fp32, few clusters, 20 iterations: 88 fits of 50 million entries in rows of 300, 600 and
-// 1000 channels with K = 2, 3, 5, 8 and 20 or 30 iterations, skewed clusters among them: 1.00 to 1.30, the least 83333 x 600, K = 8, 20, skewed
-// 1230 / 1235; 123 random ones 0.98 to 1.51.
+// Fits of 64 to 500 MB, two launches a pass against this, 540 random ones (24 .. 256 channels, K = 1 .. 128, 3 .. 30 iterations, four kinds of
+// data).  Where the panel takes whole rows at once: 0.98 to 1.5, 1.12 on average from five iterations on (with four, the one pass in between
+// gains nothing: 0.97 to 1.03).  In parts, rows are read again for each, which more passes make up for: up to three parts 1.15 on average from
+// eight iterations on, the least 0.96 of 139 (us: 1092872 x 212 bf16, K = 44, 13 iterations 1781 / 1861); more parts 1.13 from twelve on, 69 of
+// 76 no slower, skewed clusters down to 0.90 (312223 x 220 bf16, K = 57, 22: 1743 / 1927; 88281 x 221, K = 61, 27, even ones 960 / 633); with
+// fewer iterations 649628 x 128 bf16, K = 117, 7: 1335 / 1522; 717591 x 256 bf16, K = 54, 6: 1034 / 1153.  Longer rows: the first passes after the
+// full ones list many rows, which k_delta_prep adds faster than the members' atomics, and only a long run of short lists makes up for it: 40000
+// x 1000, K = 5, 10 iterations 553 / 670; 117187 x 512, K = 28, 6: 635 / 774; 50000 x 1000, K = 16, 30, skewed clusters 1756 / 1888 (logits 965 /
+// 725); 80000 x 1000 bf16, K = 5, 30: 1380 / 1602.  So there fp32, few clusters, 20 iterations: 88 fits of 50 million entries in rows of 300, 600
+// and 1000 channels with K = 2, 3, 5, 8 and 20 or 30 iterations, skewed clusters among them: 1.00 to 1.30, the least 83333 x 600, K = 8, 20,
+// skewed 1230 / 1235; 123 random ones 0.98 to 1.51.
 bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
-    if (g_loop_members.load() < 0 || lloyd_list_capacity() != kListCap || rerank_queue_capacity() != kQueueCap || profile_on()) return false;
+    if (!loops_on()) return false;
     const LoopCfg c = loop_config(N, D, K, dt, true);
     if (!c.ok || g_loop_members.load() > 0) return c.ok;
     if (D > 256) return dt == CAT_F32 && (int64_t)K * D <= 5120 && iters >= 20;
-    return c.W >= D && iters >= 5;
+    const int64_t parts = (D + c.W - 1) / c.W;
+    return iters >= (parts == 1 ? 5 : parts <= 3 ? 8 : 12);
 }
 
 cat_status loop_lloyd_bounds(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_t K, int32_t iters, float* cent_io, double* sums,

@@ -15,6 +15,7 @@
 #include <atomic>
 
 #include "cat_infer.h"
+#include "cat_rank.h"
 #include "cat_short.h"
 #include "cat_tile_kernel.h"
 
@@ -36,17 +37,6 @@ struct ShortParams {
     uint32_t off_rows, row_stride, wave_stride;  // LDS: operand, norms, the waves' rows, (PL) the parameters
     uint32_t off_params;
 };
-
-__device__ __forceinline__ void short_pair16(uint32_t v, uint32_t& a, uint32_t& b) {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    a = r[0];
-    b = r[1];
-}
-__device__ __forceinline__ void short_pair32(uint32_t v, uint32_t& a, uint32_t& b) {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    a = r[0];
-    b = r[1];
-}
 
 // PL: the folded parameters lie in LDS, gamma and beta of a channel side by side.  KT: cluster tiles.  VV: 16-byte groups of a tile per lane (rows of up to 64 VV bytes).  UA: rows that are not whole 16-byte groups.
 template <bool BF16, int KT, int VV, bool UA, bool PL>
@@ -199,10 +189,7 @@ __global__ __launch_bounds__(kShortT) void k_apply_short(const ShortParams p) {
             }
         }
         // ---- ranking: lane (n, q) has the clusters 16 u + 4 q .. + 3 of row n ----
-        uint32_t a, b;
-        short_pair16(__float_as_uint(nrm), a, b);
-        short_pair32(__float_as_uint(__uint_as_float(a) + __uint_as_float(b)), a, b);
-        const float xn2 = __uint_as_float(a) + __uint_as_float(b);
+        const float xn2 = sum_groups(nrm);
         float f1 = __builtin_inff(), f2 = __builtin_inff();
         int i1 = 0;
 #pragma unroll
@@ -216,24 +203,7 @@ __global__ __launch_bounds__(kShortT) void k_apply_short(const ShortParams p) {
                 f1 = s < f1 ? s : f1;
             }
         }
-#pragma unroll
-        for (int o = 0; o < 2; o++) {
-            uint32_t a1, c1, a2, c2, ai, ci;
-            if (o == 0) {
-                short_pair16(__float_as_uint(f1), a1, c1);
-                short_pair16(__float_as_uint(f2), a2, c2);
-                short_pair16((uint32_t)i1, ai, ci);
-            } else {
-                short_pair32(__float_as_uint(f1), a1, c1);
-                short_pair32(__float_as_uint(f2), a2, c2);
-                short_pair32((uint32_t)i1, ai, ci);
-            }
-            const float x1 = __uint_as_float(a1), y1 = __uint_as_float(c1);
-            const bool take = y1 < x1 || (y1 == x1 && (int)ci < (int)ai);
-            f1 = take ? y1 : x1;
-            i1 = take ? (int)ci : (int)ai;
-            f2 = fminf(fminf(__uint_as_float(a2), __uint_as_float(c2)), take ? x1 : y1);
-        }
+        best_two_groups(f1, i1, f2);
         i1 = i1 < K ? i1 : K - 1;  // (non-finite rows: any cluster number)
         const bool valid = tile * 16 + n < p.N;
         const float bound = p.tau * sqrtf(xn2) * cmax + p.tau2 * cmax * cmax;
@@ -453,9 +423,8 @@ cat_status short_apply(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32
     p.gamma = gamma;
     p.beta = beta;
     p.alpha = alpha;
-    // the error bound of the split arithmetic as in the tile kernels (cat_tile.hip: base_params)
-    p.tau = (dt == CAT_BF16 ? 3.1e-5f : 9.4e-5f) + 4.f * (float)((dt == CAT_BF16 ? 2 : 3) * c.nsteps + 8) * 5.96e-8f;
-    p.tau2 = 4.0e-7f;
+    p.tau = split_tau(dt, (dt == CAT_BF16 ? 2 : 3) * c.nsteps + 8);
+    p.tau2 = kSplitTau2;
     p.off_rows = c.off_rows;
     p.row_stride = c.row_stride;
     p.wave_stride = c.wave_stride;

@@ -103,12 +103,14 @@ def test_passes_that_leave_rows_out(N, D, K, iters, dtype, members):
     # bf16, each number of cluster tiles, whole 16-byte groups and not
     (150001, 256, 5, 7, "bf16"), (300001, 128, 17, 6, "bf16"), (400003, 90, 33, 6, "bf16"), (420001, 80, 100, 6, "bf16"),
     # fp32, two tiles of clusters; long rows, whose channels four or eight waves share
-    (200003, 100, 20, 6, "f32"), (33001, 600, 8, 20, "f32"), (17001, 1000, 5, 20, "f32")])
+    (200003, 100, 20, 6, "f32"), (33001, 600, 8, 20, "f32"), (17001, 1000, 5, 20, "f32"),
+    # the panel takes part of the channels at a time, two and eight parts
+    (90001, 192, 50, 8, "f32"), (150001, 128, 119, 12, "f32")])
 def test_shapes_that_are_dispatched_there(N, D, K, iters, dtype):
     _bounded(N, D, K, iters, dtype, 0)
 
 
-@pytest.mark.parametrize("N,D,K,iters,dtype", [(636254, 144, 91, 5, "bf16"), (135001, 128, 5, 4, "f32"), (40000, 1000, 5, 10, "f32"), (80000, 1000, 5, 30, "bf16")])
+@pytest.mark.parametrize("N,D,K,iters,dtype", [(636254, 144, 91, 5, "bf16"), (477132, 192, 57, 5, "bf16"), (349631, 96, 117, 7, "f32"), (135001, 128, 5, 4, "f32"), (40000, 1000, 5, 10, "f32"), (80000, 1000, 5, 30, "bf16")])
 def test_fits_that_two_launches_a_pass_are_faster_for(N, D, K, iters, dtype):
     """channels taken in parts; a single pass in between; long rows with few iterations or of bf16"""
     lq = torch.randn(N, D, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
