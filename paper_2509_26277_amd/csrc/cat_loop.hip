@@ -33,7 +33,9 @@ constexpr int kLoopMax = 256;      // workgroups
 constexpr int kLoopDirect = 16;    // changed rows of a workgroup that may go to the sums without the panel (see loop_lloyd)
 constexpr int kLoopList = 64;      // changed rows of a workgroup whose entries are kept in LDS too
 constexpr uint32_t kLoopClosed = 0x80000000u;        // in the word that counts who has come: the loop is through
-constexpr uint32_t kLoopRegroup = 0x80000000u;       // in the tag of the first workgroup's flag: the rows are shared out anew after this pass
+// a flag's lower word: the number of the pass, whether the rows are shared out anew after it (the first workgroup's), and in pass 0, from
+// bit 16 on, the exponents of the workgroup's squared norms: the largest, and 255 less the smallest one
+constexpr uint32_t kLoopTag = 0x7FFFu, kLoopRegroup = 0x8000u;
 constexpr unsigned long long kLoopOver = ~0ull;      // in place of the number of a group: the loop is through
 
 struct LoopParams {
@@ -50,7 +52,7 @@ struct LoopParams {
     double* sums;             // 3 x K x D; the first third zero on entry
     int32_t* dn;              // 3 x K; the first third zero on entry
     // zero on entry: [0] who has come, [1] number of the group << 32 | its members, [2] .. [5] for a change of groups: the pass to go on
-    // with, the drift so far, who has handed over, who has taken over; from [8] on by parity of the pass NM words a workgroup (the
+    // with and `full` << 32, the drift so far, who has handed over, who has taken over; from [8] on by parity of the pass NM words a workgroup (the
     // clusters it changed, 32 to a word) and two words a workgroup (halves of its share of the objective)
     unsigned long long* words;
     unsigned long long* list; // N
@@ -70,17 +72,19 @@ struct LoopParams {
     const double* sumsq;      // kSumSqSlots shares of the sum of |x|^2
 };
 constexpr int kLoopBounds = 2;
-// Passes whose sums are made afresh from all rows, as with two launches a pass.  Most rows still move in pass 1; and what a row of
-// large entries leaves behind where it is added and taken away again (a rounding of the sum it was in) would stay in that cluster's
-// sum.  us per cat_fit, pass 1 by differences / afresh: 4096 x 64, K = 4, 20 iterations: 129 / 131; 41590 x 40 bf16, K = 21, 18: 246 / 252;
-// 562555 x 38 bf16, K = 3, 30: 446 / 507.
-constexpr int kLoopFull = 2;
+// Two launches a pass make the sums of passes 0 and 1 afresh from all rows.  Here pass 1 takes the rows that move from one sum and adds
+// them to another, unless a row of large entries could leave a rounding of the sum that it was in: then, rows whose squared norms
+// differ by more than 2^kLoopSpread, pass 1 is made afresh too.  us per cat_fit, always afresh / here: 3945 x 824, K = 2, 15
+// iterations: 86 / 70; 15665 x 576, K = 2, 6: 107 / 90; 41877 x 136, K = 4, 25: 115 / 107; 14807 x 108 bf16, K = 4, 29: 74 / 67.
+constexpr int kLoopSpread = 20;
 struct LoopQueued {  // a row that is measured when the workgroup has run out of tiles
     uint32_t row;
     int prev;
     unsigned long long cand[2];
 };
 constexpr int kLoopQueue = 32;
+static_assert(kLoopQueue * sizeof(LoopQueued) >= kLoopW * 16 * sizeof(int), "the loop without bounds keeps exponents there");
+static_assert(kLoopMax <= 4 * kWave, "four words of exponents");
 
 template <typename V>
 __device__ __forceinline__ V far_load(const V* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -112,6 +116,19 @@ __device__ __forceinline__ double dpp_value(double v) {
     const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), CTRL, 0xF, 0xF, true);
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// the larger ones of two pairs of bytes
+__device__ __forceinline__ int larger_halves(int a, int b) {
+    const int l = (a & 0xFF) > (b & 0xFF) ? a & 0xFF : b & 0xFF, h = (a >> 8) > (b >> 8) ? a >> 8 : b >> 8;
+    return l | h << 8;
+}
+__device__ __forceinline__ int wave_larger(int v) {  // of all lanes
+    v = larger_halves(v, __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true));
+    v = larger_halves(v, __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true));
+    v = larger_halves(v, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, true));
+    v = larger_halves(v, __builtin_amdgcn_update_dpp(0, v, 0x140, 0xF, 0xF, true));
+    return larger_halves(larger_halves(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+                         larger_halves(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
 __device__ __forceinline__ void two_more(double& v1, double& v2, double o1, double o2) {
     v2 = fmax(fmin(v1, o1), fmax(v2, o2));
@@ -174,9 +191,10 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     int* s_n = (int*)(s_cnorm + KT * 16);             // KT * 16
     int* s_dn = s_n + KT * 16;                        // KT * 16
     uint32_t* s_mask = (uint32_t*)(s_dn + KT * 16);   // 4: own changes; 2 x 4: everybody's, by parity of the pass
-    // [0] rank, [1] members, [2] rows that changed, [3] queued rows, [4] due rows, [5] whether the group changes, [6] its number
+    // [0] rank, [1] members, [2] rows that changed, [3] queued rows, [4] due rows, [5] whether the group changes, [6] its number;
+    // [8] .. [11] the exponents of the squared norms, of 64 workgroups each
     int* s_misc = (int*)(s_mask + 12);
-    unsigned long long* s_list = (unsigned long long*)(s_misc + 8);  // kLoopList
+    unsigned long long* s_list = (unsigned long long*)(s_misc + 12);  // kLoopList
     LoopQueued* s_queue = (LoopQueued*)(s_list + kLoopList);  // kLoopQueue
     float* s_score = (float*)(s_queue + kLoopQueue);  // kLoopW x KT * 16
     double* s_mv = (double*)(s_score + kLoopW * KT * 16);  // BOUNDS, KT * 16 each: squared movements; the first member: the clusters'
@@ -192,7 +210,10 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         s_misc[0] = (int)__hip_atomic_fetch_add((uint32_t*)p.words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_misc[2] = s_misc[3] = s_misc[4] = s_misc[5] = 0;
     }
+    int* s_exp = (int*)s_queue;  // !BOUNDS, kLoopW x 16: the exponents of what a lane had in pass 0, largest | (255 - smallest) << 8
     if (tid < 12) s_mask[tid] = 0;
+    if (tid < 4) s_misc[8 + tid] = 0;
+    if (!BOUNDS && tid < kLoopW * 16) s_exp[tid] = 0;
     for (int i = tid; i < (int)(p.off_cent / 16); i += kLoopT) ((u32x4*)smem)[i] = (u32x4){0u, 0u, 0u, 0u};
     for (int i = tid; i < K * W; i += kLoopT) s_panel[i] = 0.0;
     if (tid < KT * 16) {
@@ -316,10 +337,12 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     };
     // the centroids in memory, all of them (a workgroup that comes late may read some that are being written, and reads them again later)
     auto load_centroids = [&]() {
-        int k = tid / D, ch = tid - k * D;
-        const int qd = kLoopT / D, rd = kLoopT - qd * D;
+        int id = tid, row = D;
+        asm volatile("" : "+v"(id), "+s"(row));  // (what follows from them is not to be kept in registers through the passes)
+        int k = id / row, ch = id - k * row;
+        const int qd = kLoopT / row, rd = kLoopT - qd * row;
 #pragma unroll 4
-        for (int i = tid; i < KD; i += kLoopT) {
+        for (int i = id; i < KD; i += kLoopT) {
             s_cent[k * Ds + ch] = p.cent[i];
             ch += rd;
             k += qd;
@@ -391,6 +414,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     f32x4 acc[KT];
     float nrm = 0.f, cmax = 0.f;
     double in_acc = 0.0;
+    int full = 2;  // passes whose sums are made afresh
     int t = BOUNDS ? kLoopBounds : 0, tl = 0, cl = 0, tc = 0, cc = 0;
 #pragma unroll
     for (int u = 0; u < KT; u++) acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
@@ -486,7 +510,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
     };
     // a row's cluster (the lanes with `on` hold one each): the label, and the lists of what changed (the first passes: of all rows)
     auto book = [&](bool on, int64_t row, int prev, int k) {
-        const bool changed = on && prev != k, afresh = !BOUNDS && t < kLoopFull && (t == 0 || K > 1), listed = changed || (on && afresh);
+        const bool changed = on && prev != k, afresh = !BOUNDS && t < full && (t == 0 || K > 1), listed = changed || (on && afresh);
         const unsigned long long cm = __ballot(listed);
         if (!cm) return;
         int pos = 0;
@@ -609,7 +633,14 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         for (int u = 0; u < KT; u++) acc[u] = (f32x4){0.f, 0.f, 0.f, 0.f};
         nrm = 0.f;
         const bool owner = q == 0 && valid && !queued;
-        if (!BOUNDS && owner) in_acc += (double)dmin;
+        if (!BOUNDS && owner) {
+            in_acc += (double)dmin;
+            if (t == 0) {
+                const int x = (int)(__float_as_uint(xn2) >> 23 & 0xFFu);
+                int* at = s_exp + wave * 16 + n;
+                *at = larger_halves(*at, x | (255 - x) << 8);
+            }
+        }
         if (BOUNDS && owner) {
             // as in finish_tile (cat_tile_kernel.h): the drift that leaves the nearest centroid the nearest
             double m = 0.0;
@@ -658,7 +689,9 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
         share_out();
         list = own_list;
         if (group > 1) {  // goes on where the last group has stopped
-            t = __builtin_amdgcn_readfirstlane((int)far_load(p.words + 2));
+            const unsigned long long at = far_load(p.words + 2);
+            t = __builtin_amdgcn_readfirstlane((int)at);
+            full = __builtin_amdgcn_readfirstlane((int)(at >> 32));
             regroup = true;  // (BOUNDS: the bounds of its rows have not been requested yet)
             gnow = __longlong_as_double((long long)far_load(p.words + 3));
             const int turn = (t - (BOUNDS ? kLoopBounds : 0)) % 3, after = turn == 2 ? 0 : turn + 1, before = turn == 0 ? 2 : turn - 1;
@@ -677,7 +710,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             }
             __syncthreads();
             if (rank == 0 && tid < K) far_store(p.rep + tid, ~0ull);
-            carry = z_lo + tid < z_hi && (BOUNDS || t >= kLoopFull) ? far_load(sums_prev + z_lo + tid) : 0.0;
+            carry = z_lo + tid < z_hi && (BOUNDS || t >= full) ? far_load(sums_prev + z_lo + tid) : 0.0;
         } else if (BOUNDS) {
             const int64_t len = (int64_t)*p.list_count;
             e0 = (int)(len * rank / M);
@@ -737,7 +770,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             // everybody did before raising the flag of pass t - 1: it is free now, and clear before the flags of pass t.
             // The share of the sums so far moves on to this pass's (unless that adds up all rows), and the buffers of the pass that follows are cleared.
             for (int i = z_lo + tid; i < z_hi; i += kLoopT) {
-                if (i != z_lo + tid) carry = t > (BOUNDS ? kLoopBounds : kLoopFull - 1) ? far_load(sums_prev + i) : 0.0;
+                if (i != z_lo + tid) carry = t >= (BOUNDS ? kLoopBounds + 1 : full) ? far_load(sums_prev + i) : 0.0;
                 if (carry != 0.0) atomicAdd(sums + i, carry);
                 far_store(sums_next + i, 0.0);
             }
@@ -910,8 +943,11 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             }
             unsigned long long* flags = p.words + 8 + (t & 1) * (NM + 2) * G;
             const int par = t & 1;
+            uint32_t exps = 0;
+            if (!BOUNDS && t == 0 && wave == 0) exps = (uint32_t)wave_larger(larger_halves(s_exp[lane], s_exp[lane + kWave]));
             if (tid < NM) {
-                uint32_t tag = (uint32_t)(t + 1);
+                uint32_t tag = (uint32_t)(t + 1) & kLoopTag;
+                if (!BOUNDS && t == 0 && tid == 0) tag |= exps << 16;
                 // others have come since (not before the last pass, which nothing follows that would wait for the first workgroup)
                 if (tid == 0 && rank == 0 && M < G && t + 1 < p.iters) {
                     const int come = (int)far_load((uint32_t*)p.words);
@@ -938,12 +974,20 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                 if (m0 >= M) continue;
                 const unsigned long long* f = flags + w * G + (m0 + lane < M ? m0 + lane : M - 1);
                 unsigned long long v = far_load(f);
-                while (__any(((uint32_t)v & ~kLoopRegroup) != (uint32_t)(t + 1))) v = far_load(f);
-                if (i0 == 0 && lane == 0 && ((uint32_t)v & kLoopRegroup)) s_misc[5] = 1;
+                while (__any(((uint32_t)v & kLoopTag) != ((uint32_t)(t + 1) & kLoopTag))) v = far_load(f);
+                if (w == 0 && lane == 0 && ((uint32_t)v & kLoopRegroup)) s_misc[5] = 1;
+                if (!BOUNDS && t == 0 && w == 0) {
+                    const int x = wave_larger((int)((uint32_t)v >> 16));
+                    if (lane == 0) s_misc[8 + wave] = x;
+                }
                 const uint32_t bits = (uint32_t)(v >> 32);
                 if (bits) atomicOr(&s_mask[4 + 4 * par + w], bits);
             }
             __syncthreads();
+            if (!BOUNDS && t == 0) {
+                const int x = __builtin_amdgcn_readfirstlane(larger_halves(larger_halves(s_misc[8], s_misc[9]), larger_halves(s_misc[10], s_misc[11])));
+                full = (x & 0xFF) + (x >> 8) - 255 > kLoopSpread ? 2 : 1;
+            }
             if (!BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia) {
                 double v = 0.0;
                 for (int m = lane; m < M; m += kWave) v += tagged_load(flags + NM * G + m, G, (uint32_t)(t + 1));
@@ -961,7 +1005,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
             // ---- the next centroids ----
             const bool last = BOUNDS && t == p.iters;
             if (last && rank != 0) break;
-            if (z_lo + tid < z_hi && (BOUNDS || t >= kLoopFull - 1)) carry = far_load(sums + z_lo + tid);
+            if (z_lo + tid < z_hi && (BOUNDS || t >= full - 1)) carry = far_load(sums + z_lo + tid);
             build(mask, sums, dn, BOUNDS && rank == 0 && p.inertia, last);
             __syncthreads();
             if (BOUNDS && rank == 0 && wave == kLoopW - 1 && p.inertia && t > kLoopBounds) {
@@ -1010,7 +1054,7 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
                 for (int ch = lane; ch < D; ch += kWave) far_store(p.cent + k * D + ch, s_cent[k * Ds + ch]);
             if (tid < K) far_store(p.rep + tid, (unsigned long long)(uint32_t)s_n[tid]);
             if (tid == 0) {
-                far_store(p.words + 2, (unsigned long long)t);
+                far_store(p.words + 2, ((unsigned long long)full << 32) | (uint32_t)t);
                 far_store(p.words + 3, (unsigned long long)__double_as_longlong(gnow));
             }
         }
@@ -1112,7 +1156,7 @@ static LoopCfg loop_config(int64_t N, int64_t D, int32_t K, cat_dtype dt, bool b
     c.nsteps = (int)((D + 31) / 32);
     c.off_cent = (uint32_t)(c.nsteps * c.KT * 2048);
     c.off_panel = c.off_cent + (uint32_t)(K * (D + 4) * 4);
-    const size_t small = (size_t)c.KT * 16 * (4 + 4 + 4) + kLoopW * 8 + 20 * 4 + kLoopList * 8 + kLoopQueue * sizeof(LoopQueued) +
+    const size_t small = (size_t)c.KT * 16 * (4 + 4 + 4) + kLoopW * 8 + 24 * 4 + kLoopList * 8 + kLoopQueue * sizeof(LoopQueued) +
                          (size_t)kLoopW * c.KT * 16 * 4 + (bounds ? 3 * (size_t)c.KT * 16 * 8 : 0);
     if (c.off_panel + small + (size_t)K * 16 * 8 > kLdsLimit) return c;
     int64_t W = (int64_t)((kLdsLimit - small - c.off_panel) / ((size_t)K * 8)) / 16 * 16;
@@ -1247,7 +1291,7 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
     p.looks = 10;
     p.patience = (int64_t)((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) / 30000.0);
     // The words lie in the scratch of the counting sort, 4 N + 8 K + 8 bytes: 64 + 16 (NM + 2) groups + 12 K are needed, NM <= 4, and there are
-    // at most N share / 128 + 1 groups of rows that `share` <= 8 waves work on (272 x 112, K = 104: five, 1796 of 1928 bytes, the narrowest)
+    // at most N share / 128 + 1 groups of rows that `share` <= 8 waves work on (272 x 112, K = 104: five, 1792 of 1928 bytes, the narrowest)
     const int nm = c.KT < 4 ? 1 : c.KT / 2;
     if (64 + 16 * (int64_t)(nm + 2) * groups + 12 * (int64_t)K > 4 * N + 8 * (int64_t)K + 8)
         return set_error(CAT_ERR_WORKSPACE, "loop in one launch: the scratch of %lld rows does not hold the words of %d workgroups", (long long)N, groups);

@@ -353,11 +353,11 @@ static ShortCfg short_config(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
 bool short_apply_pays(int64_t N, int64_t D, int32_t K, cat_dtype dt) {
     const ShortCfg c = short_config(N, D, K, dt);
     if (!c.ok) return false;
-    if (N >= 16384 || !infer_two_parts(D, K, dt)) return true;
+    if (N >= 16384) return true;
     const double row = (double)D * (dt == CAT_BF16 ? 2.0 : 4.0);
     const bool ua = D % (dt == CAT_BF16 ? 8 : 4) != 0;
     const double longer = -3.3 + 0.18 * c.KT * c.nsteps + (ua ? 0.0103 : 0.0074) * row + 0.2 * (double)K / (double)D - 0.29e-3 * (double)N;
-    return longer + (K > 64 ? 0.9 : 0.0) < -0.35;
+    return longer + (K > 64 ? 0.9 : 0.0) < -0.35 || !infer_two_parts(D, K, dt);
 }
 
 template <bool BF16, int KT, int VV, bool UA, bool PL>
