@@ -1191,12 +1191,13 @@ static int loop_groups(int64_t N, int share, int cus, bool bounds) {
 // channels, K = 1 .. 128, 1 .. 32 iterations, four kinds of data):
 //   saved: 6 a pass (launches, trips) and 4 more in the first four, and 400 per million rows (no sort by cluster for the full sums);
 //   lost: 16 per million additions to the sums in memory if every workgroup adds to all of them, once a full pass; 70 per thousand rows
-//   of a workgroup for each part of the channels that the panel takes at a time; 2.5 per million entries of bf16 rows (the rows of
-//   a tile kernel come faster, and there are twice as many to 64 MB).
+//   of a workgroup for each part of the channels that the panel takes at a time; 1.5 per million entries of bf16 rows (the rows of
+//   a tile kernel come faster, and there are twice as many to 64 MB), less with fewer than eight clusters.
 // Both sides, two launches / one: 28835 x 1000 bf16, K = 16, 4 iterations 230 / 420 (two here); 60074 x 480 bf16, K = 16, 10: 430 / 525
 // (two); 14417 x 1000, K = 16, 4: 222 / 281 (two); 1715 x 136 bf16, K = 98, 2: 116 / 206 (two); 30037 x 480, K = 16, 10: 359 / 283 (one);
-// 6291 x 1000 bf16, K = 3, 10: 174 / 132 (one).  Over 1200 other fits of the same ranges: 1.43 times as fast on average, 5 of them slower
-// than 0.98 of two launches a pass, the least 0.92.
+// 6291 x 1000 bf16, K = 3, 10: 174 / 132 (one); 89422 x 296 bf16, K = 1, 5: 344 / 196 (one).  Over 1460 other fits of the same ranges: 1.79 times
+// as fast on average, 1.0005 times what the faster way takes; three more than 2 % slower than two launches a pass, the worst 266 / 291 (42629 x
+// 456 bf16, K = 7, 6 iterations).
 bool loop_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
     if ((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) >= 64.0 * 1024 * 1024 || iters < 1 || !loops_on()) return false;
     const LoopCfg c = loop_config(N, D, K, dt);
@@ -1204,7 +1205,7 @@ bool loop_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
     const double groups = loop_groups(N, loop_share(c, N, K, kLoopMax, false), kLoopMax, false);
     const double saved = 6.0 * iters + 4.0 * (iters < 4 ? iters : 4) + 400e-6 * (double)N;
     const double lost = 16e-6 * groups * (double)K * (double)D + 70e-3 * (double)N / groups * (double)((D + c.W - 1) / c.W) +
-                        (dt == CAT_BF16 ? 2.5e-6 * (double)N * (double)D : 0.0);
+                        (dt == CAT_BF16 ? 1.5e-6 * (double)N * (double)D * (K < 8 ? K / 8.0 : 1.0) : 0.0);
     return saved - lost > 10.0;
 }
 

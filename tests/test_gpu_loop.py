@@ -284,7 +284,7 @@ def test_replayed_from_a_graph():
 @pytest.mark.parametrize("N,D,K,iters,dtype,one", [
     # measured on both sides: where the additions of all workgroups, channels taken in parts or bf16 rows outweigh the launches saved
     (28835, 1000, 16, 4, "bf16", False), (60074, 480, 16, 10, "bf16", False), (14417, 1000, 16, 4, "f32", False), (1715, 136, 98, 2, "bf16", False),
-    (30037, 480, 16, 10, "f32", True), (6291, 1000, 3, 10, "bf16", True), (4096, 64, 4, 20, "f32", True), (33816, 80, 37, 30, "f32", True)])
+    (30037, 480, 16, 10, "f32", True), (6291, 1000, 3, 10, "bf16", True), (4096, 64, 4, 20, "f32", True), (33816, 80, 37, 30, "f32", True), (89422, 296, 1, 5, "bf16", True), (25269, 230, 37, 7, "bf16", True)])
 def test_small_fits_take_the_faster_way(N, D, K, iters, dtype, one):
     x, y = _rows(N, D, K, dtype, 1)
     _, shared = _fit_on(0, dev_matrix(x, dtype), dev_matrix(y, dtype), K, iters)
