@@ -9,14 +9,15 @@
 //   wait for everybody's flag;  read the sums of the touched clusters and rebuild those centroids (every workgroup for itself).
 // The loop ends when no row changes any more.  What bounds it: three trips through memory in a row (additions, flags, sums, some
 // 1 us each; 256 flags 2.4 us, 32 flags 0.9), the additions of all workgroups to the same addresses in the first passes, and the
-// instructions of one tile.  us per cat_fit, two launches a pass -> this: 4096 x 64, K = 4, 20 iterations: 361 -> 179 (6.5 a pass);
-// 33816 x 80, K = 37, 30 iterations: 788 -> 371; 3178 x 28, K = 123: 449 -> 220; 11787 x 768, K = 15, 5 iterations: 251 -> 197.
+// instructions of one tile.  us per cat_fit of a planted mixture, two launches a pass -> this, three seeds: 4096 x 64, K = 4, 20
+// iterations: 363, 181, 275 -> 171, 74, 121; 33816 x 80, K = 37, 30: 747, 781, 764 -> 402, 397, 399; 3178 x 28, K = 123, 20: 518, 390, 346
+// -> 200, 166, 143.
 // From 64 MB on (BOUNDS) the passes that leave rows out by distance bounds run here too: tile_lloyd's passes 0 .. 2 read every row, the
 // last of them lists the rows that changed and leaves the bounds; then every workgroup selects the due ones of its own rows, and
 // the waves share the channels of a tile where a pass has few tiles.  A row within the error bound is measured at the end of the
-// workgroup's tiles, by any wave.  us per cat_fit: 563519 x 40, K = 91: 1992 -> 1747; 1048576 x 256,
-// K = 32: 2423 -> 2357; longer rows only where every kind of data gained (loop_bounds_pays).
-// Tried: as many copies of the sums as spread those additions (a copy more to read is a trip more: 179 -> 228 with two); a third and
+// workgroup's tiles, by any wave.  us per cat_fit: 563519 x 40, K = 91, 30
+// iterations, logits: 1986, 2098, 1999 -> 1323, 1388, 1318; 1048576 x 256, K = 32, 15, a feature map: 2453, 2102, 2639 -> 2303, 2038, 2536.
+// Tried: as many copies of the sums as spread those additions (a copy more to read is a trip more: 27 % more time with two); a third and
 // fourth chunk of rows in flight (registers spill, 7 .. 20 % slower); a delay before the first look at the flags (alone it makes a
 // barrier of 256 workgroups 1.1 us instead of 2.4, here it is lost beside the waits for the last one to arrive).  The code has to
 // stay small: at 64 KB (loops unrolled) it no longer fits the instruction cache and every phase took half as long again.
@@ -1274,7 +1275,7 @@ static cat_status run_loop(const void* lq, cat_dtype dt, int64_t N, int64_t D, i
     p.tau = split_tau(dt, n_acc);
     const int groups = loop_groups(N, p.share, v, lb != nullptr);
     // Rows that go to the sums directly come to 2 rows / K additions an address and workgroup, through the panel to one at most; all
-    // workgroups add to the same addresses.  us per cat_fit with up to 2 / 4 / 16 rows directly: 89551 x 128 bf16, K = 7 (256 workgroups)
+    // workgroups add to the same addresses.  us per cat_fit with up to 2 / 4 / 16 rows directly, as the loop was when this was chosen: 89551 x 128 bf16, K = 7 (256 workgroups)
     // 242 / 268 / 308; 7294 x 776, K = 3 (228) 115 / 115 / 150; 14629 x 998 bf16, K = 4 (229) 249 / 228 / 233; 4096 x 64, K = 4 (32)
     // 194 / 189 / 188; 2652 x 640, K = 11 192 / 185 / 186.
     p.direct = 64 * K / groups * (int)((D + c.W - 1) / c.W);
