@@ -1139,7 +1139,8 @@ __global__ __launch_bounds__(kLoopT) void k_lloyd_loop(const LoopParams p) {
 static std::atomic<int> g_loop_members{0};  // cat_debug_loop
 
 // (what concerns the launches of a pass, hooks and the record of their times, keeps two launches a pass)
-static bool loops_on() {
+static bool loops_on(int32_t iters) {
+    if (iters >= (int32_t)kLoopTag) return false;  // (a flag has that many numbers for a pass)
     return g_loop_members.load() >= 0 && lloyd_list_capacity() == kListCap && rerank_queue_capacity() == kQueueCap && !profile_on();
 }
 
@@ -1200,7 +1201,7 @@ static int loop_groups(int64_t N, int share, int cus, bool bounds) {
 // as fast on average, 1.0005 times what the faster way takes; three more than 2 % slower than two launches a pass, the worst 266 / 291 (42629 x
 // 456 bf16, K = 7, 6 iterations).
 bool loop_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
-    if ((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) >= 64.0 * 1024 * 1024 || iters < 1 || !loops_on()) return false;
+    if ((double)N * (double)D * (dt == CAT_BF16 ? 2.0 : 4.0) >= 64.0 * 1024 * 1024 || iters < 1 || !loops_on(iters)) return false;
     const LoopCfg c = loop_config(N, D, K, dt);
     if (!c.ok || g_loop_members.load() > 0) return c.ok;
     const double groups = loop_groups(N, loop_share(c, N, K, kLoopMax, false), kLoopMax, false);
@@ -1333,7 +1334,7 @@ cat_status loop_lloyd(const void* lq, cat_dtype dt, int64_t N, int64_t D, int32_
 // and 1000 channels with K = 2, 3, 5, 8 and 20 or 30 iterations, skewed clusters among them: 1.00 to 1.30, the least 83333 x 600, K = 8, 20,
 // skewed 1230 / 1235; 123 random ones 0.98 to 1.51.
 bool loop_bounds_pays(int64_t N, int64_t D, int32_t K, int32_t iters, cat_dtype dt) {
-    if (!loops_on()) return false;
+    if (!loops_on(iters)) return false;
     const LoopCfg c = loop_config(N, D, K, dt, true);
     if (!c.ok || g_loop_members.load() > 0) return c.ok;
     if (D > 256) return dt == CAT_F32 && (int64_t)K * D <= 5120 && iters >= 20;

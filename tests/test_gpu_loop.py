@@ -10,6 +10,7 @@ import torch
 import oracle
 from paper_2509_26277_amd import binding, cat_fit
 
+from test_gpu_pca_grid import _stream_with
 from parity_util import CENTROID_RTOL, check_assignments_lazy, check_values, dev_matrix, f32_round, host_matrix
 
 pytestmark = pytest.mark.gpu
@@ -188,6 +189,21 @@ def test_a_fit_begun_beside_another_kernel_gets_the_whole_chip(N, D, K, dtype):
         assert binding.debug_loop_members(N, D, K, binding.CAT_F32, ws[1]) == every
     assert int((got[1]["assignments"] != want["assignments"]).sum()) <= N // 1000
     np.testing.assert_allclose(got[1]["inertia"].cpu().numpy(), want["inertia"].cpu().numpy(), rtol=1e-4)
+
+
+@pytest.mark.parametrize("cus", [64, 128])
+def test_a_stream_with_some_of_the_cus(cus):
+    """the workgroups that have no place there never come while the loop runs; those that are there do all of it (LDS: one a CU)"""
+    g = torch.Generator(device="cuda").manual_seed(cus)
+    mu = torch.randn(100, 128, generator=g, device="cuda") * 0.5
+    lq = mu[torch.randint(0, 100, (40000,), generator=g, device="cuda")] + torch.randn(40000, 128, generator=g, device="cuda")
+    fp = (lq * 1.1).contiguous()
+    want, every = _fit_on(ALL, lq, fp, 100, 6)
+    with _stream_with(cus) as s, torch.cuda.stream(s):
+        got, shared = _fit_on(ALL, lq, fp, 100, 6)
+    assert every == 256 and 0 < shared <= cus
+    assert int((got["assignments"] != want["assignments"]).sum()) <= 3
+    check_values(host_matrix(got["centroids"]), host_matrix(want["centroids"]), 1e-4, "centroids")
 
 
 def test_ties_and_empty_clusters():
