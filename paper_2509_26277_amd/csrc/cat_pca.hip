@@ -1148,13 +1148,18 @@ bool apply_pca_fused_supported(const void* lq, int64_t D, int32_t K, int32_t p, 
                             (uintptr_t)corrected;
     return (D & 3) == 0 && (bases & 15u) == 0 && p <= 64 && K <= 256;
 }
-// 17 .. 32 directions: a second loop for the steps of a row's last chunk leaves registers for four waves a SIMD instead of six, which hold
-// 65536 and 98304 rows.  Up to 65536 it is the faster one or the same, above that for fp32 rows but the short ones and, in between, those
+// Whether the fused kernel does the steps past a row's end too.  17 .. 32 directions: a second loop for the steps of a row's last chunk
+// leaves registers for four waves a SIMD instead of six, which hold 65536 and 98304 rows.  Up to 65536 it is the faster one or the same, above that for fp32 rows but the short ones and, in between, those
 // of up to 384 channels.  us, without / with it: 7223 x 1712, p = 27: 100 / 84; 10482 x 2040 bf16, p = 21: 118 / 101; 82158 x 640, p =
 // 17: 154 / 128; 145618 x 336, p = 31: 125 / 115; 237125 x 40, p = 26: 57.8 / 55.4; 76306 x 96, p = 25: 30.0 / 34.5; 86893 x 336, p = 32: 64.1 /
 // 68.5; 311291 x 112, p = 20: 128 / 142; bf16: 83338 x 240, p = 26: 42.4 / 48.5; 97899 x 624, p = 30: 85 / 99; 799341 x 72, p = 24: 253 / 284.
-static bool project_all_steps(int64_t N, int64_t D, cat_dtype dt) {
+// 33 .. 64: fp32 rows of which less than one step in 32 is left out, up to 32768 of them: 365 x 1272, p = 64: 88 / 93; 2376 x 768, p = 35: 47.8 / 49.9.
+static bool project_all_steps(int64_t N, int64_t D, int32_t p, cat_dtype dt) {
     constexpr int64_t kFour = 65536, kSix = 98304;
+    if (p > 32) {
+        const int64_t all = (D + kProjChunk - 1) / kProjChunk * (kProjChunk / 16), needed = (D + 15) / 16;
+        return dt == CAT_F32 && N <= 32768 && 32 * (all - needed) < all;
+    }
     if (N <= kFour) return false;
     return dt == CAT_BF16 || (D <= 128 && (D > 48 || N > 8 * kFour)) || (D <= 384 && N <= kSix);
 }
@@ -1172,10 +1177,12 @@ cat_status launch_apply_pca_fused(const void* lq, int64_t N, int64_t D, int32_t 
 #define CAT_FUSE_P(T)                                                        \
     if (p <= 16) CAT_FUSE(T, 1, true);                                       \
     else if (p > 32) CAT_FUSE(T, 4, false);                                  \
-    else if (project_all_steps(N, D, dt)) CAT_FUSE(T, 2, true);              \
+    else if (all) CAT_FUSE(T, 2, true);                                      \
     else CAT_FUSE(T, 2, false)
+    const bool all = project_all_steps(N, D, p, dt);
     if (dt == CAT_F32) {
-        CAT_FUSE_P(float);
+        if (p > 32 && all) CAT_FUSE(float, 4, true);
+        else CAT_FUSE_P(float);
     } else {
         CAT_FUSE_P(bf16_t);
     }

@@ -74,3 +74,21 @@ def test_fused_inference_with_many_rows(D, p, dtype):
     finally:
         binding.select_path(binding.CAT_PATH_AUTO)
     assert torch.equal(a, c) and torch.equal(out, steps)
+
+
+@pytest.mark.parametrize("N,D,p", [(301, 512, 64), (129, 1000, 33), (32768, 120, 50), (32769, 120, 50), (700, 104, 40)])
+def test_fused_inference_equals_the_steps_either_side_of_its_lines(N, D, p):
+    """33 .. 64 directions on fp32 rows: with the steps past a row's end (few of them, few rows) and without"""
+    g = torch.Generator(device="cuda").manual_seed(N + D)
+    K = 9
+    lq = torch.randn(N, D, generator=g, device="cuda")
+    mean, comps = torch.randn(D, generator=g, device="cuda"), torch.randn(p, D, generator=g, device="cuda") / D ** 0.5
+    cz = torch.randn(K, p, generator=g, device="cuda")
+    gamma, beta = torch.rand(K, D, generator=g, device="cuda") + 0.5, torch.randn(K, D, generator=g, device="cuda")
+    out, a = cat_apply_pca(lq, mean, comps, cz, gamma, beta, alpha=0.7)
+    try:
+        binding.select_path(binding.CAT_PATH_STREAM)
+        steps, c = cat_apply_pca(lq, mean, comps, cz, gamma, beta, alpha=0.7)
+    finally:
+        binding.select_path(binding.CAT_PATH_AUTO)
+    assert torch.equal(a, c) and torch.equal(out, steps)
